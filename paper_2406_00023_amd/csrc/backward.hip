@@ -12,7 +12,7 @@
 // slow one in memory (Wd for u, Wg / Wu for dXp, the row-major activations for the weight gradients) are
 // read as they lie: the persistent kernel stages such k-tiles k-major in LDS and takes its MFMA fragments
 // through transposing LDS reads, so nothing is transposed in memory.  Only shapes that kernel does not take
-// (fp32, H % 64 != 0, fewer than 128 padded rows) go through the fall-back that transposes the weights once per
+// (fp32, widths below 128) go through the fall-back that transposes the weights once per
 // call and has the element-wise kernel write transposed copies of the per-row quantities.
 #include "etr_internal.h"
 
@@ -429,6 +429,13 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
     }
 }
 
+// Rows per expert of the padded per-row buffers.  bf16: at least 128, so that the weight-gradient products have the
+// contraction length the transposing kernel needs and a small capacity does not fall back to transposed weights.
+int padded_capacity(const etr_config& c) {
+    const int Cp = (c.capacity + 63) / 64 * 64;
+    return c.dtype == ETR_BF16 && Cp < 128 ? 128 : Cp;
+}
+
 struct BackwardWs {
     size_t wdT, wguT, a, b, u, dab, daT, dbT, hT, xpT, dypT, dxp, dgate_part, gate_eff, total;
 };
@@ -438,7 +445,7 @@ BackwardWs backward_layout(const etr_config& c) {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
     const size_t es = elt_bytes(c.dtype), E = c.E, C = c.capacity, H = c.H, d = c.d;
-    const size_t Cp = (C + 63) / 64 * 64;
+    const size_t Cp = padded_capacity(c);
     w.wdT = take(E * H * d * es);
     w.wguT = take(E * d * 2 * H * es);
     w.a = take(E * C * H * es);
@@ -467,7 +474,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     char* base = static_cast<char*>(ws);
     auto at = [&](size_t off) { return reinterpret_cast<T*>(base + off); };
     const int E = c.E, C = c.capacity, H = c.H, d = c.d, Tn = c.T;
-    const int Cp = (C + 63) / 64 * 64;
+    const int Cp = padded_capacity(c);
     const unsigned cd = (d + kTile - 1) / kTile, cH = (H + kTile - 1) / kTile, cC = Cp / kTile;
     hipError_t err;
 #define ETR_BW(call) do { if ((err = (call)) != hipSuccess) return err; } while (0)

@@ -475,6 +475,18 @@ __device__ __forceinline__ void store_blocks_staged16(const GemmParams& p, const
 typedef const __attribute__((address_space(1))) void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
+// Ragged contractions (TAIL instantiations of the persistent kernels).  A copy into LDS cannot be masked per lane
+// without leaving stale data behind, so the lanes whose 16-byte piece lies past the end of the contraction ask a
+// buffer descriptor for an offset past its range: such a lane reads nothing and zeros land in its LDS slot.  The
+// descriptor spans all but the last 256 bytes of 4 GiB from the tile's base; real offsets stay below it (a launch
+// condition), so the check never touches a piece that exists.
+constexpr uint32_t kBufferRange = 0xFFFFFF00u, kPastRange = 0xFFFFFF80u;
+__device__ __forceinline__ void buffer_copy_to_lds(uint32_t base_lo, uint32_t base_hi, uint32_t off, uint4* dst) {
+    void* base = reinterpret_cast<void*>((static_cast<uint64_t>(base_hi) << 32) | base_lo);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(kBufferRange), 0x00027000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr)dst, 16, static_cast<int>(off), 0, 0, 0);
+}
+
 // ---------------------------------------------------------------------------------------
 // Pipelined bf16 MFMA grouped GEMM (launched for K % 64 == 0; one workgroup per tile; the fall-back of the
 // persistent kernels below): 256 x 256 staged rows, BK = 32, a ring of four 32 KiB LDS buffers.
@@ -666,10 +678,15 @@ constexpr int kMaxSuperWide = 2048;      // the same for the 64-wide kernel, who
 // reads its row number; the per-lane source address of a copy is then
 // base + row * row bytes + the lane's fixed column offset.  Every row number is clamped into [0, k_rows), so a
 // stale or foreign ring word can at worst fetch a wrong but existing row.
-template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0>
+//
+// TAIL (row-major A, transposed B): the contraction, or each half of a split one, need not be whole k-tiles.  The
+// last k-tile of it is short: pieces of a token row and whole weight rows past its end are zero-filled
+// (buffer_copy_to_lds).
+template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0, bool TAIL = false>
 __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
     static_assert(!(GLU && TRB), "the transposed B operand is for plain products");
     static_assert(KG == 0 || (KG == 1 && TRA) || (KG == 2 && TRB), "the gathered operand is a transposed one");
+    static_assert(!TAIL || (TRB && !TRA && KG == 0), "short k-tiles: row-major A, transposed B");
     constexpr int IDX_AHEAD = 7, IDX_SLOTS = 16;        // index prefetch distance in k-tiles, ring slots of 32 indices
     constexpr int BM = 256, BR = 256, CPR = 4, NBUF = 4, AHEAD = NBUF - 1;
     constexpr int BN = GLU ? 128 : 256;
@@ -689,6 +706,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
     const size_t stepA = TRA ? static_cast<size_t>(32) * KCA * 16 : CPR * 16;
     const size_t stepB = TRB ? static_cast<size_t>(32) * KCB * 16 : CPR * 16;
     const bool splitB = TRB && p.B1 != nullptr;
+    // TAIL: contraction length and k-tiles of the whole product, or of each half of a split one
+    const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 31) / 32;
+    const int k_rem = (Kh & 31) ? (Kh & 31) : 32;        // valid k of the last k-tile
+    const bool over_a = TAIL && 8 * ((lane & 3) ^ ((lane >> 4) & 3)) >= k_rem;           // this lane's piece of a token row
+    const bool over_b[2] = {TAIL && (lane >> 2) >= k_rem, TAIL && 16 + (lane >> 2) >= k_rem};   // its k row, per copy
     const uint32_t kg_row_bytes = static_cast<uint32_t>(KG == 1 ? KCA : KCB) * 16u;
     int32_t* idx_ring = reinterpret_cast<int32_t*>(lds_raw + static_cast<size_t>(NBUF) * STAGE * 16);
 
@@ -765,7 +787,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
         const int mt = mg * p.SM + u % vm, nt = ng * p.SN + u / vm;
         t.e = e; t.m0 = mt * BM; t.n0 = nt * BN;
         t.count = group_rows(p, e);
-        t.KT = group_k(p, e) / 32;
+        t.KT = TAIL ? (splitB ? 2 * KTh : KTh) : group_k(p, e) / 32;
         if constexpr (KG == 1) t.Abase = reinterpret_cast<const char*>(p.A);
         else if constexpr (TRA) t.Abase = reinterpret_cast<const char*>(p.A) + static_cast<size_t>(e) * p.K * KCA * 16;
         else t.Abase = reinterpret_cast<const char*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * KCA * 16);
@@ -805,14 +827,29 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
         const int kk = second ? k - (kt_count >> 1) : k;
         return reinterpret_cast<uint64_t>(second ? b1 : b0) + kk * stepB;
     };
+    // address of k-tile k of the A operand
+    auto a_ktile = [&](const char* a, int k) -> uint64_t {
+        if constexpr (TAIL) {
+            const bool second = splitB && k >= KTh;
+            return reinterpret_cast<uint64_t>(a) + (second ? static_cast<size_t>(Kh) * 2 + (k - KTh) * stepA : k * stepA);
+        }
+        return reinterpret_cast<uint64_t>(a) + k * stepA;
+    };
+    auto short_ktile = [&](int k) { return TAIL && (k == KTh - 1 || k == 2 * KTh - 1); };
+    static_assert(NCP == 2, "over_b holds one flag per copy");
     // copy j (0..NCP-1: A row groups, NCP..2NCP-1: B row groups) of k-tile k of tile t into the ring slot of step g
     auto issue_copy = [&](const Tile& t, int k, int g, int j, uint32_t row_off) {
         uint4* dst = lds + (g & (NBUF - 1)) * STAGE + (j / NCP) * (BM * CPR) + (wave * NCP + (j % NCP)) * 64;
         const bool gathered = (KG == 1 && j < NCP) || (KG == 2 && j >= NCP);
         const uint64_t b64 = gathered ? reinterpret_cast<uint64_t>(j < NCP ? t.Abase : t.Bbase)
-                           : j < NCP ? reinterpret_cast<uint64_t>(t.Abase) + k * stepA : b_ktile(t.Bbase, t.Bbase1, t.KT, k);
+                           : j < NCP ? a_ktile(t.Abase, k) : b_ktile(t.Bbase, t.Bbase1, t.KT, k);
         const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
         const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
+        if constexpr (TAIL) {
+            const bool past = short_ktile(k) && (j < NCP ? over_a : over_b[j - NCP]);
+            buffer_copy_to_lds(lo, hi, past ? kPastRange : t.off[j], dst);
+            return;
+        }
         const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
         __builtin_amdgcn_global_load_lds((global_cptr)(base + t.off[j] + row_off), (lds_ptr)dst, 16, 0, 0);
     };
@@ -1028,11 +1065,16 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
             const char* srcA = in_cur ? cur.Abase : nxt.Abase;
             const char* srcB0 = in_cur ? cur.Bbase : nxt.Bbase;
             const char* srcB1 = in_cur ? cur.Bbase1 : nxt.Bbase1;
-            const uint64_t baseA = reinterpret_cast<uint64_t>(srcA) + kf * stepA;
+            const uint64_t baseA = a_ktile(srcA, kf);
             const uint64_t baseB = b_ktile(srcB0, srcB1, in_cur ? KT : nxt.KT, kf);
             uint32_t offs[2 * NCP];
 #pragma unroll
             for (int j = 0; j < 2 * NCP; ++j) offs[j] = in_cur ? cur.off[j] : nxt.off[j];
+            if constexpr (TAIL) {
+                const bool sk = short_ktile(kf);
+#pragma unroll
+                for (int j = 0; j < 2 * NCP; ++j) offs[j] = sk && (j < NCP ? over_a : over_b[j % NCP]) ? kPastRange : offs[j];
+            }
 
             auto copy = [&](int j) {
                 uint4* dst = lds + ((g + AHEAD) & (NBUF - 1)) * STAGE + (j / NCP) * (BM * CPR) + (wave * NCP + (j % NCP)) * 64;
@@ -1040,6 +1082,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
                 const uint64_t b64 = gathered ? reinterpret_cast<uint64_t>(j < NCP ? srcA : srcB0) : j < NCP ? baseA : baseB;
                 const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
                 const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
+                if constexpr (TAIL) {
+                    buffer_copy_to_lds(lo, hi, offs[j], dst);
+                    return;
+                }
                 const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
                 __builtin_amdgcn_global_load_lds((global_cptr)(base + offs[j]), (lds_ptr)dst, 16, 0, 0);
             };
@@ -1206,7 +1252,11 @@ __device__ __forceinline__ void live_tile_prefix(const GemmParams& p, int BM, in
 // 1.49 GHz: the same time.  One wave per SIMD with 128 x 128 slices (a third fewer LDS bytes per flop) needs
 // 2700-2900 cycles of issue alone.  One memory instruction behind each MFMA instead of groups: the same time.
 // ---------------------------------------------------------------------------------------
-template <bool GLU, bool DUAL = false, bool KEEP = false>
+//
+// TAIL: the contraction need not be whole k-tiles (K % 8 == 0 suffices); the 16-byte pieces of the last k-tile that
+// lie past its end are zero-filled by the copy (buffer_copy_to_lds).  An instantiation of its own, so that the plain
+// one keeps its address forms and scalar registers.
+template <bool GLU, bool DUAL = false, bool KEEP = false, bool TAIL = false>
 __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p) {
     static_assert(!KEEP || (GLU && !DUAL), "the pre-activations are kept by the SwiGLU epilogue only");
     constexpr int NW = 8;                                // waves: 2 (token halves) x 4 (weight quarters)
@@ -1246,6 +1296,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     const uint32_t laneB[2] = {(static_cast<uint32_t>(lane >> 3) * KCB + ((lane & 7) ^ ((lane >> 4) & 7))) * 16u,
                                (static_cast<uint32_t>(lane >> 3) * KCB + ((lane & 7) ^ ((lane >> 4) & 7) ^ 4)) * 16u};
     const uint64_t strideB8 = static_cast<uint64_t>(8) * KCB * 16;      // 8 weight rows further on
+    // TAIL: whether this lane's piece of the last k-tile lies past the contraction, for row groups of even / odd index
+    // (the swizzle term of a lane is the same for both operands: a wave's rows start at a multiple of 32)
+    const bool over[2] = {TAIL && 8 * c0 >= (p.K & 63), TAIL && 8 * (c0 ^ 4) >= (p.K & 63)};
 
     auto decode = [&](int q, Tile& t) {                  // scalar part of the tile with list index q
         int lo = 0, hi = S;                              // largest s with pre[s] <= q
@@ -1263,7 +1316,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
         // neighbour once more and stores the same values, and no weight-row address or store needs a bound)
         t.e = e; t.m0 = mt * BM; t.n0 = min(nt * BN, p.N - BN);
         t.count = group_rows(p, e);
-        t.KT = group_k(p, e) / 64;
+        t.KT = TAIL ? (p.K + 63) / 64 : group_k(p, e) / 64;
         t.Abase = reinterpret_cast<uint64_t>(p.A) + (gather ? 0 : static_cast<uint64_t>(e) * p.capacity * KCA * 16);
         // this wave's staged weight rows: GLU stages 128 gate rows, then the 128 up rows of the same columns
         const int nrow = t.n0 + (GLU ? (wave % (NW / 2)) * WROWS : wave * WROWS);
@@ -1295,15 +1348,20 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     auto copy_to = [&](uint64_t b64, uint32_t off, uint4* dst) {
         const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
         const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
-        const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-        __builtin_amdgcn_global_load_lds((global_cptr)(base + off), (lds_ptr)dst, 16, 0, 0);
+        if constexpr (TAIL) {
+            buffer_copy_to_lds(lo, hi, off, dst);
+        } else {
+            const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+            __builtin_amdgcn_global_load_lds((global_cptr)(base + off), (lds_ptr)dst, 16, 0, 0);
+        }
     };
-    // token-row group i / weight-row group i of the k-tile at abase / bbase into buffer buf
+    // token-row group i / weight-row group i of the k-tile at abase / bbase into buffer buf; `last`: the short k-tile
     auto copy_a = [&](uint64_t abase, uint32_t off, int buf, int i) {
         copy_to(abase, off, lds + buf * STAGE + (wave * NCP + i) * 64);
     };
-    auto copy_b = [&](uint64_t bbase, int buf, int i) {
-        copy_to(bbase + i * strideB8, laneB[i & 1], lds + buf * STAGE + BM * CPR + (wave * NCP + i) * 64);
+    auto copy_b = [&](uint64_t bbase, int buf, int i, bool last) {
+        const uint32_t off = TAIL && last && over[i & 1] ? kPastRange : laneB[i & 1];
+        copy_to(bbase + i * strideB8, off, lds + buf * STAGE + BM * CPR + (wave * NCP + i) * 64);
     };
 
     // fragments: fah[h][i] = token block 4 h + i, fbk[ks][j] = weight block j of k-step ks
@@ -1357,7 +1415,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 #pragma unroll
         for (int i = 0; i < NCP; ++i) copy_a(cur.Abase + t * 128, cur.offA[i], t, i);
 #pragma unroll
-        for (int i = 0; i < NCP; ++i) copy_b(cur.Bbase + t * 128, t, i);
+        for (int i = 0; i < NCP; ++i) copy_b(cur.Bbase + t * 128, t, i, false);   // (TAIL: KT >= 3)
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * NCP, false));             // the first k-tile (copies retire in order)
     __builtin_amdgcn_s_barrier();
@@ -1365,6 +1423,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     for (int i = 0; i < 4; ++i) { read_a(0, 0, 0, i); read_b(0, 0, i); }
     uint64_t lateB = cur.Bbase + 128;                    // weight rows still owed to the other buffer (none yet:
                                                          // the second k-tile's own once more)
+    bool late_last = false;                              // they belong to a short k-tile
     for (;;) {
         const int qn = q + 8 * GS;                       // same XCD, next round
         const bool has_next = qn < total;
@@ -1395,12 +1454,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
             uint32_t offs[NCP];
 #pragma unroll
             for (int i = 0; i < NCP; ++i) offs[i] = from_next ? nxt.offA[i] : cur.offA[i];
+            const bool last = TAIL && kf == KT - 1;      // (every tile has the same KT here)
+            if constexpr (TAIL) {
+#pragma unroll
+                for (int i = 0; i < NCP; ++i) offs[i] = last && over[i & 1] ? kPastRange : offs[i];
+            }
             const int buf = g & 1;
             __builtin_amdgcn_sched_barrier(0);
             substep(0, [&](int m) {                      // token blocks 4..7 of this k-step, half of the next k-step's weights,
                 if (m < 4) read_a(buf, 0, 1, m);         // and the weight rows of k-tile g + 1 into the other buffer
                 else if (m < 6) read_b(buf, 1, m - 4);
-                if (m < 8 && (m & 1)) copy_b(lateB, buf ^ 1, m >> 1);
+                if (m < 8 && (m & 1)) copy_b(lateB, buf ^ 1, m >> 1, late_last);
             });
             substep(1, [&](int m) {
                 if (m < 4) read_a(buf, 1, 0, m);
@@ -1419,6 +1483,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
                 if (m < 8 && (m & 1)) copy_a(baseA, offs[m >> 1], buf, m >> 1);
             });
             lateB = baseB;
+            late_last = last;
         }
         // ---- epilogue of cur (the copies of the next tile are in flight)
         store_blocks_staged16<GLU, DUAL, KEEP>(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * (GLU ? 32 : 64), cur.count, lane,
@@ -1541,11 +1606,21 @@ hipError_t launch_bf16_ring(GemmParams p, hipStream_t st) {
 
 // Persistent ring kernel: needs every group's contraction length >= 96 (three k-tiles to prefetch)
 // and the super-tile prefix to fit in LDS.
-template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0>
+template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0, bool TAIL = false>
 hipError_t launch_bf16_persist(GemmParams p, hipStream_t st, int n_cu) {
     constexpr size_t lds = 4ull * 512 * 32 * 2 + (KG != 0 ? 16 * 32 * 4 : 0);        // (+ the ring of row numbers)
     plan_tiles(p, 256, GLU ? 128 : 256);
-    auto kern = gemm_bf16_persist_kernel<GLU, DUAL, TRA, TRB, KG>;
+    auto kern = gemm_bf16_persist_kernel<GLU, DUAL, TRA, TRB, KG, TAIL>;
+    hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
+    return hipGetLastError();
+}
+template <bool GLU, bool DUAL = false, bool KEEP = false, bool TAIL = false>
+hipError_t launch_bf16_persistent_form(GemmParams p, hipStream_t st, int n_cu) {
+    constexpr size_t lds = 2ull * 512 * 64 * 2;                             // two buffers of 256 + 256 rows x 64 bf16
+    plan_tiles(p, 256, GLU ? 128 : 256, true);
+    auto kern = gemm_bf16_persistent_kernel<GLU, DUAL, KEEP, TAIL>;
     hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
@@ -1553,13 +1628,8 @@ hipError_t launch_bf16_persist(GemmParams p, hipStream_t st, int n_cu) {
 }
 template <bool GLU, bool DUAL = false, bool KEEP = false>
 hipError_t launch_bf16_persistent(GemmParams p, hipStream_t st, int n_cu) {
-    constexpr size_t lds = 2ull * 512 * 64 * 2;                             // two buffers of 256 + 256 rows x 64 bf16
-    plan_tiles(p, 256, GLU ? 128 : 256, true);
-    auto kern = gemm_bf16_persistent_kernel<GLU, DUAL, KEEP>;
-    hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
-    return hipGetLastError();
+    return p.K % 64 == 0 ? launch_bf16_persistent_form<GLU, DUAL, KEEP, false>(p, st, n_cu)
+                         : launch_bf16_persistent_form<GLU, DUAL, KEEP, true>(p, st, n_cu);
 }
 // the 64-wide persistent kernel bounds no weight-row address: at least one whole column tile, and 16-byte stores
 // (its ragged last tile overlaps the one before)
@@ -1585,12 +1655,23 @@ size_t ffn_ws_bytes(const etr_config& c) {
     return align_up(static_cast<size_t>(c.E) * c.capacity * c.H * elt_bytes(c.dtype));
 }
 
-// The pipelined kernels need K % 64 == 0 (copies cannot zero-fill a K tail) and 32-bit byte
-// offsets inside one operand; everything else takes the register-staged kernel.
-static bool pipelined_ok(const GemmParams& g, size_t a_rows) {
+// Which kernel a row-major bf16 product takes.  Both pipelined kernels need 32-bit byte offsets inside one operand.
+//   PERSISTENT  at least one whole column tile, a contraction of 128 or more, the super-tile prefix in LDS.  A
+//               contraction that is not whole 64-wide k-tiles takes its zero-filling instantiation (per-group lengths
+//               are always whole k-tiles).  12 experts of 135-938 rows, 1080 x 2744 (K % 64 = 56): 262 -> 150 us for
+//               the gate/up product, 242 -> 95 us for the down one against the register-staged kernel.
+//   RING        whole k-tiles where the persistent kernel does not apply (narrow outputs, short contractions)
+//   STAGED      everything else
+enum class Bf16Kernel { PERSISTENT, RING, STAGED };
+static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows) {
     const size_t a_row_bytes = static_cast<size_t>(g.lda ? g.lda : g.K) * 2, b_row_bytes = static_cast<size_t>(g.ldb ? g.ldb : g.K) * 2;
-    return g.K % 64 == 0 && a_row_bytes % 16 == 0 && b_row_bytes % 16 == 0 && a_rows * a_row_bytes < (1ull << 32) &&
-           static_cast<size_t>(g.N) * b_row_bytes < (1ull << 32);
+    const size_t a_bytes = a_rows * a_row_bytes, b_bytes = static_cast<size_t>(g.N) * b_row_bytes;
+    if (g.K % 8 != 0 || a_row_bytes % 16 != 0 || b_row_bytes % 16 != 0 || a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32))
+        return Bf16Kernel::STAGED;
+    const bool whole = g.K % 64 == 0;
+    if (!whole && (g.k_counts || a_bytes >= kBufferRange || b_bytes >= kBufferRange)) return Bf16Kernel::STAGED;
+    if (persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu)) return Bf16Kernel::PERSISTENT;
+    return whole ? Bf16Kernel::RING : Bf16Kernel::STAGED;
 }
 
 // General entry for the other stages of the library: grouped "NT" product
@@ -1606,17 +1687,21 @@ static GemmParams params_of(const GroupedGemm& q) {
 // Operands stored with the contraction index slow run only on the persistent bf16 kernel.
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !(q.ta || q.tb)) return false;
-    if (q.K < 128 || q.K % 64 != 0 || q.N % 4 != 0) return false;
+    // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
+    const bool tail_form = q.tb && !q.ta && !q.k_counts;
+    const int half_k = q.B1 ? q.K / 2 : q.K;
+    if (q.K < 128 || half_k % (tail_form ? 8 : 64) != 0 || q.N % 4 != 0) return false;
     if (q.tb && (q.N % 8 != 0 || q.N < 8)) return false;           // 16-byte chunks along the rows of a [K][rows] operand
     if (q.ta && (q.M % 8 != 0 || q.M < 8)) return false;
     const int lda = q.lda ? q.lda : q.K, ldb = q.ldb ? q.ldb : q.K;
     if (lda % 8 != 0 || ldb % 8 != 0) return false;
     if (q.ta && (q.row_index || q.m_counts)) return false;
-    if (q.B1 && !(q.tb && q.K % 128 == 0 && !q.k_counts)) return false;          // split B: two halves of whole k-tiles
+    if (q.B1 && !(tail_form && q.K % 2 == 0)) return false;                      // split B: two halves of the contraction
     // 32-bit per-lane offsets inside one k-tile / one operand
     const size_t a_span = q.ta ? 32ull * lda * 2 : (q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M)) * lda * 2;
     const size_t b_span = q.tb ? 32ull * ldb * 2 : static_cast<size_t>(q.N) * ldb * 2;
-    if (a_span >= (1ull << 32) || b_span >= (1ull << 32)) return false;
+    const size_t limit = half_k % 32 == 0 ? (1ull << 32) : kBufferRange;          // zero-filling copies: see buffer_copy_to_lds
+    if (a_span >= limit || b_span >= limit) return false;
     if (q.split_m && (!q.ta || q.split_m % 32 != 0 || q.M != 2 * q.split_m || !q.C2 || q.m_counts)) return false;
     if (q.k_gather) {
         // gathered contraction rows: both operands transposed, eight k-tiles per group at least, 32-bit row offsets
@@ -1636,13 +1721,18 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
         if (q.k_gather == 1) return launch_bf16_persist<false, false, true, true, 1>(g, st, n_cu);
         if (q.k_gather == 2) return launch_bf16_persist<false, false, true, true, 2>(g, st, n_cu);
         if (q.ta && q.tb) return launch_bf16_persist<false, false, true, true>(g, st, n_cu);
-        if (q.tb) return launch_bf16_persist<false, false, false, true>(g, st, n_cu);
+        if (q.tb) {
+            // a contraction (or half of a split one) that is not whole 32-wide k-tiles: the zero-filling instantiation
+            return (q.B1 ? q.K / 2 : q.K) % 32 == 0 ? launch_bf16_persist<false, false, false, true>(g, st, n_cu)
+                                                    : launch_bf16_persist<false, false, false, true, 0, true>(g, st, n_cu);
+        }
         return launch_bf16_persist<false, false, true, false>(g, st, n_cu);
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;
-        const bool ring = pipelined_ok(g, q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M));
-        if (ring && persist_ok(g, q.epilogue != GEMM_PLAIN, kMaxSuperWide) && whole_column_tiles(g, q.epilogue != GEMM_PLAIN)) {
+        const Bf16Kernel kind = choose_bf16(g, q.epilogue != GEMM_PLAIN, q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M));
+        const bool ring = kind == Bf16Kernel::RING;
+        if (kind == Bf16Kernel::PERSISTENT) {
             const int n_cu = cu_count();
             switch (q.epilogue) {
                 case GEMM_PLAIN: return launch_bf16_persistent<false>(g, st, n_cu);
@@ -1669,7 +1759,10 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
 bool ffn_can_gather(const etr_config& c) {
     if (c.dtype != ETR_BF16) return false;
     GemmParams g1{nullptr, nullptr, nullptr, nullptr, nullptr, c.E, c.capacity, c.H, c.d, 0, 0, 0, 0, nullptr, c.T};
-    return pipelined_ok(g1, static_cast<size_t>(c.T));
+    // every kernel reads its rows through an index if asked; only a token matrix past the 32-bit offsets of the
+    // pipelined kernels is better rearranged first, where the per-expert buffers are within them
+    return choose_bf16(g1, true, static_cast<size_t>(c.T)) != Bf16Kernel::STAGED ||
+           choose_bf16(g1, true, static_cast<size_t>(c.capacity)) == Bf16Kernel::STAGED;
 }
 
 hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t* counts, const void* w_gate,
@@ -1683,16 +1776,16 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
     hipError_t err;
     if (c.dtype == ETR_BF16) {
         if (gather_rows && !ffn_can_gather(c)) return hipErrorInvalidValue;
-        const bool pipe1 = pipelined_ok(g1, gather_rows ? static_cast<size_t>(c.T) : static_cast<size_t>(c.capacity));
+        const Bf16Kernel kind1 = choose_bf16(g1, true, gather_rows ? static_cast<size_t>(c.T) : static_cast<size_t>(c.capacity));
+        const Bf16Kernel kind2 = choose_bf16(g2, false, static_cast<size_t>(c.capacity));
         const int n_cu = cu_count();
-        if (pipe1 && persist_ok(g1, true, kMaxSuperWide) && whole_column_tiles(g1, true))
+        if (kind1 == Bf16Kernel::PERSISTENT)
             err = g1.C3 ? launch_bf16_persistent<true, false, true>(g1, st, n_cu) : launch_bf16_persistent<true>(g1, st, n_cu);
-        else err = (pipe1 && !g1.C3) ? launch_bf16_ring<true, 4>(g1, st) : launch_bf16<128, 64, 64, 2, 2, true, 1>(g1, st);
+        else err = (kind1 == Bf16Kernel::RING && !g1.C3) ? launch_bf16_ring<true, 4>(g1, st) : launch_bf16<128, 64, 64, 2, 2, true, 1>(g1, st);
         if (err != hipSuccess) return err;
         if (between && (err = hipEventRecord(between, st)) != hipSuccess) return err;
-        if (!pipelined_ok(g2, c.capacity)) return launch_bf16<128, 128, 64, 2, 2, false, 1>(g2, st);
-        if (persist_ok(g2, false, kMaxSuperWide) && whole_column_tiles(g2, false)) return launch_bf16_persistent<false>(g2, st, n_cu);
-        return launch_bf16_ring<false, 4>(g2, st);
+        if (kind2 == Bf16Kernel::STAGED) return launch_bf16<128, 128, 64, 2, 2, false, 1>(g2, st);
+        return kind2 == Bf16Kernel::PERSISTENT ? launch_bf16_persistent<false>(g2, st, n_cu) : launch_bf16_ring<false, 4>(g2, st);
     }
     if (gather_rows) return hipErrorInvalidValue;
     err = launch_f32<true>(g1, st);

@@ -1,0 +1,50 @@
+"""Layer widths that are no multiple of the GEMM kernels' k-tiles: the pipelined kernels zero-fill the end of the last
+k-tile (forward, recomputation and kept pre-activations on the 64-wide kernel, u and the input gradient on the 32-wide
+transposing one), and a capacity below 128 rows takes the same path on padded buffers."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_00023_amd import binding as B
+from paper_2406_00023_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# (d, H, capacity): the contraction of the gate/up product is d, that of the down product H, that of the input gradient
+# twice H; remainders of 8, 24, 32, 40 and 56 past whole 64s, the shortest contraction the kernels take (three k-tiles),
+# one and two row tiles, a capacity of 40 (padded to 128 contraction rows)
+@pytest.mark.parametrize("d,Hh,C", [(264, 184, 500), (280, 136, 300), (312, 160, 500), (296, 152, 40), (288, 296, 129),
+                                    (1080, 2744, 260)])
+def test_ragged_widths_forward_and_backward(oracle, d, Hh, C):
+    import gpu_helpers as H
+    from test_gpu_backward import Backward, _err
+    B.load_library()
+    shape = I.EtrShape("ragged", 11, T=600, d=d, E=3, D=8, k=2, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR,
+                       recipe="bias")
+    print(f"ragged widths d={d} H={Hh} C={C}", flush=True)
+    L = H.GpuLayer(shape)
+    hx = L.host_inputs()
+    L.forward()
+    r = H.check_routing_against_oracle(oracle, L, hx)
+    H.check_output_against_oracle(oracle, L, hx, r["score"])
+    bw = Backward(H, shape, shape.mode)                  # (its workspace is filled with NaN patterns)
+    hb = bw.host()
+    ref = oracle.moe_backward(hb["x"], hb["w_emb"], hb["w_gate"], hb["w_up"], hb["w_down"], hb["slot_of"], hb["dout"],
+                              D=shape.D, dtype=shape.dtype)
+    for got, key in ((bw.dx, "dx"), (bw.dwg, "dw_gate"), (bw.dwu, "dw_up"), (bw.dwd, "dw_down")):
+        assert _err(H, oracle, got, ref[key], shape.dtype) <= H.TOL_OUT[shape.dtype], key
+    # kept pre-activations: the same output and, through the backward, the same bits as the recomputation
+    t, cfg = L.t, L.cfg
+    a, b = (torch.empty(shape.E, C, Hh, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    out = torch.empty_like(L.out)
+    B.etr_moe_forward_train(cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], out, a, b,
+                            B.alloc_workspace(B.etr_workspace_bytes(cfg)))
+    dx, dwg, dwu, dwd = (torch.empty_like(v) for v in (bw.dx, bw.dwg, bw.dwu, bw.dwd))
+    B.etr_moe_backward(cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], bw.L.score, bw.L.gate, bw.L.slot_of,
+                       bw.L.slot_token, bw.L.counts, bw.dout, dx, dwg, dwu, dwd,
+                       B.alloc_workspace(B.etr_backward_workspace_bytes(cfg)), a_saved=a, b_saved=b)
+    torch.cuda.synchronize()
+    assert torch.equal(out, L.out)
+    for got, want in ((dx, bw.dx), (dwg, bw.dwg), (dwu, bw.dwu), (dwd, bw.dwd)):
+        assert np.array_equal(H.to_np(got), H.to_np(want))
