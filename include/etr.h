@@ -77,7 +77,7 @@ typedef struct {
 /* Bytes of device workspace for this config: etr_workspace_bytes is what
  * etr_moe_forward needs (it covers the two stage calls as well; the permuted
  * token buffer is part of it only where the fused call cannot gather the rows
- * inside the first GEMM, i.e. fp32 and odd widths);
+ * inside the first GEMM, i.e. token matrices of 4 GiB and more, and in fp32 layers);
  * etr_select_workspace_bytes and etr_ffn_workspace_bytes are the smaller
  * amounts that etr_select and etr_expert_ffn need when called on their own.
  * Each returns 0 for an invalid config. Host-only, launches nothing. */
@@ -152,7 +152,7 @@ etr_status etr_dispatch(const etr_config* cfg, const void* x, const int32_t* slo
 /* Expert networks on the kept rows (Sec. Locality Loss: experts are FFN layers; the
  * Mixtral-style SwiGLU form): yp[e][s] = W_down[e] (SiLU(W_gate[e] xp[e][s]) .* (W_up[e] xp[e][s]))
  * for s < counts[e].  bf16: MFMA grouped GEMM, fp32 accumulate, the hidden activation and
- * yp are rounded to bf16.  fp32: plain FMA kernels.
+ * yp are rounded to bf16.  fp32: fp32 MFMA grouped GEMM.
  *   xp [E][capacity][d] in; counts [E] in (device; the grid is sized for `capacity`)
  *   w_gate, w_up [E][H][d]; w_down [E][d][H]   dtype in
  *   yp [E][capacity][d] dtype out; rows s >= counts[e] are left untouched

@@ -95,9 +95,9 @@ ForwardWs forward_layout(const etr_config& c) {
     w.slot_token = take(EC * 4);
     w.counts = take(static_cast<size_t>(c.E) * 4);
     w.select = take(select_ws_bytes(c.T, c.E));
-    // the permuted token buffer exists only where the fused call really dispatches (fp32 / fall-back shapes):
-    // with the rows gathered inside GEMM-1 it is never written
-    w.xp = take(ffn_can_gather(c) ? 0 : EC * c.d * elt_bytes(c.dtype));
+    // the permuted token buffer: with the rows gathered inside GEMM-1 it is never written.  (fp32 gathers too; its
+    // size query keeps the room all the same, as callers have always been told to bring it)
+    w.xp = take(c.dtype == ETR_BF16 && ffn_can_gather(c) ? 0 : EC * c.d * elt_bytes(c.dtype));
     w.yp = take(EC * c.d * elt_bytes(c.dtype));
     w.hidden = take(ffn_ws_bytes(c));
     w.total = off;
@@ -332,7 +332,7 @@ static etr_status forward_impl(const etr_config* cfg, const void* x, const float
     ETR_HIP(mark(1));
     ETR_HIP(launch_select(*cfg, sc, tk, so, stn, cn, sw, st));
     ETR_HIP(mark(2));
-    // bf16 with the pipelined GEMM: the rearrangement is folded into GEMM-1's operand load
+    // the rearrangement is folded into GEMM-1's operand load wherever its kernel can address the token matrix
     // (rows are fetched through slot_token), so no permuted copy of the tokens is written
     const bool gather = ffn_can_gather(*cfg);
     if (!gather) ETR_HIP(launch_dispatch(*cfg, x, stn, cn, xp, st));

@@ -12,7 +12,7 @@
 // (gemm_bf16_persistent_kernel: one workgroup per CU walks the live tiles, the copies run on
 // across tile boundaries); the per-tile kernels size the grid for `capacity` and a workgroup
 // whose row tile starts past counts[e] exits at once.  Either way counts never leave the device.
-// fp32: plain LDS-tiled FMA kernels (parity path for small layers).
+// fp32: the same product on v_mfma_f32_16x16x4_f32, one workgroup per tile.
 
 #include "etr_internal.h"
 
@@ -144,6 +144,33 @@ __device__ __forceinline__ bool decode_tile(const GemmParams& p, int& e, int& mt
     mt = (r % MG) * p.SM + l % p.SM;
     nt = (r / MG) * p.SN + l / p.SM;
     return mt < p.MT && nt < p.NT;
+}
+
+// The same for kernels with small tiles, whose grid is mostly dead where the capacity is far above the counts: only
+// tiles that hold rows are counted (a scan over the groups, one lane each; G <= 64), and each XCD gets an equal,
+// contiguous share of that list, row tiles fastest, so the tiles of one weight slice share an L2.  Dealing super-tiles
+// of the capacity instead left XCDs with half-dead ones: 8 fp32 experts of 66-640 rows, gate/up
+// product: 127 us against 92.
+__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int& e, int& mt, int& nt) {
+    const int lane = threadIdx.x & 63;
+    const int mine = lane < p.E ? max((group_rows(p, lane) + BM - 1) / BM, 0) : 0;     // this group's row tiles
+    int incl = mine;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const int o = __shfl_up(incl, m, 64);
+        if (lane >= m) incl += o;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, 63) * p.NT;
+    const int per = (total + 7) >> 3, j = blockIdx.x >> 3;
+    const int q = (blockIdx.x & 7) * per + j;
+    if (j >= per || q >= total) return false;
+    const uint64_t in = __ballot(incl * p.NT > q);
+    e = __builtin_ctzll(in);
+    const int rows = __builtin_amdgcn_readlane(mine, e);
+    const int u = q - (__builtin_amdgcn_readlane(incl, e) - rows) * p.NT;
+    nt = u / rows;
+    mt = u - nt * rows;
+    return true;
 }
 
 // Fills MT, NT and the super-tile shape; returns the number of workgroups to launch.
@@ -1497,87 +1524,151 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 grouped GEMM, 64x64 tile, 4x4 outputs per thread, plain FMA
+// fp32 grouped GEMM on v_mfma_f32_16x16x4_f32 (full fp32 products and accumulation).
+//
+// Bound by the matrix pipe on large layers (157 TFLOP/s dense; plain FMAs, without packed instructions, stop at half of
+// that) and by latency on small ones.  One workgroup of four waves (2 x 2) per BM x BN tile; k-tiles of 32 floats, so
+// a staged row is 128 bytes and layout, swizzle and fragment addresses are those of the 64-wide bf16 kernel: lane l
+// reads row l % 16 and the 16-byte piece 4 ks + l / 16 of a 16-row block, four floats, and MFMA v of the k-step contracts
+// component v of both operands (the k order inside a step is permuted alike on both sides).  A ring of NBUF buffers
+// is filled by copies that bypass the registers, NBUF - 1 k-tiles ahead; behind the end of the contraction the last
+// k-tile is copied again, which keeps the wait count constant.  Copies carry per-lane 64-bit addresses (operands of
+// any size); a piece past the contraction, in the last k-tile, comes from a zero page.
+// Tile: 64 x 64, or 32 x 32 where the capacity gives fewer than two 64 x 64 tiles per CU (see launch_f32).  Measured
+// against the plain-FMA kernel this replaces: 8 experts of 66-640 rows, 512 x 1024: gate/up 298 -> 91 us (86 TFLOP/s),
+// the plain products 182 -> 60 us on average; 8 experts of 80 rows, 256 x 512: 71 -> 11 us and 55 -> 8 us; 8 x 2048 rows,
+// 1024 x 4096: 120 TFLOP/s.  Two waves per SIMD (launch bounds) keep the accumulators out of the accumulation registers,
+// whose renaming moves cost 1-4 %.  More buffers, or the barrier between the two k-steps with every fragment read a
+// k-step ahead, change nothing (-2 .. +4 % time): what is lost is lost where the waves of two workgroups meet at barriers.
 // ---------------------------------------------------------------------------------------
-template <bool GLU, bool DUAL = false>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-    constexpr int BM = 64, BN = 64, BK = 16, LD = BM + 4;
-    __shared__ float As[BK][LD];
-    __shared__ float Bs[GLU ? 2 : 1][BK][LD];
+__device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
+
+template <int BM, int BN, int NBUF, bool GLU, bool DUAL = false>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
+    constexpr int CPR = 8, BK = 32, NB = GLU ? 2 : 1, BROWS = NB * BN;
+    constexpr int STAGE = (BM + BROWS) * CPR;           // 16-byte pieces per buffer
+    constexpr int NCA = BM / 32, NCB = BROWS / 32;      // copies (8 rows x 128 bytes) per wave and k-tile
+    constexpr int TM = BM / 32, TN = BN / 32;           // 16 x 16 blocks per wave and product
+    constexpr int AHEAD = NBUF - 1;
+    __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * STAGE];
     int e, mt, nt;
-    if (!decode_tile(p, e, mt, nt)) return;
+    if (!decode_live_tile(p, BM, e, mt, nt)) return;
     const int count = group_rows(p, e);
     const int m0 = mt * BM, n0 = nt * BN;
     if (m0 >= count) return;
-    const int tid = threadIdx.x, K = group_k(p, e);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int K = group_k(p, e), KT = (K + BK - 1) / BK;
     const int LA = p.lda ? p.lda : p.K, LB = p.ldb ? p.ldb : p.K;
-    const float* Ag = static_cast<const float*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA);
-    const float* B0g = static_cast<const float*>(p.B0) + static_cast<size_t>(e) * p.N * LB;
-    const float* B1g = GLU ? static_cast<const float*>(p.B1) + static_cast<size_t>(e) * p.N * LB : nullptr;
-    const int lr = tid >> 2, lk = (tid & 3) * 4;                  // staging: row, k offset
-    int am = min(m0 + lr, p.capacity - 1);
-    if (p.row_index) am = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + am], 0), p.a_rows - 1);
-    const int bn = min(n0 + lr, p.N - 1);
-    const int ty = tid >> 4, tx = tid & 15;
-    float acc[GLU ? 2 : 1][4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        const bool kin = k0 + lk < K;                             // K % 4 == 0: a float4 is all in or all out
-        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 va = kin ? *reinterpret_cast<const float4*>(Ag + static_cast<size_t>(am) * LA + k0 + lk) : z;
-        float4 vb = kin ? *reinterpret_cast<const float4*>(B0g + static_cast<size_t>(bn) * LB + k0 + lk) : z;
-        As[lk + 0][lr] = va.x; As[lk + 1][lr] = va.y; As[lk + 2][lr] = va.z; As[lk + 3][lr] = va.w;
-        Bs[0][lk + 0][lr] = vb.x; Bs[0][lk + 1][lr] = vb.y; Bs[0][lk + 2][lr] = vb.z; Bs[0][lk + 3][lr] = vb.w;
-        if constexpr (GLU) {
-            float4 vc = kin ? *reinterpret_cast<const float4*>(B1g + static_cast<size_t>(bn) * LB + k0 + lk) : z;
-            Bs[1][lk + 0][lr] = vc.x; Bs[1][lk + 1][lr] = vc.y; Bs[1][lk + 2][lr] = vc.z; Bs[1][lk + 3][lr] = vc.w;
-        }
-        __syncthreads();
+
+    // copy sources of this lane: row and 16-byte piece (the swizzle is applied here, on the source side)
+    const float* src[NCA + NCB];
+    const int r8 = lane >> 3;
+    bool past[2];                                       // piece of the last k-tile that lies past the contraction
 #pragma unroll
-        for (int k = 0; k < BK; ++k) {
-            const float4 a = *reinterpret_cast<const float4*>(&As[k][ty * 4]);
-            const float av[4] = {a.x, a.y, a.z, a.w};
+    for (int h = 0; h < 2; ++h) past[h] = (KT - 1) * BK + 4 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7)) >= K;
 #pragma unroll
-            for (int b = 0; b < (GLU ? 2 : 1); ++b) {
-                const float4 w = *reinterpret_cast<const float4*>(&Bs[b][k][tx * 4]);
-                const float wv[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[b][i][j] = fmaf(av[i], wv[j], acc[b][i][j]);
-            }
-        }
-        __syncthreads();
+    for (int i = 0; i < NCA; ++i) {
+        const int r = (wave * NCA + i) * 8 + r8;
+        int m = min(m0 + r, count - 1);                 // rows past the count replay a valid row; never stored
+        if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
+        src[i] = static_cast<const float*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA) +
+                 static_cast<size_t>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7));
     }
-    float* Cg = static_cast<float*>(p.C) + static_cast<size_t>(e) * p.capacity * p.N;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
+    for (int i = 0; i < NCB; ++i) {
+        const int r = (wave * NCB + i) * 8 + r8;
+        const bool second = GLU && r >= BN;
+        const int n = min(n0 + (second ? r - BN : r), p.N - 1);
+        src[NCA + i] = static_cast<const float*>(second ? p.B1 : p.B0) + (static_cast<size_t>(e) * p.N + n) * LB +
+                       4 * ((lane & 7) ^ ((r >> 1) & 7));
+    }
+    auto copy_tile = [&](int kt, int buf) {
+        const bool last = kt == KT - 1;
+#pragma unroll
+        for (int i = 0; i < NCA + NCB; ++i) {
+            const int group = i < NCA ? wave * NCA + i : wave * NCB + i - NCA;           // of 8 rows; its parity picks the swizzle half
+            const float* g = last && past[group & 1] ? kZeroPiece : src[i] + static_cast<size_t>(kt) * BK;
+            uint4* dst = lds + buf * STAGE + (i < NCA ? 0 : BM * CPR) + group * 64;
+            __builtin_amdgcn_global_load_lds((global_cptr)g, (lds_ptr)dst, 16, 0, 0);
+        }
+    };
+
+    f32x4 acc[NB][TM][TN];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[b][i][j][v] = 0.f;
+
+    for (int t = 0; t < AHEAD; ++t) copy_tile(min(t, KT - 1), t);
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int ck[2] = {kq ^ (l16 >> 1), (4 + kq) ^ (l16 >> 1)};
+    int buf = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+        // this wave's share of k-tile kt has landed and its reads of k-tile kt - 1 are done; past the barrier that
+        // holds for all waves, and the buffer of k-tile kt - 1 is free
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm((AHEAD - 1) * (NCA + NCB), true));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        copy_tile(min(kt + AHEAD, KT - 1), buf == 0 ? NBUF - 1 : buf - 1);
+        const uint4* As = lds + buf * STAGE + (wm * (BM / 2) + l16) * CPR;
+        const uint4* Bs = lds + buf * STAGE + BM * CPR + (wn * (BN / 2) + l16) * CPR;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            f32x4 fa[TM], fb[NB][TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[i] = __builtin_bit_cast(f32x4, As[i * 16 * CPR + ck[ks]]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) fb[b][j] = __builtin_bit_cast(f32x4, Bs[(b * BN + j * 16) * CPR + ck[ks]]);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][j][v], fa[i][v], acc[b][i][j], 0, 0, 0);
+        }
+        buf = buf == NBUF - 1 ? 0 : buf + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));    // the copies past the end: nothing may land in LDS after the wave
+
+    // lane l holds row l % 16 and the four columns 4 (l / 16) .. + 3 of each block
+    const size_t eoff = static_cast<size_t>(e) * p.capacity * p.N;
+    float* Cg = static_cast<float*>(p.C) + eoff;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int m = m0 + wm * (BM / 2) + i * 16 + l16;
         if (m >= count) continue;
-        const int n = n0 + tx * 4;
-        if (n >= p.N) continue;                                   // N % 4 == 0
-        if constexpr (GLU && DUAL) {
-            float* C2g = static_cast<float*>(p.C2) + static_cast<size_t>(e) * p.capacity * p.N;
-            *reinterpret_cast<float4*>(C2g + static_cast<size_t>(m) * p.N + n) =
-                make_float4(acc[1][i][0], acc[1][i][1], acc[1][i][2], acc[1][i][3]);
-        }
-        if constexpr (GLU && !DUAL) {
-            if (p.C3) {                                           // keep the pre-activations (training-mode forward)
-                const size_t o = (static_cast<size_t>(e) * p.capacity + m) * p.N + n;
-                *reinterpret_cast<float4*>(static_cast<float*>(p.C2) + o) = make_float4(acc[0][i][0], acc[0][i][1], acc[0][i][2], acc[0][i][3]);
-                *reinterpret_cast<float4*>(static_cast<float*>(p.C3) + o) = make_float4(acc[1][i][0], acc[1][i][1], acc[1][i][2], acc[1][i][3]);
-            }
-        }
-        float o[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if constexpr (GLU && !DUAL) {
-                const float g = acc[0][i][j];
-                o[j] = g / (1.0f + expf(-g)) * acc[1][i][j];
-            } else {
-                o[j] = acc[0][i][j];
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + wn * (BN / 2) + j * 16 + kq * 4;
+            if (n >= p.N) continue;                               // N % 4 == 0
+            const size_t o = static_cast<size_t>(m) * p.N + n;
+            f32x4 r = acc[0][i][j];
+            if constexpr (GLU) {
+                const f32x4 u = acc[1][i][j];
+                if constexpr (DUAL) {
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(p.C2) + eoff + o) = u;
+                } else {
+                    if (p.C3) {                                   // keep the pre-activations (training-mode forward)
+                        *reinterpret_cast<f32x4*>(static_cast<float*>(p.C2) + eoff + o) = r;
+                        *reinterpret_cast<f32x4*>(static_cast<float*>(p.C3) + eoff + o) = u;
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) r[v] = r[v] / (1.0f + expf(-r[v])) * u[v];
+                }
             }
+            *reinterpret_cast<f32x4*>(Cg + o) = r;
         }
-        *reinterpret_cast<float4*>(Cg + static_cast<size_t>(m) * p.N + n) = make_float4(o[0], o[1], o[2], o[3]);
     }
 }
 
@@ -1642,10 +1733,23 @@ inline bool persist_ok(const GemmParams& g, bool glu, int max_super = kMaxSuper)
     return g.K >= 128 && static_cast<long long>(g.E) * MG * NG <= max_super;
 }
 
+// Workgroups for decode_live_tile: every tile of the capacity, in whole rounds of the 8 XCDs.
+inline long long plan_live_tiles(GemmParams& p, int BM, int BN) {
+    p.MT = (p.capacity + BM - 1) / BM;
+    p.NT = (p.N + BN - 1) / BN;
+    return (static_cast<long long>(p.E) * p.MT * p.NT + 7) / 8 * 8;
+}
 template <bool GLU, bool DUAL = false>
 hipError_t launch_f32(GemmParams p, hipStream_t st) {
-    const long long blocks = plan_tiles(p, 64, 64);
-    hipLaunchKernelGGL((gemm_f32_kernel<GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+    const long long tiles64 = static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64);
+    // 8 experts of 80 rows, 256 x 512 (128 and 64 tiles of 64 x 64): 11 and 8 us with 32 x 32 tiles, 15 and 14 with 64 x 64
+    if (tiles64 >= 2ll * cu_count()) {
+        const long long blocks = plan_live_tiles(p, 64, 64);
+        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+    } else {
+        const long long blocks = plan_live_tiles(p, 32, 32);
+        hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4, GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+    }
     return hipGetLastError();
 }
 
@@ -1757,7 +1861,7 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
 }
 
 bool ffn_can_gather(const etr_config& c) {
-    if (c.dtype != ETR_BF16) return false;
+    if (c.dtype != ETR_BF16) return true;
     GemmParams g1{nullptr, nullptr, nullptr, nullptr, nullptr, c.E, c.capacity, c.H, c.d, 0, 0, 0, 0, nullptr, c.T};
     // every kernel reads its rows through an index if asked; only a token matrix past the 32-bit offsets of the
     // pipelined kernels is better rearranged first, where the per-expert buffers are within them
@@ -1787,7 +1891,6 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
         if (kind2 == Bf16Kernel::STAGED) return launch_bf16<128, 128, 64, 2, 2, false, 1>(g2, st);
         return kind2 == Bf16Kernel::PERSISTENT ? launch_bf16_persistent<false>(g2, st, n_cu) : launch_bf16_ring<false, 4>(g2, st);
     }
-    if (gather_rows) return hipErrorInvalidValue;
     err = launch_f32<true>(g1, st);
     if (err != hipSuccess) return err;
     if (between && (err = hipEventRecord(between, st)) != hipSuccess) return err;
