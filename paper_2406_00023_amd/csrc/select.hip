@@ -85,7 +85,8 @@ template <int G> constexpr int token_threads() { return G >= 16 ? 1024 : 256; } 
 // G = lanes per token, a power of two >= E.  A workgroup takes token_tile<G>() tokens in one to four passes, all of
 // whose affinities are requested before the first is used.  Each of the k rounds of Eq. 5 is a maximum over the
 // token's lanes of the order-preserving affinities still in the contest, then a minimum over the experts that hold
-// it (the lower expert wins among equals); the winner leaves the contest.  The keys of the tile go through LDS, so
+// it (the lower expert wins among equals; from 32 lanes per token on by a ballot: 65536 tokens x 64 experts, k = 4,
+// 28 -> 20 us); the winner leaves the contest.  The keys of the tile go through LDS, so
 // that each column of the column-major copy is written in whole stretches.
 template <int G>
 __global__ __launch_bounds__(token_threads<G>()) void token_choice_kernel(const float* __restrict__ score, int T, int E,
@@ -117,7 +118,17 @@ __global__ __launch_bounds__(token_threads<G>()) void token_choice_kernel(const 
             uint32_t mine = valid ? max(order_key(val), 1u) : 0u;
             for (int r = 0; r < k; ++r) {
                 const uint32_t best = lane_group_fold<G, true>(mine);
-                const int bi = static_cast<int>(lane_group_fold<G, false>(mine == best && best != 0u ? static_cast<uint32_t>(e) : 255u));
+                int bi;
+                if constexpr (G >= 32) {
+                    // half a wave or a wave per token: the holders of the maximum as a ballot, the lowest by a scalar
+                    // bit scan.  (k <= E, so somebody is still in the contest.)
+                    const uint64_t at = __ballot(mine == best);
+                    if constexpr (G == 64) bi = __builtin_ctzll(at | (1ull << 63));
+                    else bi = (threadIdx.x & 32) ? __builtin_ctz(static_cast<uint32_t>(at >> 32) | (1u << 31))
+                                                 : __builtin_ctz(static_cast<uint32_t>(at) | (1u << 31));
+                } else {
+                    bi = static_cast<int>(lane_group_fold<G, false>(mine == best && best != 0u ? static_cast<uint32_t>(e) : 255u));
+                }
                 if (e == bi) { mine = 0u; my_rank = r; }
                 if (e == r) choice = bi;
             }
@@ -265,8 +276,8 @@ __device__ __forceinline__ void digit_pick(const uint32_t* hist, const DigitView
 //   chunk (IPT/4 neighbouring lanes of one row) together.
 // IPT == 0: keys streamed from memory, thread t owns chunk t (columns longer than 64 keys per thread).
 // PRE: the histogram of the first digit (the top kRadixBits bits) comes from key_histogram_kernel (hist1, n_slices).
-// ADAPT: with the adaptive token count (an instantiation of its own: its double-precision sums over the keys in
-//   registers would otherwise cost the plain search of the long columns a hundred spilled registers).
+// ADAPT: with the adaptive token count (an instantiation of its own: its sums over the keys in registers would otherwise
+//   cost the plain search of the long columns registers and 16 KiB of LDS).
 template <int IPT, bool PRE = false, bool ADAPT = false>
 __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32_t* __restrict__ keyT, int Tpad, int T,
                                                                     int ipt, int capacity_host, int mode,
@@ -346,50 +357,84 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
     // Adaptive token count (Sec. Routing Strategy: "l is determined by a threshold of the sum of
     // affinity scores"): walking the candidates from the highest affinity down, stop at the first
     // prefix whose affinity sum reaches the threshold.  Affinities are summed as fixed-point
-    // integers round(clamp(s,-1,1) * 2^30), so the sum of "all candidates with key >= theta" is
-    // exact and order-free, and the prefix length follows from a bisection over theta.
+    // integers round(clamp(s,-1,1) * 2^30), so the sum of "all candidates with key >= theta" is exact and order-free.
+    // The key theta at which that sum reaches the threshold is found digit by digit, as the capacity threshold below
+    // is: an LDS histogram of the terms (64-bit sums) over 11, 11 and 9 bits below the sign, walked from the top.  (A
+    // bisection over the 31 bits sums all keys up to 33 times: 64 experts x 65536 tokens, 378 us for the kernel; with
+    // the histograms 38 us.)
     if constexpr (ADAPT) if (sum_need > 0 && (mode == ETR_MODE_ECR || mode == ETR_MODE_BIDIR) && n_keep > 0) {
-        __shared__ long long red_sum[kSelThreads / kWave];
+        __shared__ __attribute__((aligned(16))) unsigned long long sums[kBins];
         __shared__ int red_cnt[kSelThreads / kWave];
-        // sum and count over the candidates with key >= thr (thr >= key(+0): positive affinities only)
-        auto sum_ge = [&](uint32_t thr, long long& sum, int& cnt) {
-            sum = 0; cnt = 0;
-            auto add = [&](uint32_t key) {
-                if (key >= thr) {
-                    const float sc = __uint_as_float(key & 0x7FFFFFFFu);
-                    sum += llrint(static_cast<double>(fminf(sc, 1.0f)) * 1073741824.0);
-                    ++cnt;
-                }
-            };
+        // term of a positive affinity (key >= key(+0)); scaling by a power of two is exact, so is its rounding in fp32
+        auto term = [](uint32_t key) {
+            return static_cast<uint32_t>(__builtin_rintf(fminf(__uint_as_float(key & 0x7FFFFFFFu), 1.0f) * 1073741824.0f));
+        };
+        auto for_keys = [&](auto&& f) {
             if constexpr (IPT > 0) {
 #pragma unroll
-                for (int j = 0; j < IPT; ++j) add(keys[j]);
+                for (int j = 0; j < IPT; ++j) {
+                    uint32_t key = keys[j];
+                    asm volatile("" : "+v"(key));       // computed anew for each digit: kept terms would spill
+                    f(key);
+                }
             } else {
-                for (int idx = tid; idx < T; idx += kSelThreads) add(col[idx]);
+                for (int idx = tid; idx < T; idx += kSelThreads) f(col[idx]);
             }
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) { sum += __shfl_xor(sum, m, kWave); cnt += __shfl_xor(cnt, m, kWave); }
-            __syncthreads();
-            if (lane == 0) { red_sum[wave] = sum; red_cnt[wave] = cnt; }
-            __syncthreads();
-            sum = 0; cnt = 0;
-#pragma unroll
-            for (int w = 0; w < kSelThreads / kWave; ++w) { sum += red_sum[w]; cnt += red_cnt[w]; }
         };
-        long long s_all; int c_all;
-        sum_ge(0x80000000u, s_all, c_all);
-        if (s_all >= sum_need) {                        // otherwise the positive affinities never get there: take all
-            uint32_t th = 0x80000000u;                  // largest theta with sum_ge(theta) >= need
-            for (int bit = 30; bit >= 0; --bit) {
-                long long sv; int cv;
-                sum_ge(th | (1u << bit), sv, cv);
-                if (sv >= sum_need) th |= 1u << bit;
+        uint32_t th = 0x80000000u;                      // the settled bits of theta
+        long long above_sum = 0;                        // sum over the candidates above them
+        bool reached = true;                            // otherwise the positive affinities never get there: take all
+        int shift = 31;
+        for (int p = 0; p < 3 && reached; ++p) {
+            const int w = p < 2 ? 11 : 9;
+            shift -= w;
+            const uint32_t span = (1u << (shift + w)) - 1u, dmask = (1u << w) - 1u;
+            __syncthreads();                            // the histogram's previous readers are done
+            sums[2 * tid] = 0ull; sums[2 * tid + 1] = 0ull;
+            __syncthreads();
+            for_keys([&](uint32_t key) {
+                if (key - th <= span) atomicAdd(&sums[(key >> shift) & dmask], static_cast<unsigned long long>(term(key)));
+            });
+            __syncthreads();
+            // every wave by itself: the highest bin at which the sum from the top reaches the threshold
+            const long long need = sum_need - above_sum;                  // > 0
+            long long own = 0;
+            for (int i = 0; i < 32; ++i)                // lane g: bins [kBins - 32 (g + 1), kBins - 32 g), rotated by the lane
+                own += static_cast<long long>(sums[kBins - 32 * (lane + 1) + ((i + lane) & 31)]);
+            auto scan = [&](long long v) {
+#pragma unroll
+                for (int m = 1; m < kWave; m <<= 1) {
+                    const long long o = __shfl_up(v, m, kWave);
+                    if (lane >= m) v += o;
+                }
+                return v;
+            };
+            const long long upto = scan(own);
+            const uint64_t m1 = __ballot(upto >= need);
+            reached = m1 != 0ull;                       // (uniform; from the second digit on always true)
+            if (reached) {
+                const int g = __builtin_ctzll(m1);
+                const long long before = __shfl(upto - own, g, kWave);
+                const long long h = lane < 32 ? static_cast<long long>(sums[kBins - 1 - 32 * g - lane]) : 0;
+                const long long upto2 = scan(h);
+                const uint64_t m2 = __ballot(before + upto2 >= need);
+                const int j = m2 ? __builtin_ctzll(m2) : 31;
+                above_sum += before + __shfl(upto2 - h, j, kWave);
+                th |= static_cast<uint32_t>(kBins - 1 - 32 * g - j) << shift;
             }
-            long long s_gt = 0; int n_gt = 0;
-            if (th != 0xFFFFFFFFu) sum_ge(th + 1u, s_gt, n_gt);
-            const long long q_th = llrint(static_cast<double>(fminf(__uint_as_float(th & 0x7FFFFFFFu), 1.0f)) * 1073741824.0);
-            const long long j = q_th > 0 ? (sum_need - s_gt + q_th - 1) / q_th : 1;
-            const long long ell = n_gt + j;
+        }
+        if (reached) {
+            // theta is settled: above_sum is the sum over the keys above it; count them
+            int n_gt = 0;
+            for_keys([&](uint32_t key) { n_gt += key > th; });
+            n_gt = wave_sum_i(n_gt);
+            if (lane == 0) red_cnt[wave] = n_gt;
+            __syncthreads();
+            n_gt = 0;
+#pragma unroll
+            for (int w = 0; w < kSelThreads / kWave; ++w) n_gt += red_cnt[w];
+            const long long q_th = term(th);
+            const long long ell = n_gt + (sum_need - above_sum + q_th - 1) / q_th;       // q_th > 0: its bin reached the sum
             if (ell < n_keep) n_keep = static_cast<int>(ell);
         }
     }
