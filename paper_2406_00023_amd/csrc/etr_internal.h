@@ -60,6 +60,7 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
 // True when GEMM-1 can read its rows straight from the token matrix through slot_token
 // (then xp is never materialised by the fused forward).
 bool ffn_can_gather(const etr_config& c);
+int rows_expected(const etr_config& c);      // rows per expert that a batch can be expected to fill
 
 // General grouped product of ffn.hip, used by the backward pass:
 //   C[g][m][n] = sum_k A[g][m][k] * B[g][n][k]   (both operands contiguous along k)
@@ -89,6 +90,8 @@ struct GroupedGemm {
     // With ta and the plain epilogue: output rows m < split_m go to C, the others (as rows m - split_m) to C2, both
     // [G][split_m][N]; M = 2 split_m, split_m a multiple of 32.  (Two products that share B in one launch.)
     int split_m = 0;
+    // rows per group that the caller expects (0: unknown); picks the kernel for few rows (row-major bf16 operands)
+    int rows_expected = 0;
 };
 hipError_t launch_grouped_gemm(const GroupedGemm& g, hipStream_t st);
 bool grouped_gemm_transposed_ok(const GroupedGemm& g);

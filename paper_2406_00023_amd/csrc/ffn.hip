@@ -1524,6 +1524,163 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 }
 
 // ---------------------------------------------------------------------------------------
+// Grouped bf16 GEMM for few rows per group (decode steps, short prompts): the weights are read once and that is all the
+// time there is, so a 256-row tile would multiply padding for longer than the weights take to arrive.
+//
+// A workgroup takes 64 weight rows (GLU: 32 gate and the 32 up rows of the same columns) and up to 64 token rows of one
+// expert.  Its four waves split the contraction: wave w takes every fourth 64-wide k-tile, all 64 weight rows and all
+// token rows, so the workgroup walks 512 contiguous bytes of each row at a time and no wave waits for another until the
+// end.  Weights and token rows go from memory straight into the MFMA fragments (lane l: row l % 16 of a 16-row block,
+// 16-byte piece l / 16 of a k-step), one k-tile ahead of its use: 8 KiB of weights in flight per wave, 64 KiB per CU
+// at two workgroups.  No barrier and no LDS until the four partial sums meet in LDS and are added in wave order.
+// The token rows are read by every workgroup of the expert, out of the caches.
+// Row blocks of 16 that hold no row are skipped (MB = 1, 2 or 4 blocks).
+// Measured: 32 tokens, 16 experts, 2048 x 5632: gate/up 194 -> 128 us (5.8 TB/s of weights), down 156 -> 64 us (5.7 TB/s)
+// against the 256-row tiles; 256 tokens, 32 experts, 4096 x 2816: 404 -> 285 us and 180 -> 156 us.
+// ---------------------------------------------------------------------------------------
+constexpr int kRowsBM = 64;                             // token rows per workgroup
+
+template <int MB, bool GLU, bool DUAL, bool KEEP>
+__device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, int n0, int count, f32x4* red) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int K = p.K;
+    const int LA = p.lda ? p.lda : p.K, LB = p.ldb ? p.ldb : p.K;
+    const char* Ab = static_cast<const char*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA * 2);
+    const size_t bgroup = static_cast<size_t>(e) * p.N * LB * 2;
+    const char* Bb[2] = {static_cast<const char*>(p.B0) + bgroup, static_cast<const char*>(GLU ? p.B1 : p.B0) + bgroup};
+    uint32_t aoff[MB], boff[4];
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        int m = min(m0 + i * 16 + l16, count - 1);      // rows past the count replay a valid row; never stored
+        if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
+        aoff[i] = (static_cast<uint32_t>(m) * LA + kq * 8) * 2u;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int n = min(n0 + (GLU ? b & 1 : b) * 16 + l16, p.N - 1);
+        boff[b] = (static_cast<uint32_t>(n) * LB + kq * 8) * 2u;
+    }
+    f32x4 acc[4][MB];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[b][i][v] = 0.f;
+
+    struct Stage { bf16x8 w[2][4], a[2][MB]; };         // one k-tile of 64
+    auto load = [&](Stage& s, int kt) {
+        const size_t at = static_cast<size_t>(kt) * 128;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                s.w[h][b] = *reinterpret_cast<const bf16x8*>(Bb[GLU ? b >> 1 : 0] + at + h * 64 + boff[b]);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) s.a[h][i] = *reinterpret_cast<const bf16x8*>(Ab + at + h * 64 + aoff[i]);
+    };
+    auto multiply = [&](const Stage& s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+                    acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s.w[h][b], s.a[h][i], acc[b][i], 0, 0, 0);
+    };
+    const int whole = K / 64;                           // whole k-tiles; wave w takes w, w + 4, ...
+    Stage s0, s1;
+    if (wave < whole) {
+        load(s0, wave);
+        for (int kt = wave; kt < whole; kt += 8) {
+            load(s1, min(kt + 4, whole - 1));           // (past the end: some k-tile again, not multiplied)
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(s0);
+            if (kt + 4 < whole) {
+                load(s0, min(kt + 8, whole - 1));
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(s1);
+            }
+        }
+    }
+    if (K % 64 != 0 && wave == (whole & 3)) {           // the short last k-tile: pieces past its end are zero
+        const bf16x8 zero = {};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool in = whole * 64 + h * 32 + kq * 8 < K;           // K % 8 == 0: a piece is all in or all out
+            const size_t at = static_cast<size_t>(whole) * 128 + h * 64;
+            bf16x8 w[4], a[MB];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) w[b] = in ? *reinterpret_cast<const bf16x8*>(Bb[GLU ? b >> 1 : 0] + at + boff[b]) : zero;
+#pragma unroll
+            for (int i = 0; i < MB; ++i) a[i] = in ? *reinterpret_cast<const bf16x8*>(Ab + at + aoff[i]) : zero;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int i = 0; i < MB; ++i) acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], a[i], acc[b][i], 0, 0, 0);
+        }
+    }
+    // the partial sums meet: red[wave][block][lane]
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < MB; ++i) red[(wave * 4 * MB + b * MB + i) * 64 + lane] = acc[b][i];
+    __syncthreads();
+    auto total = [&](int b, int i) {
+        f32x4 s = red[(b * MB + i) * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += red[(w * 4 * MB + b * MB + i) * 64 + lane];
+        return s;
+    };
+    const size_t eoff = static_cast<size_t>(e) * p.capacity * p.N;
+    auto pack4 = [](const f32x4& v) { return pack_bf16x4(v[0], v[1], v[2], v[3]); };
+    constexpr int UNITS = (GLU ? 2 : 4) * MB;           // output blocks of 16 x 16, dealt to the waves
+#pragma unroll
+    for (int u0 = 0; u0 < UNITS; u0 += 4) {
+        const int u = u0 + wave;
+        if (u >= UNITS) break;
+        const int b = u / MB, i = u - b * MB;
+        const int m = m0 + i * 16 + l16, n = n0 + b * 16 + kq * 4;
+        if (m >= count || n >= p.N) continue;           // N % 4 == 0
+        const size_t o = eoff + static_cast<size_t>(m) * p.N + n;
+        const f32x4 g = total(b, i);
+        auto put = [&](void* base, const uint2& v) { *reinterpret_cast<uint2*>(static_cast<uint16_t*>(base) + o) = v; };
+        if constexpr (!GLU) {
+            put(p.C, pack4(g));
+        } else {
+            const f32x4 up = total(2 + b, i);
+            if constexpr (DUAL) {
+                put(p.C, pack4(g));
+                put(p.C2, pack4(up));
+            } else {
+                put(p.C, pack_bf16x4(silu(g[0]) * up[0], silu(g[1]) * up[1], silu(g[2]) * up[2], silu(g[3]) * up[3]));
+                if constexpr (KEEP) {
+                    put(p.C2, pack4(g));
+                    put(p.C3, pack4(up));
+                }
+            }
+        }
+    }
+}
+
+template <bool GLU, bool DUAL = false, bool KEEP = false>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
+    __shared__ f32x4 red[4 * 16 * 64];
+    int e, mt, nt;
+    if (!decode_live_tile(p, kRowsBM, e, mt, nt)) return;
+    const int count = group_rows(p, e);
+    const int m0 = mt * kRowsBM, n0 = nt * (GLU ? 32 : 64);
+    const int rows = count - m0;
+    if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+    else if (rows <= 32) rows_tile<2, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+    else rows_tile<4, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+}
+
+// ---------------------------------------------------------------------------------------
 // fp32 grouped GEMM on v_mfma_f32_16x16x4_f32 (full fp32 products and accumulation).
 //
 // Bound by the matrix pipe on large layers (157 TFLOP/s dense; plain FMAs, without packed instructions, stop at half of
@@ -1739,6 +1896,12 @@ inline long long plan_live_tiles(GemmParams& p, int BM, int BN) {
     p.NT = (p.N + BN - 1) / BN;
     return (static_cast<long long>(p.E) * p.MT * p.NT + 7) / 8 * 8;
 }
+template <bool GLU, bool DUAL = false, bool KEEP = false>
+hipError_t launch_bf16_rows(GemmParams p, hipStream_t st) {
+    const long long blocks = plan_live_tiles(p, kRowsBM, GLU ? 32 : 64);
+    hipLaunchKernelGGL((gemm_bf16_rows_kernel<GLU, DUAL, KEEP>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+    return hipGetLastError();
+}
 template <bool GLU, bool DUAL = false>
 hipError_t launch_f32(GemmParams p, hipStream_t st) {
     const long long tiles64 = static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64);
@@ -1760,18 +1923,36 @@ size_t ffn_ws_bytes(const etr_config& c) {
 }
 
 // Which kernel a row-major bf16 product takes.  Both pipelined kernels need 32-bit byte offsets inside one operand.
+//   ROWS        few rows per group expected, or too few 256-row tiles to fill the chip: see few_rows_pay
 //   PERSISTENT  at least one whole column tile, a contraction of 128 or more, the super-tile prefix in LDS.  A
 //               contraction that is not whole 64-wide k-tiles takes its zero-filling instantiation (per-group lengths
 //               are always whole k-tiles).  12 experts of 135-938 rows, 1080 x 2744 (K % 64 = 56): 262 -> 150 us for
 //               the gate/up product, 242 -> 95 us for the down one against the register-staged kernel.
 //   RING        whole k-tiles where the persistent kernel does not apply (narrow outputs, short contractions)
 //   STAGED      everything else
-enum class Bf16Kernel { PERSISTENT, RING, STAGED };
-static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows) {
+enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
+// Estimated cost of both kernels in row x weight-row products at the persistent kernel's full rate (1100 TFLOP/s).
+// gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows.  Persistent: whole rounds of 256 x 256 tiles over the CUs, and
+// never faster than its weights arrive (3.5 TB/s, as long as 314 rows are multiplied).  Measured, both products of a layer,
+// rows per expert: time here / time there, us.  16 experts, 2048 x 5632: 16: 216 / 356, 48: 270 / 321, 64: 290 / 311, 96: 517 / 317.
+// 32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.  8 experts, 512 x 1024, 16 to 64 tiles per product:
+// 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.
+static bool few_rows_pay(const GemmParams& g, bool glu, int rows_expected) {
+    if (rows_expected < 1 || g.k_counts) return false;
+    if (static_cast<double>(g.E) * ((g.capacity + kRowsBM - 1) / kRowsBM) * (g.N / 32 + 1) >= 2.0e9) return false;   // grid size
+    const double weight_rows = static_cast<double>(g.E) * g.N * (glu ? 2 : 1);
+    const double tiles = static_cast<double>(g.E) * ((rows_expected + 255) / 256) * ((g.N + (glu ? 127 : 255)) / (glu ? 128 : 256));
+    const int n_cu = cu_count();
+    const double rounds = static_cast<double>(static_cast<long long>((tiles + n_cu - 1) / n_cu));
+    const double persistent = rounds * n_cu * 65536.0, streamed = weight_rows * 314.0;
+    return weight_rows * 262.0 * ((rows_expected + kRowsBM - 1) / kRowsBM) < (persistent > streamed ? persistent : streamed);
+}
+static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int rows_expected) {
     const size_t a_row_bytes = static_cast<size_t>(g.lda ? g.lda : g.K) * 2, b_row_bytes = static_cast<size_t>(g.ldb ? g.ldb : g.K) * 2;
     const size_t a_bytes = a_rows * a_row_bytes, b_bytes = static_cast<size_t>(g.N) * b_row_bytes;
     if (g.K % 8 != 0 || a_row_bytes % 16 != 0 || b_row_bytes % 16 != 0 || a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32))
         return Bf16Kernel::STAGED;
+    if (few_rows_pay(g, glu, rows_expected)) return Bf16Kernel::ROWS;
     const bool whole = g.K % 64 == 0;
     if (!whole && (g.k_counts || a_bytes >= kBufferRange || b_bytes >= kBufferRange)) return Bf16Kernel::STAGED;
     if (persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu)) return Bf16Kernel::PERSISTENT;
@@ -1834,7 +2015,14 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;
-        const Bf16Kernel kind = choose_bf16(g, q.epilogue != GEMM_PLAIN, q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M));
+        const Bf16Kernel kind = choose_bf16(g, q.epilogue != GEMM_PLAIN, q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M), q.rows_expected);
+        if (kind == Bf16Kernel::ROWS) {
+            switch (q.epilogue) {
+                case GEMM_PLAIN: return launch_bf16_rows<false>(g, st);
+                case GEMM_SWIGLU: return launch_bf16_rows<true>(g, st);
+                case GEMM_DUAL: return launch_bf16_rows<true, true>(g, st);
+            }
+        }
         const bool ring = kind == Bf16Kernel::RING;
         if (kind == Bf16Kernel::PERSISTENT) {
             const int n_cu = cu_count();
@@ -1860,13 +2048,21 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+// Rows per expert that a batch can be expected to fill (the counts live on the device): every token on k experts, or,
+// where the experts choose, their capacity.
+int rows_expected(const etr_config& c) {
+    const long long even = c.mode == ETR_MODE_ECR ? c.T : (static_cast<long long>(c.T) * c.k + c.E - 1) / c.E;
+    return static_cast<int>(even < c.capacity ? even : c.capacity);
+}
+
 bool ffn_can_gather(const etr_config& c) {
     if (c.dtype != ETR_BF16) return true;
     GemmParams g1{nullptr, nullptr, nullptr, nullptr, nullptr, c.E, c.capacity, c.H, c.d, 0, 0, 0, 0, nullptr, c.T};
     // every kernel reads its rows through an index if asked; only a token matrix past the 32-bit offsets of the
     // pipelined kernels is better rearranged first, where the per-expert buffers are within them
-    return choose_bf16(g1, true, static_cast<size_t>(c.T)) != Bf16Kernel::STAGED ||
-           choose_bf16(g1, true, static_cast<size_t>(c.capacity)) == Bf16Kernel::STAGED;
+    const int rows = rows_expected(c);
+    return choose_bf16(g1, true, static_cast<size_t>(c.T), rows) != Bf16Kernel::STAGED ||
+           choose_bf16(g1, true, static_cast<size_t>(c.capacity), rows) == Bf16Kernel::STAGED;
 }
 
 hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t* counts, const void* w_gate,
@@ -1880,14 +2076,17 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
     hipError_t err;
     if (c.dtype == ETR_BF16) {
         if (gather_rows && !ffn_can_gather(c)) return hipErrorInvalidValue;
-        const Bf16Kernel kind1 = choose_bf16(g1, true, gather_rows ? static_cast<size_t>(c.T) : static_cast<size_t>(c.capacity));
-        const Bf16Kernel kind2 = choose_bf16(g2, false, static_cast<size_t>(c.capacity));
+        const Bf16Kernel kind1 = choose_bf16(g1, true, gather_rows ? static_cast<size_t>(c.T) : static_cast<size_t>(c.capacity), rows_expected(c));
+        const Bf16Kernel kind2 = choose_bf16(g2, false, static_cast<size_t>(c.capacity), rows_expected(c));
         const int n_cu = cu_count();
-        if (kind1 == Bf16Kernel::PERSISTENT)
+        if (kind1 == Bf16Kernel::ROWS)
+            err = g1.C3 ? launch_bf16_rows<true, false, true>(g1, st) : launch_bf16_rows<true>(g1, st);
+        else if (kind1 == Bf16Kernel::PERSISTENT)
             err = g1.C3 ? launch_bf16_persistent<true, false, true>(g1, st, n_cu) : launch_bf16_persistent<true>(g1, st, n_cu);
         else err = (kind1 == Bf16Kernel::RING && !g1.C3) ? launch_bf16_ring<true, 4>(g1, st) : launch_bf16<128, 64, 64, 2, 2, true, 1>(g1, st);
         if (err != hipSuccess) return err;
         if (between && (err = hipEventRecord(between, st)) != hipSuccess) return err;
+        if (kind2 == Bf16Kernel::ROWS) return launch_bf16_rows<false>(g2, st);
         if (kind2 == Bf16Kernel::STAGED) return launch_bf16<128, 128, 64, 2, 2, false, 1>(g2, st);
         return kind2 == Bf16Kernel::PERSISTENT ? launch_bf16_persistent<false>(g2, st, n_cu) : launch_bf16_ring<false, 4>(g2, st);
     }

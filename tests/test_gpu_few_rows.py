@@ -1,0 +1,95 @@
+"""The bf16 GEMM for few rows per expert: one, two and four 16-row blocks, several row blocks of 64, empty experts,
+contractions of less than one k-tile, of a few k-tiles (waves without any), and ragged ones, narrow and ragged outputs; in
+the forward, the training forward and the recomputation of the backward."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_00023_amd import binding as B
+from paper_2406_00023_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,C,d,Hh,counts", [
+    (4, 16, 2048, 1024, [16, 1, 0, 15]),                 # one block of 16 rows; 32 and 16 k-tiles over four waves
+    (3, 33, 1080, 520, [33, 17, 32]),                    # two blocks and one past; k-tiles end 56 and 8 short of whole
+    (64, 64, 136, 40, [64, 0, 49, 1] * 16),              # a short k-tile on wave 2; outputs narrower than a workgroup's
+    (2, 30, 8, 8, [30, 3]),                              # less than one k-step
+    (1, 200, 320, 4096, [200]),                          # four row blocks, the last of 8 rows; k-tiles for some waves only
+    (5, 64, 192, 72, [64, 63, 48, 31, 0]),
+])
+def test_few_rows_ffn(oracle, E, C, d, Hh, counts):
+    import gpu_helpers as H
+    import test_gpu_parity
+    B.load_library()
+    # (that test's layers have T = C tokens on one expert each: C / E rows are expected, which chooses this kernel)
+    test_gpu_parity.test_expert_ffn(H, oracle, I.DT_BF16, E, C, d, Hh, counts)
+
+
+@pytest.mark.parametrize("T,d,Hh,E,k,mode", [(1, 256, 512, 8, 2, I.MODE_TCR), (7, 264, 136, 4, 4, I.MODE_BIDIR),
+                                             (100, 512, 328, 6, 2, I.MODE_BIDIR), (150, 1024, 256, 16, 1, I.MODE_ECR)])
+def test_few_rows_layer_and_backward(oracle, T, d, Hh, E, k, mode):
+    import gpu_helpers as H
+    from test_gpu_backward import Backward, _err
+    B.load_library()
+    C = T if mode != I.MODE_ECR else 12
+    shape = I.EtrShape("few", 12, T=T, d=d, E=E, D=8, k=k, capacity=C, H=Hh, dtype=I.DT_BF16, mode=mode, recipe="bias")
+    print(f"few rows T={T} d={d} H={Hh} E={E} k={k} mode={mode}", flush=True)
+    L = H.GpuLayer(shape)
+    hx = L.host_inputs()
+    L.forward()
+    r = H.check_routing_against_oracle(oracle, L, hx)
+    H.check_output_against_oracle(oracle, L, hx, r["score"])
+    bw = Backward(H, shape, mode)
+    hb = bw.host()
+    ref = oracle.moe_backward(hb["x"], hb["w_emb"], hb["w_gate"], hb["w_up"], hb["w_down"], hb["slot_of"], hb["dout"],
+                              D=shape.D, dtype=shape.dtype)
+    for got, key in ((bw.dx, "dx"), (bw.dwg, "dw_gate"), (bw.dwu, "dw_up"), (bw.dwd, "dw_down")):
+        assert _err(H, oracle, got, ref[key], shape.dtype) <= H.TOL_OUT[shape.dtype], key
+    # kept and recomputed pre-activations come from the same kernel: the same bits through the backward
+    t, cfg = L.t, L.cfg
+    a, b = (torch.empty(E, C, Hh, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    out = torch.empty_like(L.out)
+    B.etr_moe_forward_train(cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], out, a, b,
+                            B.alloc_workspace(B.etr_workspace_bytes(cfg)))
+    dx, dwg, dwu, dwd = (torch.empty_like(v) for v in (bw.dx, bw.dwg, bw.dwu, bw.dwd))
+    B.etr_moe_backward(cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], bw.L.score, bw.L.gate, bw.L.slot_of,
+                       bw.L.slot_token, bw.L.counts, bw.dout, dx, dwg, dwu, dwd,
+                       B.alloc_workspace(B.etr_backward_workspace_bytes(cfg)), a_saved=a, b_saved=b)
+    torch.cuda.synchronize()
+    assert torch.equal(out, L.out)
+    for got, want in ((dx, bw.dx), (dwg, bw.dwg), (dwu, bw.dwu), (dwd, bw.dwd)):
+        assert np.array_equal(H.to_np(got), H.to_np(want))
+
+
+@pytest.mark.parametrize("E,C,d,Hh,counts", [
+    (6, 900, 768, 1152, [900, 0, 513, 1, 899, 256]),
+    (8, 1100, 256, 2816, [1100, 700, 1, 1024, 0, 1025, 300, 1100]),
+    (8, 2048, 128, 1024, [2048, 1500, 2048, 300, 2047, 1025, 2048, 1800]),
+    (8, 2048, 2048, 128, [2048, 1500, 0, 300, 2047, 1025, 2048, 1800]),
+    (2, 4200, 1024, 384, [4200, 3333]),
+    (16, 300, 1032, 1048, [300, 0, 257, 256, 255, 1, 128, 300] * 2),     # both contractions end 8 / 24 past whole k-tiles
+    (16, 520, 1080, 1320, [520, 513, 0, 3] * 4),                         # 56 and 40 past
+])
+def test_many_rows_expected_ffn(oracle, E, C, d, Hh, counts):
+    """The same stage where every expert is expected to fill its capacity: the 256-row tiles of the persistent kernel on
+    ragged counts, contractions and column tails."""
+    import gpu_helpers as H
+    B.load_library()
+    print(f"ffn with {E} x {C} rows expected, d={d} H={Hh}", flush=True)
+    shape = I.EtrShape("m", 1, T=E * C, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_TCR, recipe="iso")
+    xp = I.normal(1, E * C * d, "cuda").reshape(E, C, d).to(torch.bfloat16)
+    wg, wu = (I.ffn_weight(s, (E, Hh, d), torch.bfloat16, "cuda", std=0.05) for s in (2, 3))
+    wd = I.ffn_weight(4, (E, d, Hh), torch.bfloat16, "cuda", std=0.05)
+    cnt = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    yp = torch.full((E, C, d), 7.0, dtype=torch.bfloat16, device="cuda")
+    cfg = B.make_config(shape)
+    B.etr_expert_ffn(cfg, xp, cnt, wg, wu, wd, yp, B.alloc_workspace(B.etr_ffn_workspace_bytes(cfg)))
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(H.to_np(xp), np.array(counts, np.int32), H.to_np(wg), H.to_np(wu), H.to_np(wd), I.DT_BF16)
+    got = oracle.to_f64(H.to_np(yp), I.DT_BF16)
+    for e, n in enumerate(counts):
+        assert np.all(got[e, n:] == 7.0)
+        if n:
+            assert H.scale_rel_err(got[e, :n], ref[e, :n]) <= H.TOL_OUT[I.DT_BF16]

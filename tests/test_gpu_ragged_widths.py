@@ -13,16 +13,18 @@ pytestmark = pytest.mark.gpu
 
 # (d, H, capacity): the contraction of the gate/up product is d, that of the down product H, that of the input gradient
 # twice H; remainders of 8, 24, 32, 40 and 56 past whole 64s, the shortest contraction the kernels take (three k-tiles),
-# one and two row tiles, a capacity of 40 (padded to 128 contraction rows)
-@pytest.mark.parametrize("d,Hh,C", [(264, 184, 500), (280, 136, 300), (312, 160, 500), (296, 152, 40), (288, 296, 129),
-                                    (1080, 2744, 260)])
-def test_ragged_widths_forward_and_backward(oracle, d, Hh, C):
+# one and two row tiles, a capacity of 40 (padded to 128 contraction rows); the last two have enough tiles for the
+# persistent kernel in the forward and the recomputation as well
+@pytest.mark.parametrize("T,E,d,Hh,C", [(600, 3, 264, 184, 500), (600, 3, 280, 136, 300), (600, 3, 312, 160, 500),
+                                        (600, 3, 296, 152, 40), (600, 3, 288, 296, 129), (600, 3, 1080, 2744, 260),
+                                        (2048, 16, 1032, 1048, 300), (1500, 12, 1112, 1384, 400)])
+def test_ragged_widths_forward_and_backward(oracle, T, E, d, Hh, C):
     import gpu_helpers as H
     from test_gpu_backward import Backward, _err
     B.load_library()
-    shape = I.EtrShape("ragged", 11, T=600, d=d, E=3, D=8, k=2, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR,
+    shape = I.EtrShape("ragged", 11, T=T, d=d, E=E, D=8, k=2, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR,
                        recipe="bias")
-    print(f"ragged widths d={d} H={Hh} C={C}", flush=True)
+    print(f"ragged widths T={T} E={E} d={d} H={Hh} C={C}", flush=True)
     L = H.GpuLayer(shape)
     hx = L.host_inputs()
     L.forward()
