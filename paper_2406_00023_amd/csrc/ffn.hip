@@ -499,6 +499,59 @@ __device__ __forceinline__ void store_blocks_staged16(const GemmParams& p, const
     }
 }
 
+// The plain epilogue of the transposing persistent kernel: 32 x 32 accumulators (lane: row lane % 32 and, per q, the four
+// columns 8 q + 4 (lane / 32) .. + 3), a wave's two blocks 64 columns wide.  Stored directly that is 16 bytes per row and
+// instruction; a weight gradient, whose contraction is an expert's few hundred rows, then spends as long storing its
+// tile as multiplying it.  Here 32 rows x 128 bytes pass through LDS and leave as whole lines, 8 rows per instruction.
+// The patch is the wave's own copy target (two pieces of 2 KiB, one per block) in the ring slot of the k-tile just
+// multiplied: behind that k-tile's barrier nobody reads the slot any more, and the next copies into these 4 KiB are
+// the wave's own, issued after its epilogue.  8-byte pieces are XORed with bits of the row (no padding fits; two-way
+// bank conflicts on the writes, none on the reads).  In assembly for the reason given above.
+// Measured, each weight gradient of the layer: 16 experts of 166-1024 rows, 2048 x 5632: 337 -> 280 us; 32 experts, 360
+// rows in all, 2304 x 6032 (0.9 GB written): 430 -> 297 us.
+__device__ __forceinline__ void store_rows_staged32(const uint2 (&pk)[2][4], uint16_t* dst, int ldc, int rows_live, int cols_live,
+                                                    uint32_t patch0, uint32_t patch1, int lane) {
+    const int r32 = lane & 31, half = lane >> 5;
+    const int sw = (r32 >> 2) & 3;
+    uint32_t wa[4];                                     // write address of piece 2 q + half of row r32
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wa[q] = r32 * 64 + ((2 * q + half) ^ (2 * sw)) * 8;
+    const uint32_t d = patch1 - patch0;
+    const int rr = lane >> 3, ch = lane & 7;
+    // rows 8 u + rr: the swizzle term is (2 u + (rr >> 2)) & 3
+    uint32_t ra[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) ra[u] = (ch & 4 ? patch1 : patch0) + (8 * u + rr) * 64 + (((ch & 3) ^ ((2 * u + (rr >> 2)) & 3)) * 16);
+    epi_v4i v0, v1, v2, v3;
+    asm volatile(
+        "ds_write_b64 %4, %12\n\t"
+        "ds_write_b64 %5, %13\n\t"
+        "ds_write_b64 %6, %14\n\t"
+        "ds_write_b64 %7, %15\n\t"
+        "ds_write_b64 %8, %16\n\t"
+        "ds_write_b64 %9, %17\n\t"
+        "ds_write_b64 %10, %18\n\t"
+        "ds_write_b64 %11, %19\n\t"
+        "ds_read_b128 %0, %20\n\t"
+        "ds_read_b128 %1, %21\n\t"
+        "ds_read_b128 %2, %20 offset:1024\n\t"
+        "ds_read_b128 %3, %21 offset:1024\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3)
+        : "v"(patch0 + wa[0]), "v"(patch0 + wa[1]), "v"(patch0 + wa[2]), "v"(patch0 + wa[3]), "v"(patch0 + d + wa[0]),
+          "v"(patch0 + d + wa[1]), "v"(patch0 + d + wa[2]), "v"(patch0 + d + wa[3]), "v"(as_v2i(pk[0][0])), "v"(as_v2i(pk[0][1])),
+          "v"(as_v2i(pk[0][2])), "v"(as_v2i(pk[0][3])), "v"(as_v2i(pk[1][0])), "v"(as_v2i(pk[1][1])), "v"(as_v2i(pk[1][2])),
+          "v"(as_v2i(pk[1][3])), "v"(ra[0]), "v"(ra[1])
+        : "memory");
+    const bool col = ch * 8 < cols_live;                // N % 8 == 0: a 16-byte piece is all in or all out
+    const epi_v4i v[4] = {v0, v1, v2, v3};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int r = 8 * u + rr;
+        if (col && r < rows_live) *reinterpret_cast<uint4*>(dst + static_cast<size_t>(r) * ldc + ch * 8) = as_uint4(v[u]);
+    }
+}
+
 typedef const __attribute__((address_space(1))) void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
@@ -711,7 +764,7 @@ constexpr int kMaxSuperWide = 2048;      // the same for the 64-wide kernel, who
 // (buffer_copy_to_lds).
 template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0, bool TAIL = false>
 __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
-    static_assert(!(GLU && TRB), "the transposed B operand is for plain products");
+    static_assert(!GLU && !DUAL, "plain products only: row-major operands with an epilogue take the 64-wide kernel");
     static_assert(KG == 0 || (KG == 1 && TRA) || (KG == 2 && TRB), "the gathered operand is a transposed one");
     static_assert(!TAIL || (TRB && !TRA && KG == 0), "short k-tiles: row-major A, transposed B");
     constexpr int IDX_AHEAD = 7, IDX_SLOTS = 16;        // index prefetch distance in k-tiles, ring slots of 32 indices
@@ -1181,12 +1234,35 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // ---- epilogue of cur (the copies of the next tile are in flight)
-        constexpr int TO = GLU ? TB / 2 : TB;
-        if (GLU && !DUAL && p.C3)
-            store_blocks<GLU, DUAL, 4, TB, GLU && !DUAL>(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * (32 * TO), cur.count, r32, half);
-        else
-            store_blocks<GLU, DUAL, 4, TB>(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * (32 * TO), cur.count, r32, half);
+        // ---- epilogue of cur (the copies of the next tile are in flight into the three other slots)
+        if constexpr (KG == 2) {
+            // (contractions of many thousands of rows, six tiles per workgroup: stored directly, 5.87 ms for the gate and
+            // up gradients of 8 experts x 32 000 rows; through the patch 6.06 ms.  With the gathered A operand it is
+            // 3.02 against 2.99 ms.)
+            store_blocks<false, false, 4, TB>(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * 64, cur.count, r32, half);
+        } else {
+            const uint32_t slot = lds_base + static_cast<uint32_t>((g - 1) & (NBUF - 1)) * (STAGE * 16);
+            const uint32_t patch0 = slot + wave * (NCP * 1024), patch1 = patch0 + BM * CPR * 16;
+            const int nb = cur.n0 + wn * 64;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int mb = cur.m0 + wm * 128 + i * 32;
+                uint2 pk[2][4];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        pk[j][v] = pack_bf16x4(acc[i][j][v * 4], acc[i][j][v * 4 + 1], acc[i][j][v * 4 + 2], acc[i][j][v * 4 + 3]);
+                uint16_t* out = reinterpret_cast<uint16_t*>(p.C) + (static_cast<size_t>(cur.e) * p.capacity + mb) * p.N + nb;
+                if (p.split_m) {                         // a block of 32 rows lies on one side of the split
+                    const bool second = mb >= p.split_m;
+                    out = reinterpret_cast<uint16_t*>(second ? p.C2 : p.C) +
+                          (static_cast<size_t>(cur.e) * p.split_m + (second ? mb - p.split_m : mb)) * p.N + nb;
+                }
+                if (mb < cur.count && nb < p.N) store_rows_staged32(pk, out, p.N, cur.count - mb, p.N - nb, patch0, patch1, lane);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
         if (!has_next) break;
         cur = nxt;
         q = qn;
@@ -1973,6 +2049,7 @@ static GemmParams params_of(const GroupedGemm& q) {
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !(q.ta || q.tb)) return false;
     // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
+    if (q.N % 8 != 0) return false;                                // 16-byte stores
     const bool tail_form = q.tb && !q.ta && !q.k_counts;
     const int half_k = q.B1 ? q.K / 2 : q.K;
     if (q.K < 128 || half_k % (tail_form ? 8 : 64) != 0 || q.N % 4 != 0) return false;
