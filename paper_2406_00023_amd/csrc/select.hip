@@ -2,7 +2,7 @@
 // rules of the pure phases from the Proof of the Theorem, parts 1 and 2) and the
 // prefix-sum permutation tables.
 //
-// Three launches (four for long columns), no global atomics, integer counting only, so the result is
+// Three launches (four for long columns, one for short batches: small_select_kernel), no global atomics, integer counting only, so the result is
 // bit-reproducible:
 //   1. token_choice_kernel   one lane per (token, expert): k rounds of arg-max inside a lane group (DPP folds)
 //                            give the token's Top-k list (Eq. 5); writes the candidate mask and, through an LDS
@@ -676,6 +676,112 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Everything in one launch for short batches (T <= kSmallTokens, no strict intersection, no affinity-sum threshold):
+// one workgroup per expert, one thread per token.  What a small call pays for is launches and dependent latencies, so
+// each workgroup reads all scores (they are in the caches) and finds its expert's place in every token's list by
+// counting the better experts of the row; the keys of its column meet in LDS, and a candidate is kept if fewer than
+// `capacity` candidates precede it (a larger key, or the same key and a lower token), again by counting: T / 4
+// broadcast reads per thread instead of a radix search.  The slot is the number of kept tokens in front, from ballots.
+// Counting grows with T^2.  One call against the three launches, T x E: 32 x 16 5.4 / 12.3 us, 256 x 32 9.0 / 14.5,
+// 512 x 8 10.2 / 12.3, 512 x 64 15.6 / 20.7; from 1024 tokens on it would be the slower one.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallTokens = 512;
+__global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float* __restrict__ score, int T, int E, int k,
+                                                                    int capacity_host, int mode,
+                                                                    const int32_t* __restrict__ capacity_dev,
+                                                                    int32_t* __restrict__ topk, int32_t* __restrict__ slot_of,
+                                                                    int32_t* __restrict__ slot_token, int32_t* __restrict__ counts) {
+    __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallTokens];
+    __shared__ int wave_kept[kSmallTokens / kWave];
+    const int e = blockIdx.x, t = threadIdx.x, nthreads = blockDim.x;       // nthreads: T rounded up to whole waves
+    const int lane = t & (kWave - 1), wave = t / kWave;
+    const int capacity = capacity_dev ? min(capacity_host, max(1, *capacity_dev)) : capacity_host;
+    uint32_t key = 0u;
+    if (t < T) {
+        const float* row = score + static_cast<size_t>(t) * E;
+        const float own_score = row[e];
+        int rank = 0;
+        if (mode != ETR_MODE_ECR) {
+            const uint32_t own = max(order_key(own_score), 1u);
+            if ((E & 3) == 0) {
+#pragma unroll 4
+                for (int q = 0; q < E; q += 4) {
+                    const float4 v = *reinterpret_cast<const float4*>(row + q);
+                    const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t other = max(order_key(f[j]), 1u);
+                        rank += other > own || (other == own && q + j < e);
+                    }
+                }
+            } else {
+#pragma unroll 4
+                for (int q = 0; q < E; ++q) {
+                    const uint32_t other = max(order_key(row[q]), 1u);
+                    rank += other > own || (other == own && q < e);
+                }
+            }
+            if (topk && rank < k) topk[static_cast<size_t>(t) * k + rank] = e;
+        }
+        key = selection_key(own_score, mode == ETR_MODE_ECR || rank < k, mode, k, rank);
+    }
+    if (mode == ETR_MODE_TCR) {                          // equal keys: the first `capacity` candidates, in their own order
+        const uint64_t in_wave = __ballot(key != 0u);
+        if (lane == 0) wave_kept[wave] = __popcll(in_wave);
+        __syncthreads();
+        int slot = __popcll(in_wave & ((1ull << lane) - 1ull)), total = 0;
+        for (int w = 0; w < nthreads / kWave; ++w) {
+            if (w < wave) slot += wave_kept[w];
+            total += wave_kept[w];
+        }
+        total = min(total, capacity);
+        const bool kept = key != 0u && slot < capacity;
+        if (t < T) slot_of[static_cast<size_t>(t) * E + e] = kept ? slot : -1;
+        int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
+        if (kept) mine[slot] = t;
+        for (int i = total + t; i < capacity_host; i += nthreads) mine[i] = -1;
+        if (t == 0) counts[e] = total;
+        return;
+    }
+    keys[t] = key;
+    __syncthreads();
+    // candidates that precede this one: of the waves before, >=; of the waves behind, >; inside the wave by lane
+    int before = 0;
+    const uint4* k4 = reinterpret_cast<const uint4*>(keys);
+    const int uwave = __builtin_amdgcn_readfirstlane(wave), waves = nthreads / kWave;
+    for (int w = 0; w < waves; ++w) {
+        if (w == uwave) continue;
+        uint4 v[kWave / 4];                             // a wave's 64 keys requested together
+#pragma unroll
+        for (int i = 0; i < kWave / 4; ++i) v[i] = k4[w * (kWave / 4) + i];
+        const uint32_t edge = w < uwave ? key - 1u : key;              // >= key as > key - 1 (candidates: key >= 1)
+#pragma unroll
+        for (int i = 0; i < kWave / 4; ++i) before += (v[i].x > edge) + (v[i].y > edge) + (v[i].z > edge) + (v[i].w > edge);
+    }
+#pragma unroll 4
+    for (int i = 0; i < kWave / 4; ++i) {
+        const uint4 v = k4[wave * (kWave / 4) + i];
+        const uint32_t f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) before += f[j] > key || (f[j] == key && 4 * i + j < lane);
+    }
+    const bool kept = key != 0u && before < capacity;    // (a key of 0 is no candidate)
+    const uint64_t in_wave = __ballot(kept);
+    if (lane == 0) wave_kept[wave] = __popcll(in_wave);
+    __syncthreads();
+    int slot = __popcll(in_wave & ((1ull << lane) - 1ull)), total = 0;
+    for (int w = 0; w < nthreads / kWave; ++w) {
+        if (w < wave) slot += wave_kept[w];
+        total += wave_kept[w];
+    }
+    if (t < T) slot_of[static_cast<size_t>(t) * E + e] = kept ? slot : -1;
+    int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
+    if (kept) mine[slot] = t;
+    for (int i = total + t; i < capacity_host; i += nthreads) mine[i] = -1;
+    if (t == 0) counts[e] = total;
+}
+
 }  // namespace
 
 // Tokens per chunk (= per thread of the per-expert kernel): a power of two from 4 to 64 while the column fits
@@ -743,6 +849,11 @@ hipError_t static_select_scratch(void** out) {
 hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_expert, int32_t* slot_of,
                          int32_t* slot_token, int32_t* counts, const SelectWs& w, hipStream_t st,
                          const int32_t* capacity_dev, long long sum_need) {
+    if (c.T <= kSmallTokens && c.mode != ETR_MODE_BIDIR_STRICT && sum_need <= 0) {
+        hipLaunchKernelGGL(small_select_kernel, dim3(c.E), dim3((c.T + kWave - 1) / kWave * kWave), 0, st, score, c.T, c.E, c.k,
+                           c.capacity, c.mode, capacity_dev, topk_expert, slot_of, slot_token, counts);
+        return hipGetLastError();
+    }
     int G = 1;
     while (G < c.E) G <<= 1;
 #define ETR_TC(GG)                                                                                              \
