@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kTileThreads) void gather_transpose_kernel(const T*
 // Element-wise middle of the FFN backward for one 64 x 64 tile (buffer rows x hidden units) of one expert.
 //   in : u, a, b [E][C][H];  gate through slot_token
 //   out: dab [E][C][2H] = (da | db);  daT, dbT, hT [E][H][Cp];
-//        dgate_part [H/64][E][C]: this tile's share of <u, h> per row (summed by dx_kernel in tile order)
+//        dgate_part [H/64][E][C]: this tile's share of <u, h> per row (summed by dx_kernel in a fixed order)
 // ROWS: no transposed copies; dab and h are [E][Cp][.] row-major with zero rows from counts[e] to padded_rows (the
 // products that contract over the rows read them through transposing LDS reads); hT then is that row-major h.
 // SCALE_H (with ROWS): hT holds gate * h, so that dW_down = dOut_p^T (gate h) needs no scaled copy of dOut's rows.
@@ -257,24 +257,31 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const T* __restrict__ 
 }
 
 // Variant with renormalised weights: gate_eff[t][e] = gate[t][e] / (sum of gate[t][.] over the experts that kept t)
-// for kept pairs, 0 otherwise.  One thread per token.
+// for kept pairs, 0 otherwise.  G lanes per token (a power of two >= E); latency-bound (one thread per token walking the
+// experts twice: 9 us for 3001 x 12, now 5).
 __global__ __launch_bounds__(256) void gate_eff_kernel(const float* __restrict__ gate, const int32_t* __restrict__ slot_of,
-                                                       float* __restrict__ gate_eff, int T_, int E) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= T_) return;
-    float sum = 0.f;
-    for (int e = 0; e < E; ++e)
-        if (slot_of[static_cast<size_t>(t) * E + e] >= 0) sum += gate[static_cast<size_t>(t) * E + e];
-    const float inv = sum > 0.f ? 1.0f / sum : 0.f;
-    for (int e = 0; e < E; ++e)
-        gate_eff[static_cast<size_t>(t) * E + e] =
-            slot_of[static_cast<size_t>(t) * E + e] >= 0 ? gate[static_cast<size_t>(t) * E + e] * inv : 0.f;
+                                                       float* __restrict__ gate_eff, int T_, int E, int G) {
+    const long long i = static_cast<long long>(blockIdx.x) * 256 + threadIdx.x;
+    const long long t = i / G;
+    const int e = static_cast<int>(i - t * G);
+    const bool in = t < T_ && e < E;
+    const size_t at = in ? static_cast<size_t>(t) * E + e : 0;
+    const float g = in && slot_of[at] >= 0 ? gate[at] : 0.f;
+    float sum = g;
+    for (int m = G >> 1; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+    if (in) gate_eff[at] = g * (sum > 0.f ? 1.0f / sum : 0.f);
 }
 
 // dx[t] = sum_e dXp[e][slot_of[t][e]] + router term; one wavefront per token.
 // Router term: dscore[e] = gate[e] (dgate[e] - sum_e' dgate[e'] gate[e']); with Eq. 4 in the form
 //   FULL:   score = sqrt(D) <g, w> / (|x| |w|)  ->  d score / d x_j = sqrt(D) w[p(j)] / (D |x| |w|) - score x_j / |x|^2
 //   POOLED: score = <g, w> / (|g| |w|)          ->  d score / d x_j = (w[p(j)] / (|g| |w|) - score g[p(j)] / |g|^2) / D
+// Bound by memory where tokens are many (65536 tokens, 8 experts: 646 us for 3.2 GB) and by latency otherwise, so
+// nothing is walked element after element: a wave takes kNormRows embedding rows at a time for their norms, and the gate-gradient
+// partials of a kept pair (one per 64 hidden units) are read by as many lanes, four pairs at a time, and folded.
+// (A thread per embedding and a lane per pair before: 8192 tokens, 16 experts, 88 partials 77 us, now 53; 3001 tokens,
+// 12 experts, 1080 wide 32 us, now 20; 4512 tokens, 8 experts, 82 partials 49, now 26.)
+constexpr int kNormRows = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const float* __restrict__ w_emb,
                                                  const float* __restrict__ score, const float* __restrict__ gate,
@@ -291,29 +298,65 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
     float* v = g + P;
     float* ds = v + P;
     int* sl = reinterpret_cast<int*>(ds + E);
-    for (int i = threadIdx.x; i < E * P; i += blockDim.x) w[i] = w_emb[i];
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-        float s = 0.f;
-        for (int p = 0; p < P; ++p) s += w[e * P + p] * w[e * P + p];
-        wn[e] = s > 0.f ? rsqrtf(s) : 0.f;
+    for (int e0 = wave; e0 < E; e0 += 4 * kNormRows) {
+        float s[kNormRows];
+#pragma unroll
+        for (int r = 0; r < kNormRows; ++r) s[r] = 0.f;
+        for (int p = lane; p < P; p += 64) {
+            float f[kNormRows];
+#pragma unroll
+            for (int r = 0; r < kNormRows; ++r) f[r] = e0 + 4 * r < E ? w_emb[static_cast<size_t>(e0 + 4 * r) * P + p] : 0.f;
+#pragma unroll
+            for (int r = 0; r < kNormRows; ++r) {
+                if (e0 + 4 * r < E) w[(e0 + 4 * r) * P + p] = f[r];
+                s[r] += f[r] * f[r];
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int r = 0; r < kNormRows; ++r) s[r] += __shfl_xor(s[r], o, 64);
+#pragma unroll
+        for (int r = 0; r < kNormRows; ++r)
+            if (lane == 0 && e0 + 4 * r < E) wn[e0 + 4 * r] = s[r] > 0.f ? rsqrtf(s[r]) : 0.f;
     }
     __syncthreads();
     const int t = blockIdx.x * 4 + wave;
     if (t >= T_) return;                 // no block-wide barrier below
     const T* xr = x + static_cast<size_t>(t) * d;
-    // softmax backward (E <= 64: lane e); its scattered reads are requested first and land while the row is walked
+    // softmax backward (E <= 64: lane e)
     float dg = 0.f, gt = 0.f, sc = 0.f;
     int slot = -1;
     if (lane < E) {
         slot = slot_of[static_cast<size_t>(t) * E + lane];
         gt = gate[static_cast<size_t>(t) * E + lane];
         sc = score[static_cast<size_t>(t) * E + lane];
-        if (slot >= 0 && slot < C) {
-            for (int i = 0; i < n_part; ++i) dg += dgate_part[(static_cast<size_t>(i) * E + lane) * C + slot];
-        } else {
-            slot = -1;
+        if (slot >= C) slot = -1;
+        if (slot < 0) slot = -1;
+    }
+    const uint64_t kept_mask = __ballot(slot >= 0);
+    for (uint64_t left = kept_mask; left;) {             // four kept pairs at a time, their partials over the lanes
+        int e4[4], s4[4];
+        float part[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            e4[j] = left ? __builtin_ctzll(left) : -1;
+            if (left) left &= left - 1;
+            s4[j] = __builtin_amdgcn_readlane(slot, e4[j] < 0 ? 0 : e4[j]);
+            part[j] = 0.f;
         }
+        for (int i = lane; i < n_part; i += 64) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (e4[j] >= 0) part[j] += dgate_part[(static_cast<size_t>(i) * E + e4[j]) * C + s4[j]];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[j] += __shfl_xor(part[j], o, 64);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (lane == e4[j]) dg = part[j];
     }
     // pooled features and norms
     float xx = 0.f, gg = 0.f;
@@ -374,7 +417,6 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) beta += __shfl_xor(beta, o, 64);
     // the token's kept pairs in ascending expert order, as rows of dxp (sl[i], i < n_kept)
-    const uint64_t kept_mask = __ballot(slot >= 0);
     const int n_kept = __popcll(kept_mask);
     if (lane < E) {
         ds[lane] = dsv;
@@ -482,7 +524,10 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     const float* gate_w = gate;
     if (c.gate_norm) {
         float* ge = reinterpret_cast<float*>(base + L.gate_eff);
-        hipLaunchKernelGGL(gate_eff_kernel, dim3((Tn + 255) / 256), dim3(256), 0, st, gate, slot_of, ge, Tn, E);
+        int G = 1;
+        while (G < E) G <<= 1;
+        hipLaunchKernelGGL(gate_eff_kernel, dim3(static_cast<unsigned>((static_cast<long long>(Tn) * G + 255) / 256)), dim3(256), 0,
+                           st, gate, slot_of, ge, Tn, E, G);
         gate_w = ge;
     }
     float* dgate_part = reinterpret_cast<float*>(base + L.dgate_part);
