@@ -14,6 +14,8 @@
 // whose row tile starts past counts[e] exits at once.  Either way counts never leave the device.
 // fp32: the same product on v_mfma_f32_16x16x4_f32, one workgroup per tile.
 
+#include <cmath>
+
 #include "etr_internal.h"
 
 namespace etr {
@@ -2007,21 +2009,29 @@ size_t ffn_ws_bytes(const etr_config& c) {
 //   RING        whole k-tiles where the persistent kernel does not apply (narrow outputs, short contractions)
 //   STAGED      everything else
 enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
-// Estimated cost of both kernels in row x weight-row products at the persistent kernel's full rate (1100 TFLOP/s).
-// gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows.  Persistent: whole rounds of 256 x 256 tiles over the CUs, and
-// never faster than its weights arrive (3.5 TB/s, as long as 314 rows are multiplied).  Measured, both products of a layer,
-// rows per expert: time here / time there, us.  16 experts, 2048 x 5632: 16: 216 / 356, 48: 270 / 321, 64: 290 / 311, 96: 517 / 317.
-// 32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.  8 experts, 512 x 1024, 16 to 64 tiles per product:
-// 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.
+// Estimated microseconds of both kernels, from measured rates.
+// gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows (a lone block of 16 or 32 rows loads 10 or 12 fragments per
+// k-tile instead of 16), at least the weights at 5 TB/s, 7 us besides.
+// Persistent: rounds of 256 x 256 tiles over the CUs, 1.95 us per 64-wide k-tile on a full chip (its power limit) and 1.2
+// where up to half of the CUs have a tile; at least the weights at 3.5 TB/s; 10 us besides.
+// Both products of a layer, rows per expert: this kernel / the persistent one, us.  16 experts, 2048 x 5632: 16: 216 / 356,
+// 48: 270 / 321, 64: 290 / 311, 96: 517 / 317.  32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.
+// 8 experts, 512 x 1024: 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.
 static bool few_rows_pay(const GemmParams& g, bool glu, int rows_expected) {
     if (rows_expected < 1 || g.k_counts) return false;
     if (static_cast<double>(g.E) * ((g.capacity + kRowsBM - 1) / kRowsBM) * (g.N / 32 + 1) >= 2.0e9) return false;   // grid size
-    const double weight_rows = static_cast<double>(g.E) * g.N * (glu ? 2 : 1);
+    const double weights = static_cast<double>(g.E) * g.N * (glu ? 2 : 1) * g.K;
+    const int blocks = rows_expected <= 16 ? 1 : (rows_expected <= 32 ? 2 : 4);
+    const double loads = rows_expected <= kRowsBM ? (8 + 2 * blocks) / 16.0 : 1.0;
+    const double mult = 2.0 * weights * kRowsBM * ((rows_expected + kRowsBM - 1) / kRowsBM) * loads / 270e6;
+    const double rows_us = (mult > weights * 2 / 5e6 ? mult : weights * 2 / 5e6) + 7.0;
+    const double n_cu = cu_count();
     const double tiles = static_cast<double>(g.E) * ((rows_expected + 255) / 256) * ((g.N + (glu ? 127 : 255)) / (glu ? 128 : 256));
-    const int n_cu = cu_count();
-    const double rounds = static_cast<double>(static_cast<long long>((tiles + n_cu - 1) / n_cu));
-    const double persistent = rounds * n_cu * 65536.0, streamed = weight_rows * 314.0;
-    return weight_rows * 262.0 * ((rows_expected + kRowsBM - 1) / kRowsBM) < (persistent > streamed ? persistent : streamed);
+    const double fill = tiles < n_cu ? tiles / n_cu : 1.0;
+    const double step = fill <= 0.5 ? 1.2 : 1.2 + 1.5 * (fill - 0.5);
+    const double walk = std::ceil(tiles / n_cu) * ((g.K + 63) / 64) * step;
+    const double tiles_us = (walk > weights * 2 / 3.5e6 ? walk : weights * 2 / 3.5e6) + 10.0;
+    return rows_us < tiles_us;
 }
 static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int rows_expected) {
     const size_t a_row_bytes = static_cast<size_t>(g.lda ? g.lda : g.K) * 2, b_row_bytes = static_cast<size_t>(g.ldb ? g.ldb : g.K) * 2;
