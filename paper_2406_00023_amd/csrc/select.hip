@@ -223,6 +223,12 @@ __device__ __forceinline__ void block_sum3(int& a, int& b, int& c, int (*red)[3]
     for (int w = 0; w < kSelThreads / kWave; ++w) { a += red[w][0]; b += red[w][1]; c += red[w][2]; }
 }
 
+// Fixed-point term of a positive affinity (key >= key(+0)): round(min(s, 1) * 2^30).  Scaling by a power of two is exact,
+// so the rounding in fp32 is that of the exact product.
+__device__ __forceinline__ uint32_t affinity_term(uint32_t key) {
+    return static_cast<uint32_t>(__builtin_rintf(fminf(__uint_as_float(key & 0x7FFFFFFFu), 1.0f) * 1073741824.0f));
+}
+
 constexpr int kRadixBits = 11;           // digit width of the threshold search
 constexpr int kBins = 1 << kRadixBits;   // 2048 bins: 32 per lane of a wave
 constexpr int kMaxDigits = 3;            // 32 key bits in digits of at most 11
@@ -365,10 +371,6 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
     if constexpr (ADAPT) if (sum_need > 0 && (mode == ETR_MODE_ECR || mode == ETR_MODE_BIDIR) && n_keep > 0) {
         __shared__ __attribute__((aligned(16))) unsigned long long sums[kBins];
         __shared__ int red_cnt[kSelThreads / kWave];
-        // term of a positive affinity (key >= key(+0)); scaling by a power of two is exact, so is its rounding in fp32
-        auto term = [](uint32_t key) {
-            return static_cast<uint32_t>(__builtin_rintf(fminf(__uint_as_float(key & 0x7FFFFFFFu), 1.0f) * 1073741824.0f));
-        };
         auto for_keys = [&](auto&& f) {
             if constexpr (IPT > 0) {
 #pragma unroll
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
             sums[2 * tid] = 0ull; sums[2 * tid + 1] = 0ull;
             __syncthreads();
             for_keys([&](uint32_t key) {
-                if (key - th <= span) atomicAdd(&sums[(key >> shift) & dmask], static_cast<unsigned long long>(term(key)));
+                if (key - th <= span) atomicAdd(&sums[(key >> shift) & dmask], static_cast<unsigned long long>(affinity_term(key)));
             });
             __syncthreads();
             // every wave by itself: the highest bin at which the sum from the top reaches the threshold
@@ -433,7 +435,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
             n_gt = 0;
 #pragma unroll
             for (int w = 0; w < kSelThreads / kWave; ++w) n_gt += red_cnt[w];
-            const long long q_th = term(th);
+            const long long q_th = affinity_term(th);
             const long long ell = n_gt + (sum_need - above_sum + q_th - 1) / q_th;       // q_th > 0: its bin reached the sum
             if (ell < n_keep) n_keep = static_cast<int>(ell);
         }
@@ -677,7 +679,7 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
 }
 
 // ---------------------------------------------------------------------------------------
-// Everything in one launch for short batches (T <= kSmallTokens, no strict intersection, no affinity-sum threshold):
+// Everything in one launch for short batches (T <= kSmallTokens, no strict intersection):
 // one workgroup per expert, one thread per token.  What a small call pays for is launches and dependent latencies, so
 // each workgroup reads all scores (they are in the caches) and finds its expert's place in every token's list by
 // counting the better experts of the row; the keys of its column meet in LDS, and a candidate is kept if fewer than
@@ -686,13 +688,19 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
 // Counting grows with T^2.  One call against the three launches, T x E: 32 x 16 5.4 / 12.3 us, 256 x 32 9.0 / 14.5,
 // 512 x 8 10.2 / 12.3, 512 x 64 15.6 / 20.7; from 1024 tokens on it would be the slower one.
 // ---------------------------------------------------------------------------------------
+// ADAPT: with the affinity-sum threshold (ECR and BIDIR).  The walk from the highest affinity down stops at the first
+// prefix whose sum of positive affinities reaches it, so a candidate is kept if the terms of those that precede it do
+// not: one more sum in the same pass (82 tokens x 8 experts: 57 us in three launches by bisection, 24 with the
+// digit histograms, 9 here).
 constexpr int kSmallTokens = 512;
+template <bool ADAPT>
 __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float* __restrict__ score, int T, int E, int k,
                                                                     int capacity_host, int mode,
-                                                                    const int32_t* __restrict__ capacity_dev,
+                                                                    const int32_t* __restrict__ capacity_dev, long long sum_need,
                                                                     int32_t* __restrict__ topk, int32_t* __restrict__ slot_of,
                                                                     int32_t* __restrict__ slot_token, int32_t* __restrict__ counts) {
     __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallTokens];
+    __shared__ __attribute__((aligned(16))) uint32_t terms[ADAPT ? kSmallTokens : 4];
     __shared__ int wave_kept[kSmallTokens / kWave];
     const int e = blockIdx.x, t = threadIdx.x, nthreads = blockDim.x;       // nthreads: T rounded up to whole waves
     const int lane = t & (kWave - 1), wave = t / kWave;
@@ -745,10 +753,13 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         return;
     }
     keys[t] = key;
+    if constexpr (ADAPT) terms[t] = key >= 0x80000000u ? affinity_term(key) : 0u;
     __syncthreads();
     // candidates that precede this one: of the waves before, >=; of the waves behind, >; inside the wave by lane
     int before = 0;
+    unsigned long long before_sum = 0ull;
     const uint4* k4 = reinterpret_cast<const uint4*>(keys);
+    const uint4* t4 = reinterpret_cast<const uint4*>(terms);
     const int uwave = __builtin_amdgcn_readfirstlane(wave), waves = nthreads / kWave;
     for (int w = 0; w < waves; ++w) {
         if (w == uwave) continue;
@@ -757,16 +768,30 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         for (int i = 0; i < kWave / 4; ++i) v[i] = k4[w * (kWave / 4) + i];
         const uint32_t edge = w < uwave ? key - 1u : key;              // >= key as > key - 1 (candidates: key >= 1)
 #pragma unroll
-        for (int i = 0; i < kWave / 4; ++i) before += (v[i].x > edge) + (v[i].y > edge) + (v[i].z > edge) + (v[i].w > edge);
+        for (int i = 0; i < kWave / 4; ++i) {
+            before += (v[i].x > edge) + (v[i].y > edge) + (v[i].z > edge) + (v[i].w > edge);
+            if constexpr (ADAPT) {
+                const uint4 q = t4[w * (kWave / 4) + i];
+                before_sum += (v[i].x > edge ? q.x : 0u);
+                before_sum += (v[i].y > edge ? q.y : 0u);
+                before_sum += (v[i].z > edge ? q.z : 0u);
+                before_sum += (v[i].w > edge ? q.w : 0u);
+            }
+        }
     }
 #pragma unroll 4
     for (int i = 0; i < kWave / 4; ++i) {
         const uint4 v = k4[wave * (kWave / 4) + i];
         const uint32_t f[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) before += f[j] > key || (f[j] == key && 4 * i + j < lane);
+        for (int j = 0; j < 4; ++j) {
+            const bool first = f[j] > key || (f[j] == key && 4 * i + j < lane);
+            before += first;
+            if constexpr (ADAPT) before_sum += first ? terms[wave * kWave + 4 * i + j] : 0u;
+        }
     }
-    const bool kept = key != 0u && before < capacity;    // (a key of 0 is no candidate)
+    bool kept = key != 0u && before < capacity;          // (a key of 0 is no candidate)
+    if constexpr (ADAPT) kept = kept && before_sum < static_cast<unsigned long long>(sum_need);
     const uint64_t in_wave = __ballot(kept);
     if (lane == 0) wave_kept[wave] = __popcll(in_wave);
     __syncthreads();
@@ -849,9 +874,11 @@ hipError_t static_select_scratch(void** out) {
 hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_expert, int32_t* slot_of,
                          int32_t* slot_token, int32_t* counts, const SelectWs& w, hipStream_t st,
                          const int32_t* capacity_dev, long long sum_need) {
-    if (c.T <= kSmallTokens && c.mode != ETR_MODE_BIDIR_STRICT && sum_need <= 0) {
-        hipLaunchKernelGGL(small_select_kernel, dim3(c.E), dim3((c.T + kWave - 1) / kWave * kWave), 0, st, score, c.T, c.E, c.k,
-                           c.capacity, c.mode, capacity_dev, topk_expert, slot_of, slot_token, counts);
+    if (c.T <= kSmallTokens && c.mode != ETR_MODE_BIDIR_STRICT) {
+        const bool by_sum = sum_need > 0 && (c.mode == ETR_MODE_ECR || c.mode == ETR_MODE_BIDIR);
+        hipLaunchKernelGGL(by_sum ? small_select_kernel<true> : small_select_kernel<false>, dim3(c.E),
+                           dim3((c.T + kWave - 1) / kWave * kWave), 0, st, score, c.T, c.E, c.k, c.capacity, c.mode, capacity_dev,
+                           sum_need, topk_expert, slot_of, slot_token, counts);
         return hipGetLastError();
     }
     int G = 1;

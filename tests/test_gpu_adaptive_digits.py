@@ -1,5 +1,5 @@
-"""The adaptive token count's digit-by-digit threshold search at every chunk length of the per-expert kernel (registers,
-slice histograms, streamed columns), on affinities that crowd into few digits, tie, or round to zero terms; and the
+"""The adaptive token count: by counting in the one-launch selection of short batches, and its digit-by-digit threshold
+search at every chunk length of the per-expert kernel (registers, slice histograms, streamed columns), on affinities that crowd into few digits, tie, or round to zero terms; and the
 routing statistics at token counts around the unrolled pass of a workgroup."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def _scores(kind, T, E):
     return s.astype(np.float32)
 
 
-@pytest.mark.parametrize("T,E,k", [(900, 3, 2), (8000, 2, 1), (15000, 5, 2), (32768, 2, 2), (65536, 33, 4), (66001, 3, 1)])
+@pytest.mark.parametrize("T,E,k", [(1, 2, 1), (130, 7, 3), (512, 4, 2), (900, 3, 2), (8000, 2, 1), (15000, 5, 2), (32768, 2, 2), (65536, 33, 4), (66001, 3, 1)])
 @pytest.mark.parametrize("kind", ["cosine", "crowded", "zeros"])
 def test_adaptive_count_digits(oracle, T, E, k, kind):
     B.load_library()
