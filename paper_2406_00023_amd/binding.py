@@ -89,16 +89,23 @@ def make_config(shape: EtrShape, mode: Optional[int] = None, capacity: Optional[
                      shape.mode if mode is None else mode, shape.cos if cos is None else cos, gate_norm)
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
+# Small calls are bound by the host: addresses go to ctypes as plain integers (None = NULL; the declared argument types
+# convert them), and the raw stream handle comes without a Stream object around it.
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_contiguous():
         raise ValueError("tensors handed to the library must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream() -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(fn: str, status: int):
