@@ -2001,7 +2001,7 @@ size_t ffn_ws_bytes(const etr_config& c) {
 }
 
 // Which kernel a row-major bf16 product takes.  Both pipelined kernels need 32-bit byte offsets inside one operand.
-//   ROWS        few rows per group expected, or too few 256-row tiles to fill the chip: see few_rows_pay
+//   ROWS        few rows per group expected, or too few 256-row tiles to fill the chip: see bf16_costs
 //   PERSISTENT  at least one whole column tile, a contraction of 128 or more, the super-tile prefix in LDS.  A
 //               contraction that is not whole 64-wide k-tiles takes its zero-filling instantiation (per-group lengths
 //               are always whole k-tiles).  12 experts of 135-938 rows, 1080 x 2744 (K % 64 = 56): 262 -> 150 us for
@@ -2009,37 +2009,46 @@ size_t ffn_ws_bytes(const etr_config& c) {
 //   RING        whole k-tiles where the persistent kernel does not apply (narrow outputs, short contractions)
 //   STAGED      everything else
 enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
-// Estimated microseconds of both kernels, from measured rates.
-// gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows (a lone block of 16 or 32 rows loads 10 or 12 fragments per
-// k-tile instead of 16), at least the weights at 5 TB/s, 7 us besides.
-// Persistent: rounds of 256 x 256 tiles over the CUs, 1.95 us per 64-wide k-tile on a full chip (its power limit) and 1.2
-// where up to half of the CUs have a tile; at least the weights at 3.5 TB/s; 10 us besides.
-// Both products of a layer, rows per expert: this kernel / the persistent one, us.  16 experts, 2048 x 5632: 16: 216 / 356,
-// 48: 270 / 321, 64: 290 / 311, 96: 517 / 317.  32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.
-// 8 experts, 512 x 1024: 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.
-static bool few_rows_pay(const GemmParams& g, bool glu, int rows_expected) {
-    if (rows_expected < 1 || g.k_counts) return false;
-    if (static_cast<double>(g.E) * ((g.capacity + kRowsBM - 1) / kRowsBM) * (g.N / 32 + 1) >= 2.0e9) return false;   // grid size
-    const double weights = static_cast<double>(g.E) * g.N * (glu ? 2 : 1) * g.K;
+// Estimated microseconds of a product on each kernel, from measured rates, for the expected rows per group.
+//   rows        gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows (a lone block of 16 or 32 rows loads 10 or 12
+//               fragments per k-tile instead of 16), at least the weights at 5 TB/s, 7 us besides
+//   persistent  rounds of 256 x 256 tiles over the CUs, 1.95 us per 64-wide k-tile on a full chip (its power limit) and
+//               1.2 where up to half of the CUs have a tile, 1.13 and 1.3 times that with zero-filling copies; at least the
+//               weights at 3.5 TB/s; 10 us besides
+//   staged      128-row tiles, 360 (gate/up) and 200 TFLOP/s, 3 us besides; a candidate for ragged contractions only
+// Both products of a layer, rows per expert: rows / persistent, us.  16 experts, 2048 x 5632: 16: 216 / 356, 48: 270 / 321,
+// 64: 290 / 311, 96: 517 / 317.  32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.  8 experts,
+// 512 x 1024: 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.  Gate/up of 4 experts x 297 rows, 1392 x 1408 (88 tiles, ragged): staged 33,
+// persistent 46; of 12 experts, 1080 x 2744 (792 tiles): 262 and 150.
+struct Bf16Costs { double rows, persistent, staged; };
+static Bf16Costs bf16_costs(const GemmParams& g, bool glu, int rows_expected) {
+    const double weights = static_cast<double>(g.E) * g.N * (glu ? 2 : 1) * g.K;       // elements; x 2 = flops per row, = bytes
+    auto mult = [&](int block) { return 2.0 * weights * ((rows_expected + block - 1) / block) * block; };
+    auto larger = [](double a, double b) { return a > b ? a : b; };
     const int blocks = rows_expected <= 16 ? 1 : (rows_expected <= 32 ? 2 : 4);
     const double loads = rows_expected <= kRowsBM ? (8 + 2 * blocks) / 16.0 : 1.0;
-    const double mult = 2.0 * weights * kRowsBM * ((rows_expected + kRowsBM - 1) / kRowsBM) * loads / 270e6;
-    const double rows_us = (mult > weights * 2 / 5e6 ? mult : weights * 2 / 5e6) + 7.0;
+    Bf16Costs c;
+    c.rows = larger(mult(kRowsBM) * loads / 270e6, weights * 2 / 5e6) + 7.0;
     const double n_cu = cu_count();
     const double tiles = static_cast<double>(g.E) * ((rows_expected + 255) / 256) * ((g.N + (glu ? 127 : 255)) / (glu ? 128 : 256));
-    const double fill = tiles < n_cu ? tiles / n_cu : 1.0;
-    const double step = fill <= 0.5 ? 1.2 : 1.2 + 1.5 * (fill - 0.5);
-    const double walk = std::ceil(tiles / n_cu) * ((g.K + 63) / 64) * step;
-    const double tiles_us = (walk > weights * 2 / 3.5e6 ? walk : weights * 2 / 3.5e6) + 10.0;
-    return rows_us < tiles_us;
+    const double fill = tiles < 0.5 * n_cu ? 0.5 : (tiles < n_cu ? tiles / n_cu : 1.0);
+    const double step = (1.2 + 1.5 * (fill - 0.5)) * (g.K % 64 ? 1.3 - 0.34 * (fill - 0.5) : 1.0);
+    c.persistent = larger(std::ceil(tiles / n_cu) * ((g.K + 63) / 64) * step, weights * 2 / 3.5e6) + 10.0;
+    c.staged = mult(128) / (glu ? 360e6 : 200e6) + 3.0;
+    return c;
 }
 static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int rows_expected) {
     const size_t a_row_bytes = static_cast<size_t>(g.lda ? g.lda : g.K) * 2, b_row_bytes = static_cast<size_t>(g.ldb ? g.ldb : g.K) * 2;
     const size_t a_bytes = a_rows * a_row_bytes, b_bytes = static_cast<size_t>(g.N) * b_row_bytes;
     if (g.K % 8 != 0 || a_row_bytes % 16 != 0 || b_row_bytes % 16 != 0 || a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32))
         return Bf16Kernel::STAGED;
-    if (few_rows_pay(g, glu, rows_expected)) return Bf16Kernel::ROWS;
     const bool whole = g.K % 64 == 0;
+    if (rows_expected > 0 && !g.k_counts) {
+        const Bf16Costs c = bf16_costs(g, glu, rows_expected);
+        const double blocks = static_cast<double>(g.E) * ((g.capacity + kRowsBM - 1) / kRowsBM) * (g.N / 32 + 1);   // grid size
+        if (blocks < 2.0e9 && c.rows < c.persistent && (whole || c.rows < c.staged)) return Bf16Kernel::ROWS;
+        if (!whole && c.staged < c.persistent) return Bf16Kernel::STAGED;
+    }
     if (!whole && (g.k_counts || a_bytes >= kBufferRange || b_bytes >= kBufferRange)) return Bf16Kernel::STAGED;
     if (persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu)) return Bf16Kernel::PERSISTENT;
     return whole ? Bf16Kernel::RING : Bf16Kernel::STAGED;
