@@ -2015,11 +2015,12 @@ enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
 //   persistent  rounds of 256 x 256 tiles over the CUs, 1.95 us per 64-wide k-tile on a full chip (its power limit) and
 //               1.2 where up to half of the CUs have a tile, 1.13 and 1.3 times that with zero-filling copies; at least the
 //               weights at 3.5 TB/s; 10 us besides
-//   staged      128-row tiles, 360 (gate/up) and 200 TFLOP/s, 3 us besides; a candidate for ragged contractions only
+//   staged      128-row tiles, two per CU: 360 (gate/up) and 200 TFLOP/s, at least 1.15 us per k-tile (its loads are waited
+//               for in each), 3 us besides; a candidate for ragged contractions only
 // Both products of a layer, rows per expert: rows / persistent, us.  16 experts, 2048 x 5632: 16: 216 / 356, 48: 270 / 321,
 // 64: 290 / 311, 96: 517 / 317.  32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.  8 experts,
 // 512 x 1024: 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.  Gate/up of 4 experts x 297 rows, 1392 x 1408 (88 tiles, ragged): staged 33,
-// persistent 46; of 12 experts, 1080 x 2744 (792 tiles): 262 and 150.
+// persistent 46; of 12 experts, 1080 x 2744 (792 tiles): 262 and 150; of 4 experts x 97 rows, 2232 x 1472: staged 42, rows 29.
 struct Bf16Costs { double rows, persistent, staged; };
 static Bf16Costs bf16_costs(const GemmParams& g, bool glu, int rows_expected) {
     const double weights = static_cast<double>(g.E) * g.N * (glu ? 2 : 1) * g.K;       // elements; x 2 = flops per row, = bytes
@@ -2034,7 +2035,8 @@ static Bf16Costs bf16_costs(const GemmParams& g, bool glu, int rows_expected) {
     const double fill = tiles < 0.5 * n_cu ? 0.5 : (tiles < n_cu ? tiles / n_cu : 1.0);
     const double step = (1.2 + 1.5 * (fill - 0.5)) * (g.K % 64 ? 1.3 - 0.34 * (fill - 0.5) : 1.0);
     c.persistent = larger(std::ceil(tiles / n_cu) * ((g.K + 63) / 64) * step, weights * 2 / 3.5e6) + 10.0;
-    c.staged = mult(128) / (glu ? 360e6 : 200e6) + 3.0;
+    const double tiles128 = static_cast<double>(g.E) * ((rows_expected + 127) / 128) * ((g.N + (glu ? 63 : 127)) / (glu ? 64 : 128));
+    c.staged = larger(mult(128) / (glu ? 360e6 : 200e6), std::ceil(tiles128 / (2 * n_cu)) * ((g.K + 63) / 64) * 1.15) + 3.0;
     return c;
 }
 static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int rows_expected) {
