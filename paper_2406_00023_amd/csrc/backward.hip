@@ -536,6 +536,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     if (!pre_a || !pre_b) {                              // nothing kept from the forward call: recompute
         GroupedGemm g1{x, w_gate, w_up, at(L.a), at(L.b), counts, nullptr, slot_token, E, C, H, d, 0, 0, Tn, GEMM_DUAL, c.dtype};
         g1.rows_expected = rows_expected(c);             // the kernel of the forward call: kept and recomputed values agree
+        g1.rows_total = rows_total(c);
         ETR_BW(launch_grouped_gemm(g1, st));
         pre_a = at(L.a); pre_b = at(L.b);
     }

@@ -61,6 +61,7 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
 // (then xp is never materialised by the fused forward).
 bool ffn_can_gather(const etr_config& c);
 int rows_expected(const etr_config& c);      // rows per expert that a batch can be expected to fill
+long long rows_total(const etr_config& c);   // rows of all experts together that the selection can keep
 
 // General grouped product of ffn.hip, used by the backward pass:
 //   C[g][m][n] = sum_k A[g][m][k] * B[g][n][k]   (both operands contiguous along k)
@@ -92,6 +93,9 @@ struct GroupedGemm {
     int split_m = 0;
     // rows per group that the caller expects (0: unknown); picks the kernel for few rows (row-major bf16 operands)
     int rows_expected = 0;
+    // rows of all groups together that the batch can fill (0: unknown); sizes the grid of the kernel for few rows, which
+    // still covers every row that m_counts names
+    long long rows_total = 0;
 };
 hipError_t launch_grouped_gemm(const GroupedGemm& g, hipStream_t st);
 bool grouped_gemm_transposed_ok(const GroupedGemm& g);
@@ -120,6 +124,13 @@ hipError_t launch_capacity_lower_bound(const etr_config& c, const float* score, 
 //                       already been set for this (device, kernel); limits up to 64 KiB need no call at all
 int cu_count();
 hipError_t ensure_dynamic_lds(const void* kernel, size_t bytes);
+
+// For the tests, which have to know that a size reaches the kernel they are about: the kernel of a product of the expert
+// networks (product 0: gate/up, 1: down; gathered: rows read through slot_token, as the fused call does) and its number
+// of workgroups.  Host only; `c` must be valid.
+// 0 register-staged, 1 few rows, 2 persistent, 3 persistent with a zero-filled last k-tile, 4 ring, 5 / 6 fp32 with
+// 64 x 64 / 32 x 32 tiles.
+extern "C" int etr_ffn_plan(const etr_config* c, int product, int gathered, long long* workgroups);
 
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 inline size_t elt_bytes(int dtype) { return dtype == ETR_F32 ? 4 : 2; }

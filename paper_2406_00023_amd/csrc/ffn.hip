@@ -14,6 +14,7 @@
 // whose row tile starts past counts[e] exits at once.  Either way counts never leave the device.
 // fp32: the same product on v_mfma_f32_16x16x4_f32, one workgroup per tile.
 
+#include <algorithm>
 #include <cmath>
 
 #include "etr_internal.h"
@@ -50,6 +51,7 @@ struct GemmParams {
     // Plain epilogue of the transposing kernel with the output rows split between two arrays: rows below split_m go
     // to C, the others (as rows m - split_m) to C2, both [E][split_m][N] (a multiple of 32, capacity = 2 split_m).
     int split_m = 0;
+    long long rows_total = 0;   // host only: rows of all groups together that the batch can fill (0: unknown)
 };
 
 // rows of group e (counts may be absent: every group has `capacity` rows) and its contraction length
@@ -148,12 +150,13 @@ __device__ __forceinline__ bool decode_tile(const GemmParams& p, int& e, int& mt
     return mt < p.MT && nt < p.NT;
 }
 
-// The same for kernels with small tiles, whose grid is mostly dead where the capacity is far above the counts: only
-// tiles that hold rows are counted (a scan over the groups, one lane each; G <= 64), and each XCD gets an equal,
-// contiguous share of that list, row tiles fastest, so the tiles of one weight slice share an L2.  Dealing super-tiles
-// of the capacity instead left XCDs with half-dead ones: 8 fp32 experts of 66-640 rows, gate/up
-// product: 127 us against 92.
-__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int& e, int& mt, int& nt) {
+// The same for kernels with small tiles: only tiles that hold rows are counted (a scan over the groups, one lane each;
+// G <= 64), and each XCD gets an equal, contiguous share of that list, row tiles fastest, so the tiles of one weight
+// slice share an L2.  Dealing super-tiles of the capacity instead left XCDs with half-dead ones: 8 fp32 experts of
+// 66-640 rows, gate/up product: 127 us against 92.
+// j: place in the XCD's share, whose length is handed back.  With a workgroup for every tile of the capacity it is
+// blockIdx.x / 8 and done; a smaller grid (whole rounds of 8 all the same) goes on in steps of gridDim.x / 8 to the end.
+__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt) {
     const int lane = threadIdx.x & 63;
     const int mine = lane < p.E ? max((group_rows(p, lane) + BM - 1) / BM, 0) : 0;     // this group's row tiles
     int incl = mine;
@@ -163,9 +166,9 @@ __device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, in
         if (lane >= m) incl += o;
     }
     const int total = __builtin_amdgcn_readlane(incl, 63) * p.NT;
-    const int per = (total + 7) >> 3, j = blockIdx.x >> 3;
-    const int q = (blockIdx.x & 7) * per + j;
-    if (j >= per || q >= total) return false;
+    share = (total + 7) >> 3;
+    const int q = (blockIdx.x & 7) * share + j;
+    if (j >= share || q >= total) return false;
     const uint64_t in = __ballot(incl * p.NT > q);
     e = __builtin_ctzll(in);
     const int rows = __builtin_amdgcn_readlane(mine, e);
@@ -1748,14 +1751,18 @@ __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, in
 template <bool GLU, bool DUAL = false, bool KEEP = false>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
     __shared__ f32x4 red[4 * 16 * 64];
-    int e, mt, nt;
-    if (!decode_live_tile(p, kRowsBM, e, mt, nt)) return;
-    const int count = group_rows(p, e);
-    const int m0 = mt * kRowsBM, n0 = nt * (GLU ? 32 : 64);
-    const int rows = count - m0;
-    if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
-    else if (rows <= 32) rows_tile<2, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
-    else rows_tile<4, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+    int share, e, mt, nt;
+    for (int j = blockIdx.x >> 3; decode_live_tile(p, kRowsBM, j, share, e, mt, nt);) {
+        const int count = group_rows(p, e);
+        const int m0 = mt * kRowsBM, n0 = nt * (GLU ? 32 : 64);
+        const int rows = count - m0;
+        if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+        else if (rows <= 32) rows_tile<2, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+        else rows_tile<4, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+        j += gridDim.x >> 3;
+        if (j >= share) return;
+        __syncthreads();                                // the partial sums have been read
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1786,11 +1793,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
     constexpr int TM = BM / 32, TN = BN / 32;           // 16 x 16 blocks per wave and product
     constexpr int AHEAD = NBUF - 1;
     __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * STAGE];
-    int e, mt, nt;
-    if (!decode_live_tile(p, BM, e, mt, nt)) return;
+    int share, e, mt, nt;
+    if (!decode_live_tile(p, BM, blockIdx.x >> 3, share, e, mt, nt)) return;
     const int count = group_rows(p, e);
     const int m0 = mt * BM, n0 = nt * BN;
-    if (m0 >= count) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -1974,17 +1980,31 @@ inline long long plan_live_tiles(GemmParams& p, int BM, int BN) {
     p.NT = (p.N + BN - 1) / BN;
     return (static_cast<long long>(p.E) * p.MT * p.NT + 7) / 8 * 8;
 }
+// Workgroups of the few-rows kernel: one for every tile that rows_total rows in E groups can fill (each group ends in
+// one partial row tile at most), never more than the capacity has.  A buffer made once for the largest batch costs
+// nothing then: 32 tokens on 16 experts of 2048 x 5632, capacity 32 / 4096: 206 / 214 us for the layer, where a grid of
+// the whole capacity took 207 / 429 (256-row tiles: 354 / 369).  Counts beyond rows_total (rows that other processes
+// sent) send workgroups round their loop again.
+inline long long plan_rows(GemmParams& p, bool glu) {
+    const long long all = plan_live_tiles(p, kRowsBM, glu ? 32 : 64);
+    constexpr long long kMost = 1 << 23;                 // 2^31 threads: within what one launch may hold
+    const long long live = p.rows_total > 0 ? ((p.E + p.rows_total / kRowsBM) * p.NT + 7) / 8 * 8 : all;
+    return std::min({all, live, kMost});
+}
 template <bool GLU, bool DUAL = false, bool KEEP = false>
 hipError_t launch_bf16_rows(GemmParams p, hipStream_t st) {
-    const long long blocks = plan_live_tiles(p, kRowsBM, GLU ? 32 : 64);
+    const long long blocks = plan_rows(p, GLU);
     hipLaunchKernelGGL((gemm_bf16_rows_kernel<GLU, DUAL, KEEP>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     return hipGetLastError();
 }
+// Whether a product gets 64 x 64 tiles (two per CU at least) or 32 x 32 ones.  8 experts of 80 rows, 256 x 512 (128 and 64
+// tiles of 64 x 64): 11 and 8 us with 32 x 32 tiles, 15 and 14 with 64 x 64
+inline bool f32_large_tiles(const GemmParams& p) {
+    return static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64) >= 2ll * cu_count();
+}
 template <bool GLU, bool DUAL = false>
 hipError_t launch_f32(GemmParams p, hipStream_t st) {
-    const long long tiles64 = static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64);
-    // 8 experts of 80 rows, 256 x 512 (128 and 64 tiles of 64 x 64): 11 and 8 us with 32 x 32 tiles, 15 and 14 with 64 x 64
-    if (tiles64 >= 2ll * cu_count()) {
+    if (f32_large_tiles(p)) {
         const long long blocks = plan_live_tiles(p, 64, 64);
         hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     } else {
@@ -2047,8 +2067,7 @@ static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int 
     const bool whole = g.K % 64 == 0;
     if (rows_expected > 0 && !g.k_counts) {
         const Bf16Costs c = bf16_costs(g, glu, rows_expected);
-        const double blocks = static_cast<double>(g.E) * ((g.capacity + kRowsBM - 1) / kRowsBM) * (g.N / 32 + 1);   // grid size
-        if (blocks < 2.0e9 && c.rows < c.persistent && (whole || c.rows < c.staged)) return Bf16Kernel::ROWS;
+        if (c.rows < c.persistent && (whole || c.rows < c.staged)) return Bf16Kernel::ROWS;
         if (!whole && c.staged < c.persistent) return Bf16Kernel::STAGED;
     }
     if (!whole && (g.k_counts || a_bytes >= kBufferRange || b_bytes >= kBufferRange)) return Bf16Kernel::STAGED;
@@ -2063,6 +2082,7 @@ static GemmParams params_of(const GroupedGemm& q) {
     g.lda = q.lda; g.ldb = q.ldb; g.k_counts = q.k_counts; g.C2 = q.C2;
     g.k_index = q.k_index; g.k_index_stride = q.k_index_stride; g.k_rows = q.k_rows; g.k_gather = q.k_gather;
     g.split_m = q.split_m;
+    g.rows_total = q.rows_total;
     return g;
 }
 
@@ -2152,6 +2172,11 @@ int rows_expected(const etr_config& c) {
     const long long even = c.mode == ETR_MODE_ECR ? c.T : (static_cast<long long>(c.T) * c.k + c.E - 1) / c.E;
     return static_cast<int>(even < c.capacity ? even : c.capacity);
 }
+// Rows of all experts together that the selection can keep.
+long long rows_total(const etr_config& c) {
+    const long long full = static_cast<long long>(c.E) * std::min(c.T, c.capacity);
+    return c.mode == ETR_MODE_ECR ? full : std::min(full, static_cast<long long>(c.T) * c.k);
+}
 
 bool ffn_can_gather(const etr_config& c) {
     if (c.dtype != ETR_BF16) return true;
@@ -2170,6 +2195,7 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
     // gather_rows[e][s] of it: the rearrangement is folded into the operand load
     GemmParams g1{xp, w_gate, w_up, hidden, counts, c.E, c.capacity, c.H, c.d, 0, 0, 0, 0, gather_rows, c.T};
     GemmParams g2{hidden, w_down, nullptr, yp, counts, c.E, c.capacity, c.d, c.H, 0, 0, 0, 0, nullptr, c.capacity};
+    g1.rows_total = g2.rows_total = rows_total(c);
     if (a_save && b_save) { g1.C2 = a_save; g1.C3 = b_save; }      // training mode: GEMM-1 also keeps W_gate x and W_up x
     hipError_t err;
     if (c.dtype == ETR_BF16) {
@@ -2195,3 +2221,23 @@ hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t*
 }
 
 }  // namespace etr
+
+extern "C" int etr_ffn_plan(const etr_config* c, int product, int gathered, long long* workgroups) {
+    using namespace etr;
+    const bool glu = product == 0;
+    GemmParams p{nullptr, nullptr, nullptr, nullptr, nullptr, c->E, c->capacity, glu ? c->H : c->d, glu ? c->d : c->H};
+    p.rows_total = rows_total(*c);
+    if (c->dtype != ETR_BF16) {
+        const bool large = f32_large_tiles(p);
+        *workgroups = plan_live_tiles(p, large ? 64 : 32, large ? 64 : 32);
+        return large ? 5 : 6;
+    }
+    const Bf16Kernel kind = choose_bf16(p, glu, static_cast<size_t>(glu && gathered ? c->T : c->capacity), rows_expected(*c));
+    switch (kind) {
+        case Bf16Kernel::ROWS: *workgroups = plan_rows(p, glu); return 1;
+        case Bf16Kernel::PERSISTENT: *workgroups = cu_count() / 8 * 8; return p.K % 64 == 0 ? 2 : 3;
+        case Bf16Kernel::RING: *workgroups = plan_tiles(p, 256, glu ? 128 : 256); return 4;
+        case Bf16Kernel::STAGED: *workgroups = plan_tiles(p, 128, glu ? 64 : 128); return 0;
+    }
+    return -1;
+}

@@ -2,6 +2,8 @@
 hand identical bytes to the CPU oracle."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -13,6 +15,19 @@ TOL_OUT = {I.DT_F32: 1e-4, I.DT_BF16: 2e-2}
 # fp32 summation-order noise on a cosine in [-1, 1]
 TOL_SCORE = 4e-6
 TOL_GATE = 4e-6
+
+
+# kernels of the expert networks, as the library's internal host query numbers them
+STAGED, ROWS, PERSISTENT, PERSISTENT_TAIL, RING, F32_64, F32_32 = range(7)
+
+
+def ffn_plan(cfg, product: int, gathered: bool = True):
+    """(kernel, workgroups) of the gate/up (0) or down (1) product under this config. Host only, launches nothing."""
+    fn = B.load_library().etr_ffn_plan
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.POINTER(B.EtrConfig), ctypes.c_int, ctypes.c_int,
+                                             ctypes.POINTER(ctypes.c_longlong)]
+    n = ctypes.c_longlong(0)
+    return fn(ctypes.byref(cfg), product, int(gathered), ctypes.byref(n)), n.value
 
 
 def to_np(t: torch.Tensor) -> np.ndarray:
@@ -142,3 +157,22 @@ def check_output_against_oracle(oracle, layer: GpuLayer, hx: dict, g_score: np.n
     dropped = (sel >= 0).sum(1) == 0
     assert np.all(a[dropped] == 0)
     return err
+
+
+def check_expert_ffn(oracle, shape: I.EtrShape, counts):
+    """etr_expert_ffn on buffers of these counts against the oracle; rows past the counts stay untouched."""
+    E, C, d, Hh, dt = shape.E, shape.capacity, shape.d, shape.H, shape.torch_dtype
+    xp = I.normal(1, E * C * d, "cuda").reshape(E, C, d).to(dt)
+    wg, wu = (I.ffn_weight(s, (E, Hh, d), dt, "cuda", std=0.05) for s in (2, 3))
+    wd = I.ffn_weight(4, (E, d, Hh), dt, "cuda", std=0.05)
+    cnt = torch.tensor(counts, dtype=torch.int32, device="cuda")
+    yp = torch.full((E, C, d), 7.0, dtype=dt, device="cuda")
+    cfg = B.make_config(shape)
+    B.etr_expert_ffn(cfg, xp, cnt, wg, wu, wd, yp, B.alloc_workspace(B.etr_ffn_workspace_bytes(cfg)))
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn(to_np(xp), np.array(counts, np.int32), to_np(wg), to_np(wu), to_np(wd), shape.dtype)
+    got = oracle.to_f64(to_np(yp), shape.dtype)
+    for e, n in enumerate(counts):
+        assert np.all(got[e, n:] == 7.0)
+        if n:
+            assert scale_rel_err(got[e, :n], ref[e, :n]) <= TOL_OUT[shape.dtype]

@@ -63,6 +63,26 @@ def test_few_rows_layer_and_backward(oracle, T, d, Hh, E, k, mode):
         assert np.array_equal(H.to_np(got), H.to_np(want))
 
 
+@pytest.mark.parametrize("T,E,C,d,Hh,counts", [
+    (8, 4, 300, 512, 1024, [300, 0, 129, 64]),           # five row tiles and more, a grid for four experts' partial ones
+    (3, 2, 1000, 512, 520, [1000, 1000]),
+    (70, 64, 200, 256, 512, [200, 1, 0, 65] * 16),
+])
+def test_counts_beyond_the_batch(oracle, T, E, C, d, Hh, counts):
+    """The stage call on rows that other processes sent: the counts exceed what this config's tokens could fill, so every
+    workgroup takes several tiles."""
+    import gpu_helpers as H
+    B.load_library()
+    print(f"counts beyond the batch T={T} E={E} C={C} d={d} H={Hh}", flush=True)
+    shape = I.EtrShape("ep", 1, T=T, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR, recipe="iso")
+    cfg = B.make_config(shape)
+    for product, cols in ((0, 32), (1, 64)):
+        kernel, groups = H.ffn_plan(cfg, product, gathered=False)
+        assert kernel == H.ROWS
+        assert groups < sum(-(-n // 64) for n in counts) * -(-(d if product else Hh) // cols)
+    H.check_expert_ffn(oracle, shape, counts)
+
+
 @pytest.mark.parametrize("E,C,d,Hh,counts", [
     (6, 900, 768, 1152, [900, 0, 513, 1, 899, 256]),
     (8, 1100, 256, 2816, [1100, 700, 1, 1024, 0, 1025, 300, 1100]),
@@ -79,17 +99,4 @@ def test_many_rows_expected_ffn(oracle, E, C, d, Hh, counts):
     B.load_library()
     print(f"ffn with {E} x {C} rows expected, d={d} H={Hh}", flush=True)
     shape = I.EtrShape("m", 1, T=E * C, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_TCR, recipe="iso")
-    xp = I.normal(1, E * C * d, "cuda").reshape(E, C, d).to(torch.bfloat16)
-    wg, wu = (I.ffn_weight(s, (E, Hh, d), torch.bfloat16, "cuda", std=0.05) for s in (2, 3))
-    wd = I.ffn_weight(4, (E, d, Hh), torch.bfloat16, "cuda", std=0.05)
-    cnt = torch.tensor(counts, dtype=torch.int32, device="cuda")
-    yp = torch.full((E, C, d), 7.0, dtype=torch.bfloat16, device="cuda")
-    cfg = B.make_config(shape)
-    B.etr_expert_ffn(cfg, xp, cnt, wg, wu, wd, yp, B.alloc_workspace(B.etr_ffn_workspace_bytes(cfg)))
-    torch.cuda.synchronize()
-    ref = oracle.expert_ffn(H.to_np(xp), np.array(counts, np.int32), H.to_np(wg), H.to_np(wu), H.to_np(wd), I.DT_BF16)
-    got = oracle.to_f64(H.to_np(yp), I.DT_BF16)
-    for e, n in enumerate(counts):
-        assert np.all(got[e, n:] == 7.0)
-        if n:
-            assert H.scale_rel_err(got[e, :n], ref[e, :n]) <= H.TOL_OUT[I.DT_BF16]
+    H.check_expert_ffn(oracle, shape, counts)
