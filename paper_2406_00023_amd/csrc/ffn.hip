@@ -1616,8 +1616,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 // at two workgroups.  No barrier and no LDS until the four partial sums meet in LDS and are added in wave order.
 // The token rows are read by every workgroup of the expert, out of the caches.
 // Row blocks of 16 that hold no row are skipped (MB = 1, 2 or 4 blocks).
-// Measured: 32 tokens, 16 experts, 2048 x 5632: gate/up 194 -> 128 us (5.8 TB/s of weights), down 156 -> 64 us (5.7 TB/s)
-// against the 256-row tiles; 256 tokens, 32 experts, 4096 x 2816: 404 -> 285 us and 180 -> 156 us.
+// Measured: 32 tokens, 16 experts, 2048 x 5632: gate/up 194 -> 130 us (5.7 TB/s of weights), down 156 -> 64 us (5.7 TB/s)
+// against the 256-row tiles; 256 tokens, 32 experts, 4096 x 2816: 404 -> 277 us and 180 -> 144 us.  (With loops that
+// drained the older loads before they requested the next k-tile: the same with one block of 16 rows, and with four
+// 582 instead of 536 us for both products of 32 experts x 64 rows, 4096 x 2816.)
 // ---------------------------------------------------------------------------------------
 constexpr int kRowsBM = 64;                             // token rows per workgroup
 
@@ -1652,17 +1654,27 @@ __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, in
             for (int v = 0; v < 4; ++v) acc[b][i][v] = 0.f;
 
     struct Stage { bf16x8 w[2][4], a[2][MB]; };         // one k-tile of 64
+    // Every address is a scalar base and a lane's 32-bit offset: with the k-tile added to 64-bit lane addresses the
+    // compiler put those into registers that loads in flight had yet to write, and waited for them.
+    typedef const __attribute__((address_space(1))) char* global_bytes;
+    typedef const __attribute__((address_space(1))) bf16x8* global_piece;
+    auto scalar = [](const char* base) { asm volatile("" : "+s"(base)); return (global_bytes)base; };
+    auto lane_off = [](uint32_t off) { asm volatile("" : "+v"(off)); return off; };      // (widened next to its use)
     auto load = [&](Stage& s, int kt) {
         const size_t at = static_cast<size_t>(kt) * 128;
+        const global_bytes b0 = scalar(Bb[0] + at), b1 = GLU ? scalar(Bb[1] + at) : b0, ab = scalar(Ab + at);
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t off = lane_off(boff[b]);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                s.w[h][b] = *reinterpret_cast<const bf16x8*>(Bb[GLU ? b >> 1 : 0] + at + h * 64 + boff[b]);
+            for (int h = 0; h < 2; ++h) s.w[h][b] = *(global_piece)((b >> 1 ? b1 : b0) + off + h * 64);
+        }
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int i = 0; i < MB; ++i) {
+            const uint32_t off = lane_off(aoff[i]);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) s.a[h][i] = *reinterpret_cast<const bf16x8*>(Ab + at + h * 64 + aoff[i]);
+            for (int h = 0; h < 2; ++h) s.a[h][i] = *(global_piece)(ab + off + h * 64);
+        }
     };
     auto multiply = [&](const Stage& s) {
 #pragma unroll
@@ -1676,17 +1688,22 @@ __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, in
     const int whole = K / 64;                           // whole k-tiles; wave w takes w, w + 4, ...
     Stage s0, s1;
     if (wave < whole) {
+        // two k-tiles per turn, no branch inside, so that each load is waited for one k-tile later on every path
+        const int last = wave + ((whole - 1 - wave) & ~3);              // this wave's last k-tile
         load(s0, wave);
-        for (int kt = wave; kt < whole; kt += 8) {
-            load(s1, min(kt + 4, whole - 1));           // (past the end: some k-tile again, not multiplied)
+        __builtin_amdgcn_sched_barrier(0);
+        int kt = wave;
+        for (; kt < last; kt += 8) {
+            load(s1, kt + 4);
             __builtin_amdgcn_sched_barrier(0);
             multiply(s0);
-            if (kt + 4 < whole) {
-                load(s0, min(kt + 8, whole - 1));
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(s1);
-            }
+            __builtin_amdgcn_sched_barrier(0);
+            load(s0, min(kt + 8, last));                // (past the end: the last k-tile again, not multiplied)
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(s1);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        if (kt == last) multiply(s0);
     }
     if (K % 64 != 0 && wave == (whole & 3)) {           // the short last k-tile: pieces past its end are zero
         const bf16x8 zero = {};
