@@ -2199,10 +2199,10 @@ bool ffn_can_gather(const etr_config& c) {
     if (c.dtype != ETR_BF16) return true;
     GemmParams g1{nullptr, nullptr, nullptr, nullptr, nullptr, c.E, c.capacity, c.H, c.d, 0, 0, 0, 0, nullptr, c.T};
     // every kernel reads its rows through an index if asked; only a token matrix past the 32-bit offsets of the
-    // pipelined kernels is better rearranged first, where the per-expert buffers are within them
-    const int rows = rows_expected(c);
-    return choose_bf16(g1, true, static_cast<size_t>(c.T), rows) != Bf16Kernel::STAGED ||
-           choose_bf16(g1, true, static_cast<size_t>(c.capacity), rows) == Bf16Kernel::STAGED;
+    // pipelined kernels is better rearranged first, where the per-expert buffers are within them.  Asked without a row
+    // count, so that the size query that depends on it needs no estimate and with it no device.
+    return choose_bf16(g1, true, static_cast<size_t>(c.T), 0) != Bf16Kernel::STAGED ||
+           choose_bf16(g1, true, static_cast<size_t>(c.capacity), 0) == Bf16Kernel::STAGED;
 }
 
 hipError_t launch_expert_ffn(const etr_config& c, const void* xp, const int32_t* counts, const void* w_gate,

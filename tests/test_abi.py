@@ -4,6 +4,8 @@ here gets past validation."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -115,3 +117,27 @@ def test_binding_refuses_missing_library(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(FileNotFoundError):
         B.load_library()
+
+
+def test_size_queries_make_no_runtime_call(lib):
+    """The size queries are host arithmetic: a process may ask them before it forks or chooses a device, so they must not
+    start the HIP runtime. Its own log, in a process of its own, shows the calls."""
+    program = """
+import ctypes, os, sys
+lib = ctypes.CDLL(sys.argv[1])
+Config = ctypes.c_int32 * 11
+for cfg in (Config(4096, 2048, 16, 16, 2, 1000, 5632, 1, 2, 0, 0), Config(32, 1080, 12, 24, 3, 938, 2744, 1, 1, 0, 1),
+            Config(512, 512, 8, 8, 2, 80, 1024, 0, 2, 0, 0)):
+    for name in ("workspace", "select_workspace", "ffn_workspace", "stats_workspace", "backward_workspace"):
+        fn = getattr(lib, "etr_" + name + "_bytes")
+        fn.restype = ctypes.c_size_t
+        assert fn(ctypes.byref(cfg)) > 0
+os.write(2, b"== queries done\\n")
+lib.hipGetDevice(ctypes.byref(ctypes.c_int()))
+"""
+    run = subprocess.run([sys.executable, "-c", program, B.LIB_PATH], capture_output=True, text=True,
+                         env={**os.environ, "AMD_LOG_LEVEL": "3"})
+    assert run.returncode == 0, run.stderr
+    queries, control = run.stderr.split("== queries done")
+    assert "hipGetDevice" in control                     # (the log does show such calls)
+    assert "hip" not in queries, queries
