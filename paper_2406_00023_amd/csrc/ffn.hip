@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <numeric>
 
 #include "etr_internal.h"
 
@@ -2043,43 +2044,69 @@ size_t ffn_ws_bytes(const etr_config& c) {
 }
 
 // Which kernel a row-major bf16 product takes.  Both pipelined kernels need 32-bit byte offsets inside one operand.
-//   ROWS        few rows per group expected, or too few 256-row tiles to fill the chip: see bf16_costs
 //   PERSISTENT  at least one whole column tile, a contraction of 128 or more, the super-tile prefix in LDS.  A
 //               contraction that is not whole 64-wide k-tiles takes its zero-filling instantiation (per-group lengths
-//               are always whole k-tiles).  12 experts of 135-938 rows, 1080 x 2744 (K % 64 = 56): 262 -> 150 us for
-//               the gate/up product, 242 -> 95 us for the down one against the register-staged kernel.
+//               are always whole k-tiles).
 //   RING        whole k-tiles where the persistent kernel does not apply (narrow outputs, short contractions)
-//   STAGED      everything else
+//   ROWS        any width; few rows per group, or too few 256-row tiles to fill the chip
+//   STAGED      any width; the only one without a limit on sizes
+// Without a row count: the first of PERSISTENT, RING, STAGED that applies.  With one, by estimate.
 enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
-// Estimated microseconds of a product on each kernel, from measured rates, for the expected rows per group.
-//   rows        gemm_bf16_rows_kernel: 270 TFLOP/s on blocks of 64 rows (a lone block of 16 or 32 rows loads 10 or 12
-//               fragments per k-tile instead of 16), at least the weights at 5 TB/s, 7 us besides
-//   persistent  rounds of 256 x 256 tiles over the CUs, 1.95 us per 64-wide k-tile on a full chip (its power limit) and
-//               1.2 where up to half of the CUs have a tile, 1.13 and 1.3 times that with zero-filling copies; at least the
-//               weights at 3.5 TB/s; 10 us besides
-//   staged      128-row tiles, two per CU: 360 (gate/up) and 200 TFLOP/s, at least 1.15 us per k-tile (its loads are waited
-//               for in each), 3 us besides; a candidate for ragged contractions only
-// Both products of a layer, rows per expert: rows / persistent, us.  16 experts, 2048 x 5632: 16: 216 / 356, 48: 270 / 321,
-// 64: 290 / 311, 96: 517 / 317.  32 experts, 4096 x 2816: 32: 442 / 538, 64: 550 / 542, 128: 1013 / 547.  8 experts,
-// 512 x 1024: 32: 17 / 43, 128: 26 / 48, 256: 38 / 50.  Gate/up of 4 experts x 297 rows, 1392 x 1408 (88 tiles, ragged): staged 33,
-// persistent 46; of 12 experts, 1080 x 2744 (792 tiles): 262 and 150; of 4 experts x 97 rows, 2232 x 1472: staged 42, rows 29.
-struct Bf16Costs { double rows, persistent, staged; };
-static Bf16Costs bf16_costs(const GemmParams& g, bool glu, int rows_expected) {
-    const double weights = static_cast<double>(g.E) * g.N * (glu ? 2 : 1) * g.K;       // elements; x 2 = flops per row, = bytes
-    auto mult = [&](int block) { return 2.0 * weights * ((rows_expected + block - 1) / block) * block; };
-    auto larger = [](double a, double b) { return a > b ? a : b; };
-    const int blocks = rows_expected <= 16 ? 1 : (rows_expected <= 32 ? 2 : 4);
-    const double loads = rows_expected <= kRowsBM ? (8 + 2 * blocks) / 16.0 : 1.0;
-    Bf16Costs c;
-    c.rows = larger(mult(kRowsBM) * loads / 270e6, weights * 2 / 5e6) + 7.0;
-    const double n_cu = cu_count();
-    const double tiles = static_cast<double>(g.E) * ((rows_expected + 255) / 256) * ((g.N + (glu ? 127 : 255)) / (glu ? 128 : 256));
-    const double fill = tiles < 0.5 * n_cu ? 0.5 : (tiles < n_cu ? tiles / n_cu : 1.0);
-    const double step = (1.2 + 1.5 * (fill - 0.5)) * (g.K % 64 ? 1.3 - 0.34 * (fill - 0.5) : 1.0);
-    c.persistent = larger(std::ceil(tiles / n_cu) * ((g.K + 63) / 64) * step, weights * 2 / 3.5e6) + 10.0;
-    const double tiles128 = static_cast<double>(g.E) * ((rows_expected + 127) / 128) * ((g.N + (glu ? 63 : 127)) / (glu ? 64 : 128));
-    c.staged = larger(mult(128) / (glu ? 360e6 : 200e6), std::ceil(tiles128 / (2 * n_cu)) * ((g.K + 63) / 64) * 1.15) + 3.0;
-    return c;
+// Estimated microseconds of a product whose groups have about `rows` rows each: rounds of tiles over the CUs, each a time
+// per 64-wide k-tile and a time besides, and at least the weights at the rate that the kernel reads them with.
+//   ROWS        tiles of 64 rows x 64 staged weight rows, two on a CU at once; a wave takes every fourth k-tile: 1.6 us per
+//               k-tile of a wave (1.25 and 0.72 for a lone block of 32 or 16 rows) and 0.24 us; 5.5 TB/s; 2.9 us per launch
+//   PERSISTENT  256-row tiles: 1.13 us per k-tile where few CUs have one, 1.69 on a full chip (its power limit), 1.08 times
+//               that with zero-filling copies, and 1.65 us; 4.65 TB/s; 5 us
+//   RING        the same tiles: 1.03 us per k-tile and 7 us
+//   STAGED      128-row tiles: 0.87 us per k-tile in the first round, 0.66 in the others (two run on a CU at once), and 3.3 us
+//               for each two rounds; 4.5 TB/s; 0.4 us
+// RING and STAGED deal super-tiles of the capacity to the XCDs (decode_tile): their rounds are those of the busiest XCD,
+// where a super-tile that is live in part keeps its CUs worse than in proportion, and their dead workgroups take 2 and
+// 0.5 us per one of each CU.  4 rows in each of 16 experts, 2048 x 5632, capacity 256 / 1024 / 4096 / 16384: RING 329 / 667 / 2600 /
+// 4980 us for both products, ROWS 190 throughout.
+// Fitted to 7190 measured products: 2 to 64 groups of 1 to 13 000 rows, even and uneven counts, capacities of 1 to 4 times
+// that, widths from 8 to 11008, half of them ragged.  A kernel newer than the ones that took everything once (PERSISTENT and
+// RING for whole k-tiles, STAGED for ragged ones) has to be estimated 5 % faster.  Against those the geometric mean is 0.66
+// of the time and 63 products are more than 3 % (and 1 us) slower; against the best kernel of each product it is 1.011.
+static double estimate_us(Bf16Kernel kernel, const GemmParams& g, bool glu, int rows) {
+    const double n_cu = cu_count(), weight_bytes = 2.0 * g.E * g.N * (glu ? 2 : 1) * g.K;
+    const int KT = (g.K + 63) / 64;
+    auto least = [&](double us, double terabytes_per_s) { return std::max(us, weight_bytes / (terabytes_per_s * 1e6)); };
+    // live row tiles of a group: half a tile more than the rows fill, on average, up to the capacity
+    auto row_tiles = [&](int BM) {
+        return std::min<double>((g.capacity + BM - 1) / BM, std::max<double>((rows + BM - 1) / BM, static_cast<double>(rows) / BM + 0.5));
+    };
+    auto tiles = [&](int BM, int BN) { return g.E * row_tiles(BM) * ((g.N + BN - 1) / BN); };
+    // super-tile dealing: live tiles of the busiest XCD, and dead workgroups per CU
+    auto deal = [&](int BM, int BN, double& busiest, double& dead) {
+        GemmParams p = g;
+        plan_tiles(p, BM, BN);
+        const int MG = (p.MT + p.SM - 1) / p.SM, NG = (p.NT + p.SN - 1) / p.SN;
+        const double live = row_tiles(BM), live_groups = std::ceil(live / p.SM);
+        const double xcds = std::min(8.0, 8 / std::gcd(MG, 8) * live_groups);         // that the live super-tiles fall on
+        busiest = std::ceil(g.E * NG * live_groups / xcds) * p.SN * std::sqrt(p.SM * live / live_groups);
+        dead = (static_cast<double>(g.E) * MG * NG * p.SM * p.SN - tiles(BM, BN)) / n_cu;
+    };
+    double busiest, dead;
+    switch (kernel) {
+        case Bf16Kernel::ROWS: {
+            const double step = rows <= 16 ? 0.72 : (rows <= 32 ? 1.25 : 1.6), rounds = tiles(kRowsBM, glu ? 32 : 64) / n_cu;
+            const int kt = std::max(1, (g.K / 64 + 3) / 4);
+            return least((rounds <= 1 ? 1.0 : rounds + 0.48) * (kt * step + 0.24), 5.5) + 2.9;
+        }
+        case Bf16Kernel::PERSISTENT: {
+            const double t = tiles(256, glu ? 128 : 256), step = (1.13 + 0.56 * std::min(1.0, t / n_cu)) * (g.K % 64 ? 1.08 : 1.0);
+            return least(std::ceil(t / n_cu) * (KT * step + 1.65), 4.65) + 5.0;
+        }
+        case Bf16Kernel::RING:
+            deal(256, glu ? 128 : 256, busiest, dead);
+            return std::ceil(busiest / (n_cu / 8)) * (KT * 1.03 + 7.0) + 2.0 * dead;
+        case Bf16Kernel::STAGED:
+            deal(128, glu ? 64 : 128, busiest, dead);
+            return least(KT * (0.21 + 0.66 * std::ceil(busiest / (n_cu / 8))) + std::ceil(busiest / (n_cu / 4)) * 3.3, 4.5) + 0.4 + 0.5 * dead;
+    }
+    return 0.0;
 }
 static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int rows_expected) {
     const size_t a_row_bytes = static_cast<size_t>(g.lda ? g.lda : g.K) * 2, b_row_bytes = static_cast<size_t>(g.ldb ? g.ldb : g.K) * 2;
@@ -2087,14 +2114,19 @@ static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int 
     if (g.K % 8 != 0 || a_row_bytes % 16 != 0 || b_row_bytes % 16 != 0 || a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32))
         return Bf16Kernel::STAGED;
     const bool whole = g.K % 64 == 0;
-    if (rows_expected > 0 && !g.k_counts) {
-        const Bf16Costs c = bf16_costs(g, glu, rows_expected);
-        if (c.rows < c.persistent && (whole || c.rows < c.staged)) return Bf16Kernel::ROWS;
-        if (!whole && c.staged < c.persistent) return Bf16Kernel::STAGED;
-    }
-    if (!whole && (g.k_counts || a_bytes >= kBufferRange || b_bytes >= kBufferRange)) return Bf16Kernel::STAGED;
-    if (persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu)) return Bf16Kernel::PERSISTENT;
-    return whole ? Bf16Kernel::RING : Bf16Kernel::STAGED;
+    const bool persistent = persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu) &&
+                            (whole || (!g.k_counts && a_bytes < kBufferRange && b_bytes < kBufferRange));
+    if (rows_expected <= 0 || g.k_counts)
+        return persistent ? Bf16Kernel::PERSISTENT : (whole ? Bf16Kernel::RING : Bf16Kernel::STAGED);
+    Bf16Kernel best = !whole ? Bf16Kernel::STAGED : (persistent ? Bf16Kernel::PERSISTENT : Bf16Kernel::RING);
+    double best_us = 0.95 * estimate_us(best, g, glu, rows_expected);
+    auto offer = [&](Bf16Kernel kernel) {
+        const double us = estimate_us(kernel, g, glu, rows_expected);
+        if (us < best_us) { best = kernel; best_us = us; }
+    };
+    offer(Bf16Kernel::ROWS);
+    if (!whole && persistent) offer(Bf16Kernel::PERSISTENT);
+    return best;
 }
 
 // General entry for the other stages of the library: grouped "NT" product
