@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (3, 33, 1080, 520, [33, 17, 32]),                    # two blocks and one past; k-tiles end 56 and 8 short of whole
     (64, 64, 136, 40, [64, 0, 49, 1] * 16),              # a short k-tile on wave 2; outputs narrower than a workgroup's
     (2, 30, 8, 8, [30, 3]),                              # less than one k-step
+    (64, 64, 56, 4096, [64, 17, 0, 16] * 16),            # less than one k-tile, many columns; then 16 k-tiles per wave
     (1, 200, 320, 4096, [200]),                          # four row blocks, the last of 8 rows; k-tiles for some waves only
     (5, 64, 192, 72, [64, 63, 48, 31, 0]),
 ])
@@ -24,6 +25,9 @@ def test_few_rows_ffn(oracle, E, C, d, Hh, counts):
     import test_gpu_parity
     B.load_library()
     # (that test's layers have T = C tokens on one expert each: C / E rows are expected, which chooses this kernel)
+    cfg = B.make_config(I.EtrShape("f", 1, T=C, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_TCR,
+                                   recipe="iso"))
+    assert [H.ffn_plan(cfg, p, gathered=False)[0] for p in (0, 1)] == [H.ROWS, H.ROWS]
     test_gpu_parity.test_expert_ffn(H, oracle, I.DT_BF16, E, C, d, Hh, counts)
 
 
@@ -37,6 +41,7 @@ def test_few_rows_layer_and_backward(oracle, T, d, Hh, E, k, mode):
     shape = I.EtrShape("few", 12, T=T, d=d, E=E, D=8, k=k, capacity=C, H=Hh, dtype=I.DT_BF16, mode=mode, recipe="bias")
     print(f"few rows T={T} d={d} H={Hh} E={E} k={k} mode={mode}", flush=True)
     L = H.GpuLayer(shape)
+    assert [H.ffn_plan(L.cfg, p)[0] for p in (0, 1)] == [H.ROWS, H.ROWS]
     hx = L.host_inputs()
     L.forward()
     r = H.check_routing_against_oracle(oracle, L, hx)
@@ -83,20 +88,35 @@ def test_counts_beyond_the_batch(oracle, T, E, C, d, Hh, counts):
     H.check_expert_ffn(oracle, shape, counts)
 
 
-@pytest.mark.parametrize("E,C,d,Hh,counts", [
-    (6, 900, 768, 1152, [900, 0, 513, 1, 899, 256]),
-    (8, 1100, 256, 2816, [1100, 700, 1, 1024, 0, 1025, 300, 1100]),
-    (8, 2048, 128, 1024, [2048, 1500, 2048, 300, 2047, 1025, 2048, 1800]),
-    (8, 2048, 2048, 128, [2048, 1500, 0, 300, 2047, 1025, 2048, 1800]),
-    (2, 4200, 1024, 384, [4200, 3333]),
-    (16, 300, 1032, 1048, [300, 0, 257, 256, 255, 1, 128, 300] * 2),     # both contractions end 8 / 24 past whole k-tiles
-    (16, 520, 1080, 1320, [520, 513, 0, 3] * 4),                         # 56 and 40 past
+_P, _Z, _R = "PERSISTENT", "PERSISTENT_TAIL", "ROWS"
+
+
+@pytest.mark.parametrize("E,C,d,Hh,kernels,counts", [
+    (6, 900, 768, 1152, (_P, _P), [900, 0, 513, 1, 899, 256]),
+    (16, 1100, 256, 2816, (_P, _P), [1100, 700, 1, 1024, 0, 1025, 300, 1100] * 2),
+    (8, 2048, 128, 1024, (_P, _R), [2048, 1500, 2048, 300, 2047, 1025, 2048, 1800]),     # two k-tiles; a narrow output
+    (8, 2048, 2048, 128, (_P, _P), [2048, 1500, 0, 300, 2047, 1025, 2048, 1800]),
+    (2, 4200, 1024, 384, (_P, _P), [4200, 3333]),
+    (16, 520, 1080, 1320, (_Z, _Z), [520, 513, 0, 3] * 4),               # both contractions end 56 and 40 past whole k-tiles
+    (16, 700, 1032, 1048, (_Z, _Z), [700, 0, 257, 256, 255, 1, 128, 300] * 2),           # 8 and 24 past
+    # three k-tiles, the third short: its token rows are the first copies behind the prologue, its weight rows follow a
+    # k-tile later, and a workgroup's second tile starts inside that; gate/up, then down
+    (16, 1100, 136, 1048, (_Z, None), [1100, 0, 1025, 769, 1, 512, 1100, 300] * 2),
+    (16, 1100, 184, 1048, (_Z, None), [1100, 0, 1025, 769, 1, 512, 1100, 300] * 2),
+    (32, 700, 1048, 136, (None, _Z), [700, 0, 513, 256, 1, 512, 699, 300] * 4),
+    (32, 700, 1048, 184, (None, _Z), [700, 0, 513, 256, 1, 512, 699, 300] * 4),
+    # the kernels with a workgroup per tile: outputs too narrow for the persistent one; ragged and small
+    (16, 3000, 128, 64, ("RING", "RING"), [3000, 0, 2049, 1, 256, 257, 1025, 2999] * 2),
+    (16, 300, 1032, 1048, ("STAGED", "STAGED"), [300, 0, 257, 256, 255, 1, 128, 300] * 2),
 ])
-def test_many_rows_expected_ffn(oracle, E, C, d, Hh, counts):
-    """The same stage where every expert is expected to fill its capacity: the 256-row tiles of the persistent kernel on
-    ragged counts, contractions and column tails."""
+def test_many_rows_expected_ffn(oracle, E, C, d, Hh, kernels, counts):
+    """The same stage where every expert is expected to fill its capacity: mostly the 256-row tiles of the persistent kernel,
+    on ragged counts, contractions and column tails."""
     import gpu_helpers as H
     B.load_library()
     print(f"ffn with {E} x {C} rows expected, d={d} H={Hh}", flush=True)
     shape = I.EtrShape("m", 1, T=E * C, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_TCR, recipe="iso")
+    for product, kernel in enumerate(kernels):
+        if kernel:
+            assert H.ffn_plan(B.make_config(shape), product, gathered=False)[0] == getattr(H, kernel)
     H.check_expert_ffn(oracle, shape, counts)

@@ -1,6 +1,6 @@
-"""Layer widths that are no multiple of the GEMM kernels' k-tiles: the pipelined kernels zero-fill the end of the last
-k-tile (forward, recomputation and kept pre-activations on the 64-wide kernel, u and the input gradient on the 32-wide
-transposing one), and a capacity below 128 rows takes the same path on padded buffers."""
+"""Layer widths that are no multiple of the GEMM kernels' k-tiles, forward and backward. u and the input gradient always run
+on the 32-wide transposing kernel, which zero-fills the end of the last k-tile; the forward, the recomputation and the kept
+pre-activations run on the kernel that the case names; a capacity below 128 rows takes the same path on padded buffers."""
 import numpy as np
 import pytest
 import torch
@@ -12,13 +12,15 @@ pytestmark = pytest.mark.gpu
 
 
 # (d, H, capacity): the contraction of the gate/up product is d, that of the down product H, that of the input gradient
-# twice H; remainders of 8, 24, 32, 40 and 56 past whole 64s, the shortest contraction the kernels take (three k-tiles),
-# one and two row tiles, a capacity of 40 (padded to 128 contraction rows); the last two have enough tiles for the
-# persistent kernel in the forward and the recomputation as well
-@pytest.mark.parametrize("T,E,d,Hh,C", [(600, 3, 264, 184, 500), (600, 3, 280, 136, 300), (600, 3, 312, 160, 500),
-                                        (600, 3, 296, 152, 40), (600, 3, 288, 296, 129), (600, 3, 1080, 2744, 260),
-                                        (2048, 16, 1032, 1048, 300), (1500, 12, 1112, 1384, 400)])
-def test_ragged_widths_forward_and_backward(oracle, T, E, d, Hh, C):
+# twice H (two halves); remainders of 8, 24, 32, 40 and 56 past whole 64s, one and two row tiles, a capacity of 40 (padded
+# to 128 contraction rows).  The kernel named is the gate/up product's; the last two cases have three k-tiles, the least
+# that the 64-wide kernel takes, and more tiles than workgroups.
+@pytest.mark.parametrize("T,E,d,Hh,C,kernel", [
+    (600, 3, 264, 184, 500, "ROWS"), (600, 3, 280, 136, 300, "ROWS"), (600, 3, 312, 160, 500, "ROWS"),
+    (600, 3, 296, 152, 40, "ROWS"), (600, 3, 288, 296, 129, "ROWS"), (600, 3, 1080, 2744, 260, "STAGED"),
+    (2048, 16, 1032, 1048, 300, "PERSISTENT_TAIL"), (1500, 12, 1112, 1384, 400, "PERSISTENT_TAIL"),
+    (4096, 8, 136, 1048, 1100, "PERSISTENT_TAIL"), (4096, 8, 184, 1048, 1100, "PERSISTENT_TAIL")])
+def test_ragged_widths_forward_and_backward(oracle, T, E, d, Hh, C, kernel):
     import gpu_helpers as H
     from test_gpu_backward import Backward, _err
     B.load_library()
@@ -26,6 +28,7 @@ def test_ragged_widths_forward_and_backward(oracle, T, E, d, Hh, C):
                        recipe="bias")
     print(f"ragged widths T={T} E={E} d={d} H={Hh} C={C}", flush=True)
     L = H.GpuLayer(shape)
+    assert H.ffn_plan(L.cfg, 0)[0] == getattr(H, kernel)
     hx = L.host_inputs()
     L.forward()
     r = H.check_routing_against_oracle(oracle, L, hx)
