@@ -768,14 +768,15 @@ constexpr int kMaxSuperWide = 2048;      // the same for the 64-wide kernel, who
 // TAIL (row-major A, transposed B): the contraction, or each half of a split one, need not be whole k-tiles.  The
 // last k-tile of it is short: pieces of a token row and whole weight rows past its end are zero-filled
 // (buffer_copy_to_lds).
-template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0, bool TAIL = false>
+//
+// Plain products only: row-major operands with an epilogue take the 64-wide kernel.
+template <bool TRA, bool TRB, int KG = 0, bool TAIL = false>
 __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
-    static_assert(!GLU && !DUAL, "plain products only: row-major operands with an epilogue take the 64-wide kernel");
     static_assert(KG == 0 || (KG == 1 && TRA) || (KG == 2 && TRB), "the gathered operand is a transposed one");
     static_assert(!TAIL || (TRB && !TRA && KG == 0), "short k-tiles: row-major A, transposed B");
     constexpr int IDX_AHEAD = 7, IDX_SLOTS = 16;        // index prefetch distance in k-tiles, ring slots of 32 indices
     constexpr int BM = 256, BR = 256, CPR = 4, NBUF = 4, AHEAD = NBUF - 1;
-    constexpr int BN = GLU ? 128 : 256;
+    constexpr int BN = 256;
     constexpr int STAGE = (BM + BR) * CPR;
     constexpr int WN = 4, NW = 8, TB = 2, NCP = 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -882,7 +883,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
             t.Bbase = reinterpret_cast<const char*>(p.B0) + e * per_group;
             t.Bbase1 = splitB ? reinterpret_cast<const char*>(p.B1) + e * per_group : t.Bbase;
         } else {
-            t.Bbase = reinterpret_cast<const char*>((GLU && wave >= NW / 2) ? p.B1 : p.B0) + static_cast<size_t>(e) * p.N * KCB * 16;
+            t.Bbase = reinterpret_cast<const char*>(p.B0) + static_cast<size_t>(e) * p.N * KCB * 16;
             t.Bbase1 = t.Bbase;
         }
 #pragma unroll
@@ -900,7 +901,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
             if constexpr (TRB) {
                 t.off[NCP + i] = kmajor_off(wave * NCP + i, t.n0, p.N, KCB, KG == 2);
             } else {
-                int n = t.n0 + (GLU ? (rr & 127) : rr);
+                int n = t.n0 + rr;
                 n = n < p.N ? n : p.N - 1;
                 t.off[NCP + i] = (static_cast<uint32_t>(n) * KCB + c) * 16u;
             }
@@ -954,10 +955,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) a_row[i] = (wm * 128 + i * 32 + r32) * CPR;
 #pragma unroll
-    for (int j = 0; j < TB; ++j) {
-        const int br = GLU ? ((j / (TB / 2)) * 128 + wn * (16 * TB) + (j % (TB / 2)) * 32) : (wn * (32 * TB) + j * 32);
-        b_row[j] = BM * CPR + (br + r32) * CPR;
-    }
+    for (int j = 0; j < TB; ++j) b_row[j] = BM * CPR + (wn * (32 * TB) + j * 32 + r32) * CPR;
     const int ck0 = half ^ sw, ck1 = (2 + half) ^ sw;
     // transposing reads: byte offset, inside the operand's part of a ring slot, of this lane's 4 elements for the
     // 32-row fragment that starts at row rf (first k-substep, first half of its 8 k)
@@ -1961,11 +1959,11 @@ hipError_t launch_bf16_ring(GemmParams p, hipStream_t st) {
 
 // Persistent ring kernel: needs every group's contraction length >= 96 (three k-tiles to prefetch)
 // and the super-tile prefix to fit in LDS.
-template <bool GLU, bool DUAL = false, bool TRA = false, bool TRB = false, int KG = 0, bool TAIL = false>
+template <bool TRA, bool TRB, int KG = 0, bool TAIL = false>
 hipError_t launch_bf16_persist(GemmParams p, hipStream_t st, int n_cu) {
     constexpr size_t lds = 4ull * 512 * 32 * 2 + (KG != 0 ? 16 * 32 * 4 : 0);        // (+ the ring of row numbers)
-    plan_tiles(p, 256, GLU ? 128 : 256);
-    auto kern = gemm_bf16_persist_kernel<GLU, DUAL, TRA, TRB, KG, TAIL>;
+    plan_tiles(p, 256, 256);
+    auto kern = gemm_bf16_persist_kernel<TRA, TRB, KG, TAIL>;
     hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
@@ -2144,11 +2142,10 @@ static GemmParams params_of(const GroupedGemm& q) {
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !(q.ta || q.tb)) return false;
     // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
-    if (q.N % 8 != 0) return false;                                // 16-byte stores
+    if (q.N % 8 != 0 || q.N < 8) return false;                     // 16-byte stores, and chunks along the rows of a [K][rows] operand
     const bool tail_form = q.tb && !q.ta && !q.k_counts;
     const int half_k = q.B1 ? q.K / 2 : q.K;
-    if (q.K < 128 || half_k % (tail_form ? 8 : 64) != 0 || q.N % 4 != 0) return false;
-    if (q.tb && (q.N % 8 != 0 || q.N < 8)) return false;           // 16-byte chunks along the rows of a [K][rows] operand
+    if (q.K < 128 || half_k % (tail_form ? 8 : 64) != 0) return false;
     if (q.ta && (q.M % 8 != 0 || q.M < 8)) return false;
     const int lda = q.lda ? q.lda : q.K, ldb = q.ldb ? q.ldb : q.K;
     if (lda % 8 != 0 || ldb % 8 != 0) return false;
@@ -2175,15 +2172,15 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     if (q.ta || q.tb) {
         if (!grouped_gemm_transposed_ok(q)) return hipErrorInvalidValue;
         const int n_cu = cu_count();
-        if (q.k_gather == 1) return launch_bf16_persist<false, false, true, true, 1>(g, st, n_cu);
-        if (q.k_gather == 2) return launch_bf16_persist<false, false, true, true, 2>(g, st, n_cu);
-        if (q.ta && q.tb) return launch_bf16_persist<false, false, true, true>(g, st, n_cu);
+        if (q.k_gather == 1) return launch_bf16_persist<true, true, 1>(g, st, n_cu);
+        if (q.k_gather == 2) return launch_bf16_persist<true, true, 2>(g, st, n_cu);
+        if (q.ta && q.tb) return launch_bf16_persist<true, true>(g, st, n_cu);
         if (q.tb) {
             // a contraction (or half of a split one) that is not whole 32-wide k-tiles: the zero-filling instantiation
-            return (q.B1 ? q.K / 2 : q.K) % 32 == 0 ? launch_bf16_persist<false, false, false, true>(g, st, n_cu)
-                                                    : launch_bf16_persist<false, false, false, true, 0, true>(g, st, n_cu);
+            return (q.B1 ? q.K / 2 : q.K) % 32 == 0 ? launch_bf16_persist<false, true>(g, st, n_cu)
+                                                    : launch_bf16_persist<false, true, 0, true>(g, st, n_cu);
         }
-        return launch_bf16_persist<false, false, true, false>(g, st, n_cu);
+        return launch_bf16_persist<true, false>(g, st, n_cu);
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;
