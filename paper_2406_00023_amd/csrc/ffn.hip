@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <cmath>
 #include <numeric>
+#include <type_traits>
 
 #include "etr_internal.h"
 
@@ -1608,162 +1609,145 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 // time there is, so a 256-row tile would multiply padding for longer than the weights take to arrive.
 //
 // A workgroup takes 64 weight rows (GLU: 32 gate and the 32 up rows of the same columns) and up to 64 token rows of one
-// expert.  Its four waves split the contraction: wave w takes every fourth 64-wide k-tile, all 64 weight rows and all
-// token rows, so the workgroup walks 512 contiguous bytes of each row at a time and no wave waits for another until the
-// end.  Weights and token rows go from memory straight into the MFMA fragments (lane l: row l % 16 of a 16-row block,
-// 16-byte piece l / 16 of a k-step), one k-tile ahead of its use: 8 KiB of weights in flight per wave, 64 KiB per CU
-// at two workgroups.  No barrier and no LDS until the four partial sums meet in LDS and are added in wave order.
-// The token rows are read by every workgroup of the expert, out of the caches.
+// expert; wave w has 16 of the weight rows (GLU: 8 and 8) over the whole contraction.  Weights go from memory straight into
+// the MFMA fragments (lane l: row l % 16, 16-byte piece l / 16 of a k-step); the token rows, which all four waves need,
+// come once per workgroup through LDS.  Both are requested in chunks of two 64-wide k-tiles, two chunks ahead: 8 KiB of
+// weights in flight per wave, 64 KiB per CU at two workgroups, and one barrier per chunk.  Pieces past the contraction, in
+// the last chunk, come from a zero page.
+// LDS rows are 256 bytes; piece j of row r lies at j ^ (r % 16) (applied on the source side of the copy), so that the 16
+// lanes of a fragment read touch all banks once.
 // Row blocks of 16 that hold no row are skipped (MB = 1, 2 or 4 blocks).
-// Measured: 32 tokens, 16 experts, 2048 x 5632: gate/up 194 -> 130 us (5.7 TB/s of weights), down 156 -> 64 us (5.7 TB/s)
-// against the 256-row tiles; 256 tokens, 32 experts, 4096 x 2816: 404 -> 277 us and 180 -> 144 us.  (With loops that
-// drained the older loads before they requested the next k-tile, and requested one k-tile too many at the end: both
-// products of 16 experts, 2048 x 5632, 204 instead of 192 us with 16 rows each, 298 instead of 268 with 64.)
+// The products are added in ascending k, 32 at a time, as on the 64-wide persistent kernel, so few rows give the same bits
+// as many (a form whose waves split the contraction instead did not, and took 8 % longer at 32 rows and 6-22 % at 64).
+// Measured, both products, 256-row tiles / this: 16 experts, 2048 x 5632, 2, 32, 64 rows each: 316 / 187, 328 / 209,
+// 331 / 252 us; 32 experts, 4096 x 2816: 507 / 364, 536 / 411, 543 / 483; 8 experts, 512 x 1024: 39 / 12, 40 / 13, 41 / 15.
+// (1.11 GB of weights in 187 us: 5.9 TB/s.)
 // ---------------------------------------------------------------------------------------
 constexpr int kRowsBM = 64;                             // token rows per workgroup
+constexpr int kRowsBuffers = 3, kRowsPieces = 16;       // LDS buffers; 16-byte pieces of a staged token row (128 k)
+__device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
 
 template <int MB, bool GLU, bool DUAL, bool KEEP>
-__device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, int n0, int count, f32x4* red) {
+__device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, int n0, int count, uint4* lds) {
+    constexpr int BK = 128, KS = BK / 32;               // k per chunk, MFMA k-steps
+    constexpr int STAGE = 16 * MB * kRowsPieces;        // pieces per LDS buffer
+    constexpr int NCP = MB, LOADS = NCP + KS;           // per wave and chunk: copies (4 rows each), all requests
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kq = lane >> 4;
-    const int K = p.K;
+    const int K = p.K, n_chunks = (K + BK - 1) / BK, n_whole = K / BK;
     const int LA = p.lda ? p.lda : p.K, LB = p.ldb ? p.ldb : p.K;
-    const char* Ab = static_cast<const char*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA * 2);
-    const size_t bgroup = static_cast<size_t>(e) * p.N * LB * 2;
-    const char* Bb[2] = {static_cast<const char*>(p.B0) + bgroup, static_cast<const char*>(GLU ? p.B1 : p.B0) + bgroup};
-    uint32_t aoff[MB], boff[4];
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        int m = min(m0 + i * 16 + l16, count - 1);      // rows past the count replay a valid row; never stored
-        if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
-        aoff[i] = (static_cast<uint32_t>(m) * LA + kq * 8) * 2u;
-    }
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const int n = min(n0 + (GLU ? b & 1 : b) * 16 + l16, p.N - 1);
-        boff[b] = (static_cast<uint32_t>(n) * LB + kq * 8) * 2u;
-    }
-    f32x4 acc[4][MB];
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[b][i][v] = 0.f;
-
-    struct Stage { bf16x8 w[2][4], a[2][MB]; };         // one k-tile of 64
-    // Every address is a scalar base and a lane's 32-bit offset: with the k-tile added to 64-bit lane addresses the
-    // compiler put those into registers that loads in flight had yet to write, and waited for them.
     typedef const __attribute__((address_space(1))) char* global_bytes;
     typedef const __attribute__((address_space(1))) bf16x8* global_piece;
-    auto scalar = [](const char* base) { asm volatile("" : "+s"(base)); return (global_bytes)base; };
-    auto lane_off = [](uint32_t off) { asm volatile("" : "+v"(off)); return off; };      // (widened next to its use)
-    auto load = [&](Stage& s, int kt) {
-        const size_t at = static_cast<size_t>(kt) * 128;
-        const global_bytes b0 = scalar(Bb[0] + at), b1 = GLU ? scalar(Bb[1] + at) : b0, ab = scalar(Ab + at);
+    const char* zero = reinterpret_cast<const char*>(kZeroPiece);
+
+    // copy i of this wave: rows 4 (wave * NCP + i) .. + 3; this lane's row and piece
+    const char* Ab = static_cast<const char*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA * 2);
+    auto copy_row = [&](int i) { return (wave * NCP + i) * 4 + (lane >> 4); };
+    auto copy_piece = [&](int i) { return (lane & 15) ^ (copy_row(i) & 15); };
+    uint32_t aoff[NCP];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t off = lane_off(boff[b]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) s.w[h][b] = *(global_piece)((b >> 1 ? b1 : b0) + off + h * 64);
-        }
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            const uint32_t off = lane_off(aoff[i]);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) s.a[h][i] = *(global_piece)(ab + off + h * 64);
-        }
-    };
-    auto multiply = [&](const Stage& s) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int i = 0; i < MB; ++i)
-                    acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s.w[h][b], s.a[h][i], acc[b][i], 0, 0, 0);
-    };
-    const int whole = K / 64;                           // whole k-tiles; wave w takes w, w + 4, ...
-    Stage s0, s1;
-    if (wave < whole) {
-        // two k-tiles per turn, no branch inside, so that each load is waited for one k-tile later on every path
-        const int last = wave + ((whole - 1 - wave) & ~3);              // this wave's last k-tile
-        load(s0, wave);
-        __builtin_amdgcn_sched_barrier(0);
-        int kt = wave;
-        for (; kt + 4 < last; kt += 8) {
-            load(s1, kt + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(s0);
-            __builtin_amdgcn_sched_barrier(0);
-            load(s0, kt + 8);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(s1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // one or two k-tiles are left, the first of them in s0
-        if (kt < last) load(s1, last);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(s0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (kt < last) multiply(s1);
+    for (int i = 0; i < NCP; ++i) {
+        int m = min(m0 + copy_row(i), count - 1);       // rows past the count replay a valid row; never stored
+        if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
+        aoff[i] = (static_cast<uint32_t>(m) * LA + copy_piece(i) * 8) * 2u;
     }
-    if (K % 64 != 0 && wave == (whole & 3)) {           // the short last k-tile: pieces past its end are zero
-        const bf16x8 zero = {};
+    // this lane's weight row; GLU: 8 gate rows, then the 8 up rows of the same columns
+    const int nw = n0 + wave * (GLU ? 8 : 16);
+    const int nrow = min(nw + (GLU ? l16 & 7 : l16), p.N - 1);
+    const global_bytes wrow = (global_bytes)(static_cast<const char*>(GLU && l16 >= 8 ? p.B1 : p.B0) +
+                                             ((static_cast<size_t>(e) * p.N + nrow) * LB + kq * 8) * 2);
+    f32x4 acc[MB];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const bool in = whole * 64 + h * 32 + kq * 8 < K;           // K % 8 == 0: a piece is all in or all out
-            const size_t at = static_cast<size_t>(whole) * 128 + h * 64;
-            bf16x8 w[4], a[MB];
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) w[b] = in ? *reinterpret_cast<const bf16x8*>(Bb[GLU ? b >> 1 : 0] + at + boff[b]) : zero;
+        for (int v = 0; v < 4; ++v) acc[i][v] = 0.f;
+
+    struct Weights { bf16x8 w[KS]; };                   // one chunk
+    auto request = [&](auto whole, Weights& s, int c, int buf) {        // whole: the chunk does not end past the contraction
+        constexpr bool W = decltype(whole)::value;
+        const int k0 = c * BK;
+        const uint64_t a64 = reinterpret_cast<uint64_t>(Ab) + static_cast<size_t>(k0) * 2;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a64));
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a64 >> 32));
+        const char* ab = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+        const global_bytes wp = wrow + static_cast<size_t>(k0) * 2;
 #pragma unroll
-            for (int i = 0; i < MB; ++i) a[i] = in ? *reinterpret_cast<const bf16x8*>(Ab + at + aoff[i]) : zero;
+        for (int q = 0; q < KS; ++q) s.w[q] = *(global_piece)(W || k0 + q * 32 + kq * 8 < K ? wp + q * 64 : (global_bytes)zero);
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int i = 0; i < MB; ++i) acc[b][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b], a[i], acc[b][i], 0, 0, 0);
+        for (int i = 0; i < NCP; ++i) {
+            const char* src = W || k0 + copy_piece(i) * 8 < K ? ab + aoff[i] : zero;
+            __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(lds + buf * STAGE + (wave * NCP + i) * 64), 16, 0, 0);
         }
-    }
-    // the partial sums meet: red[wave][block][lane]
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int i = 0; i < MB; ++i) red[(wave * 4 * MB + b * MB + i) * 64 + lane] = acc[b][i];
-    __syncthreads();
-    auto total = [&](int b, int i) {
-        f32x4 s = red[(b * MB + i) * 64 + lane];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) s += red[(w * 4 * MB + b * MB + i) * 64 + lane];
-        return s;
+        __builtin_amdgcn_sched_barrier(0);
     };
+    // chunk c in buffer buf: this wave's requests for it have landed (those for chunk c + 1 may be in flight); past the
+    // barrier that holds for all waves, and the buffer of chunk c - 1 is free for chunk c + 2
+    auto step = [&](auto steady, Weights& now, Weights& free, int c, int buf) {         // steady: chunk c + 2 is whole
+        constexpr bool S = decltype(steady)::value;
+        if (S || c + 1 < n_chunks) __builtin_amdgcn_s_waitcnt(waitcnt_imm(LOADS, true));
+        else __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (S || c + 2 < n_chunks) request(steady, free, c + 2, buf == 0 ? 2 : buf - 1);
+        const uint4* As = lds + buf * STAGE + l16 * kRowsPieces;
+        bf16x8 a[KS][MB];
+#pragma unroll
+        for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) a[q][i] = __builtin_bit_cast(bf16x8, As[i * 16 * kRowsPieces + ((4 * q + kq) ^ l16)]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < KS; ++q)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.w[q], a[q][i], acc[i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr std::integral_constant<bool, true> yes{};
+    constexpr std::integral_constant<bool, false> no{};
+    static_assert(kRowsBuffers == 3, "step and its callers count three buffers");
+    Weights w0, w1, w2;
+    int c = 0;
+    if (n_whole >= 2) {                                 // (straight into the loop: a wait there must not cover other paths)
+        request(yes, w0, 0, 0);
+        request(yes, w1, 1, 1);
+        for (; c + 5 <= n_whole; c += 3) {
+            step(yes, w0, w2, c, 0);
+            step(yes, w1, w0, c + 1, 1);
+            step(yes, w2, w1, c + 2, 2);
+        }
+    } else {
+        request(no, w0, 0, 0);
+        if (n_chunks > 1) request(no, w1, 1, 1);
+    }
+    for (; c < n_chunks; c += 3) {                      // at most five chunks, the first two of them requested
+        step(no, w0, w2, c, 0);
+        if (c + 1 < n_chunks) step(no, w1, w0, c + 1, 1);
+        if (c + 2 < n_chunks) step(no, w2, w1, c + 2, 2);
+    }
+
+    // a lane holds token row l16 of block i and, of the wave's 16 weight rows, 4 kq .. + 3
     const size_t eoff = static_cast<size_t>(e) * p.capacity * p.N;
     auto pack4 = [](const f32x4& v) { return pack_bf16x4(v[0], v[1], v[2], v[3]); };
-    constexpr int UNITS = (GLU ? 2 : 4) * MB;           // output blocks of 16 x 16, dealt to the waves
+    const int n = nw + (GLU ? kq & 1 : kq) * 4;
 #pragma unroll
-    for (int u0 = 0; u0 < UNITS; u0 += 4) {
-        const int u = u0 + wave;
-        if (u >= UNITS) break;
-        const int b = u / MB, i = u - b * MB;
-        const int m = m0 + i * 16 + l16, n = n0 + b * 16 + kq * 4;
-        if (m >= count || n >= p.N) continue;           // N % 4 == 0
+    for (int i = 0; i < MB; ++i) {
+        const int m = m0 + i * 16 + l16;
+        const bool in = m < count && n < p.N;           // N % 4 == 0
         const size_t o = eoff + static_cast<size_t>(m) * p.N + n;
-        const f32x4 g = total(b, i);
         auto put = [&](void* base, const uint2& v) { *reinterpret_cast<uint2*>(static_cast<uint16_t*>(base) + o) = v; };
+        const f32x4 g = acc[i];                         // GLU: the gate product in lanes 0..31, the up product in the others
         if constexpr (!GLU) {
-            put(p.C, pack4(g));
+            if (in) put(p.C, pack4(g));
+        } else if constexpr (DUAL) {
+            if (in) put(kq < 2 ? p.C : p.C2, pack4(g));
         } else {
-            const f32x4 up = total(2 + b, i);
-            if constexpr (DUAL) {
-                put(p.C, pack4(g));
-                put(p.C2, pack4(up));
-            } else {
-                put(p.C, pack_bf16x4(silu(g[0]) * up[0], silu(g[1]) * up[1], silu(g[2]) * up[2], silu(g[3]) * up[3]));
-                if constexpr (KEEP) {
-                    put(p.C2, pack4(g));
-                    put(p.C3, pack4(up));
-                }
+            f32x4 up;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) up[v] = __shfl_xor(g[v], 32, kWave);
+            if (in && kq < 2) put(p.C, pack_bf16x4(silu(g[0]) * up[0], silu(g[1]) * up[1], silu(g[2]) * up[2], silu(g[3]) * up[3]));
+            if constexpr (KEEP) {
+                if (in) put(kq < 2 ? p.C2 : p.C3, pack4(g));
             }
         }
     }
@@ -1771,18 +1755,18 @@ __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, in
 
 template <bool GLU, bool DUAL = false, bool KEEP = false>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
-    __shared__ f32x4 red[4 * 16 * 64];
+    __shared__ __attribute__((aligned(16))) uint4 lds[kRowsBuffers * kRowsBM * kRowsPieces];
     int share, e, mt, nt;
     for (int j = blockIdx.x >> 3; decode_live_tile(p, kRowsBM, j, share, e, mt, nt);) {
         const int count = group_rows(p, e);
         const int m0 = mt * kRowsBM, n0 = nt * (GLU ? 32 : 64);
         const int rows = count - m0;
-        if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
-        else if (rows <= 32) rows_tile<2, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
-        else rows_tile<4, GLU, DUAL, KEEP>(p, e, m0, n0, count, red);
+        if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, lds);
+        else if (rows <= 32) rows_tile<2, GLU, DUAL, KEEP>(p, e, m0, n0, count, lds);
+        else rows_tile<4, GLU, DUAL, KEEP>(p, e, m0, n0, count, lds);
         j += gridDim.x >> 3;
         if (j >= share) return;
-        __syncthreads();                                // the partial sums have been read
+        __syncthreads();                                // every wave has read its last fragments: the buffers are free
     }
 }
 
@@ -1804,8 +1788,6 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
 // whose renaming moves cost 1-4 %.  More buffers, or the barrier between the two k-steps with every fragment read a
 // k-step ahead, change nothing (-2 .. +4 % time): what is lost is lost where the waves of two workgroups meet at barriers.
 // ---------------------------------------------------------------------------------------
-__device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
-
 template <int BM, int BN, int NBUF, bool GLU, bool DUAL = false>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
     constexpr int CPR = 8, BK = 32, NB = GLU ? 2 : 1, BROWS = NB * BN;

@@ -1,5 +1,5 @@
-"""The few-rows GEMM is bound by its loads, so its loop must never wait for a load of the k-tile it has just requested: in
-the compiled loop the strictest wait leaves one whole k-tile in flight. CPU only: compiled to assembly, nothing runs."""
+"""The few-rows GEMM is bound by its loads, so its loop must not wait for more than the chunk it is about to multiply: in the
+compiled loop the strictest wait leaves one whole chunk in flight. CPU only: compiled to assembly, nothing runs."""
 import os
 import re
 import shutil
@@ -28,10 +28,10 @@ def matrix_loops(asm: str, kernel: str):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
-def test_loop_keeps_one_k_tile_in_flight():
+def test_loop_keeps_one_chunk_in_flight():
     loops = matrix_loops(build.device_assembly("ffn.hip"), "gemm_bf16_rows_kernel")
-    assert {m for m, _, _ in loops} == {16, 32, 64}              # two k-tiles of one, two and four row blocks
+    assert {m for m, _, _ in loops} == {12, 24, 48}              # three chunks of four k-steps, one, two and four row blocks
     for mfma, loads, vmcnt in loops:
-        blocks = mfma // 16
-        assert loads == 2 * (8 + 2 * blocks)
-        assert vmcnt >= loads // 2, (mfma, loads, vmcnt)
+        blocks = mfma // 12
+        assert loads == 3 * (4 + blocks)                         # weight pieces and copies of token rows
+        assert vmcnt >= loads // 3, (mfma, loads, vmcnt)

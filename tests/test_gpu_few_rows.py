@@ -88,6 +88,37 @@ def test_counts_beyond_the_batch(oracle, T, E, C, d, Hh, counts):
     H.check_expert_ffn(oracle, shape, counts)
 
 
+@pytest.mark.parametrize("E,C,d,Hh", [(16, 700, 2048, 1024), (16, 520, 512, 1408), (64, 300, 320, 512), (16, 700, 1032, 1048),
+                                      (32, 700, 1048, 184)])
+def test_same_bits_as_many_rows(E, C, d, Hh):
+    """The few-rows kernel adds the products in the order of the persistent one: the same rows give the same bits whichever
+    of the two a batch takes."""
+    import gpu_helpers as H
+    B.load_library()
+    print(f"same bits E={E} C={C} d={d} H={Hh}", flush=True)
+    dt = torch.bfloat16
+    xp = I.normal(1, E * C * d, "cuda").reshape(E, C, d).to(dt)
+    wg, wu = (I.ffn_weight(s, (E, Hh, d), dt, "cuda", std=0.05) for s in (2, 3))
+    wd = I.ffn_weight(4, (E, d, Hh), dt, "cuda", std=0.05)
+    counts = torch.tensor([max(0, C - 37 * e) if e != 1 else 0 for e in range(E)], dtype=torch.int32, device="cuda")
+    out, hidden, kernels = [], [], []
+    for T in (1, 64 * 4096):
+        cfg = B.make_config(I.EtrShape("b", 1, T=T, d=d, E=E, D=8, k=1, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR,
+                                       recipe="iso"))
+        kernels.append([H.ffn_plan(cfg, p, gathered=False)[0] for p in (0, 1)])
+        ws = torch.zeros(B.etr_ffn_workspace_bytes(cfg) // 2, dtype=dt, device="cuda")
+        yp = torch.zeros(E, C, d, dtype=dt, device="cuda")
+        B.etr_expert_ffn(cfg, xp, counts, wg, wu, wd, yp, ws)
+        torch.cuda.synchronize()
+        out.append(yp)
+        hidden.append(ws[:E * C * Hh])                   # the scratch is the hidden activation
+    assert kernels[0] == [H.ROWS, H.ROWS]
+    assert kernels[1] == [H.PERSISTENT if n % 64 == 0 else H.PERSISTENT_TAIL for n in (d, Hh)]
+    live = torch.arange(C, device="cuda").unsqueeze(0) < counts.unsqueeze(1)
+    assert torch.equal(hidden[0].view(E, C, Hh)[live], hidden[1].view(E, C, Hh)[live])
+    assert torch.equal(out[0], out[1])
+
+
 _P, _Z, _R = "PERSISTENT", "PERSISTENT_TAIL", "ROWS"
 
 
