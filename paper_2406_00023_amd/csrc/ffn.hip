@@ -2034,8 +2034,8 @@ size_t ffn_ws_bytes(const etr_config& c) {
 enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
 // Estimated microseconds of a product whose groups have about `rows` rows each: rounds of tiles over the CUs, each a time
 // per 64-wide k-tile and a time besides, and at least the weights at the rate that the kernel reads them with.
-//   ROWS        tiles of 64 rows x 64 staged weight rows, two on a CU at once; a wave takes every fourth k-tile: 1.6 us per
-//               k-tile of a wave (1.25 and 0.72 for a lone block of 32 or 16 rows) and 0.24 us; 5.5 TB/s; 2.9 us per launch
+//   ROWS        tiles of 64 rows x 64 staged weight rows, two on a CU at once: 0.58 us per two k-tiles (0.47 and 0.25 for a
+//               lone block of 32 or 16 rows) and 0.95 us; 5.2 TB/s; 2.8 us per launch
 //   PERSISTENT  256-row tiles: 1.13 us per k-tile where few CUs have one, 1.69 on a full chip (its power limit), 1.08 times
 //               that with zero-filling copies, and 1.65 us; 4.65 TB/s; 5 us
 //   RING        the same tiles: 1.03 us per k-tile and 7 us
@@ -2047,8 +2047,8 @@ enum class Bf16Kernel { ROWS, PERSISTENT, RING, STAGED };
 // 4980 us for both products, ROWS 190 throughout.
 // Fitted to 7190 measured products: 2 to 64 groups of 1 to 13 000 rows, even and uneven counts, capacities of 1 to 4 times
 // that, widths from 8 to 11008, half of them ragged.  A kernel newer than the ones that took everything once (PERSISTENT and
-// RING for whole k-tiles, STAGED for ragged ones) has to be estimated 5 % faster.  Against those the geometric mean is 0.66
-// of the time and 63 products are more than 3 % (and 1 us) slower; against the best kernel of each product it is 1.011.
+// RING for whole k-tiles, STAGED for ragged ones) has to be estimated 5 % faster.  Against those the geometric mean is 0.63
+// of the time and 69 products are more than 3 % (and 1 us) slower; against the best kernel of each product it is 1.009.
 static double estimate_us(Bf16Kernel kernel, const GemmParams& g, bool glu, int rows) {
     const double n_cu = cu_count(), weight_bytes = 2.0 * g.E * g.N * (glu ? 2 : 1) * g.K;
     const int KT = (g.K + 63) / 64;
@@ -2071,9 +2071,8 @@ static double estimate_us(Bf16Kernel kernel, const GemmParams& g, bool glu, int 
     double busiest, dead;
     switch (kernel) {
         case Bf16Kernel::ROWS: {
-            const double step = rows <= 16 ? 0.72 : (rows <= 32 ? 1.25 : 1.6), rounds = tiles(kRowsBM, glu ? 32 : 64) / n_cu;
-            const int kt = std::max(1, (g.K / 64 + 3) / 4);
-            return least((rounds <= 1 ? 1.0 : rounds + 0.48) * (kt * step + 0.24), 5.5) + 2.9;
+            const double step = rows <= 16 ? 0.25 : (rows <= 32 ? 0.47 : 0.58), rounds = tiles(kRowsBM, glu ? 32 : 64) / n_cu;
+            return least((rounds <= 1 ? 1.0 : rounds + 0.37) * ((g.K + 127) / 128 * step + 0.95), 5.2) + 2.8;
         }
         case Bf16Kernel::PERSISTENT: {
             const double t = tiles(256, glu ? 128 : 256), step = (1.13 + 0.56 * std::min(1.0, t / n_cu)) * (g.K % 64 ? 1.08 : 1.0);

@@ -1,5 +1,5 @@
 """The bf16 GEMM for few rows per expert: one, two and four 16-row blocks, several row blocks of 64, empty experts,
-contractions of less than one k-tile, of a few k-tiles (waves without any), and ragged ones, narrow and ragged outputs; in
+contractions of less than one chunk, of whole chunks and ragged ones, narrow and ragged outputs; in
 the forward, the training forward and the recomputation of the backward."""
 import numpy as np
 import pytest
@@ -12,12 +12,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("E,C,d,Hh,counts", [
-    (4, 16, 2048, 1024, [16, 1, 0, 15]),                 # one block of 16 rows; 32 and 16 k-tiles over four waves
-    (3, 33, 1080, 520, [33, 17, 32]),                    # two blocks and one past; k-tiles end 56 and 8 short of whole
-    (64, 64, 136, 40, [64, 0, 49, 1] * 16),              # a short k-tile on wave 2; outputs narrower than a workgroup's
+    (4, 16, 2048, 1024, [16, 1, 0, 15]),                 # one block of 16 rows; 16 and 8 chunks of k
+    (3, 33, 1080, 520, [33, 17, 32]),                    # two blocks and one past; short last chunks
+    (64, 64, 136, 40, [64, 0, 49, 1] * 16),              # one whole chunk and a short one; outputs narrower than a workgroup's
     (2, 30, 8, 8, [30, 3]),                              # less than one k-step
-    (64, 64, 56, 4096, [64, 17, 0, 16] * 16),            # less than one k-tile, many columns; then 16 k-tiles per wave
-    (1, 200, 320, 4096, [200]),                          # four row blocks, the last of 8 rows; k-tiles for some waves only
+    (4, 64, 56, 1024, [64, 17, 0, 16]),                  # less than one k-tile, many columns; then eight chunks
+    (1, 200, 320, 4096, [200]),                          # four row blocks, the last of 8 rows; two whole chunks and a half one
     (5, 64, 192, 72, [64, 63, 48, 31, 0]),
 ])
 def test_few_rows_ffn(oracle, E, C, d, Hh, counts):
