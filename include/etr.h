@@ -153,7 +153,9 @@ etr_status etr_dispatch(const etr_config* cfg, const void* x, const int32_t* slo
  * Mixtral-style SwiGLU form): yp[e][s] = W_down[e] (SiLU(W_gate[e] xp[e][s]) .* (W_up[e] xp[e][s]))
  * for s < counts[e].  bf16: MFMA grouped GEMM, fp32 accumulate, the hidden activation and
  * yp are rounded to bf16.  fp32: fp32 MFMA grouped GEMM.
- *   xp [E][capacity][d] in; counts [E] in (device; the grid is sized for `capacity`)
+ *   xp [E][capacity][d] in; counts [E] in (device; every row up to min(counts[e], capacity) is computed).
+ *     The rows that cfg's T, k and mode let expect choose the kernel and size its grid: a caller whose
+ *     rows come from elsewhere passes a T that stands for them, or pays in time, not in results.
  *   w_gate, w_up [E][H][d]; w_down [E][d][H]   dtype in
  *   yp [E][capacity][d] dtype out; rows s >= counts[e] are left untouched
  *   ws, ws_bytes: scratch, >= etr_ffn_workspace_bytes(cfg); holds the hidden activation [E][capacity][H]
