@@ -3,15 +3,16 @@
 // Experimental Setup: Mixtral experts).  This is the one dense contraction of the layer
 // and the operator the paper reports as dominant ("FFN MatMul").
 //
-// bf16: two grouped "NT" GEMMs on the MFMA units (v_mfma_f32_16x16x32_bf16 in the persistent
-// kernel the layer launches, v_mfma_f32_32x32x16_bf16 in the other forms), fp32
-// accumulation.  Both operands are K-contiguous, staged through LDS in 16-byte chunks
-// with an XOR swizzle, double-buffered.  GEMM-1 computes the gate and the up projection
-// of the same output tile so that SiLU(g)*u is its epilogue and the hidden activation
-// crosses HBM once, in bf16.  The kernel the layer launches is the persistent one
-// (gemm_bf16_persistent_kernel: one workgroup per CU walks the live tiles, the copies run on
-// across tile boundaries); the per-tile kernels size the grid for `capacity` and a workgroup
-// whose row tile starts past counts[e] exits at once.  Either way counts never leave the device.
+// bf16: two grouped "NT" GEMMs on the MFMA units (v_mfma_f32_16x16x32_bf16 in the two kernels
+// most layers run on, v_mfma_f32_32x32x16_bf16 in the other forms), fp32 accumulation.  Both
+// operands are K-contiguous, staged through LDS in 16-byte chunks with an XOR swizzle.
+// GEMM-1 computes the gate and the up projection of the same output tile so that SiLU(g)*u is
+// its epilogue and the hidden activation crosses HBM once, in bf16.  choose_bf16 picks the
+// kernel: the persistent one for many rows per expert (gemm_bf16_persistent_kernel: one
+// workgroup per CU walks the live tiles, the copies run on across tile boundaries), the
+// few-rows one for few (gemm_bf16_rows_kernel, whose weights go straight to the fragments), and
+// two per-tile kernels, whose grid is that of `capacity` and where a workgroup whose row tile
+// starts past counts[e] exits at once.  In all of them counts never leave the device.
 // fp32: the same product on v_mfma_f32_16x16x4_f32, one workgroup per tile.
 
 #include <algorithm>
