@@ -507,51 +507,43 @@ __device__ __forceinline__ void store_blocks_staged16(const GemmParams& p, const
     }
 }
 
-// The plain epilogue of the transposing persistent kernel: 32 x 32 accumulators (lane: row lane % 32 and, per q, the four
-// columns 8 q + 4 (lane / 32) .. + 3), a wave's two blocks 64 columns wide.  Stored directly that is 16 bytes per row and
-// instruction; a weight gradient, whose contraction is an expert's few hundred rows, then spends as long storing its
-// tile as multiplying it.  Here 32 rows x 128 bytes pass through LDS and leave as whole lines, 8 rows per instruction.
-// The patch is the wave's own copy target (two pieces of 2 KiB, one per block) in the ring slot of the k-tile just
-// multiplied: behind that k-tile's barrier nobody reads the slot any more, and the next copies into these 4 KiB are
-// the wave's own, issued after its epilogue.  8-byte pieces are XORed with bits of the row (no padding fits; two-way
-// bank conflicts on the writes, none on the reads).  In assembly for the reason given above.
-// Measured, each weight gradient of the layer: 16 experts of 166-1024 rows, 2048 x 5632: 337 -> 280 us; 32 experts, 360
-// rows in all, 2304 x 6032 (0.9 GB written): 430 -> 297 us.
-__device__ __forceinline__ void store_rows_staged32(const uint2 (&pk)[2][4], uint16_t* dst, int ldc, int rows_live, int cols_live,
-                                                    uint32_t patch0, uint32_t patch1, int lane) {
-    const int r32 = lane & 31, half = lane >> 5;
-    const int sw = (r32 >> 2) & 3;
-    uint32_t wa[4];                                     // write address of piece 2 q + half of row r32
+// The epilogue of the transposing persistent kernel: 32 rows x 64 columns of a wave (pk[bi][bj]: its 16 x 16 accumulators
+// packed, lane: row 16 bi + l % 16 and the four columns 16 bj + 4 (l / 16) .. + 3) pass through LDS and leave as whole
+// 128-byte lines, 8 rows per instruction.  Stored directly an instruction would write 32 bytes of 16 rows; a weight
+// gradient, whose contraction is an expert's few hundred rows, then spends as long storing its tile as multiplying it.
+// The patch is four pieces of 1 KiB, 8 KiB apart (8 rows x 128 bytes each): the wave's own copy target, see the kernel.  The
+// 16-byte pieces of a row are XORed with the row (no padding fits): two-way bank conflicts on the writes, none on the
+// reads.  In assembly for the reason given above.  N % 8 == 0: a 16-byte piece is all in or all out.
+__device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4], uint16_t* dst, int ldc, int rows_live, int cols_live,
+                                                        uint32_t patch, int lane) {
+    const int l16 = lane & 15, kq = lane >> 4;
+    const uint32_t wbase = patch + (l16 >> 3) * 8192 + (l16 & 7) * 128 + (kq & 1) * 8;
+    uint32_t wa[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wa[q] = r32 * 64 + ((2 * q + half) ^ (2 * sw)) * 8;
-    const uint32_t d = patch1 - patch0;
+    for (int bj = 0; bj < 4; ++bj) wa[bj] = wbase + (((2 * bj + (kq >> 1)) ^ (l16 & 7)) * 16);
     const int rr = lane >> 3, ch = lane & 7;
-    // rows 8 u + rr: the swizzle term is (2 u + (rr >> 2)) & 3
-    uint32_t ra[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) ra[u] = (ch & 4 ? patch1 : patch0) + (8 * u + rr) * 64 + (((ch & 3) ^ ((2 * u + (rr >> 2)) & 3)) * 16);
+    const uint32_t ra = patch + rr * 128 + ((ch ^ rr) * 16);
     epi_v4i v0, v1, v2, v3;
     asm volatile(
-        "ds_write_b64 %4, %12\n\t"
-        "ds_write_b64 %5, %13\n\t"
-        "ds_write_b64 %6, %14\n\t"
-        "ds_write_b64 %7, %15\n\t"
-        "ds_write_b64 %8, %16\n\t"
-        "ds_write_b64 %9, %17\n\t"
-        "ds_write_b64 %10, %18\n\t"
-        "ds_write_b64 %11, %19\n\t"
-        "ds_read_b128 %0, %20\n\t"
-        "ds_read_b128 %1, %21\n\t"
-        "ds_read_b128 %2, %20 offset:1024\n\t"
-        "ds_read_b128 %3, %21 offset:1024\n\t"
+        "ds_write_b64 %4, %9\n\t"
+        "ds_write_b64 %5, %10\n\t"
+        "ds_write_b64 %6, %11\n\t"
+        "ds_write_b64 %7, %12\n\t"
+        "ds_write_b64 %4, %13 offset:16384\n\t"
+        "ds_write_b64 %5, %14 offset:16384\n\t"
+        "ds_write_b64 %6, %15 offset:16384\n\t"
+        "ds_write_b64 %7, %16 offset:16384\n\t"
+        "ds_read_b128 %0, %8\n\t"
+        "ds_read_b128 %1, %8 offset:8192\n\t"
+        "ds_read_b128 %2, %8 offset:16384\n\t"
+        "ds_read_b128 %3, %8 offset:24576\n\t"
         "s_waitcnt lgkmcnt(0)"
         : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3)
-        : "v"(patch0 + wa[0]), "v"(patch0 + wa[1]), "v"(patch0 + wa[2]), "v"(patch0 + wa[3]), "v"(patch0 + d + wa[0]),
-          "v"(patch0 + d + wa[1]), "v"(patch0 + d + wa[2]), "v"(patch0 + d + wa[3]), "v"(as_v2i(pk[0][0])), "v"(as_v2i(pk[0][1])),
+        : "v"(wa[0]), "v"(wa[1]), "v"(wa[2]), "v"(wa[3]), "v"(ra), "v"(as_v2i(pk[0][0])), "v"(as_v2i(pk[0][1])),
           "v"(as_v2i(pk[0][2])), "v"(as_v2i(pk[0][3])), "v"(as_v2i(pk[1][0])), "v"(as_v2i(pk[1][1])), "v"(as_v2i(pk[1][2])),
-          "v"(as_v2i(pk[1][3])), "v"(ra[0]), "v"(ra[1])
+          "v"(as_v2i(pk[1][3]))
         : "memory");
-    const bool col = ch * 8 < cols_live;                // N % 8 == 0: a 16-byte piece is all in or all out
+    const bool col = ch * 8 < cols_live;
     const epi_v4i v[4] = {v0, v1, v2, v3};
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -729,11 +721,10 @@ __global__ __launch_bounds__(128 * WN) void gemm_bf16_ring_kernel(GemmParams p) 
 }
 
 // ---------------------------------------------------------------------------------------
-// Persistent form of the ring kernel: one workgroup per CU walks a list of tiles, and the ring
-// of copies runs on across tile boundaries: while the last k-tiles of one tile are multiplied
-// the first k-tiles of the next are already being fetched, and the stores of the epilogue
-// overlap with them.  (A workgroup per tile pays launch, address set-up, the first-tile latency
-// and the epilogue with the matrix pipe idle: about 5 us per tile, 5-10 % at K = 2048.)
+// Persistent kernels: one workgroup per CU walks a list of tiles, and the copies run on across tile boundaries: while the
+// last k-tiles of one tile are multiplied the first k-tiles of the next are already being fetched, and the stores of the
+// epilogue overlap with them.  (A workgroup per tile pays launch, address set-up, the first-tile latency and the epilogue
+// with the matrix pipe idle: about 5 us per tile, 5-10 % at K = 2048.)
 //
 // Tile list: only tiles that hold rows (m0 < counts[e]) are enumerated, super-tile by super-tile
 // (see decode_tile), from an exclusive prefix over the super-tiles that every workgroup builds in
@@ -741,539 +732,9 @@ __global__ __launch_bounds__(128 * WN) void gemm_bf16_ring_kernel(GemmParams p) 
 // tiles that run together on one XCD are still (pieces of) one super-tile and share operand
 // slices through its L2, and every workgroup gets the same number of tiles +- 1.
 // No atomics, no flags: the schedule is a pure function of counts[].
-//
-// Waits: copies and stores complete in issue order, so "at most 3*NCP operations outstanding"
-// always implies that everything older than the newest 3*NCP has landed; operations that are not
-// copies of the ring (the epilogue's stores) only make that wait conservative, never unsafe.
 // ---------------------------------------------------------------------------------------
-constexpr int kMaxSuper = 4096;          // super-tiles the LDS prefix can hold (16 KiB)
-constexpr int kMaxSuperWide = 2048;      // the same for the 64-wide kernel, whose two 64 KiB buffers leave less room
-
-//
-// Operands whose contraction index is the slow one (TRA: A is [K][M], TRB: B is [K][N], row strides lda / ldb,
-// group stride K * ld; with TRB and B1 the contraction is split in the middle: first half from B0, second half
-// from B1, each [K/2][N]).  Such a tile is staged in LDS as [block of 32 rows][32 k][32 rows] (64 bytes per k) and
-// the MFMA fragments come out through the transposing read ds_read_b64_tr_b16: inside a group of 16 lanes, lane i
-// supplies the address of 4 consecutive elements and receives element i % 4 of lanes i/4, i/4 + 4, i/4 + 8,
-// i/4 + 12.  With lane (q = i % 4, j = i / 4) pointing at (k0 + j, r0 + 4 q) lane i receives rows r0 + i at
-// k0 .. k0 + 3: two reads give the 8 consecutive k of one row that the MFMA operand layout wants.  The four k of a
-// group are 64 bytes apart, so 32 lanes cover all 64 banks once: conflict-free without a swizzle.
-//
-// KG (1: A, 2: B): the contraction rows of that operand are fetched through p.k_index (a gather along the slow
-// index).  The indices of a k-tile (32 of them) travel like the tiles themselves: wave 0 copies them into a ring
-// of 16 LDS slots seven k-tiles before the tile is multiplied, i.e. four iterations before its copies are issued,
-// so that its wait and the barrier of an earlier iteration have made them visible to every wave by the time a lane
-// reads its row number; the per-lane source address of a copy is then
-// base + row * row bytes + the lane's fixed column offset.  Every row number is clamped into [0, k_rows), so a
-// stale or foreign ring word can at worst fetch a wrong but existing row.
-//
-// TAIL (row-major A, transposed B): the contraction, or each half of a split one, need not be whole k-tiles.  The
-// last k-tile of it is short: pieces of a token row and whole weight rows past its end are zero-filled
-// (buffer_copy_to_lds).
-//
-// Plain products only: row-major operands with an epilogue take the 64-wide kernel.
-template <bool TRA, bool TRB, int KG = 0, bool TAIL = false>
-__global__ __launch_bounds__(512) void gemm_bf16_persist_kernel(GemmParams p) {
-    static_assert(KG == 0 || (KG == 1 && TRA) || (KG == 2 && TRB), "the gathered operand is a transposed one");
-    static_assert(!TAIL || (TRB && !TRA && KG == 0), "short k-tiles: row-major A, transposed B");
-    constexpr int IDX_AHEAD = 7, IDX_SLOTS = 16;        // index prefetch distance in k-tiles, ring slots of 32 indices
-    constexpr int BM = 256, BR = 256, CPR = 4, NBUF = 4, AHEAD = NBUF - 1;
-    constexpr int BN = 256;
-    constexpr int STAGE = (BM + BR) * CPR;
-    constexpr int WN = 4, NW = 8, TB = 2, NCP = 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-    uint4* lds = reinterpret_cast<uint4*>(lds_raw);
-    __shared__ int pre[kMaxSuper + 1];
-    __shared__ int wave_tot[NW];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    const int r32 = lane & 31, half = lane >> 5;
-    const int KCA = (p.lda ? p.lda : p.K) / 8, KCB = (p.ldb ? p.ldb : p.K) / 8;
-    // bytes from one k-tile of an operand to the next
-    const size_t stepA = TRA ? static_cast<size_t>(32) * KCA * 16 : CPR * 16;
-    const size_t stepB = TRB ? static_cast<size_t>(32) * KCB * 16 : CPR * 16;
-    const bool splitB = TRB && p.B1 != nullptr;
-    // TAIL: contraction length and k-tiles of the whole product, or of each half of a split one
-    const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 31) / 32;
-    const int k_rem = (Kh & 31) ? (Kh & 31) : 32;        // valid k of the last k-tile
-    const bool over_a = TAIL && 8 * ((lane & 3) ^ ((lane >> 4) & 3)) >= k_rem;           // this lane's piece of a token row
-    const bool over_b[2] = {TAIL && (lane >> 2) >= k_rem, TAIL && 16 + (lane >> 2) >= k_rem};   // its k row, per copy
-    const uint32_t kg_row_bytes = static_cast<uint32_t>(KG == 1 ? KCA : KCB) * 16u;
-    int32_t* idx_ring = reinterpret_cast<int32_t*>(lds_raw + static_cast<size_t>(NBUF) * STAGE * 16);
-
-    // ---- exclusive prefix of the number of live tiles per super-tile
-    const int MG = (p.MT + p.SM - 1) / p.SM, NG = (p.NT + p.SN - 1) / p.SN;
-    const int S = p.E * MG * NG;
-    auto live_rows = [&](int e, int mg) {                // live row tiles of super-tile row mg of expert e
-        const int mtv = (group_rows(p, e) + BM - 1) / BM;
-        return min(max(mtv - mg * p.SM, 0), p.SM);
-    };
-    auto live_cols = [&](int ng) { return min(p.NT - ng * p.SN, p.SN); };
-    {
-        const int CH = (S + 511) / 512;
-        int sum = 0;
-        for (int i = 0; i < CH; ++i) {
-            const int s = tid * CH + i;
-            if (s < S) {
-                const int e = s / (MG * NG), r = s - e * (MG * NG);
-                sum += live_rows(e, r % MG) * live_cols(r / MG);
-            }
-        }
-        int inc = sum;
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) {
-            const int o = __shfl_up(inc, m, 64);
-            if (lane >= m) inc += o;
-        }
-        if (lane == 63) wave_tot[wave] = inc;
-        __syncthreads();
-        int run = inc - sum;
-        for (int w = 0; w < wave; ++w) run += wave_tot[w];
-        for (int i = 0; i < CH; ++i) {
-            const int s = tid * CH + i;
-            if (s < S) {
-                pre[s] = run;
-                const int e = s / (MG * NG), r = s - e * (MG * NG);
-                run += live_rows(e, r % MG) * live_cols(r / MG);
-            }
-        }
-        if (tid == 511) pre[S] = run;                    // thread 511 owns the last chunk (or nothing): run = total
-        __syncthreads();
-    }
-    const int total = pre[S];
-    const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
-    const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
-
-    struct Tile {
-        int e, m0, n0, count, KT;
-        const char* Abase;
-        const char* Bbase;
-        const char* Bbase1;                              // second half of a split transposed B
-        uint32_t off[2 * NCP];
-    };
-    // per-lane byte offset inside a k-tile of a [K][rows] operand.  Copy unit u = (block of 32 rows, half of the 32 k):
-    // 16 k x 64 bytes, four lanes per k, the access shape of the row-major copies (64-byte pieces of 16 memory rows)
-    auto kmajor_off = [&](int u, int r0, int limit, int kc, bool gathered) -> uint32_t {
-        const int krow = gathered ? 0 : (u & 1) * 16 + (lane >> 2);      // (a gathered row comes from the index ring)
-        int r = r0 + (u >> 1) * 32 + (lane & 3) * 8;
-        r = r + 8 <= limit ? r : limit - 8;              // stay inside the row; such columns are never stored
-        return (static_cast<uint32_t>(krow) * kc * 8 + r) * 2u;
-    };
-    // the tile with list index q (q < total)
-    auto setup = [&](int q, Tile& t) {
-        int lo = 0, hi = S;                              // largest s with pre[s] <= q
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= q) lo = mid; else hi = mid;
-        }
-        const int s = __builtin_amdgcn_readfirstlane(lo);
-        const int u = __builtin_amdgcn_readfirstlane(q - pre[s]);
-        const int e = s / (MG * NG), r = s - e * (MG * NG);
-        const int mg = r % MG, ng = r / MG;
-        const int vm = live_rows(e, mg);
-        const int mt = mg * p.SM + u % vm, nt = ng * p.SN + u / vm;
-        t.e = e; t.m0 = mt * BM; t.n0 = nt * BN;
-        t.count = group_rows(p, e);
-        t.KT = TAIL ? (splitB ? 2 * KTh : KTh) : group_k(p, e) / 32;
-        if constexpr (KG == 1) t.Abase = reinterpret_cast<const char*>(p.A);
-        else if constexpr (TRA) t.Abase = reinterpret_cast<const char*>(p.A) + static_cast<size_t>(e) * p.K * KCA * 16;
-        else t.Abase = reinterpret_cast<const char*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * KCA * 16);
-        if constexpr (TRB) {
-            const size_t per_group = KG == 2 ? 0 : static_cast<size_t>(splitB ? p.K / 2 : p.K) * KCB * 16;
-            t.Bbase = reinterpret_cast<const char*>(p.B0) + e * per_group;
-            t.Bbase1 = splitB ? reinterpret_cast<const char*>(p.B1) + e * per_group : t.Bbase;
-        } else {
-            t.Bbase = reinterpret_cast<const char*>(p.B0) + static_cast<size_t>(e) * p.N * KCB * 16;
-            t.Bbase1 = t.Bbase;
-        }
-#pragma unroll
-        for (int i = 0; i < NCP; ++i) {
-            const int rr = (wave * NCP + i) * 16 + (lane >> 2);
-            const int c = (lane & 3) ^ ((rr >> 2) & 3);
-            if constexpr (TRA) {
-                t.off[i] = kmajor_off(wave * NCP + i, t.m0, p.capacity, KCA, KG == 1);
-            } else {
-                int m = t.m0 + rr;
-                m = m < t.count ? m : t.count - 1;
-                const int row = p.row_index ? min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1) : m;
-                t.off[i] = (static_cast<uint32_t>(row) * KCA + c) * 16u;
-            }
-            if constexpr (TRB) {
-                t.off[NCP + i] = kmajor_off(wave * NCP + i, t.n0, p.N, KCB, KG == 2);
-            } else {
-                int n = t.n0 + rr;
-                n = n < p.N ? n : p.N - 1;
-                t.off[NCP + i] = (static_cast<uint32_t>(n) * KCB + c) * 16u;
-            }
-        }
-    };
-    // address of k-tile k of the B operand (wave-uniform); all arguments by value, so that the tile records stay in
-    // registers
-    auto b_ktile = [&](const char* b0, const char* b1, int kt_count, int k) -> uint64_t {
-        const bool second = splitB && k >= (kt_count >> 1);
-        const int kk = second ? k - (kt_count >> 1) : k;
-        return reinterpret_cast<uint64_t>(second ? b1 : b0) + kk * stepB;
-    };
-    // address of k-tile k of the A operand
-    auto a_ktile = [&](const char* a, int k) -> uint64_t {
-        if constexpr (TAIL) {
-            const bool second = splitB && k >= KTh;
-            return reinterpret_cast<uint64_t>(a) + (second ? static_cast<size_t>(Kh) * 2 + (k - KTh) * stepA : k * stepA);
-        }
-        return reinterpret_cast<uint64_t>(a) + k * stepA;
-    };
-    auto short_ktile = [&](int k) { return TAIL && (k == KTh - 1 || k == 2 * KTh - 1); };
-    static_assert(NCP == 2, "over_b holds one flag per copy");
-    // copy j (0..NCP-1: A row groups, NCP..2NCP-1: B row groups) of k-tile k of tile t into the ring slot of step g
-    auto issue_copy = [&](const Tile& t, int k, int g, int j, uint32_t row_off) {
-        uint4* dst = lds + (g & (NBUF - 1)) * STAGE + (j / NCP) * (BM * CPR) + (wave * NCP + (j % NCP)) * 64;
-        const bool gathered = (KG == 1 && j < NCP) || (KG == 2 && j >= NCP);
-        const uint64_t b64 = gathered ? reinterpret_cast<uint64_t>(j < NCP ? t.Abase : t.Bbase)
-                           : j < NCP ? a_ktile(t.Abase, k) : b_ktile(t.Bbase, t.Bbase1, t.KT, k);
-        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
-        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
-        if constexpr (TAIL) {
-            const bool past = short_ktile(k) && (j < NCP ? over_a : over_b[j - NCP]);
-            buffer_copy_to_lds(lo, hi, past ? kPastRange : t.off[j], dst);
-            return;
-        }
-        const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-        __builtin_amdgcn_global_load_lds((global_cptr)(base + t.off[j] + row_off), (lds_ptr)dst, 16, 0, 0);
-    };
-    // KG: the 32 row numbers of k-tile kl of group e go to the ring slot of global step gstep (lanes 0..31 of the
-    // calling wave); positions past the index row are clamped onto its last entry
-    auto issue_idx = [&](int e, int kl, int gstep) {
-        int pos = kl * 32 + (lane & 31);
-        pos = pos < p.k_index_stride ? pos : p.k_index_stride - 1;
-        const int32_t* src = p.k_index + static_cast<size_t>(e) * p.k_index_stride + pos;
-        int32_t* dst = idx_ring + (gstep & (IDX_SLOTS - 1)) * 32;
-        if (lane < 32) __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)dst, 4, 0, 0);
-    };
-
-    const int sw = (r32 >> 2) & 3;
-    int a_row[4], b_row[TB];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a_row[i] = (wm * 128 + i * 32 + r32) * CPR;
-#pragma unroll
-    for (int j = 0; j < TB; ++j) b_row[j] = BM * CPR + (wn * (32 * TB) + j * 32 + r32) * CPR;
-    const int ck0 = half ^ sw, ck1 = (2 + half) ^ sw;
-    // transposing reads: byte offset, inside the operand's part of a ring slot, of this lane's 4 elements for the
-    // 32-row fragment that starts at row rf (first k-substep, first half of its 8 k)
-    auto tr_off = [&](int rf) -> uint32_t {
-        const int r = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);           // inside the block of 32 rows
-        const int kb = 8 * (lane >> 5) + ((lane & 15) >> 2);
-        return static_cast<uint32_t>((rf >> 5) * 2048 + kb * 64 + r * 2);
-    };
-    uint32_t a_tr[4], b_tr[TB];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a_tr[i] = tr_off(wm * 128 + i * 32);
-#pragma unroll
-    for (int j = 0; j < TB; ++j) b_tr[j] = BM * CPR * 16 + tr_off(wn * (32 * TB) + j * 32);
-    // The reads are written as assembly: through the compiler's builtin every such read waits for ALL outstanding
-    // copies (vmcnt(0)), because it is taken to alias the asynchronous LDS writes.  The compiler does not track the
-    // LDS counter for assembly, so every statement below carries its own wait (lgkmcnt(0)) behind its reads: when
-    // the statement ends its outputs are ordinary, fully written registers, and nothing depends on how the register
-    // allocator treats them afterwards.  All reads of one statement are in flight together; the statement is placed
-    // one k-substep before the fragments are used, so the wait overlaps with the MFMAs of the other wave of the SIMD.
-    typedef int v2i __attribute__((ext_vector_type(2)));
-    typedef int v4i __attribute__((ext_vector_type(4)));
-    const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds_raw));
-    // KG: byte offsets of the source rows of this wave's two copies (k rows lane / 4 and 16 + lane / 4) of the k-tile
-    // of global step gstep, from the index ring (its words are visible: see the kernel's header)
-    auto idx_addr = [&](int gstep) -> uint32_t {
-        return lds_base + static_cast<uint32_t>(NBUF) * STAGE * 16 + (gstep & (IDX_SLOTS - 1)) * 128 + (lane >> 2) * 4;
-    };
-    auto idx_rows = [&](int gstep, uint32_t& r0, uint32_t& r1) {
-        const uint32_t a = idx_addr(gstep);
-        int i0, i1;
-        asm volatile("ds_read_b32 %0, %2\n\t"
-                     "ds_read_b32 %1, %2 offset:64\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : "=&v"(i0), "=&v"(i1) : "v"(a));
-        r0 = static_cast<uint32_t>(min(max(i0, 0), p.k_rows - 1)) * kg_row_bytes;
-        r1 = static_cast<uint32_t>(min(max(i1, 0), p.k_rows - 1)) * kg_row_bytes;
-    };
-    auto tr_pack = [](v2i lo, v2i hi) -> bf16x8 {          // k .. k+3 and k+4 .. k+7 of one row
-        const v4i r = {lo.x, lo.y, hi.x, hi.y};
-        return __builtin_bit_cast(bf16x8, r);
-    };
-    auto tr_frags4 = [&](bf16x8* f, uint32_t slot, const uint32_t* off) {
-        const uint32_t a0 = lds_base + slot + off[0], a1 = lds_base + slot + off[1];
-        const uint32_t a2 = lds_base + slot + off[2], a3 = lds_base + slot + off[3];
-        v2i x0, x1, x2, x3, x4, x5, x6, x7;
-        asm volatile(
-            "ds_read_b64_tr_b16 %0, %8\n\t"
-            "ds_read_b64_tr_b16 %1, %8 offset:256\n\t"
-            "ds_read_b64_tr_b16 %2, %9\n\t"
-            "ds_read_b64_tr_b16 %3, %9 offset:256\n\t"
-            "ds_read_b64_tr_b16 %4, %10\n\t"
-            "ds_read_b64_tr_b16 %5, %10 offset:256\n\t"
-            "ds_read_b64_tr_b16 %6, %11\n\t"
-            "ds_read_b64_tr_b16 %7, %11 offset:256\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7)
-            : "v"(a0), "v"(a1), "v"(a2), "v"(a3));
-        f[0] = tr_pack(x0, x1); f[1] = tr_pack(x2, x3); f[2] = tr_pack(x4, x5); f[3] = tr_pack(x6, x7);
-    };
-    auto tr_frags2 = [&](bf16x8* f, uint32_t slot, const uint32_t* off) {
-        const uint32_t a0 = lds_base + slot + off[0], a1 = lds_base + slot + off[1];
-        v2i x0, x1, x2, x3;
-        asm volatile(
-            "ds_read_b64_tr_b16 %0, %4\n\t"
-            "ds_read_b64_tr_b16 %1, %4 offset:256\n\t"
-            "ds_read_b64_tr_b16 %2, %5\n\t"
-            "ds_read_b64_tr_b16 %3, %5 offset:256\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3)
-            : "v"(a0), "v"(a1));
-        f[0] = tr_pack(x0, x1); f[1] = tr_pack(x2, x3);
-    };
-    auto tr_frags6 = [&](bf16x8* f, bf16x8* h, uint32_t slot, const uint32_t* off, const uint32_t* off2) {
-        const uint32_t a0 = lds_base + slot + off[0], a1 = lds_base + slot + off[1];
-        const uint32_t a2 = lds_base + slot + off[2], a3 = lds_base + slot + off[3];
-        const uint32_t a4 = lds_base + slot + off2[0], a5 = lds_base + slot + off2[1];
-        v2i x0, x1, x2, x3, x4, x5, x6, x7, x8, x9, x10, x11;
-        asm volatile(
-            "ds_read_b64_tr_b16 %0, %12\n\t"
-            "ds_read_b64_tr_b16 %1, %12 offset:256\n\t"
-            "ds_read_b64_tr_b16 %2, %13\n\t"
-            "ds_read_b64_tr_b16 %3, %13 offset:256\n\t"
-            "ds_read_b64_tr_b16 %4, %14\n\t"
-            "ds_read_b64_tr_b16 %5, %14 offset:256\n\t"
-            "ds_read_b64_tr_b16 %6, %15\n\t"
-            "ds_read_b64_tr_b16 %7, %15 offset:256\n\t"
-            "ds_read_b64_tr_b16 %8, %16\n\t"
-            "ds_read_b64_tr_b16 %9, %16 offset:256\n\t"
-            "ds_read_b64_tr_b16 %10, %17\n\t"
-            "ds_read_b64_tr_b16 %11, %17 offset:256\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7), "=&v"(x8),
-              "=&v"(x9), "=&v"(x10), "=&v"(x11)
-            : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(a4), "v"(a5));
-        f[0] = tr_pack(x0, x1); f[1] = tr_pack(x2, x3); f[2] = tr_pack(x4, x5); f[3] = tr_pack(x6, x7);
-        h[0] = tr_pack(x8, x9); h[1] = tr_pack(x10, x11);
-    };
-    // the same with the two row numbers of a gathered operand's next copies riding on the statement's wait
-    auto tr_frags6_idx = [&](bf16x8* f, bf16x8* h, uint32_t slot, const uint32_t* off, const uint32_t* off2, uint32_t ia,
-                             int& i0, int& i1) {
-        const uint32_t a0 = lds_base + slot + off[0], a1 = lds_base + slot + off[1];
-        const uint32_t a2 = lds_base + slot + off[2], a3 = lds_base + slot + off[3];
-        const uint32_t a4 = lds_base + slot + off2[0], a5 = lds_base + slot + off2[1];
-        v2i x0, x1, x2, x3, x4, x5, x6, x7, x8, x9, x10, x11;
-        asm volatile(
-            "ds_read_b64_tr_b16 %0, %14\n\t"
-            "ds_read_b64_tr_b16 %1, %14 offset:256\n\t"
-            "ds_read_b64_tr_b16 %2, %15\n\t"
-            "ds_read_b64_tr_b16 %3, %15 offset:256\n\t"
-            "ds_read_b64_tr_b16 %4, %16\n\t"
-            "ds_read_b64_tr_b16 %5, %16 offset:256\n\t"
-            "ds_read_b64_tr_b16 %6, %17\n\t"
-            "ds_read_b64_tr_b16 %7, %17 offset:256\n\t"
-            "ds_read_b64_tr_b16 %8, %18\n\t"
-            "ds_read_b64_tr_b16 %9, %18 offset:256\n\t"
-            "ds_read_b64_tr_b16 %10, %19\n\t"
-            "ds_read_b64_tr_b16 %11, %19 offset:256\n\t"
-            "ds_read_b32 %12, %20\n\t"
-            "ds_read_b32 %13, %20 offset:64\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3), "=&v"(x4), "=&v"(x5), "=&v"(x6), "=&v"(x7), "=&v"(x8),
-              "=&v"(x9), "=&v"(x10), "=&v"(x11), "=&v"(i0), "=&v"(i1)
-            : "v"(a0), "v"(a1), "v"(a2), "v"(a3), "v"(a4), "v"(a5), "v"(ia));
-        f[0] = tr_pack(x0, x1); f[1] = tr_pack(x2, x3); f[2] = tr_pack(x4, x5); f[3] = tr_pack(x6, x7);
-        h[0] = tr_pack(x8, x9); h[1] = tr_pack(x10, x11);
-    };
-    static_assert(TB == 2, "tr_frags2 / tr_frags6 read the two weight fragments of a wave");
-
-    f32x16 acc[4][TB];
-    bf16x8 fa[2][4], fb[2][TB];
-    // set = k-substep (0: k 0..15 of the tile, 1: k 16..31); ck is the swizzled chunk of the row-major layout
-    auto load_frags = [&](int set, int g, int ck) {
-        const uint4* base = lds + (g & (NBUF - 1)) * STAGE + ck;
-        const uint32_t slot = static_cast<uint32_t>(g & (NBUF - 1)) * (STAGE * 16) + set * 1024;
-        // row-major operands first: their reads are in flight while the transposing statement waits
-        if constexpr (!TRA) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) fa[set][i] = __builtin_bit_cast(bf16x8, base[a_row[i]]);
-        }
-        if constexpr (!TRB) {
-#pragma unroll
-            for (int j = 0; j < TB; ++j) fb[set][j] = __builtin_bit_cast(bf16x8, base[b_row[j]]);
-        }
-        if constexpr (TRA && TRB) tr_frags6(fa[set], fb[set], slot, a_tr, b_tr);
-        else if constexpr (TRA) tr_frags4(fa[set], slot, a_tr);
-        else if constexpr (TRB) tr_frags2(fb[set], slot, b_tr);
-    };
-
-    int q = xcd * GS + slot_l;                           // first pass over the list
-    if (q >= total) return;                              // uniform: nothing for this workgroup
-    Tile cur, nxt;
-    setup(q, cur);
-    int g = 0;                                           // global step (ring position) of the next k-tile to multiply
-    if constexpr (KG != 0) {                             // row numbers of k-tiles 0 .. AHEAD + 1, before anything else
-        for (int t = 0; t < AHEAD + 2; ++t) issue_idx(cur.e, t, t);
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));
-        __builtin_amdgcn_s_barrier();
-    }
-    for (int t = 0; t < AHEAD; ++t) {                    // KT >= AHEAD is a launch condition (KG: KT >= 8)
-        uint32_t kr[NCP] = {};
-        if constexpr (KG != 0) idx_rows(t, kr[0], kr[1]);
-#pragma unroll
-        for (int j = 0; j < 2 * NCP; ++j)
-            issue_copy(cur, t, t, j, (KG == 1 && j < NCP) ? kr[j] : (KG == 2 && j >= NCP) ? kr[j - NCP] : 0u);
-        // the order of the steady state: ... tile, tile, indices, tile, indices, so that its wait counts hold from
-        // the first iteration on
-        if constexpr (KG != 0) if (t >= 1 && wave == 0) issue_idx(cur.e, t + AHEAD + 1, t + AHEAD + 1);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_imm((AHEAD - 1) * 2 * NCP, false));
-    __builtin_amdgcn_s_barrier();
-    load_frags(0, 0, ck0);
-
-    for (;;) {
-        const int qn = q + 8 * GS;                       // same XCD, next round
-        const bool has_next = qn < total;
-        if (has_next) setup(qn, nxt);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < TB; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-        const int KT = cur.KT;
-        // Fetching part: k-tile kt + AHEAD, which past KT is a k-tile of the next tile.  The source is
-        // chosen with selects outside the unrolled MFMA sequences, which carry no branches.
-        const int kt_fetch = has_next ? KT : KT - AHEAD;
-        int kt = 0;
-        for (; kt < kt_fetch; ++kt, ++g) {
-            const bool in_cur = kt + AHEAD < KT;
-            const int kf = in_cur ? kt + AHEAD : kt + AHEAD - KT;
-            const char* srcA = in_cur ? cur.Abase : nxt.Abase;
-            const char* srcB0 = in_cur ? cur.Bbase : nxt.Bbase;
-            const char* srcB1 = in_cur ? cur.Bbase1 : nxt.Bbase1;
-            const uint64_t baseA = a_ktile(srcA, kf);
-            const uint64_t baseB = b_ktile(srcB0, srcB1, in_cur ? KT : nxt.KT, kf);
-            uint32_t offs[2 * NCP];
-#pragma unroll
-            for (int j = 0; j < 2 * NCP; ++j) offs[j] = in_cur ? cur.off[j] : nxt.off[j];
-            if constexpr (TAIL) {
-                const bool sk = short_ktile(kf);
-#pragma unroll
-                for (int j = 0; j < 2 * NCP; ++j) offs[j] = sk && (j < NCP ? over_a : over_b[j % NCP]) ? kPastRange : offs[j];
-            }
-
-            auto copy = [&](int j) {
-                uint4* dst = lds + ((g + AHEAD) & (NBUF - 1)) * STAGE + (j / NCP) * (BM * CPR) + (wave * NCP + (j % NCP)) * 64;
-                const bool gathered = (KG == 1 && j < NCP) || (KG == 2 && j >= NCP);
-                const uint64_t b64 = gathered ? reinterpret_cast<uint64_t>(j < NCP ? srcA : srcB0) : j < NCP ? baseA : baseB;
-                const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
-                const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
-                if constexpr (TAIL) {
-                    buffer_copy_to_lds(lo, hi, offs[j], dst);
-                    return;
-                }
-                const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-                __builtin_amdgcn_global_load_lds((global_cptr)(base + offs[j]), (lds_ptr)dst, 16, 0, 0);
-            };
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (KG != 0) {
-                // the fragments of the second k-substep and, on the same wait, the rows of the gathered operand for
-                // k-tile step g + AHEAD
-                int i0, i1;
-                tr_frags6_idx(fa[1], fb[1], static_cast<uint32_t>(g & (NBUF - 1)) * (STAGE * 16) + 1024, a_tr, b_tr,
-                              idx_addr(g + AHEAD), i0, i1);
-                offs[(KG - 1) * NCP] += static_cast<uint32_t>(min(max(i0, 0), p.k_rows - 1)) * kg_row_bytes;
-                offs[(KG - 1) * NCP + 1] += static_cast<uint32_t>(min(max(i1, 0), p.k_rows - 1)) * kg_row_bytes;
-            } else {
-                load_frags(1, g, ck1);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < TB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
-                if (i & 1) copy(i >> 1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // step g+1 is in LDS (KG, wave 0: two index copies lie between its tile copies and now)
-            if (KG != 0 && wave == 0) __builtin_amdgcn_s_waitcnt(waitcnt_imm(3 * NCP + 2, true));
-            else __builtin_amdgcn_s_waitcnt(waitcnt_imm(3 * NCP, true));
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            load_frags(0, g + 1, ck0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < TB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[1][j], fa[1][i], acc[i][j], 0, 0, 0);
-                if (i & 1) copy(NCP + (i >> 1));
-                if constexpr (KG != 0) {
-                    if (i == 3 && wave == 0) {           // row numbers of the k-tile IDX_AHEAD steps on (one copy per
-                        const bool in7 = kt + IDX_AHEAD < KT;        // iteration, whether anything needs it or not)
-                        const int e7 = in7 ? cur.e : (has_next ? nxt.e : cur.e);
-                        const int k7 = in7 ? kt + IDX_AHEAD : (has_next ? kt + IDX_AHEAD - KT : 0);
-                        issue_idx(e7, k7, g + IDX_AHEAD);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        for (; kt < KT; ++kt, ++g) {                                 // tail of this workgroup's last tile: nothing to fetch
-            __builtin_amdgcn_sched_barrier(0);
-            load_frags(1, g, ck1);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < TB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            if (kt + 1 < KT) load_frags(0, g + 1, ck0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma unroll
-                for (int j = 0; j < TB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[1][j], fa[1][i], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // ---- epilogue of cur (the copies of the next tile are in flight into the three other slots)
-        if constexpr (KG == 2) {
-            // (contractions of many thousands of rows, six tiles per workgroup: stored directly, 5.87 ms for the gate and
-            // up gradients of 8 experts x 32 000 rows; through the patch 6.06 ms.  With the gathered A operand it is
-            // 3.02 against 2.99 ms.)
-            store_blocks<false, false, 4, TB>(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * 64, cur.count, r32, half);
-        } else {
-            const uint32_t slot = lds_base + static_cast<uint32_t>((g - 1) & (NBUF - 1)) * (STAGE * 16);
-            const uint32_t patch0 = slot + wave * (NCP * 1024), patch1 = patch0 + BM * CPR * 16;
-            const int nb = cur.n0 + wn * 64;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int mb = cur.m0 + wm * 128 + i * 32;
-                uint2 pk[2][4];
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        pk[j][v] = pack_bf16x4(acc[i][j][v * 4], acc[i][j][v * 4 + 1], acc[i][j][v * 4 + 2], acc[i][j][v * 4 + 3]);
-                uint16_t* out = reinterpret_cast<uint16_t*>(p.C) + (static_cast<size_t>(cur.e) * p.capacity + mb) * p.N + nb;
-                if (p.split_m) {                         // a block of 32 rows lies on one side of the split
-                    const bool second = mb >= p.split_m;
-                    out = reinterpret_cast<uint16_t*>(second ? p.C2 : p.C) +
-                          (static_cast<size_t>(cur.e) * p.split_m + (second ? mb - p.split_m : mb)) * p.N + nb;
-                }
-                if (mb < cur.count && nb < p.N) store_rows_staged32(pk, out, p.N, cur.count - mb, p.N - nb, patch0, patch1, lane);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if (!has_next) break;
-        cur = nxt;
-        q = qn;
-    }
-}
+constexpr int kMaxSuper = 4096;          // super-tiles the LDS prefix of the transposing kernel can hold (16 KiB)
+constexpr int kMaxSuperWide = 2048;      // the same for the row-major kernel, whose epilogue patches leave less room
 
 __device__ __forceinline__ int live_row_tiles(const GemmParams& p, int e, int mg, int BM) {
     const int mtv = (group_rows(p, e) + BM - 1) / BM;
@@ -1318,11 +779,10 @@ __device__ __forceinline__ void live_tile_prefix(const GemmParams& p, int BM, in
 }
 
 // ---------------------------------------------------------------------------------------
-// Persistent kernel with 64-wide k-tiles for row-major operands (the one the forward pass and every row-major
-// product of the backward pass run): the tile list and the run-on across tile boundaries of the ring form above,
-// but every copy instruction fetches whole 128-byte lines (8 rows x 128 bytes instead of 16 rows x 64 bytes).
-// Measured on a copy-only loop over L2-resident data the line-sized pieces move 1.6 times the bytes per cycle of
-// the half-line ones, and in the ring kernel the copies, not the matrix pipe, set the cycle count.
+// Persistent kernel for row-major operands (the one the forward pass and every row-major product of the backward pass
+// run).  k-tiles of 64, and every copy instruction fetches whole 128-byte lines (8 rows x 128 bytes instead of the 16
+// rows x 64 bytes of a 32-wide k-tile): on a copy-only loop over L2-resident data the line-sized pieces move 1.6 times the
+// bytes per cycle of the half-line ones, and with 32-wide k-tiles the copies, not the matrix pipe, set the cycle count.
 //
 // Matrix instruction: v_mfma_f32_16x16x32_bf16.  The part is power-limited under this kernel, and a register-
 // resident loop on random operands sustains 2.0 PFLOP/s with this shape against 1.77 with 32x32x16 (a fifth fewer
@@ -1604,6 +1064,421 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
 }
+
+// ---------------------------------------------------------------------------------------
+// Persistent kernel for operands whose contraction index is the slow one (backward pass): B is [K][N], and A is row-major
+// [M][K] or, with TRA, [K][M] (row strides lda / ldb, group stride K * ld).  With B1 the contraction is split in the
+// middle: first half from B0, second half from B1, each [K/2][N].  Plain products only: row-major operands with an
+// epilogue take the kernel above, whose tile list, k-tiles of 64, two LDS buffers and substeps this one shares.
+//
+// Staging.  A k-tile of such an operand is 64 k x 256 rows; a copy instruction takes 8 k x 128 bytes (whole lines), and LDS
+// holds it as [4 groups of 64 rows][64 k][128 bytes].  Wave w copies the k rows 8 w .. 8 w + 7 of all four groups.
+// Fragments come out through the transposing read ds_read_b64_tr_b16: inside a group of 16 lanes, lane i supplies the
+// address of 4 consecutive elements and receives element i % 4 of lanes i/4, i/4 + 4, i/4 + 8, i/4 + 12.  With lane
+// (q = i % 4, j = i / 4) pointing at (k0 + j, r0 + 4 q) lane i receives rows r0 + i at k0 .. k0 + 3: two reads give the 8
+// consecutive k of one row that the MFMA operand layout wants.  Half a wave reads 32 bytes of each of the k rows 8 kq + j (kq =
+// 0, 1 or 2, 3; j = 0..3), which lie on two half sets of banks: the 32-byte piece o of a k row is stored at o ^ f(k), f(k) =
+// bit 1 of k, bit 3 of k, so that the eight pieces cover all 64 banks (applied on the source side of the copy).
+//
+// KG (1: A, 2: B): the contraction rows of that operand are fetched through p.k_index (a gather along the slow index).  The
+// four copies of a lane share one k row, so a lane needs one row number per k-tile, loaded three k-tiles ahead.  Row
+// numbers are clamped into [0, k_rows).
+//
+// TAIL (row-major A): the contraction, or each half of a split one, need not be whole k-tiles.  The last k-tile of it is
+// short: pieces of a token row and whole weight rows past its end are zero-filled (buffer_copy_to_lds).
+//
+// Bound as the kernel above is.  Measured against the form it replaces (32-wide k-tiles in a ring of four, v_mfma_f32_32x32x16,
+// the wait of every fragment read in the open): weight gradients of 8 experts x 32 000 gathered rows, 4096 x 1408: 2864 ->
+// 2452 us and, both gate and up, 5561 -> 4757 us (1.06 -> 1.24 PFLOP/s); 16 experts of 166-1024 rows, 2048 x 5632: 281 -> 278 us
+// each, input gradient 603 -> 586 us.
+// ---------------------------------------------------------------------------------------
+template <bool TRA, int KG = 0, bool TAIL = false>
+__global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p) {
+    static_assert(KG == 0 || TRA, "gathered contraction rows: both operands transposed");
+    static_assert(!TAIL || (!TRA && KG == 0), "short k-tiles: row-major A");
+    constexpr int NW = 8, BM = 256, BN = 256, CPR = 8, SWZ = 1;
+    constexpr int HALF = 256 * CPR;                      // uint4 per operand and LDS buffer (32 KiB)
+    constexpr int STAGE = 2 * HALF;
+    constexpr int NCP = 4;                               // copies per wave, operand and k-tile
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    uint4* lds = reinterpret_cast<uint4*>(lds_raw);
+    __shared__ int pre[kMaxSuper + 1];
+    __shared__ int wave_tot[NW];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    const int lda = p.lda ? p.lda : p.K, ldb = p.ldb ? p.ldb : p.K;
+    const bool splitB = p.B1 != nullptr;
+    const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 63) / 64;         // of the whole product, or of each half of a split one
+    const int k_rem = (Kh & 63) ? (Kh & 63) : 64;        // valid k of the last k-tile
+
+    const int MG = (p.MT + p.SM - 1) / p.SM, NG = (p.NT + p.SN - 1) / p.SN;
+    const int S = p.E * MG * NG;
+    live_tile_prefix<NW * 64>(p, BM, MG, NG, pre, wave_tot);
+    const int total = pre[S];
+    const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
+    const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
+
+    struct Tile {
+        int e, m0, n0, count, KT;
+        uint64_t Abase, Bbase, Bbase1;                   // wave-uniform; Bbase1: second half of a split B
+        uint32_t offA[TRA ? 1 : NCP];                    // row-major A: byte offsets of this lane's row groups
+    };
+    // row-major A: this lane's copies are rows rr0 + 8 i, chunk c0 ^ 4 (i & 1) of the swizzle
+    const int rr0 = wave * 32 + (lane >> 3);
+    const int c0 = (lane & 7) ^ ((rr0 >> SWZ) & 7);
+    const bool over_a[2] = {TAIL && 8 * c0 >= k_rem, TAIL && 8 * (c0 ^ 4) >= k_rem};
+    // transposed operands: k row of this lane's copies, and its first row inside a group of 64 rows
+    const int k_row = wave * 8 + (lane >> 3);
+    const int lane_r = 16 * (((lane & 7) >> 1) ^ (((k_row >> 1) & 1) | ((k_row >> 2) & 2))) + 8 * (lane & 1);
+    const bool over_b = TAIL && k_row >= k_rem;
+    const uint32_t fixedA = KG == 1 ? 0u : static_cast<uint32_t>(k_row) * lda * 2u;      // (a gathered row comes from the ring)
+    const uint32_t fixedB = KG == 2 ? 0u : static_cast<uint32_t>(k_row) * ldb * 2u;
+    const int limitA = p.capacity - 8, limitB = p.N - 8; // copies stay inside the k row; what they repeat is never stored
+
+    auto decode = [&](int q, Tile& t) {                  // the tile with list index q
+        int lo = 0, hi = S;                              // largest s with pre[s] <= q
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= q) lo = mid; else hi = mid;
+        }
+        const int s = __builtin_amdgcn_readfirstlane(lo);
+        const int u = __builtin_amdgcn_readfirstlane(q - pre[s]);
+        const int e = s / (MG * NG), r = s - e * (MG * NG);
+        const int mg = r % MG, ng = r / MG;
+        const int vm = live_row_tiles(p, e, mg, BM);
+        t.e = e; t.m0 = (mg * p.SM + u % vm) * BM; t.n0 = (ng * p.SN + u / vm) * BN;
+        t.count = group_rows(p, e);
+        t.KT = TRA ? group_k(p, e) / 64 : (splitB ? 2 * KTh : KTh);
+        t.Abase = reinterpret_cast<uint64_t>(p.A);
+        if (KG != 1) t.Abase += TRA ? static_cast<uint64_t>(e) * p.K * lda * 2
+                                    : (p.row_index ? 0 : static_cast<uint64_t>(e) * p.capacity * lda * 2);
+        const uint64_t group = KG == 2 ? 0 : static_cast<uint64_t>(e) * Kh * ldb * 2;
+        t.Bbase = reinterpret_cast<uint64_t>(p.B0) + group;
+        t.Bbase1 = splitB ? reinterpret_cast<uint64_t>(p.B1) + group : t.Bbase;
+        if constexpr (!TRA) {
+#pragma unroll
+            for (int i = 0; i < NCP; ++i) {
+                int row = min(t.m0 + rr0 + 8 * i, t.count - 1);          // rows past the count replay a valid row; never stored
+                if (p.row_index) row = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + row], 0), p.a_rows - 1);
+                t.offA[i] = (static_cast<uint32_t>(row) * lda + (c0 ^ (4 * (i & 1))) * 8) * 2u;
+            }
+        }
+    };
+    auto a_ktile = [&](uint64_t a, int k) -> uint64_t {
+        if constexpr (TRA) return KG == 1 ? a : a + static_cast<uint64_t>(k) * (static_cast<uint64_t>(lda) * 128);
+        const bool second = splitB && k >= KTh;
+        return a + (second ? static_cast<uint64_t>(Kh) * 2 + static_cast<uint64_t>(k - KTh) * 128 : static_cast<uint64_t>(k) * 128);
+    };
+    auto b_ktile = [&](uint64_t b0, uint64_t b1, int k) -> uint64_t {
+        if constexpr (KG == 2) return b0;
+        const bool second = splitB && k >= KTh;
+        return (second ? b1 : b0) + static_cast<uint64_t>(second ? k - KTh : k) * (static_cast<uint64_t>(ldb) * 128);
+    };
+    auto is_short = [&](int k) { return TAIL && (k == KTh - 1 || k == 2 * KTh - 1); };
+    auto copy_to = [&](uint64_t b64, uint32_t off, uint4* dst) {
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
+        if constexpr (TAIL) {
+            buffer_copy_to_lds(lo, hi, off, dst);
+        } else {
+            const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
+            __builtin_amdgcn_global_load_lds((global_cptr)(base + off), (lds_ptr)dst, 16, 0, 0);
+        }
+    };
+    // copy i of the A / B operand of one k-tile into buffer buf (off_row: row-major A's offset, or the k row's)
+    auto copy_a = [&](uint64_t base, uint32_t off_row, int m0, int buf, int i) {
+        if constexpr (TRA)
+            copy_to(base, off_row + 2u * min(m0 + 64 * i + lane_r, limitA), lds + buf * STAGE + i * (HALF / 4) + wave * 64);
+        else
+            copy_to(base, off_row, lds + buf * STAGE + (wave * NCP + i) * 64);
+    };
+    auto copy_b = [&](uint64_t base, uint32_t off_row, int n0, bool last, int buf, int i) {
+        uint32_t off = off_row + 2u * min(n0 + 64 * i + lane_r, limitB);
+        if (TAIL) off = last && over_b ? kPastRange : off;
+        copy_to(base, off, lds + buf * STAGE + HALF + i * (HALF / 4) + wave * 64);
+    };
+    // KG: this lane's row number in k-tile kl of group e (positions past the index row are clamped onto its last entry),
+    // and the byte offset of that row
+    auto load_index = [&](int e, int kl) -> int {
+        return p.k_index[static_cast<size_t>(e) * p.k_index_stride + min(kl * 64 + k_row, p.k_index_stride - 1)];
+    };
+    auto row_offset = [&](int index) -> uint32_t {
+        return static_cast<uint32_t>(min(max(index, 0), p.k_rows - 1)) * static_cast<uint32_t>(KG == 1 ? lda : ldb) * 2u;
+    };
+
+    const int l16 = lane & 15, kq = lane >> 4;
+    // row-major A: as in the kernel above
+    const int a_row = (wm * 128 + l16) * CPR;
+    const int ck[2] = {kq ^ ((l16 >> SWZ) & 7), (4 + kq) ^ ((l16 >> SWZ) & 7)};
+    // transposing reads: LDS byte address (buffer 0) of this lane's 4 elements of the 16-row blocks 0..3 of a group of 64
+    // rows, first k-step; + 512: the k four further on, + 4096: the second k-step, + 8192: the next group
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    const uint32_t lds_base = lds_address(lds_raw);
+    uint32_t a_tr[4], b_tr[4];
+    {
+        const int q = l16 & 3, j = l16 >> 2, f = ((j >> 1) & 1) | ((kq & 1) << 1);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+            const uint32_t at = lds_base + (8 * kq + j) * 128 + ((o ^ f) * 32) + q * 8;
+            a_tr[o] = at + wm * 2 * 8192;
+            b_tr[o] = at + HALF * 16 + wn * 8192;
+        }
+    }
+    f32x4 acc[8][4];
+    bf16x8 fah[2][4], fbk[2][4];
+    auto tr_pack = [](v2i lo, v2i hi) -> bf16x8 {        // k .. k + 3 and k + 4 .. k + 7 of one row
+        const v4i r = {lo.x, lo.y, hi.x, hi.y};
+        return __builtin_bit_cast(bf16x8, r);
+    };
+    // The transposing reads are assembly: through the compiler's builtin every such read waits for ALL outstanding copies
+    // (vmcnt(0)), because it is taken to alias the asynchronous LDS writes.  A statement holds eight MFMAs (two token blocks,
+    // four weight blocks) with the reads of up to four fragments behind the first of them and its own wait at the end: the
+    // reads land under the remaining MFMAs, and the outputs are ordinary, fully written registers when it ends.  (The reads
+    // in statements of their own, with the wait right behind them: 5 % slower over 32 000 rows.)  What the compiler
+    // cannot see inside: two wait states between an ordinary write of an operand and its use (the s_nop in front); it must
+    // not touch an accumulator right behind a statement (settle() before the epilogue).
+#define ETR_MF(C, B, A) "v_mfma_f32_16x16x32_bf16 %[c" #C "], %[b" #B "], %[a" #A "], %[c" #C "]\n\t"
+#define ETR_TR(N) "ds_read_b64_tr_b16 %[x" #N "], %[p" #N "] offset:%c[o" #N "]\n\tds_read_b64_tr_b16 %[y" #N "], %[p" #N "] offset:%c[q" #N "]\n\t"
+#define ETR_ACC(i) [c0] "+v"(acc[i][0]), [c1] "+v"(acc[i][1]), [c2] "+v"(acc[i][2]), [c3] "+v"(acc[i][3]), \
+                   [c4] "+v"(acc[i + 1][0]), [c5] "+v"(acc[i + 1][1]), [c6] "+v"(acc[i + 1][2]), [c7] "+v"(acc[i + 1][3])
+#define ETR_FRAGS [a0] "v"(fa[0]), [a1] "v"(fa[1]), [b0] "v"(fb[0]), [b1] "v"(fb[1]), [b2] "v"(fb[2]), [b3] "v"(fb[3])
+#define ETR_OUT(N) [x##N] "=&v"(x[N]), [y##N] "=&v"(y[N])
+#define ETR_AT(N, OFF) [p##N] "v"(at##N + slot), [o##N] "n"(OFF), [q##N] "n"(OFF + 512)
+    // MFMAs of token blocks I, I + 1 (accumulators) = fa[0], fa[1] with fb[0..3]; reads fragments 0 .. R - 1 from at0.. at the
+    // constant offsets O0..
+    auto mfma8 = [&](auto reads, auto block, const bf16x8* fa, const bf16x8* fb, uint32_t slot, bf16x8* f0, uint32_t at0, auto o0,
+                     bf16x8* f1, uint32_t at1, auto o1, bf16x8* f2, uint32_t at2, auto o2, bf16x8* f3, uint32_t at3, auto o3) {
+        constexpr int R = decltype(reads)::value, I = decltype(block)::value;
+        constexpr int O0 = decltype(o0)::value, O1 = decltype(o1)::value, O2 = decltype(o2)::value, O3 = decltype(o3)::value;
+        v2i x[4], y[4];
+        if constexpr (R == 1)
+            asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_MF(2, 2, 0) ETR_MF(3, 3, 0)
+                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         : ETR_ACC(I), ETR_OUT(0) : ETR_FRAGS, ETR_AT(0, O0));
+        if constexpr (R == 2)
+            asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_MF(3, 3, 0)
+                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1) : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1));
+        if constexpr (R == 3)
+            asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_TR(2) ETR_MF(3, 3, 0)
+                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1), ETR_OUT(2) : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1), ETR_AT(2, O2));
+        if constexpr (R == 4)
+            asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_TR(2) ETR_MF(3, 3, 0)
+                         ETR_TR(3) ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1), ETR_OUT(2), ETR_OUT(3)
+                         : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1), ETR_AT(2, O2), ETR_AT(3, O3));
+        if constexpr (R == 0) {
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                acc[I + (m >> 2)][m & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[m & 3], fa[m >> 2], acc[I + (m >> 2)][m & 3], 0, 0, 0);
+        }
+        if constexpr (R > 0) *f0 = tr_pack(x[0], y[0]);
+        if constexpr (R > 1) *f1 = tr_pack(x[1], y[1]);
+        if constexpr (R > 2) *f2 = tr_pack(x[2], y[2]);
+        if constexpr (R > 3) *f3 = tr_pack(x[3], y[3]);
+    };
+#define ETR_OFF(x) std::integral_constant<int, (x)>{}
+    auto read_a_rows = [&](int buf, int ks, int h, int idx) {           // row-major A, one block
+        fah[h][idx] = __builtin_bit_cast(bf16x8, lds[buf * STAGE + a_row + (4 * h + idx) * 16 * CPR + ck[ks]]);
+    };
+    // substep u = 2 ks + h: 16 MFMAs, and the reads of what substep u + 1 needs (from buffer `buf`; u = 3: of the next k-tile);
+    // mem(0), mem(1), mem(2): memory work in front of the first eight MFMAs, between the two eights, behind them
+    auto substep = [&](auto u, int buf, auto&& mem) {
+        constexpr int U = decltype(u)::value, ks = U >> 1, h = U & 1;
+        const uint32_t slot = static_cast<uint32_t>(buf) * (STAGE * 16);
+        bf16x8* const na = fah[h ^ 1];                   // fragments of substep u + 1
+        bf16x8* const nb = fbk[U == 3 ? 0 : 1];
+        constexpr int OA = U == 0 ? 8192 : (U == 1 ? 4096 : (U == 2 ? 8192 + 4096 : 0)), OB = U == 3 ? 0 : 4096;
+        constexpr int J = U == 1 ? 2 : 0;                // weight blocks read in substeps 0 and 1: two each
+        const auto oa = ETR_OFF(OA);
+        const auto ob = ETR_OFF(OB);
+        if constexpr (!TRA) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) read_a_rows(buf, U == 3 ? 0 : (U + 1) >> 1, h ^ 1, i);
+        }
+        mem(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TRA && U < 2)
+            mfma8(ETR_OFF(3), ETR_OFF(4 * h), fah[h], fbk[ks], slot, na, a_tr[0], oa, na + 1, a_tr[1], oa, na + 2, a_tr[2], oa, na, 0u, oa);
+        else if constexpr (TRA && U == 2)
+            mfma8(ETR_OFF(2), ETR_OFF(4 * h), fah[h], fbk[ks], slot, na, a_tr[0], oa, na + 1, a_tr[1], oa, na, 0u, oa, na, 0u, oa);
+        else if constexpr (TRA)
+            mfma8(ETR_OFF(4), ETR_OFF(4 * h), fah[h], fbk[ks], slot, na, a_tr[0], oa, na + 1, a_tr[1], oa, na + 2, a_tr[2], oa, na + 3, a_tr[3], oa);
+        else if constexpr (U < 2)
+            mfma8(ETR_OFF(1), ETR_OFF(4 * h), fah[h], fbk[ks], slot, nb + J, b_tr[J], ob, na, 0u, oa, na, 0u, oa, na, 0u, oa);
+        else if constexpr (U == 2)
+            mfma8(ETR_OFF(0), ETR_OFF(4 * h), fah[h], fbk[ks], slot, na, 0u, oa, na, 0u, oa, na, 0u, oa, na, 0u, oa);
+        else
+            mfma8(ETR_OFF(2), ETR_OFF(4 * h), fah[h], fbk[ks], slot, nb, b_tr[0], ob, nb + 1, b_tr[1], ob, na, 0u, oa, na, 0u, oa);
+        __builtin_amdgcn_sched_barrier(0);
+        mem(1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (TRA && U < 2)
+            mfma8(ETR_OFF(3), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, na + 3, a_tr[3], oa, nb + J, b_tr[J], ob, nb + J + 1, b_tr[J + 1], ob, na, 0u, oa);
+        else if constexpr (TRA && U == 2)
+            mfma8(ETR_OFF(2), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, na + 2, a_tr[2], oa, na + 3, a_tr[3], oa, na, 0u, oa, na, 0u, oa);
+        else if constexpr (TRA)
+            mfma8(ETR_OFF(4), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, nb, b_tr[0], ob, nb + 1, b_tr[1], ob, nb + 2, b_tr[2], ob, nb + 3, b_tr[3], ob);
+        else if constexpr (U < 2)
+            mfma8(ETR_OFF(1), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, nb + J + 1, b_tr[J + 1], ob, na, 0u, oa, na, 0u, oa, na, 0u, oa);
+        else if constexpr (U == 2)
+            mfma8(ETR_OFF(0), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, na, 0u, oa, na, 0u, oa, na, 0u, oa, na, 0u, oa);
+        else
+            mfma8(ETR_OFF(2), ETR_OFF(4 * h + 2), fah[h] + 2, fbk[ks], slot, nb + 2, b_tr[2], ob, nb + 3, b_tr[3], ob, na, 0u, oa, na, 0u, oa);
+        __builtin_amdgcn_sched_barrier(0);
+        mem(2);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the first fragments of a workgroup (buffer 0), read and waited for on their own
+    auto read_first = [&]() {
+        auto tr = [&](uint32_t at) {
+            v2i x, y;
+            asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:512\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(x), "=&v"(y) : "v"(at));
+            return tr_pack(x, y);
+        };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (TRA) fah[0][i] = tr(a_tr[i]);
+            else read_a_rows(0, 0, 0, i);
+            fbk[0][i] = tr(b_tr[i]);
+        }
+    };
+    // nothing the compiler places behind this reads an accumulator sooner than its MFMA has written it
+    auto settle = [&]() {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2)
+            asm volatile("s_nop 15\n\ts_nop 3" : ETR_ACC(i));
+    };
+
+    int q = xcd * GS + slot_l;                           // first pass over the list
+    if (q >= total) return;                              // uniform: nothing for this workgroup
+    Tile cur, nxt;
+    decode(q, cur);
+    int g = 0;                                           // global step: buffer g & 1
+    int index = 0;                                       // KG: this lane's row number in k-tile g + 2
+    if constexpr (KG != 0) index = load_index(cur.e, 2); // (KT >= 4)
+    uint32_t row_a = fixedA, row_b = fixedB;             // byte offset of this lane's k row in the k-tile to copy next
+    for (int t = 0; t < 2; ++t) {                        // KT >= 2 is a launch condition
+        if constexpr (KG == 1) row_a = row_offset(load_index(cur.e, t));
+        if constexpr (KG == 2) row_b = row_offset(load_index(cur.e, t));
+        const uint64_t baseA = a_ktile(cur.Abase, t), baseB = b_ktile(cur.Bbase, cur.Bbase1, t);
+#pragma unroll
+        for (int i = 0; i < NCP; ++i) {
+            uint32_t off = row_a;
+            if constexpr (!TRA) off = is_short(t) && over_a[i & 1] ? kPastRange : cur.offA[i];
+            copy_a(baseA, off, cur.m0, t, i);
+        }
+#pragma unroll
+        for (int i = 0; i < NCP; ++i) copy_b(baseB, row_b, cur.n0, is_short(t), t, i);
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * NCP, false));             // the first k-tile (copies retire in order)
+    __builtin_amdgcn_s_barrier();
+    read_first();
+    // B rows still owed to the other buffer (none yet: the second k-tile's own once more)
+    uint64_t late_base = b_ktile(cur.Bbase, cur.Bbase1, 1);
+    int late_n0 = cur.n0;
+    bool late_last = is_short(1);
+    for (;;) {
+        const int qn = q + 8 * GS;                       // same XCD, next round
+        const bool has_next = qn < total;
+        if (has_next) decode(qn, nxt);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+        const int KT = cur.KT;
+        for (int kt = 0; kt < KT; ++kt, ++g) {
+            // k-tile g + 2: of this tile, else of the next one, else (nothing left) this tile's last one again
+            const bool in_cur = kt + 2 < KT;
+            const bool from_next = !in_cur && has_next;
+            const int kf = in_cur ? kt + 2 : (from_next ? kt + 2 - KT : KT - 1);
+            const uint64_t baseA = a_ktile(from_next ? nxt.Abase : cur.Abase, kf);
+            const uint64_t baseB = b_ktile(from_next ? nxt.Bbase : cur.Bbase, from_next ? nxt.Bbase1 : cur.Bbase1, kf);
+            const int m0 = from_next ? nxt.m0 : cur.m0, n0 = from_next ? nxt.n0 : cur.n0;
+            const bool last = is_short(kf);
+            uint32_t offs[NCP] = {};
+            if constexpr (!TRA) {
+#pragma unroll
+                for (int i = 0; i < NCP; ++i) {
+                    offs[i] = from_next ? nxt.offA[i] : cur.offA[i];
+                    if (TAIL) offs[i] = last && over_a[i & 1] ? kPastRange : offs[i];
+                }
+            }
+            const int buf = g & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            substep(ETR_OFF(0), buf, [&](int m) {        // and the B rows of k-tile g + 1 into the other buffer
+                if (m == 2) return;
+                copy_b(late_base, row_b, late_n0, late_last, buf ^ 1, 2 * m);
+                copy_b(late_base, row_b, late_n0, late_last, buf ^ 1, 2 * m + 1);
+            });
+            if constexpr (KG == 1) row_a = row_offset(index);
+            if constexpr (KG == 2) row_b = row_offset(index);
+            substep(ETR_OFF(1), buf, [&](int m) {        // and the row number in k-tile g + 3, wanted one step from now
+                if constexpr (KG != 0) {
+                    const bool stay = kt + 3 < KT || !has_next;
+                    if (m == 0) index = load_index(stay ? cur.e : nxt.e, stay ? kt + 3 : kt + 3 - KT);
+                }
+            });
+            substep(ETR_OFF(2), buf, [&](int) {});
+            // k-tile g + 1 has landed and this wave's reads of buffer buf are done; past the barrier that holds for all
+            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            substep(ETR_OFF(3), buf ^ 1, [&](int m) {    // the next k-tile's first fragments, and the A rows of k-tile
+                if (m == 2) return;                      // g + 2 into the buffer just released
+                copy_a(baseA, TRA ? row_a : offs[2 * m], m0, buf, 2 * m);
+                copy_a(baseA, TRA ? row_a : offs[2 * m + 1], m0, buf, 2 * m + 1);
+            });
+            late_base = baseB;
+            late_n0 = n0;
+            late_last = last;
+        }
+        settle();
+        // ---- epilogue of cur (the copies of the next tile are in flight).  The patch is the wave's own copy target in the
+        // B half of the buffer just multiplied: behind the last barrier nobody reads it any more, and the next copies into
+        // it are the wave's own, in its next substep 0.
+        {
+            const uint32_t patch = lds_base + static_cast<uint32_t>((g - 1) & 1) * (STAGE * 16) + HALF * 16 + wave * 1024;
+            const int nb = cur.n0 + wn * 64;
+            auto pack4 = [](const f32x4& v) { return pack_bf16x4(v[0], v[1], v[2], v[3]); };
+#pragma unroll
+            for (int ib = 0; ib < 4; ++ib) {
+                const int mb = cur.m0 + wm * 128 + ib * 32;
+                uint2 pk[2][4];
+#pragma unroll
+                for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                    for (int bj = 0; bj < 4; ++bj) pk[bi][bj] = pack4(acc[2 * ib + bi][bj]);
+                uint16_t* out = reinterpret_cast<uint16_t*>(p.C) + (static_cast<size_t>(cur.e) * p.capacity + mb) * p.N + nb;
+                if (p.split_m) {                         // a block of 32 rows lies on one side of the split
+                    const bool second = mb >= p.split_m;
+                    out = reinterpret_cast<uint16_t*>(second ? p.C2 : p.C) +
+                          (static_cast<size_t>(cur.e) * p.split_m + (second ? mb - p.split_m : mb)) * p.N + nb;
+                }
+                if (mb < cur.count && nb < p.N) store_rows_staged_lines(pk, out, p.N, cur.count - mb, p.N - nb, patch, lane);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (!has_next) break;
+        cur = nxt;
+        q = qn;
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
+}
+#undef ETR_OFF
+#undef ETR_AT
+#undef ETR_OUT
+#undef ETR_FRAGS
+#undef ETR_ACC
+#undef ETR_TR
+#undef ETR_MF
 
 // ---------------------------------------------------------------------------------------
 // Grouped bf16 GEMM for few rows per group (decode steps, short prompts): the weights are read once and that is all the
@@ -1940,13 +1815,13 @@ hipError_t launch_bf16_ring(GemmParams p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Persistent ring kernel: needs every group's contraction length >= 96 (three k-tiles to prefetch)
-// and the super-tile prefix to fit in LDS.
-template <bool TRA, bool TRB, int KG = 0, bool TAIL = false>
-hipError_t launch_bf16_persist(GemmParams p, hipStream_t st, int n_cu) {
-    constexpr size_t lds = 4ull * 512 * 32 * 2 + (KG != 0 ? 16 * 32 * 4 : 0);        // (+ the ring of row numbers)
+// Transposing kernel: needs every group's contraction length >= 128 (two k-tiles to prefetch; 256 where it fetches rows
+// through an index) and the super-tile prefix to fit in LDS.
+template <bool TRA, int KG = 0, bool TAIL = false>
+hipError_t launch_bf16_transposing(GemmParams p, hipStream_t st, int n_cu) {
+    constexpr size_t lds = 2ull * 512 * 64 * 2;                             // two buffers of 256 + 256 rows x 64 bf16
     plan_tiles(p, 256, 256);
-    auto kern = gemm_bf16_persist_kernel<TRA, TRB, KG, TAIL>;
+    auto kern = gemm_bf16_transposing_kernel<TRA, KG, TAIL>;
     hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
@@ -2122,10 +1997,11 @@ static GemmParams params_of(const GroupedGemm& q) {
 
 // Operands stored with the contraction index slow run only on the persistent bf16 kernel.
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
-    if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !(q.ta || q.tb)) return false;
+    if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !q.tb) return false;
     // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
     if (q.N % 8 != 0 || q.N < 8) return false;                     // 16-byte stores, and chunks along the rows of a [K][rows] operand
-    const bool tail_form = q.tb && !q.ta && !q.k_counts;
+    if (!q.ta && q.k_counts) return false;
+    const bool tail_form = !q.ta;
     const int half_k = q.B1 ? q.K / 2 : q.K;
     if (q.K < 128 || half_k % (tail_form ? 8 : 64) != 0) return false;
     if (q.ta && (q.M % 8 != 0 || q.M < 8)) return false;
@@ -2134,9 +2010,9 @@ bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (q.ta && (q.row_index || q.m_counts)) return false;
     if (q.B1 && !(tail_form && q.K % 2 == 0)) return false;                      // split B: two halves of the contraction
     // 32-bit per-lane offsets inside one k-tile / one operand
-    const size_t a_span = q.ta ? 32ull * lda * 2 : (q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M)) * lda * 2;
-    const size_t b_span = q.tb ? 32ull * ldb * 2 : static_cast<size_t>(q.N) * ldb * 2;
-    const size_t limit = half_k % 32 == 0 ? (1ull << 32) : kBufferRange;          // zero-filling copies: see buffer_copy_to_lds
+    const size_t a_span = q.ta ? 64ull * lda * 2 : (q.row_index ? static_cast<size_t>(q.a_rows) : static_cast<size_t>(q.M)) * lda * 2;
+    const size_t b_span = 64ull * ldb * 2;
+    const size_t limit = half_k % 64 == 0 ? (1ull << 32) : kBufferRange;          // zero-filling copies: see buffer_copy_to_lds
     if (a_span >= limit || b_span >= limit) return false;
     if (q.split_m && (!q.ta || q.split_m % 32 != 0 || q.M != 2 * q.split_m || !q.C2 || q.m_counts)) return false;
     if (q.k_gather) {
@@ -2154,15 +2030,12 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     if (q.ta || q.tb) {
         if (!grouped_gemm_transposed_ok(q)) return hipErrorInvalidValue;
         const int n_cu = cu_count();
-        if (q.k_gather == 1) return launch_bf16_persist<true, true, 1>(g, st, n_cu);
-        if (q.k_gather == 2) return launch_bf16_persist<true, true, 2>(g, st, n_cu);
-        if (q.ta && q.tb) return launch_bf16_persist<true, true>(g, st, n_cu);
-        if (q.tb) {
-            // a contraction (or half of a split one) that is not whole 32-wide k-tiles: the zero-filling instantiation
-            return (q.B1 ? q.K / 2 : q.K) % 32 == 0 ? launch_bf16_persist<false, true>(g, st, n_cu)
-                                                    : launch_bf16_persist<false, true, 0, true>(g, st, n_cu);
-        }
-        return launch_bf16_persist<true, false>(g, st, n_cu);
+        if (q.k_gather == 1) return launch_bf16_transposing<true, 1>(g, st, n_cu);
+        if (q.k_gather == 2) return launch_bf16_transposing<true, 2>(g, st, n_cu);
+        if (q.ta) return launch_bf16_transposing<true>(g, st, n_cu);
+        // a contraction (or half of a split one) that is not whole k-tiles: the zero-filling instantiation
+        return (q.B1 ? q.K / 2 : q.K) % 64 == 0 ? launch_bf16_transposing<false>(g, st, n_cu)
+                                                : launch_bf16_transposing<false, 0, true>(g, st, n_cu);
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;
