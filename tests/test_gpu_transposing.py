@@ -32,7 +32,7 @@ def test_transposed_products(oracle, T, E, d, Hh, C, k, recipe):
     from test_gpu_backward import Backward, _err
     B.load_library()
     shape = I.EtrShape("transposed", 17, T=T, d=d, E=E, D=8, k=k, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR,
-                       recipe=recipe)
+                       recipe=recipe, n_centroids=E)
     print(f"transposed products T={T} E={E} d={d} H={Hh} C={C}", flush=True)
     bw = Backward(H, shape, shape.mode)                  # (its workspace is filled with NaN patterns)
     hb = bw.host()
