@@ -736,46 +736,103 @@ __global__ __launch_bounds__(128 * WN) void gemm_bf16_ring_kernel(GemmParams p) 
 constexpr int kMaxSuper = 4096;          // super-tiles the LDS prefix of the transposing kernel can hold (16 KiB)
 constexpr int kMaxSuperWide = 2048;      // the same for the row-major kernel, whose epilogue patches leave less room
 
-__device__ __forceinline__ int live_row_tiles(const GemmParams& p, int e, int mg, int BM) {
-    const int mtv = (group_rows(p, e) + BM - 1) / BM;
-    return min(max(mtv - mg * p.SM, 0), p.SM);
+// a / d for 0 <= a < 2^20, d >= 1: (a + 1/2) / d is at least 1 / (2 d) away from a whole number, more than the reciprocal and
+// the product round off.  For wave-uniform operands.  (The empty statements keep the reciprocal out of loops and the result
+// in a scalar register; either would hold a vector register of the kernels' 256.)
+__device__ __forceinline__ int small_div(int a, int d) {
+    d = __builtin_amdgcn_readfirstlane(d);
+    asm volatile("" : "+s"(d));
+    int q = static_cast<int>((static_cast<float>(a) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(d)));
+    asm volatile("" : "+v"(q));
+    return __builtin_amdgcn_readfirstlane(q);
 }
-__device__ __forceinline__ int live_col_tiles(const GemmParams& p, int ng) { return min(p.NT - ng * p.SN, p.SN); }
 
-// pre[s] = number of live tiles in the super-tiles before s (s <= S = E * MG * NG), by NTH threads
-template <int NTH = 512>
-__device__ __forceinline__ void live_tile_prefix(const GemmParams& p, int BM, int MG, int NG, int* pre, int* wave_tot) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int S = p.E * MG * NG;
-    const int CH = (S + NTH - 1) / NTH;
-    auto tiles_of = [&](int s) {
-        const int e = s / (MG * NG), r = s - e * (MG * NG);
-        return live_row_tiles(p, e, r % MG, BM) * live_col_tiles(p, r / MG);
-    };
-    int sum = 0;
-    for (int i = 0; i < CH; ++i) {
-        const int s = tid * CH + i;
-        if (s < S) sum += tiles_of(s);
+// The list of live tiles.  Nothing here touches global memory once the list is built: a load in the tile set-up would wait
+// for every copy in flight and for the stores of the epilogue before it.  The rows and k-tiles of the groups (E <= 64) lie in LDS
+// beside the prefix; the super-tile of the next tile is found by one ballot over 64 entries, as a workgroup's tiles ascend.
+struct LiveTiles {
+    const int* pre;              // pre[s] = number of live tiles in the super-tiles before s (s <= S)
+    const int* rows;             // rows of each group, then its k-tiles
+    int BM, MG, NG, S, total;
+    int s = 0, first = 0;        // super-tile of the tile found last, and its first tile's place in the list
+
+    __device__ __forceinline__ static int live_rows(const GemmParams& p, int count, int mg, int BM) {
+        return min(max((count + BM - 1) / BM - mg * p.SM, 0), p.SM);
     }
-    int inc = sum;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const int o = __shfl_up(inc, m, 64);
-        if (lane >= m) inc += o;
-    }
-    if (lane == 63) wave_tot[wave] = inc;
-    __syncthreads();
-    int run = inc - sum;
-    for (int w = 0; w < wave; ++w) run += wave_tot[w];
-    for (int i = 0; i < CH; ++i) {
-        const int s = tid * CH + i;
-        if (s < S) {
-            pre[s] = run;
-            run += tiles_of(s);
+    // by NTH threads, with LDS for S + 1, NTH / 64 and 128 numbers
+    template <int NTH>
+    __device__ __forceinline__ void build(const GemmParams& p, int tile_rows, int* lds_pre, int* wave_tot, int* lds_rows) {
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+        pre = lds_pre;
+        BM = tile_rows;
+        MG = __builtin_amdgcn_readfirstlane((p.MT + p.SM - 1) / p.SM);
+        NG = __builtin_amdgcn_readfirstlane((p.NT + p.SN - 1) / p.SN);
+        S = p.E * MG * NG;
+        rows = lds_rows;
+        if (tid < p.E) {
+            lds_rows[tid] = group_rows(p, tid);
+            lds_rows[64 + tid] = group_k(p, tid) / 64;
         }
+        __syncthreads();
+        const int CH = (S + NTH - 1) / NTH;
+        auto tiles_of = [&](int at) {
+            const int e = at / (MG * NG), r = at - e * (MG * NG);
+            return live_rows(p, lds_rows[e], r % MG, BM) * min(p.NT - (r / MG) * p.SN, p.SN);
+        };
+        int sum = 0;
+        for (int i = 0; i < CH; ++i) {
+            const int at = tid * CH + i;
+            if (at < S) sum += tiles_of(at);
+        }
+        int inc = sum;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) {
+            const int o = __shfl_up(inc, m, 64);
+            if (lane >= m) inc += o;
+        }
+        if (lane == 63) wave_tot[wave] = inc;
+        __syncthreads();
+        int run = inc - sum;
+        for (int w = 0; w < wave; ++w) run += wave_tot[w];
+        for (int i = 0; i < CH; ++i) {
+            const int at = tid * CH + i;
+            if (at < S) {
+                lds_pre[at] = run;
+                run += tiles_of(at);
+            }
+        }
+        if (tid == NTH - 1) lds_pre[S] = run;            // the last thread owns the last chunk (or nothing): run = total
+        __syncthreads();
+        total = __builtin_amdgcn_readfirstlane(lds_pre[S]);
     }
-    if (tid == NTH - 1) pre[S] = run;                    // the last thread owns the last chunk (or nothing): run = total
-    __syncthreads();
+    struct Place { int e, mt, nt; };
+    // the tile with list index q (q < total, not below the q of the call before); all lanes active
+    __device__ __forceinline__ Place find(const GemmParams& p, int q) {
+        const int lane = threadIdx.x & 63;
+        for (;;) {
+            const int v = pre[min(s + 1 + lane, S)];     // ascending; the last entry is above every q
+            const int n = __popcll(__ballot(v <= q));
+            if (n > 0) first = __builtin_amdgcn_readlane(v, n - 1);
+            s += n;
+            if (n < 64) break;
+        }
+        const int e = small_div(s, MG * NG);
+        const int r = s - e * (MG * NG), ng = small_div(r, MG), mg = r - ng * MG;
+        const int vm = live_rows(p, count(e), mg, BM);
+        const int c = small_div(q - first, vm);
+        return {e, mg * p.SM + (q - first) - c * vm, ng * p.SN + c};
+    }
+    __device__ __forceinline__ int count(int e) const { return __builtin_amdgcn_readfirstlane(rows[e]); }
+    __device__ __forceinline__ int k_tiles(int e) const { return __builtin_amdgcn_readfirstlane(rows[64 + e]); }
+};
+
+// Row indices of a tile of 256 rows, on their way through LDS (see the kernels): asynchronous copy by waves 0..3, 64 rows each
+__device__ __forceinline__ void request_row_ids(const GemmParams& p, int e, int m0, int count, int wave, int lane, int* dst) {
+    if (wave < 4) {
+        const int m = min(m0 + wave * 64 + lane, count - 1);             // rows past the count replay a valid row; never stored
+        const int32_t* src = p.row_index + static_cast<size_t>(e) * p.capacity + m;
+        __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(dst + wave * 64), 4, 0, 0);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -837,7 +894,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     uint4* lds = reinterpret_cast<uint4*>(lds_raw);
     __shared__ int pre[kMaxSuperWide + 1];
-    __shared__ int wave_tot[NW];
+    __shared__ int wave_tot[NW], rows_of_group[128];
     __shared__ int row_ids[3][BM];                       // gathered rows of a tile: this, the next, the one after
     __shared__ __attribute__((aligned(16))) unsigned char stage_all[NW * kStageBytes];   // epilogue patches, one per wave
 
@@ -847,10 +904,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     const int KCA = (p.lda ? p.lda : p.K) / 8, KCB = (p.ldb ? p.ldb : p.K) / 8;
     const bool gather = p.row_index != nullptr;
 
-    const int MG = (p.MT + p.SM - 1) / p.SM, NG = (p.NT + p.SN - 1) / p.SN;
-    const int S = p.E * MG * NG;
-    live_tile_prefix<NW * 64>(p, BM, MG, NG, pre, wave_tot);
-    const int total = pre[S];
+    LiveTiles tiles;
+    tiles.build<NW * 64>(p, BM, pre, wave_tot, rows_of_group);
+    const int total = tiles.total;
     const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
     const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
 
@@ -869,37 +925,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     // (the swizzle term of a lane is the same for both operands: a wave's rows start at a multiple of 32)
     const bool over[2] = {TAIL && 8 * c0 >= (p.K & 63), TAIL && 8 * (c0 ^ 4) >= (p.K & 63)};
 
-    auto decode = [&](int q, Tile& t) {                  // scalar part of the tile with list index q
-        int lo = 0, hi = S;                              // largest s with pre[s] <= q
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= q) lo = mid; else hi = mid;
-        }
-        const int s = __builtin_amdgcn_readfirstlane(lo);
-        const int u = __builtin_amdgcn_readfirstlane(q - pre[s]);
-        const int e = s / (MG * NG), r = s - e * (MG * NG);
-        const int mg = r % MG, ng = r / MG;
-        const int vm = live_row_tiles(p, e, mg, BM);
-        const int mt = mg * p.SM + u % vm, nt = ng * p.SN + u / vm;
+    auto fill = [&](const LiveTiles::Place& at, Tile& t) {              // scalar part of a tile
+        const int e = at.e;
         // (a ragged last column tile is moved back to end on the last column: it computes some columns of its left
         // neighbour once more and stores the same values, and no weight-row address or store needs a bound)
-        t.e = e; t.m0 = mt * BM; t.n0 = min(nt * BN, p.N - BN);
-        t.count = group_rows(p, e);
-        t.KT = TAIL ? (p.K + 63) / 64 : group_k(p, e) / 64;
+        t.e = e; t.m0 = at.mt * BM; t.n0 = min(at.nt * BN, p.N - BN);
+        t.count = tiles.count(e);
+        t.KT = TAIL ? (p.K + 63) / 64 : tiles.k_tiles(e);
         t.Abase = reinterpret_cast<uint64_t>(p.A) + (gather ? 0 : static_cast<uint64_t>(e) * p.capacity * KCA * 16);
         // this wave's staged weight rows: GLU stages 128 gate rows, then the 128 up rows of the same columns
         const int nrow = t.n0 + (GLU ? (wave % (NW / 2)) * WROWS : wave * WROWS);
         t.Bbase = reinterpret_cast<uint64_t>((GLU && wave >= NW / 2) ? p.B1 : p.B0) +
                   (static_cast<uint64_t>(e) * p.N + nrow) * KCB * 16;
-    };
-    // asynchronous copy of the tile's row indices into slot `slot` (waves 0..3, 64 rows each)
-    auto request_rows = [&](const Tile& t, int slot) {
-        if (wave < 4) {
-            int m = t.m0 + wave * 64 + lane;
-            m = m < t.count ? m : t.count - 1;           // rows past the count replay a valid row; never stored
-            const int32_t* src = p.row_index + static_cast<size_t>(t.e) * p.capacity + m;
-            __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(&row_ids[slot][wave * 64]), 4, 0, 0);
-        }
     };
     // per-lane offsets of the token rows; with `gather` the indices have landed in slot `slot`
     auto finish = [&](Tile& t, int slot) {
@@ -967,14 +1004,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     int q = xcd * GS + slot_l;                           // first pass over the list
     if (q >= total) return;                              // uniform: nothing for this workgroup
     Tile cur, nxt;
-    decode(q, cur);
+    LiveTiles::Place next_at{0, 0, 0}, after{0, 0, 0};
+    fill(tiles.find(p, q), cur);
     int seq = 0;                                         // tiles this workgroup has started; tile n uses slot n % 3
+    bool has_next = q + 8 * GS < total;                  // same XCD, next round
+    if (has_next) next_at = tiles.find(p, q + 8 * GS);
     if (gather) {
-        request_rows(cur, 0);
-        if (q + 8 * GS < total) {
-            decode(q + 8 * GS, nxt);
-            request_rows(nxt, 1);
-        }
+        request_row_ids(p, cur.e, cur.m0, cur.count, wave, lane, row_ids[0]);
+        if (has_next) request_row_ids(p, next_at.e, next_at.mt * BM, tiles.count(next_at.e), wave, lane, row_ids[1]);
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));
         __builtin_amdgcn_s_barrier();                    // the indices were fetched by other waves
     }
@@ -994,17 +1031,14 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
                                                          // the second k-tile's own once more)
     bool late_last = false;                              // they belong to a short k-tile
     for (;;) {
-        const int qn = q + 8 * GS;                       // same XCD, next round
-        const bool has_next = qn < total;
         if (has_next) {
-            decode(qn, nxt);
+            fill(next_at, nxt);
             finish(nxt, (seq + 1) % 3);
-            const int qnn = qn + 8 * GS;
-            if (gather && qnn < total) {
-                Tile t2;
-                decode(qnn, t2);
-                request_rows(t2, (seq + 2) % 3);
-            }
+        }
+        const bool has_after = q + 16 * GS < total;      // its row indices are requested two tiles ahead
+        if (has_after) {
+            after = tiles.find(p, q + 16 * GS);
+            if (gather) request_row_ids(p, after.e, after.mt * BM, tiles.count(after.e), wave, lane, row_ids[(seq + 2) % 3]);
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -1059,7 +1093,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
                                                stage_all + wave * kStageBytes);
         if (!has_next) break;
         cur = nxt;
-        q = qn;
+        next_at = after;
+        has_next = has_after;
+        q += 8 * GS;
         ++seq;
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
@@ -1103,20 +1139,21 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     uint4* lds = reinterpret_cast<uint4*>(lds_raw);
     __shared__ int pre[kMaxSuper + 1];
-    __shared__ int wave_tot[NW];
+    __shared__ int wave_tot[NW], rows_of_group[128];
+    __shared__ int row_ids[TRA ? 1 : 3][BM];             // gathered rows of a tile: this, the next, the one after
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
+    const bool gather = !TRA && p.row_index != nullptr;
     const int lda = p.lda ? p.lda : p.K, ldb = p.ldb ? p.ldb : p.K;
     const bool splitB = p.B1 != nullptr;
     const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 63) / 64;         // of the whole product, or of each half of a split one
     const int k_rem = (Kh & 63) ? (Kh & 63) : 64;        // valid k of the last k-tile
 
-    const int MG = (p.MT + p.SM - 1) / p.SM, NG = (p.NT + p.SN - 1) / p.SN;
-    const int S = p.E * MG * NG;
-    live_tile_prefix<NW * 64>(p, BM, MG, NG, pre, wave_tot);
-    const int total = pre[S];
+    LiveTiles tiles;
+    tiles.build<NW * 64>(p, BM, pre, wave_tot, rows_of_group);
+    const int total = tiles.total;
     const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
     const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
 
@@ -1137,33 +1174,31 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     const uint32_t fixedB = KG == 2 ? 0u : static_cast<uint32_t>(k_row) * ldb * 2u;
     const int limitA = p.capacity - 8, limitB = p.N - 8; // copies stay inside the k row; what they repeat is never stored
 
-    auto decode = [&](int q, Tile& t) {                  // the tile with list index q
-        int lo = 0, hi = S;                              // largest s with pre[s] <= q
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= q) lo = mid; else hi = mid;
-        }
-        const int s = __builtin_amdgcn_readfirstlane(lo);
-        const int u = __builtin_amdgcn_readfirstlane(q - pre[s]);
-        const int e = s / (MG * NG), r = s - e * (MG * NG);
-        const int mg = r % MG, ng = r / MG;
-        const int vm = live_row_tiles(p, e, mg, BM);
-        t.e = e; t.m0 = (mg * p.SM + u % vm) * BM; t.n0 = (ng * p.SN + u / vm) * BN;
-        t.count = group_rows(p, e);
-        t.KT = TRA ? group_k(p, e) / 64 : (splitB ? 2 * KTh : KTh);
+    auto fill = [&](const LiveTiles::Place& at, Tile& t) {              // scalar part of a tile
+        const int e = at.e;
+        t.e = e; t.m0 = at.mt * BM; t.n0 = at.nt * BN;
+        t.count = tiles.count(e);
+        t.KT = TRA ? tiles.k_tiles(e) : (splitB ? 2 * KTh : KTh);
         t.Abase = reinterpret_cast<uint64_t>(p.A);
         if (KG != 1) t.Abase += TRA ? static_cast<uint64_t>(e) * p.K * lda * 2
                                     : (p.row_index ? 0 : static_cast<uint64_t>(e) * p.capacity * lda * 2);
         const uint64_t group = KG == 2 ? 0 : static_cast<uint64_t>(e) * Kh * ldb * 2;
         t.Bbase = reinterpret_cast<uint64_t>(p.B0) + group;
         t.Bbase1 = splitB ? reinterpret_cast<uint64_t>(p.B1) + group : t.Bbase;
+    };
+    // row-major A: per-lane offsets of the token rows; with `gather` the indices have landed in slot `slot`
+    auto finish = [&](Tile& t, int slot) {
         if constexpr (!TRA) {
+            int row[NCP];
+            if (gather) {                                // one uniform branch around straight-line code
 #pragma unroll
-            for (int i = 0; i < NCP; ++i) {
-                int row = min(t.m0 + rr0 + 8 * i, t.count - 1);          // rows past the count replay a valid row; never stored
-                if (p.row_index) row = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + row], 0), p.a_rows - 1);
-                t.offA[i] = (static_cast<uint32_t>(row) * lda + (c0 ^ (4 * (i & 1))) * 8) * 2u;
+                for (int i = 0; i < NCP; ++i) row[i] = min(max(row_ids[slot][rr0 + 8 * i], 0), p.a_rows - 1);
+            } else {
+#pragma unroll
+                for (int i = 0; i < NCP; ++i) row[i] = min(t.m0 + rr0 + 8 * i, t.count - 1);
             }
+#pragma unroll
+            for (int i = 0; i < NCP; ++i) t.offA[i] = (static_cast<uint32_t>(row[i]) * lda + (c0 ^ (4 * (i & 1))) * 8) * 2u;
         }
     };
     auto a_ktile = [&](uint64_t a, int k) -> uint64_t {
@@ -1358,7 +1393,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     int q = xcd * GS + slot_l;                           // first pass over the list
     if (q >= total) return;                              // uniform: nothing for this workgroup
     Tile cur, nxt;
-    decode(q, cur);
+    LiveTiles::Place next_at{0, 0, 0}, after{0, 0, 0};
+    fill(tiles.find(p, q), cur);
+    int seq = 0;                                         // tiles this workgroup has started; tile n uses slot n % 3
+    bool has_next = q + 8 * GS < total;                  // same XCD, next round
+    if (has_next) next_at = tiles.find(p, q + 8 * GS);
+    if (gather) {
+        request_row_ids(p, cur.e, cur.m0, cur.count, wave, lane, row_ids[0]);
+        if (has_next) request_row_ids(p, next_at.e, next_at.mt * BM, tiles.count(next_at.e), wave, lane, row_ids[TRA ? 0 : 1]);
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));
+        __builtin_amdgcn_s_barrier();                    // the indices were fetched by other waves
+    }
+    finish(cur, 0);
     int g = 0;                                           // global step: buffer g & 1
     int index = 0;                                       // KG: this lane's row number in k-tile g + 2
     if constexpr (KG != 0) index = load_index(cur.e, 2); // (KT >= 4)
@@ -1384,9 +1430,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     int late_n0 = cur.n0;
     bool late_last = is_short(1);
     for (;;) {
-        const int qn = q + 8 * GS;                       // same XCD, next round
-        const bool has_next = qn < total;
-        if (has_next) decode(qn, nxt);
+        if (has_next) {
+            fill(next_at, nxt);
+            finish(nxt, (seq + 1) % 3);
+        }
+        const bool has_after = q + 16 * GS < total;      // its row indices are requested two tiles ahead
+        if (has_after) {
+            after = tiles.find(p, q + 16 * GS);
+            if (gather) request_row_ids(p, after.e, after.mt * BM, tiles.count(after.e), wave, lane, row_ids[TRA ? 0 : (seq + 2) % 3]);
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1468,7 +1520,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
         }
         if (!has_next) break;
         cur = nxt;
-        q = qn;
+        next_at = after;
+        has_next = has_after;
+        q += 8 * GS;
+        ++seq;
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
 }

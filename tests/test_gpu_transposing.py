@@ -22,6 +22,7 @@ CASES = [
     (2000, 16, 128, 2056, 200, 2, "cluster"),   # many short tiles per workgroup
     (1500, 8, 1160, 520, 700, 3, "zipf"),       # ragged both ways, uneven experts
     (900, 4, 264, 72, 8192, 2, "bias"),         # fetched rows, capacity above the tokens
+    (2000, 16, 128, 264, 20000, 2, "bias"),     # a list of tiles whose live ones lie far apart
     (9000, 6, 136, 136, 8200, 2, "zipf"),       # fetched rows, capacity no multiple of 64, experts from few rows to thousands
 ]
 
