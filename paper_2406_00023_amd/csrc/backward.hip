@@ -563,15 +563,15 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     GroupedGemm k4 = t4, k5 = t5, k6 = t6;
     k4.A = dout; k4.k_gather = 1; k5.B0 = x; k5.k_gather = 2; k6.B0 = x; k6.k_gather = 2;
     for (GroupedGemm* g : {&k4, &k5, &k6}) { g->k_index = slot_token; g->k_index_stride = C; g->k_rows = Tn; }
-    // It pays where the copies are large: 8 experts x 32 000 rows, 23.0 -> 21.9 ms per call (the fetching products are
-    // 3-8 % slower than the plain ones, the two copies cost 1.6 ms); 16-64 experts with 500-2000 rows each, equal or
-    // 1.5 % slower.  As above, the capacity stands in for the row count.
+    // It saves the two copies (8 experts x 32 000 rows: 1.6 ms of 23; 16 experts of 166-1024 rows, 2048 wide: 42 us, the step
+    // 2652 -> 2633 us; 12 experts of 677 rows, 1080 wide: 21 us, 1000 -> 978) at the price of at least 256 contraction rows
+    // per expert, so experts that expect no more than 128 rows take the copies.
     // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
     // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
     GroupedGemm k56 = k5;
     k56.M = 2 * H; k56.a_rows = 2 * H; k56.C = dw_gate; k56.C2 = dw_up; k56.split_m = H;
     const bool both_gates = H % 32 == 0 && grouped_gemm_transposed_ok(k56);
-    const bool fetch_rows = C >= 8192 && direct && grouped_gemm_transposed_ok(k4) && grouped_gemm_transposed_ok(k5) &&
+    const bool fetch_rows = rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k4) && grouped_gemm_transposed_ok(k5) &&
                             grouped_gemm_transposed_ok(k6);
     int dxp_rows = C;
     if (direct) {
