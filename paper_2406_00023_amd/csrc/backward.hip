@@ -566,22 +566,24 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     // It saves the two copies (8 experts x 32 000 rows: 1.6 ms of 23; 16 experts of 166-1024 rows, 2048 wide: 42 us, the step
     // 2652 -> 2633 us; 12 experts of 677 rows, 1080 wide: 21 us, 1000 -> 978) at the price of at least 256 contraction rows
     // per expert, so experts that expect no more than 128 rows take the copies.
-    // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
-    // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
-    GroupedGemm k56 = k5;
-    k56.M = 2 * H; k56.a_rows = 2 * H; k56.C = dw_gate; k56.C2 = dw_up; k56.split_m = H;
-    const bool both_gates = H % 32 == 0 && grouped_gemm_transposed_ok(k56);
     const bool fetch_rows = rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k4) && grouped_gemm_transposed_ok(k5) &&
                             grouped_gemm_transposed_ok(k6);
+    // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
+    // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
+    const GroupedGemm down = fetch_rows ? k4 : t4;
+    GroupedGemm gates[2] = {fetch_rows ? k5 : t5, fetch_rows ? k6 : t6};
+    GroupedGemm both = gates[0];
+    both.M = 2 * H; both.a_rows = 2 * H; both.C = dw_gate; both.C2 = dw_up; both.split_m = H;
+    const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;
+    if (n_gates == 1) gates[0] = both;
     int dxp_rows = C;
     if (direct) {
-        // The two products whose only awkward operand is a weight matrix run faster on the row-major kernel with
-        // that weight transposed once per call: the 64-wide row-major kernel sustains a tenth to a fifth more than
-        // the transposing one.  The copy moves E*d*H elements, the product works on every kept row, so it pays
-        // from a few thousand rows per expert on (8-expert workload, 32 000 rows per expert: the input-gradient
-        // product 5.1 -> 4.7 ms for 0.08 ms of copies; 16 experts with 760 rows each: 0.43 ms of copies for less
-        // than 0.1 ms).  The row count lives on the device; the capacity stands in for it.  The kernel wants at least
-        // one whole 256-column tile of the output.
+        // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
+        // that weight transposed once per call.  The copy moves E*d*H elements, the product works on every kept row, so it
+        // pays from a few thousand rows per expert on (8-expert workload, 32 000 rows per expert: the training step 22.95 ->
+        // 22.74 ms with 0.1 ms of copies; 16 experts with 760 rows each: 0.43 ms of copies for less than 0.1 ms, and the
+        // input gradient shares a launch with the weight gradients there).  The row count lives on the device; the capacity
+        // stands in for it.  The kernel wants at least one whole 256-column tile of the output.
         const bool many_rows = C >= 8192;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
@@ -616,15 +618,10 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             ETR_BW(hipGetLastError());
             GroupedGemm g3{at(L.dab), at(L.wguT), nullptr, at(L.dxp), nullptr, counts, nullptr, nullptr, E, Cp, d, 2 * H, 0, 0, Cp, GEMM_PLAIN, c.dtype};
             ETR_BW(launch_grouped_gemm(g3, st));
+            ETR_BW(launch_grouped_gemm(down, st));
+            for (int i = 0; i < n_gates; ++i) ETR_BW(launch_grouped_gemm(gates[i], st));
         } else {
-            ETR_BW(launch_grouped_gemm(t3, st));
-        }
-        ETR_BW(launch_grouped_gemm(fetch_rows ? k4 : t4, st));
-        if (fetch_rows && both_gates) {
-            ETR_BW(launch_grouped_gemm(k56, st));
-        } else {
-            ETR_BW(launch_grouped_gemm(fetch_rows ? k5 : t5, st));
-            ETR_BW(launch_grouped_gemm(fetch_rows ? k6 : t6, st));
+            ETR_BW(launch_backward_products(t3, down, gates, n_gates, st));
         }
         dxp_rows = Cp;
     } else {

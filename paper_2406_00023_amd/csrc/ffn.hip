@@ -826,6 +826,26 @@ struct LiveTiles {
     __device__ __forceinline__ int k_tiles(int e) const { return __builtin_amdgcn_readfirstlane(rows[64 + e]); }
 };
 
+// Which tiles of a list this workgroup takes, in ascending order: in rounds over all workgroups, starting at place `turn`, and
+// before that `extra` rounds over the workgroups from place `idle` on, which have nothing else to do (see
+// gemm_bf16_backward_kernel).
+struct Deal {
+    int W, v;                    // workgroups, this one's place: the workgroups of an XCD are neighbours
+    int idle, extra = 0, turn = 0;
+    __device__ __forceinline__ Deal() {
+        W = gridDim.x;
+        v = (blockIdx.x & 7) * (W >> 3) + (blockIdx.x >> 3);
+        idle = W;
+    }
+    // list index of this workgroup's i-th tile; at or past the end of the list: none
+    __device__ __forceinline__ int tile(int i) const {
+        const int own = v >= idle ? extra : 0;
+        if (i < own) return i * (W - idle) + v - idle;
+        const int w = v >= turn ? v - turn : v - turn + W;
+        return extra * (W - idle) + (i - own) * W + w;
+    }
+};
+
 // Row indices of a tile of 256 rows, on their way through LDS (see the kernels): asynchronous copy by waves 0..3, 64 rows each
 __device__ __forceinline__ void request_row_ids(const GemmParams& p, int e, int m0, int count, int wave, int lane, int* dst) {
     if (wave < 4) {
@@ -907,8 +927,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     LiveTiles tiles;
     tiles.build<NW * 64>(p, BM, pre, wave_tot, rows_of_group);
     const int total = tiles.total;
-    const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
-    const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
+    const Deal deal;
 
     struct Tile {
         int e, m0, n0, count, KT;
@@ -1001,14 +1020,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
         }
     };
 
-    int q = xcd * GS + slot_l;                           // first pass over the list
-    if (q >= total) return;                              // uniform: nothing for this workgroup
+    if (deal.tile(0) >= total) return;                   // uniform: nothing for this workgroup
     Tile cur, nxt;
-    LiveTiles::Place next_at{0, 0, 0}, after{0, 0, 0};
-    fill(tiles.find(p, q), cur);
+    LiveTiles::Place next_at{}, after{};
+    fill(tiles.find(p, deal.tile(0)), cur);
     int seq = 0;                                         // tiles this workgroup has started; tile n uses slot n % 3
-    bool has_next = q + 8 * GS < total;                  // same XCD, next round
-    if (has_next) next_at = tiles.find(p, q + 8 * GS);
+    bool has_next = deal.tile(1) < total;
+    if (has_next) next_at = tiles.find(p, deal.tile(1));
     if (gather) {
         request_row_ids(p, cur.e, cur.m0, cur.count, wave, lane, row_ids[0]);
         if (has_next) request_row_ids(p, next_at.e, next_at.mt * BM, tiles.count(next_at.e), wave, lane, row_ids[1]);
@@ -1035,9 +1053,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
             fill(next_at, nxt);
             finish(nxt, (seq + 1) % 3);
         }
-        const bool has_after = q + 16 * GS < total;      // its row indices are requested two tiles ahead
+        const bool has_after = deal.tile(seq + 2) < total;               // its row indices are requested two tiles ahead
         if (has_after) {
-            after = tiles.find(p, q + 16 * GS);
+            after = tiles.find(p, deal.tile(seq + 2));
             if (gather) request_row_ids(p, after.e, after.mt * BM, tiles.count(after.e), wave, lane, row_ids[(seq + 2) % 3]);
         }
 #pragma unroll
@@ -1095,7 +1113,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
         cur = nxt;
         next_at = after;
         has_next = has_after;
-        q += 8 * GS;
         ++seq;
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
@@ -1128,8 +1145,45 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 // 2452 us and, both gate and up, 5561 -> 4757 us (1.06 -> 1.24 PFLOP/s); 16 experts of 166-1024 rows, 2048 x 5632: 281 -> 278 us
 // each, input gradient 603 -> 586 us.
 // ---------------------------------------------------------------------------------------
-template <bool TRA, int KG = 0, bool TAIL = false>
-__global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p) {
+struct TransposingLds {                                  // beside the two buffers
+    int pre[kMaxSuper + 1];
+    int wave_tot[8], rows_of_group[128];
+    int row_ids[3][256];                                 // gathered rows of a tile: this, the next, the one after
+};
+// What a product leaves to the ones behind it in the same launch: the workgroups from place `idle` on are `ahead` k-tiles
+// ahead of the others (a tile counts kTileSteps more than it has); the next list's rounds begin at place `turn`.
+constexpr int kTileSteps = 2;
+struct DealState {
+    int idle, ahead = 0, turn = 0;
+    // uniform: k-tiles of every tile (0: the groups' own)
+    __device__ __forceinline__ void deal(const GemmParams& p, const LiveTiles& tiles, int uniform, Deal& d) {
+        int steps = uniform;                             // of a tile on average: every group has the same number of tiles here
+        if (uniform == 0) {
+            const int lane = threadIdx.x & 63;
+            steps = lane < p.E ? tiles.rows[64 + lane] : 0;
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) steps += __shfl_xor(steps, m, 64);
+            steps = small_div(__builtin_amdgcn_readfirstlane(steps), p.E);
+        }
+        steps += kTileSteps;
+        const int free = d.W - idle;
+        if (free > 0 && ahead >= steps) {
+            const int most = small_div(tiles.total, free), wanted = small_div(ahead, steps);
+            d.idle = idle;
+            d.extra = wanted < most ? wanted : most;
+            ahead -= d.extra * steps;
+        }
+        d.turn = turn;
+        const int rest = tiles.total - d.extra * free, late = rest - small_div(rest, d.W) * d.W;
+        if (uniform != 0 && turn == 0 && ahead == 0) {   // the long product in front: a partly filled last round
+            idle = late > 0 ? late : d.W;
+            ahead = late > 0 ? steps : 0;
+        }
+        turn = turn + late < d.W ? turn + late : turn + late - d.W;
+    }
+};
+template <bool TRA, int KG, bool TAIL>
+__device__ __forceinline__ void transposing_tiles(const GemmParams& p, TransposingLds& sh, DealState& state) {
     static_assert(KG == 0 || TRA, "gathered contraction rows: both operands transposed");
     static_assert(!TAIL || (!TRA && KG == 0), "short k-tiles: row-major A");
     constexpr int NW = 8, BM = 256, BN = 256, CPR = 8, SWZ = 1;
@@ -1138,9 +1192,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     constexpr int NCP = 4;                               // copies per wave, operand and k-tile
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     uint4* lds = reinterpret_cast<uint4*>(lds_raw);
-    __shared__ int pre[kMaxSuper + 1];
-    __shared__ int wave_tot[NW], rows_of_group[128];
-    __shared__ int row_ids[TRA ? 1 : 3][BM];             // gathered rows of a tile: this, the next, the one after
+    int (&row_ids)[3][BM] = sh.row_ids;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1152,10 +1204,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
     const int k_rem = (Kh & 63) ? (Kh & 63) : 64;        // valid k of the last k-tile
 
     LiveTiles tiles;
-    tiles.build<NW * 64>(p, BM, pre, wave_tot, rows_of_group);
+    tiles.build<NW * 64>(p, BM, sh.pre, sh.wave_tot, sh.rows_of_group);
     const int total = tiles.total;
-    const int GS = gridDim.x >> 3;                       // tiles per group = workgroups per XCD
-    const int xcd = blockIdx.x & 7, slot_l = blockIdx.x >> 3;
+    Deal deal;
+    state.deal(p, tiles, TRA ? 0 : (splitB ? 2 * KTh : KTh), deal);
 
     struct Tile {
         int e, m0, n0, count, KT;
@@ -1390,14 +1442,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
             asm volatile("s_nop 15\n\ts_nop 3" : ETR_ACC(i));
     };
 
-    int q = xcd * GS + slot_l;                           // first pass over the list
-    if (q >= total) return;                              // uniform: nothing for this workgroup
+    if (deal.tile(0) >= total) return;                   // uniform: nothing for this workgroup
     Tile cur, nxt;
-    LiveTiles::Place next_at{0, 0, 0}, after{0, 0, 0};
-    fill(tiles.find(p, q), cur);
+    LiveTiles::Place next_at{}, after{};
+    fill(tiles.find(p, deal.tile(0)), cur);
     int seq = 0;                                         // tiles this workgroup has started; tile n uses slot n % 3
-    bool has_next = q + 8 * GS < total;                  // same XCD, next round
-    if (has_next) next_at = tiles.find(p, q + 8 * GS);
+    bool has_next = deal.tile(1) < total;
+    if (has_next) next_at = tiles.find(p, deal.tile(1));
     if (gather) {
         request_row_ids(p, cur.e, cur.m0, cur.count, wave, lane, row_ids[0]);
         if (has_next) request_row_ids(p, next_at.e, next_at.mt * BM, tiles.count(next_at.e), wave, lane, row_ids[TRA ? 0 : 1]);
@@ -1434,9 +1485,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
             fill(next_at, nxt);
             finish(nxt, (seq + 1) % 3);
         }
-        const bool has_after = q + 16 * GS < total;      // its row indices are requested two tiles ahead
+        const bool has_after = deal.tile(seq + 2) < total;               // its row indices are requested two tiles ahead
         if (has_after) {
-            after = tiles.find(p, q + 16 * GS);
+            after = tiles.find(p, deal.tile(seq + 2));
             if (gather) request_row_ids(p, after.e, after.mt * BM, tiles.count(after.e), wave, lane, row_ids[TRA ? 0 : (seq + 2) % 3]);
         }
 #pragma unroll
@@ -1522,10 +1573,39 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
         cur = nxt;
         next_at = after;
         has_next = has_after;
-        q += 8 * GS;
         ++seq;
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
+}
+template <bool TRA, int KG = 0, bool TAIL = false>
+__global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p) {
+    __shared__ TransposingLds sh;
+    DealState state;
+    state.idle = gridDim.x;
+    transposing_tiles<TRA, KG, TAIL>(p, sh, state);
+}
+
+// The last products of the backward in one launch: the input gradient (p[0]: row-major A, TAIL as above), then the weight
+// gradients (p[1]: down; p[2] and, with two, p[3]: gate and up), with FETCH the rows of A, resp. B, through an index.  They do
+// not depend on each other, and the input gradient is few tiles with a long contraction (2 H): its last round leaves
+// workgroups idle, which here start on the weight gradients' many short tiles, as many rounds of them as its k-tiles stand
+// for.  Bound as the kernels above are.  Training step, a launch for each product / this: 12 experts of 677 rows, 1080 x 2744
+// (180 tiles of 86 k-tiles): 990 / 880 us; 4 of 300, 2048 x 5632: 721 / 633; 8 of 512, 1024 x 2816: 520 / 434; 16 of 166-1024,
+// 2048 x 5632 (1.6 rounds, at the power limit): 2665 / 2625; without fetched rows, 8 of 64, 2048 x 5632: 763 / 646, 32 of 32,
+// 512 x 1024: 193 / 157.
+struct BackwardProducts { GemmParams p[4]; int n_gates; };
+template <bool TAIL, bool FETCH>
+__global__ __launch_bounds__(512) void gemm_bf16_backward_kernel(BackwardProducts b) {
+    __shared__ TransposingLds sh;
+    DealState state;
+    state.idle = gridDim.x;
+    transposing_tiles<false, 0, TAIL>(b.p[0], sh, state);
+    __syncthreads();                                     // the tile list and the buffers are free
+    transposing_tiles<true, FETCH ? 1 : 0, false>(b.p[1], sh, state);
+    for (int i = 0; i < b.n_gates; ++i) {
+        __syncthreads();
+        transposing_tiles<true, FETCH ? 2 : 0, false>(b.p[2 + i], sh, state);
+    }
 }
 #undef ETR_OFF
 #undef ETR_AT
@@ -1882,6 +1962,16 @@ hipError_t launch_bf16_transposing(GemmParams p, hipStream_t st, int n_cu) {
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
     return hipGetLastError();
 }
+template <bool TAIL, bool FETCH>
+hipError_t launch_bf16_backward_form(BackwardProducts b, hipStream_t st, int n_cu) {
+    constexpr size_t lds = 2ull * 512 * 64 * 2;
+    for (int i = 0; i < 2 + b.n_gates; ++i) plan_tiles(b.p[i], 256, 256);
+    auto kern = gemm_bf16_backward_kernel<TAIL, FETCH>;
+    hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, b);
+    return hipGetLastError();
+}
 template <bool GLU, bool DUAL = false, bool KEEP = false, bool TAIL = false>
 hipError_t launch_bf16_persistent_form(GemmParams p, hipStream_t st, int n_cu) {
     constexpr size_t lds = 2ull * 512 * 64 * 2;                             // two buffers of 256 + 256 rows x 64 bf16
@@ -2077,6 +2167,24 @@ bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
         if (static_cast<size_t>(q.k_rows) * (q.k_gather == 1 ? lda : ldb) * 2 >= (1ull << 32)) return false;
     }
     return persist_ok(params_of(q), false);
+}
+
+hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& down, const GroupedGemm* gates, int n_gates, hipStream_t st) {
+    BackwardProducts b{};
+    const bool fetch = down.k_gather == 1;
+    if (n_gates < 1 || n_gates > 2 || dx.ta || !down.ta || down.k_gather == 2) return hipErrorInvalidValue;
+    b.n_gates = n_gates;
+    b.p[0] = params_of(dx);
+    b.p[1] = params_of(down);
+    if (!grouped_gemm_transposed_ok(dx) || !grouped_gemm_transposed_ok(down)) return hipErrorInvalidValue;
+    for (int i = 0; i < n_gates; ++i) {
+        if (!grouped_gemm_transposed_ok(gates[i]) || !gates[i].ta || gates[i].k_gather != (fetch ? 2 : 0)) return hipErrorInvalidValue;
+        b.p[2 + i] = params_of(gates[i]);
+    }
+    const int n_cu = cu_count();
+    if ((dx.B1 ? dx.K / 2 : dx.K) % 64 == 0)
+        return fetch ? launch_bf16_backward_form<false, true>(b, st, n_cu) : launch_bf16_backward_form<false, false>(b, st, n_cu);
+    return fetch ? launch_bf16_backward_form<true, true>(b, st, n_cu) : launch_bf16_backward_form<true, false>(b, st, n_cu);
 }
 
 hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
