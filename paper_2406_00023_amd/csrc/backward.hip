@@ -555,8 +555,9 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     t5.ta = t5.tb = true;
     GroupedGemm t6 = t5;
     t6.A = at(L.dab) + H; t6.C = dw_up;
-    const bool direct = grouped_gemm_transposed_ok(t2) && grouped_gemm_transposed_ok(t3) && grouped_gemm_transposed_ok(t4) &&
-                        grouped_gemm_transposed_ok(t5) && grouped_gemm_transposed_ok(t6);
+    const bool f32 = c.dtype == ETR_F32;                 // its kernel takes all widths
+    const bool direct = f32 || (grouped_gemm_transposed_ok(t2) && grouped_gemm_transposed_ok(t3) && grouped_gemm_transposed_ok(t4) &&
+                        grouped_gemm_transposed_ok(t5) && grouped_gemm_transposed_ok(t6));
     // The same three weight-gradient products with the rows of dOut and x fetched through slot_token by the
     // products themselves: dWd = dOut_p^T (gate h), dWg = da^T x_p, dWu = db^T x_p.  (da, db, h hold zeros from
     // counts[e] on, so whatever row an empty slot fetches is multiplied by zero.)
@@ -566,15 +567,15 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     // It saves the two copies (8 experts x 32 000 rows: 1.6 ms of 23; 16 experts of 166-1024 rows, 2048 wide: 42 us, the step
     // 2652 -> 2633 us; 12 experts of 677 rows, 1080 wide: 21 us, 1000 -> 978) at the price of at least 256 contraction rows
     // per expert, so experts that expect no more than 128 rows take the copies.
-    const bool fetch_rows = rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k4) && grouped_gemm_transposed_ok(k5) &&
-                            grouped_gemm_transposed_ok(k6);
+    const bool fetch_rows = f32 || (rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k4) &&
+                                    grouped_gemm_transposed_ok(k5) && grouped_gemm_transposed_ok(k6));
     // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
     // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
     const GroupedGemm down = fetch_rows ? k4 : t4;
     GroupedGemm gates[2] = {fetch_rows ? k5 : t5, fetch_rows ? k6 : t6};
     GroupedGemm both = gates[0];
     both.M = 2 * H; both.a_rows = 2 * H; both.C = dw_gate; both.C2 = dw_up; both.split_m = H;
-    const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;
+    const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;        // (fp32: 2)
     if (n_gates == 1) gates[0] = both;
     int dxp_rows = C;
     if (direct) {
@@ -584,7 +585,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         // 22.74 ms with 0.1 ms of copies; 16 experts with 760 rows each: 0.43 ms of copies for less than 0.1 ms, and the
         // input gradient shares a launch with the weight gradients there).  The row count lives on the device; the capacity
         // stands in for it.  The kernel wants at least one whole 256-column tile of the output.
-        const bool many_rows = C >= 8192;
+        const bool many_rows = !f32 && C >= 8192;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
             hipLaunchKernelGGL(transpose_kernel<T>, dim3(cH, cd, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_down),

@@ -157,9 +157,13 @@ __device__ __forceinline__ bool decode_tile(const GemmParams& p, int& e, int& mt
 // G <= 64), and each XCD gets an equal, contiguous share of that list, row tiles fastest, so the tiles of one weight
 // slice share an L2.  Dealing super-tiles of the capacity instead left XCDs with half-dead ones: 8 fp32 experts of
 // 66-640 rows, gate/up product: 127 us against 92.
+// by_chunks: groups of very unequal cost per tile (their own contraction lengths): chunks of 8 tiles go round the XCDs, so
+// that each has its part of every group (weight gradients of 8 fp32 experts of 66-640 rows, one expert to an XCD: 57 us each, 52
+// so).  The grid is then whole 64s.
 // j: place in the XCD's share, whose length is handed back.  With a workgroup for every tile of the capacity it is
 // blockIdx.x / 8 and done; a smaller grid (whole rounds of 8 all the same) goes on in steps of gridDim.x / 8 to the end.
-__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt) {
+__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt,
+                                                 bool by_chunks = false) {
     const int lane = threadIdx.x & 63;
     const int mine = lane < p.E ? max((group_rows(p, lane) + BM - 1) / BM, 0) : 0;     // this group's row tiles
     int incl = mine;
@@ -170,7 +174,8 @@ __device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, in
     }
     const int total = __builtin_amdgcn_readlane(incl, 63) * p.NT;
     share = (total + 7) >> 3;
-    const int q = (blockIdx.x & 7) * share + j;
+    if (by_chunks) share = (share + 7) & ~7;
+    const int q = by_chunks ? ((j >> 3) * 8 + (blockIdx.x & 7)) * 8 + (j & 7) : (blockIdx.x & 7) * share + j;
     if (j >= share || q >= total) return false;
     const uint64_t in = __ballot(incl * p.NT > q);
     e = __builtin_ctzll(in);
@@ -1798,24 +1803,36 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
 // 1024 x 4096: 120 TFLOP/s.  Two waves per SIMD (launch bounds) keep the accumulators out of the accumulation registers,
 // whose renaming moves cost 1-4 %.  More buffers, or the barrier between the two k-steps with every fragment read a
 // k-step ahead, change nothing (-2 .. +4 % time): what is lost is lost where the waves of two workgroups meet at barriers.
+//
+// Operands whose contraction index is the slow one (backward; TRB: B is [K][N], TRA: A is [K][M] too): a k-tile is staged as
+// [32 k][rows], and lane l takes its elements one by one: row l % 16 of a block at k = 16 ks + 4 (l / 16) + v, 64 bytes of four k
+// rows per read.  The 64-byte piece b of k row k is stored at b ^ (k / 4 % 4) (applied on the copy's source side), so that
+// the four lie on different banks (32-row tiles have two pieces: two-way conflicts).  k rows past the contraction come
+// from the zero page.  With B1 the contraction is split in the middle ([K/2][ldb] each); with k_gather (1: A, 2: B) the k
+// rows of that operand are rows k_index[g * k_index_stride + k] of one [k_rows][ld] matrix.
 // ---------------------------------------------------------------------------------------
-template <int BM, int BN, int NBUF, bool GLU, bool DUAL = false>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
+template <int BM, int BN, int NBUF, bool GLU> constexpr int f32_pieces() { return NBUF * (BM + (GLU ? 2 : 1) * BN) * 8; }
+// tile j of this XCD's share of the list; lds: f32_pieces
+template <int BM, int BN, int NBUF, bool GLU, bool DUAL, bool TRA, bool TRB>
+__device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4* lds) {
+    static_assert(!GLU || !TRB, "epilogues: row-major operands");
+    static_assert(!TRA || TRB, "transposed A: both are");
     constexpr int CPR = 8, BK = 32, NB = GLU ? 2 : 1, BROWS = NB * BN;
     constexpr int STAGE = (BM + BROWS) * CPR;           // 16-byte pieces per buffer
-    constexpr int NCA = BM / 32, NCB = BROWS / 32;      // copies (8 rows x 128 bytes) per wave and k-tile
+    constexpr int NCA = BM / 32, NCB = BROWS / 32;      // copies (1 KiB: 8 rows x 128 bytes, or 4 k rows x 256) per wave and k-tile
     constexpr int TM = BM / 32, TN = BN / 32;           // 16 x 16 blocks per wave and product
     constexpr int AHEAD = NBUF - 1;
-    __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * STAGE];
     int share, e, mt, nt;
-    if (!decode_live_tile(p, BM, blockIdx.x >> 3, share, e, mt, nt)) return;
+    if (!decode_live_tile(p, BM, j, share, e, mt, nt, TRA)) return;
     const int count = group_rows(p, e);
     const int m0 = mt * BM, n0 = nt * BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int K = group_k(p, e), KT = (K + BK - 1) / BK;
+    // (transposed: the zero page stands for the k rows past the group's own, so that no padding is multiplied)
+    const int K = TRA ? (p.k_counts ? min(max(p.k_counts[e], 0), p.K) : p.K) : group_k(p, e), KT = max((K + BK - 1) / BK, 1);
     const int LA = p.lda ? p.lda : p.K, LB = p.ldb ? p.ldb : p.K;
+    const bool splitB = TRB && p.B1 != nullptr;
 
     // copy sources of this lane: row and 16-byte piece (the swizzle is applied here, on the source side)
     const float* src[NCA + NCB];
@@ -1823,29 +1840,72 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
     bool past[2];                                       // piece of the last k-tile that lies past the contraction
 #pragma unroll
     for (int h = 0; h < 2; ++h) past[h] = (KT - 1) * BK + 4 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7)) >= K;
+    // transposed: k row of copy i of a wave's NC and first row of the piece
+    constexpr int PA = BM / 4, PB = BN / 4;             // 16-byte pieces of a k row
+    auto k_of = [&](int i, int NC, int pieces) { return ((wave * NC + i) * 64 + lane) / pieces; };
+    auto r_of = [&](int i, int NC, int pieces) {
+        const int slot = ((wave * NC + i) * 64 + lane) % pieces;
+        return 16 * ((slot >> 2) ^ ((k_of(i, NC, pieces) >> 2) & (pieces / 4 - 1))) + 4 * (slot & 3);
+    };
 #pragma unroll
     for (int i = 0; i < NCA; ++i) {
-        const int r = (wave * NCA + i) * 8 + r8;
-        int m = min(m0 + r, count - 1);                 // rows past the count replay a valid row; never stored
-        if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
-        src[i] = static_cast<const float*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA) +
-                 static_cast<size_t>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7));
+        if constexpr (TRA) {
+            src[i] = static_cast<const float*>(p.A) + (p.k_gather == 1 ? 0 : static_cast<size_t>(e) * p.K * LA) +
+                     min(m0 + r_of(i, NCA, PA), p.capacity - 4);         // (pieces past the row repeat; never stored)
+        } else {
+            const int r = (wave * NCA + i) * 8 + r8;
+            int m = min(m0 + r, count - 1);             // rows past the count replay a valid row; never stored
+            if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
+            src[i] = static_cast<const float*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA) +
+                     static_cast<size_t>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7));
+        }
     }
 #pragma unroll
     for (int i = 0; i < NCB; ++i) {
-        const int r = (wave * NCB + i) * 8 + r8;
-        const bool second = GLU && r >= BN;
-        const int n = min(n0 + (second ? r - BN : r), p.N - 1);
-        src[NCA + i] = static_cast<const float*>(second ? p.B1 : p.B0) + (static_cast<size_t>(e) * p.N + n) * LB +
-                       4 * ((lane & 7) ^ ((r >> 1) & 7));
+        if constexpr (TRB) {
+            src[NCA + i] = static_cast<const float*>(p.B0) +
+                           (p.k_gather == 2 ? 0 : static_cast<size_t>(e) * (splitB ? p.K / 2 : p.K) * LB) + min(n0 + r_of(i, NCB, PB), p.N - 4);
+        } else {
+            const int r = (wave * NCB + i) * 8 + r8;
+            const bool second = GLU && r >= BN;
+            const int n = min(n0 + (second ? r - BN : r), p.N - 1);
+            src[NCA + i] = static_cast<const float*>(second ? p.B1 : p.B0) + (static_cast<size_t>(e) * p.N + n) * LB +
+                           4 * ((lane & 7) ^ ((r >> 1) & 7));
+        }
     }
+    const ptrdiff_t to_second = splitB ? static_cast<const float*>(p.B1) - static_cast<const float*>(p.B0) - static_cast<ptrdiff_t>(K / 2) * LB : 0;
+    // row numbers of this lane's gathered k rows in the k-tile requested next
+    constexpr int NG = TRA ? (NCA > NCB ? NCA : NCB) : 1;
+    int rows[NG], rows_next[NG];
+    auto load_rows = [&](int kt, int (&rows)[NG]) {
+        if constexpr (TRA) {
+            if (p.k_gather) {
+#pragma unroll
+                for (int i = 0; i < NG; ++i) {
+                    const int k = min(kt, KT - 1) * BK + (p.k_gather == 1 ? k_of(i < NCA ? i : 0, NCA, PA) : k_of(i < NCB ? i : 0, NCB, PB));
+                    rows[i] = min(max(p.k_index[static_cast<size_t>(e) * p.k_index_stride + min(k, p.k_index_stride - 1)], 0), p.k_rows - 1);
+                }
+            }
+        }
+    };
     auto copy_tile = [&](int kt, int buf) {
         const bool last = kt == KT - 1;
 #pragma unroll
         for (int i = 0; i < NCA + NCB; ++i) {
-            const int group = i < NCA ? wave * NCA + i : wave * NCB + i - NCA;           // of 8 rows; its parity picks the swizzle half
-            const float* g = last && past[group & 1] ? kZeroPiece : src[i] + static_cast<size_t>(kt) * BK;
-            uint4* dst = lds + buf * STAGE + (i < NCA ? 0 : BM * CPR) + group * 64;
+            const bool a = i < NCA;
+            const int n = a ? i : i - NCA, group = wave * (a ? NCA : NCB) + n;           // of 8 rows; its parity picks the swizzle half
+            const float* g;
+            if (a ? TRA : TRB) {
+                const int k = kt * BK + (a ? k_of(n, NCA, PA) : k_of(n, NCB, PB));
+                const bool by_index = TRA && p.k_gather == (a ? 1 : 2);
+                const int row = by_index ? rows[n < NG ? n : 0] : k;
+                g = src[i] + static_cast<size_t>(row) * (a ? LA : LB);
+                if (!a && splitB && k >= K / 2) g += to_second;
+                if (k >= K) g = kZeroPiece;
+            } else {
+                g = last && past[group & 1] ? kZeroPiece : src[i] + static_cast<size_t>(kt) * BK;
+            }
+            uint4* dst = lds + buf * STAGE + (a ? 0 : BM * CPR) + group * 64;
             __builtin_amdgcn_global_load_lds((global_cptr)g, (lds_ptr)dst, 16, 0, 0);
         }
     };
@@ -1856,13 +1916,22 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int n = 0; n < TN; ++n)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[b][i][j][v] = 0.f;
+                for (int v = 0; v < 4; ++v) acc[b][i][n][v] = 0.f;
 
-    for (int t = 0; t < AHEAD; ++t) copy_tile(min(t, KT - 1), t);
+    for (int t = 0; t < AHEAD; ++t) {
+        load_rows(t, rows);
+        copy_tile(min(t, KT - 1), t);
+    }
+    load_rows(AHEAD, rows);
     const int l16 = lane & 15, kq = lane >> 4;
     const int ck[2] = {kq ^ (l16 >> 1), (4 + kq) ^ (l16 >> 1)};
+    // fragment of the 16-row block blk of an operand of `pieces` pieces a k row
+    auto transposed = [&](const uint4* at, int pieces, int blk, int ks) {
+        const float* f = reinterpret_cast<const float*>(at) + (16 * ks + 4 * kq) * pieces * 4 + 16 * (blk ^ (kq & (pieces / 4 - 1))) + l16;
+        return f32x4{f[0], f[pieces * 4], f[pieces * 8], f[pieces * 12]};
+    };
     int buf = 0;
     for (int kt = 0; kt < KT; ++kt) {
         // this wave's share of k-tile kt has landed and its reads of k-tile kt - 1 are done; past the barrier that
@@ -1870,18 +1939,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
         __builtin_amdgcn_s_waitcnt(waitcnt_imm((AHEAD - 1) * (NCA + NCB), true));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
+        load_rows(kt + AHEAD + 1, rows_next);            // in front of the copies: its wait leaves them in flight
         copy_tile(min(kt + AHEAD, KT - 1), buf == 0 ? NBUF - 1 : buf - 1);
-        const uint4* As = lds + buf * STAGE + (wm * (BM / 2) + l16) * CPR;
-        const uint4* Bs = lds + buf * STAGE + BM * CPR + (wn * (BN / 2) + l16) * CPR;
+        const uint4* Ab = lds + buf * STAGE;
+        const uint4* Bb = Ab + BM * CPR;
+        const uint4* As = Ab + (wm * (BM / 2) + l16) * CPR;
+        const uint4* Bs = Bb + (wn * (BN / 2) + l16) * CPR;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             f32x4 fa[TM], fb[NB][TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) fa[i] = __builtin_bit_cast(f32x4, As[i * 16 * CPR + ck[ks]]);
+            for (int i = 0; i < TM; ++i) {
+                if constexpr (TRA) fa[i] = transposed(Ab, PA, wm * TM + i, ks);
+                else fa[i] = __builtin_bit_cast(f32x4, As[i * 16 * CPR + ck[ks]]);
+            }
 #pragma unroll
             for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) fb[b][j] = __builtin_bit_cast(f32x4, Bs[(b * BN + j * 16) * CPR + ck[ks]]);
+                for (int n = 0; n < TN; ++n) {
+                    if constexpr (TRB) fb[b][n] = transposed(Bb, PB, wn * TN + n, ks);
+                    else fb[b][n] = __builtin_bit_cast(f32x4, Bs[(b * BN + n * 16) * CPR + ck[ks]]);
+                }
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -1889,10 +1967,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int j = 0; j < TN; ++j)
-                            acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][j][v], fa[i][v], acc[b][i][j], 0, 0, 0);
+                        for (int n = 0; n < TN; ++n)
+                            acc[b][i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][n][v], fa[i][v], acc[b][i][n], 0, 0, 0);
         }
         buf = buf == NBUF - 1 ? 0 : buf + 1;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) rows[i] = rows_next[i];
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));    // the copies past the end: nothing may land in LDS after the wave
 
@@ -1904,13 +1984,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
         const int m = m0 + wm * (BM / 2) + i * 16 + l16;
         if (m >= count) continue;
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn * (BN / 2) + j * 16 + kq * 4;
+        for (int c = 0; c < TN; ++c) {
+            const int n = n0 + wn * (BN / 2) + c * 16 + kq * 4;
             if (n >= p.N) continue;                               // N % 4 == 0
             const size_t o = static_cast<size_t>(m) * p.N + n;
-            f32x4 r = acc[0][i][j];
+            f32x4 r = acc[0][i][c];
             if constexpr (GLU) {
-                const f32x4 u = acc[1][i][j];
+                const f32x4 u = acc[1][i][c];
                 if constexpr (DUAL) {
                     *reinterpret_cast<f32x4*>(static_cast<float*>(p.C2) + eoff + o) = u;
                 } else {
@@ -1925,6 +2005,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
             *reinterpret_cast<f32x4*>(Cg + o) = r;
         }
     }
+}
+template <int BM, int BN, int NBUF, bool GLU, bool DUAL = false, bool TRB = false>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
+    __shared__ __attribute__((aligned(16))) uint4 lds[f32_pieces<BM, BN, NBUF, GLU>()];
+    gemm_f32_tile<BM, BN, NBUF, GLU, DUAL, false, TRB>(p, blockIdx.x >> 3, lds);
+}
+
+// The last products of the backward in one launch, as in gemm_bf16_backward_kernel: the workgroups of p[0], the input
+// gradient, come first, and the tiles of the weight gradients fill in behind them as CUs fall free.
+// MEASURED
+struct BackwardProductsF32 { GemmParams p[4]; int first[4]; };       // first[i]: workgroup at which product i begins (a multiple of 8)
+template <int BM, int BN, int NBUF>
+__global__ __launch_bounds__(256, 2) void gemm_f32_backward_kernel(BackwardProductsF32 b) {
+    __shared__ __attribute__((aligned(16))) uint4 lds[f32_pieces<BM, BN, NBUF, false>()];
+    const int blk = blockIdx.x;
+    if (blk < b.first[1]) {
+        gemm_f32_tile<BM, BN, NBUF, false, false, false, true>(b.p[0], blk >> 3, lds);
+        return;
+    }
+    const int i = blk >= b.first[3] ? 3 : (blk >= b.first[2] ? 2 : 1);
+    gemm_f32_tile<BM, BN, NBUF, false, false, true, true>(b.p[i], (blk - b.first[i]) >> 3, lds);
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, bool GLU, int SWZ, bool DUAL = false>
@@ -2026,15 +2127,33 @@ hipError_t launch_bf16_rows(GemmParams p, hipStream_t st) {
 inline bool f32_large_tiles(const GemmParams& p) {
     return static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64) >= 2ll * cu_count();
 }
-template <bool GLU, bool DUAL = false>
+template <bool GLU, bool DUAL = false, bool TRB = false>
 hipError_t launch_f32(GemmParams p, hipStream_t st) {
     if (f32_large_tiles(p)) {
         const long long blocks = plan_live_tiles(p, 64, 64);
-        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL, TRB>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     } else {
         const long long blocks = plan_live_tiles(p, 32, 32);
-        hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4, GLU, DUAL>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4, GLU, DUAL, TRB>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     }
+    return hipGetLastError();
+}
+// Products [from, to) of b in one launch (as many workgroups as one launch may hold, else one by one).
+template <int T, int NBUF>
+hipError_t launch_f32_backward_tiles(BackwardProductsF32 b, int from, int to, hipStream_t st) {
+    long long at = 0;
+    for (int i = 0; i < 4; ++i) {
+        b.first[i] = static_cast<int>(std::min<long long>(at, 1 << 30));
+        if (i >= from && i < to) at += (plan_live_tiles(b.p[i], T, T) + 63) / 64 * 64;
+    }
+    if (at > (1 << 23) && to - from > 1) {               // 2^31 threads
+        for (int i = from; i < to; ++i) {
+            const hipError_t err = launch_f32_backward_tiles<T, NBUF>(b, i, i + 1, st);
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((gemm_f32_backward_kernel<T, T, NBUF>), dim3(static_cast<unsigned>(at)), dim3(256), 0, st, b);
     return hipGetLastError();
 }
 
@@ -2170,6 +2289,18 @@ bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
 }
 
 hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& down, const GroupedGemm* gates, int n_gates, hipStream_t st) {
+    if (dx.dtype == ETR_F32) {
+        BackwardProductsF32 f{};
+        long long tiles = 0;
+        for (int i = 0; i < 2 + n_gates; ++i) {
+            const GroupedGemm& q = i == 0 ? dx : (i == 1 ? down : gates[i - 2]);
+            if (!q.tb || q.ta != (i > 0) || q.split_m || q.N < 8 || q.M < 4 || (i > 0 && q.M < 8)) return hipErrorInvalidValue;
+            f.p[i] = params_of(q);
+            tiles += static_cast<long long>(q.G) * ((q.M + 63) / 64) * ((q.N + 63) / 64);
+        }
+        return tiles >= 2ll * cu_count() ? launch_f32_backward_tiles<64, 3>(f, 0, 2 + n_gates, st)
+                                         : launch_f32_backward_tiles<32, 4>(f, 0, 2 + n_gates, st);
+    }
     BackwardProducts b{};
     const bool fetch = down.k_gather == 1;
     if (n_gates < 1 || n_gates > 2 || dx.ta || !down.ta || down.k_gather == 2) return hipErrorInvalidValue;
@@ -2190,6 +2321,10 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
 hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     GemmParams g = params_of(q);
     if (q.N % 4 != 0 || q.K < 0 || q.G < 1 || q.M < 1) return hipErrorInvalidValue;
+    if (q.dtype == ETR_F32 && q.tb) {
+        if (q.ta || q.epilogue != GEMM_PLAIN || q.N < 8) return hipErrorInvalidValue;
+        return launch_f32<false, false, true>(g, st);
+    }
     if (q.ta || q.tb) {
         if (!grouped_gemm_transposed_ok(q)) return hipErrorInvalidValue;
         const int n_cu = cu_count();
