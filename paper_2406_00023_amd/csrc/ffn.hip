@@ -881,11 +881,12 @@ __device__ __forceinline__ void request_row_ids(const GemmParams& p, int e, int 
 // for nobody reads that buffer any more: behind one wait (all copies landed, all own LDS reads done) and one
 // barrier it is released.
 //
-// Copies (global_load_lds, no registers).  A wave's copies of k-tile g + 2 go out behind every other MFMA of the
-// first half of two substeps: its groups of token rows in the fourth substep of step g (right behind the barrier),
-// its groups of weight rows in the first substep of step g + 1.  All eight in one substep is twice what a CU's
-// address unit takes in that time, and a wave that waits for a slot there issues no MFMA either (7 % slower); half
-// a substep later in each costs 1-4 %.  All of them land before the barrier of step g + 1.  The weight rows of a
+// Copies (global_load_lds, no registers).  A wave's copies of k-tile g + 2 go out in two bursts, each behind the first MFMA
+// of a substep: its groups of token rows in the fourth substep of step g (right behind the barrier), its groups of weight
+// rows in the first substep of step g + 1.  They are bound by the time they take to land, before the barrier of step
+// g + 1: spread behind every other MFMA of half a substep they cost 1-2 % more (gate/up and down product, 16 experts of 1280,
+// 4096 x 11008: 4177 / 4110 us; 8 of 32 000, 4096 x 1408: 6601 / 6525; 16 of 600-1024, 2048 x 5632: 871 / 852), half a substep
+// later another 1-4 %.  All eight in one substep is twice what a CU's address unit takes in that time (5-10 %).  The weight rows of a
 // tile are whole column tiles (a launch condition), so their addresses are a wave-uniform base plus one of two
 // per-lane offsets that never change; only the token rows carry per-tile lane offsets.  There is always something
 // to copy: past the end of a workgroup's list the last k-tile is fetched again into a buffer nobody reads any
@@ -1090,7 +1091,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
             substep(0, [&](int m) {                      // token blocks 4..7 of this k-step, half of the next k-step's weights,
                 if (m < 4) read_a(buf, 0, 1, m);         // and the weight rows of k-tile g + 1 into the other buffer
                 else if (m < 6) read_b(buf, 1, m - 4);
-                if (m < 8 && (m & 1)) copy_b(lateB, buf ^ 1, m >> 1, late_last);
+                if (m == 0) {
+#pragma unroll
+                    for (int i = 0; i < NCP; ++i) copy_b(lateB, buf ^ 1, i, late_last);
+                }
             });
             substep(1, [&](int m) {
                 if (m < 4) read_a(buf, 1, 0, m);
@@ -1106,7 +1110,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
             substep(3, [&](int m) {                      // the next k-tile's first fragments, and the token rows of k-tile
                 if (m < 4) read_a(buf ^ 1, 0, 0, m);     // g + 2 into the buffer just released
                 else if (m < 8) read_b(buf ^ 1, 0, m - 4);
-                if (m < 8 && (m & 1)) copy_a(baseA, offs[m >> 1], buf, m >> 1);
+                if (m == 0) {
+#pragma unroll
+                    for (int i = 0; i < NCP; ++i) copy_a(baseA, offs[i], buf, i);
+                }
             });
             lateB = baseB;
             late_last = last;
