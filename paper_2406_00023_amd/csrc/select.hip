@@ -367,7 +367,10 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
     // The key theta at which that sum reaches the threshold is found digit by digit, as the capacity threshold below
     // is: an LDS histogram of the terms (64-bit sums) over 11, 11 and 9 bits below the sign, walked from the top.  (A
     // bisection over the 31 bits sums all keys up to 33 times: 64 experts x 65536 tokens, 378 us for the kernel; with
-    // the histograms 38 us.)
+    // the histograms 38 us.)  Where the sum binds before the capacity, theta is the threshold the search below would look
+    // for: the n_keep candidates end among the keys equal to it.
+    bool settled = false;
+    uint32_t theta = 0u;
     if constexpr (ADAPT) if (sum_need > 0 && (mode == ETR_MODE_ECR || mode == ETR_MODE_BIDIR) && n_keep > 0) {
         __shared__ __attribute__((aligned(16))) unsigned long long sums[kBins];
         __shared__ int red_cnt[kSelThreads / kWave];
@@ -437,7 +440,9 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
             for (int w = 0; w < kSelThreads / kWave; ++w) n_gt += red_cnt[w];
             const long long q_th = affinity_term(th);
             const long long ell = n_gt + (sum_need - above_sum + q_th - 1) / q_th;       // q_th > 0: its bin reached the sum
-            if (ell < n_keep) n_keep = static_cast<int>(ell);
+            settled = ell <= n_keep;
+            theta = th;
+            if (settled) n_keep = static_cast<int>(ell);
         }
     }
 
@@ -446,6 +451,8 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
         tau = 0xFFFFFFFFu;
     } else if (mode == ETR_MODE_TCR) {
         tau = 1u;                                       // every candidate carries key 1
+    } else if (ADAPT && settled) {
+        tau = theta;
     } else {
         // The n_keep-th largest key, by radix search from the top.  Only the bits in which the candidates differ
         // have to be resolved (affinities of one expert share sign, exponent and often leading mantissa bits), so
