@@ -288,7 +288,8 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
                                                  const int32_t* __restrict__ slot_of, const float* __restrict__ dgate_part, int n_part,
                                                  const T* __restrict__ dxp, T* __restrict__ dx, float* __restrict__ dgate_out,
                                                  float* __restrict__ dscore_out, int T_, int d, int E, int D, int C,
-                                                 int cos_mode, int gate_norm, int Cx) {     // Cx: rows per expert of dxp
+                                                 int cos_mode, int gate_norm, int Cx,       // Cx: rows per expert of dxp
+                                                 int pieces) {       // > 1: dxp is float [pieces][E][Cx][d], to be added up
     extern __shared__ float sm[];
     const int P = d / D;
     float* w = sm;                       // [E][P]
@@ -452,7 +453,24 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
         }
         // ascending expert order, as in the forward sum; four rows requested at a time (past the last kept pair the
         // last one is requested again and not added)
-        for (int i0 = 0; i0 < n_kept; i0 += 4) {
+        for (int i0 = 0; pieces > 1 && i0 < n_kept * pieces; i0 += 4) {          // (few rows: out of the caches)
+            float r[4][V];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int at = min(i0 + q, n_kept * pieces - 1), i = at / pieces;
+                const float* src = reinterpret_cast<const float*>(dxp) + (static_cast<size_t>(at - i * pieces) * E * Cx + sl[i]) * d + j;
+#pragma unroll
+                for (int h = 0; h < V; h += 4) Elt<float>::load_vec(src + h, r[q] + h);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (i0 + q < n_kept * pieces) {
+#pragma unroll
+                    for (int i = 0; i < V; ++i) acc[i] += r[q][i];
+                }
+            }
+        }
+        for (int i0 = 0; pieces <= 1 && i0 < n_kept; i0 += 4) {
             float r[4][V];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -476,6 +494,25 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
 int padded_capacity(const etr_config& c) {
     const int Cp = (c.capacity + 63) / 64 * 64;
     return c.dtype == ETR_BF16 && Cp < 128 ? 128 : Cp;
+}
+
+// Parts of the input gradient's contraction (bf16, one launch with the weight gradients).  It has few tiles of 2 H / 64
+// k-tiles; where one of them is longer than an even share of all the launch's k-tiles, it is what the launch waits for, so it
+// is cut until it is not: each part's sums go to memory in fp32 and dx_kernel adds them up.  The parts lie where the
+// weights' transposes would.  Step, one part / cut: 8 experts, 1024 x 2816, 64 tokens
+// (32 tiles of 88 k-tiles, 3 parts): 246 / 186 us; 8 of 64 rows, 2048 x 5632: 646 / 588; 16 of 64, 1024 x 2816: 369 / 336; 8 of
+// 128, 2048 x 2816: 417 / 395; 16 of 64, 1080 x 1000: 202 / 195.
+int dx_pieces(const etr_config& c, int Cp, bool fetch_rows) {
+    const int KT = 2 * ((c.H + 63) / 64), rows = rows_expected(c), kr = (rows + 63) / 64;
+    const double columns = (c.d + 255) / 256, tiles = c.E * ((rows + 255) / 256) * columns;
+    const double steps = tiles * KT + 3.0 * c.E * columns * ((c.H + 255) / 256) * ((kr > (fetch_rows ? 4 : 2) ? kr : (fetch_rows ? 4 : 2)) + 2);
+    const double share = steps / cu_count() > 12.0 ? steps / cu_count() : 12.0;
+    const double room = 3.0 * c.E * c.H * c.d * elt_bytes(c.dtype), each = 4.0 * c.E * Cp * c.d;
+    const long long supers = static_cast<long long>(c.E) * ((Cp + 255) / 256) * ((c.d + 255) / 256);
+    int pieces = 1;
+    while (pieces < 8 && KT > 1.2 * share * pieces) ++pieces;
+    while (pieces > 1 && (KT - (pieces - 1) * ((KT + pieces - 1) / pieces) < 2 || pieces * each > room || pieces * supers > 2048)) --pieces;
+    return pieces;
 }
 
 struct BackwardWs {
@@ -577,7 +614,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     both.M = 2 * H; both.a_rows = 2 * H; both.C = dw_gate; both.C2 = dw_up; both.split_m = H;
     const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;        // (fp32: 2)
     if (n_gates == 1) gates[0] = both;
-    int dxp_rows = C;
+    int dxp_rows = C, pieces = 1;
     if (direct) {
         // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
         // that weight transposed once per call.  The copy moves E*d*H elements, the product works on every kept row, so it
@@ -622,6 +659,9 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             ETR_BW(launch_grouped_gemm(down, st));
             for (int i = 0; i < n_gates; ++i) ETR_BW(launch_grouped_gemm(gates[i], st));
         } else {
+            if (!f32 && !nt_u) pieces = dx_pieces(c, Cp, fetch_rows);
+            t3.pieces = pieces;
+            if (pieces > 1) t3.C = at(L.wdT);            // (behind it the gate and up projections' room, unused here as well)
             ETR_BW(launch_backward_products(t3, down, gates, n_gates, st));
         }
         dxp_rows = Cp;
@@ -661,8 +701,8 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     auto kern = dx_kernel<T>;
     ETR_BW(ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds));
     hipLaunchKernelGGL(kern, dim3((Tn + 3) / 4), dim3(256), lds, st, static_cast<const T*>(x), w_emb, score, gate, slot_of,
-                       dgate_part, static_cast<int>(cH), at(L.dxp), static_cast<T*>(dx), dgate, dscore,
-                       Tn, d, E, c.D, C, static_cast<int>(c.cos), static_cast<int>(c.gate_norm), dxp_rows);
+                       dgate_part, static_cast<int>(cH), pieces > 1 ? at(L.wdT) : at(L.dxp), static_cast<T*>(dx), dgate, dscore,
+                       Tn, d, E, c.D, C, static_cast<int>(c.cos), static_cast<int>(c.gate_norm), dxp_rows, pieces);
 #undef ETR_BW
     return hipGetLastError();
 }

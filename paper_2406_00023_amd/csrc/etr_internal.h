@@ -96,6 +96,8 @@ struct GroupedGemm {
     // rows of all groups together that the batch can fill (0: unknown); sizes the grid of the kernel for few rows, which
     // still covers every row that m_counts names
     long long rows_total = 0;
+    // input gradient in launch_backward_products, bf16: the contraction in this many parts; C is float [pieces][G][M][N]
+    int pieces = 1;
 };
 hipError_t launch_grouped_gemm(const GroupedGemm& g, hipStream_t st);
 bool grouped_gemm_transposed_ok(const GroupedGemm& g);

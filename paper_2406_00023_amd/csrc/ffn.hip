@@ -55,6 +55,9 @@ struct GemmParams {
     // to C, the others (as rows m - split_m) to C2, both [E][split_m][N] (a multiple of 32, capacity = 2 split_m).
     int split_m = 0;
     long long rows_total = 0;   // host only: rows of all groups together that the batch can fill (0: unknown)
+    // Input gradient only (transposing kernel, row-major A): the contraction in `pieces` parts, each a tile of its own whose
+    // fp32 sums go to C as [pieces][E][capacity][N] (NT counts the column tiles of all parts)
+    int pieces = 1;
 };
 
 // rows of group e (counts may be absent: every group has `capacity` rows) and its contraction length
@@ -1219,10 +1222,12 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     tiles.build<NW * 64>(p, BM, sh.pre, sh.wave_tot, sh.rows_of_group);
     const int total = tiles.total;
     Deal deal;
-    state.deal(p, tiles, TRA ? 0 : (splitB ? 2 * KTh : KTh), deal);
+    const int k_all = splitB ? 2 * KTh : KTh, k_piece = (k_all + p.pieces - 1) / p.pieces;      // k-tiles of the product, of a part
+    state.deal(p, tiles, TRA ? 0 : k_piece, deal);
 
     struct Tile {
         int e, m0, n0, count, KT;
+        int k0, piece;                                   // first k-tile, part of the contraction
         uint64_t Abase, Bbase, Bbase1;                   // wave-uniform; Bbase1: second half of a split B
         uint32_t offA[TRA ? 1 : NCP];                    // row-major A: byte offsets of this lane's row groups
     };
@@ -1240,9 +1245,12 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
 
     auto fill = [&](const LiveTiles::Place& at, Tile& t) {              // scalar part of a tile
         const int e = at.e;
-        t.e = e; t.m0 = at.mt * BM; t.n0 = at.nt * BN;
+        const int columns = (p.N + BN - 1) / BN;
+        t.piece = !TRA && p.pieces > 1 ? small_div(at.nt, columns) : 0;
+        t.e = e; t.m0 = at.mt * BM; t.n0 = (at.nt - t.piece * columns) * BN;
         t.count = tiles.count(e);
-        t.KT = TRA ? tiles.k_tiles(e) : (splitB ? 2 * KTh : KTh);
+        t.k0 = t.piece * k_piece;
+        t.KT = TRA ? tiles.k_tiles(e) : min(k_piece, k_all - t.k0);
         t.Abase = reinterpret_cast<uint64_t>(p.A);
         if (KG != 1) t.Abase += TRA ? static_cast<uint64_t>(e) * p.K * lda * 2
                                     : (p.row_index ? 0 : static_cast<uint64_t>(e) * p.capacity * lda * 2);
@@ -1475,23 +1483,23 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     for (int t = 0; t < 2; ++t) {                        // KT >= 2 is a launch condition
         if constexpr (KG == 1) row_a = row_offset(load_index(cur.e, t));
         if constexpr (KG == 2) row_b = row_offset(load_index(cur.e, t));
-        const uint64_t baseA = a_ktile(cur.Abase, t), baseB = b_ktile(cur.Bbase, cur.Bbase1, t);
+        const uint64_t baseA = a_ktile(cur.Abase, cur.k0 + t), baseB = b_ktile(cur.Bbase, cur.Bbase1, cur.k0 + t);
 #pragma unroll
         for (int i = 0; i < NCP; ++i) {
             uint32_t off = row_a;
-            if constexpr (!TRA) off = is_short(t) && over_a[i & 1] ? kPastRange : cur.offA[i];
+            if constexpr (!TRA) off = is_short(cur.k0 + t) && over_a[i & 1] ? kPastRange : cur.offA[i];
             copy_a(baseA, off, cur.m0, t, i);
         }
 #pragma unroll
-        for (int i = 0; i < NCP; ++i) copy_b(baseB, row_b, cur.n0, is_short(t), t, i);
+        for (int i = 0; i < NCP; ++i) copy_b(baseB, row_b, cur.n0, is_short(cur.k0 + t), t, i);
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * NCP, false));             // the first k-tile (copies retire in order)
     __builtin_amdgcn_s_barrier();
     read_first();
     // B rows still owed to the other buffer (none yet: the second k-tile's own once more)
-    uint64_t late_base = b_ktile(cur.Bbase, cur.Bbase1, 1);
+    uint64_t late_base = b_ktile(cur.Bbase, cur.Bbase1, cur.k0 + 1);
     int late_n0 = cur.n0;
-    bool late_last = is_short(1);
+    bool late_last = is_short(cur.k0 + 1);
     for (;;) {
         if (has_next) {
             fill(next_at, nxt);
@@ -1513,7 +1521,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
             // k-tile g + 2: of this tile, else of the next one, else (nothing left) this tile's last one again
             const bool in_cur = kt + 2 < KT;
             const bool from_next = !in_cur && has_next;
-            const int kf = in_cur ? kt + 2 : (from_next ? kt + 2 - KT : KT - 1);
+            const int kf = in_cur ? cur.k0 + kt + 2 : (from_next ? nxt.k0 + kt + 2 - KT : cur.k0 + KT - 1);
             const uint64_t baseA = a_ktile(from_next ? nxt.Abase : cur.Abase, kf);
             const uint64_t baseB = b_ktile(from_next ? nxt.Bbase : cur.Bbase, from_next ? nxt.Bbase1 : cur.Bbase1, kf);
             const int m0 = from_next ? nxt.m0 : cur.m0, n0 = from_next ? nxt.n0 : cur.n0;
@@ -1559,7 +1567,18 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         // ---- epilogue of cur (the copies of the next tile are in flight).  The patch is the wave's own copy target in the
         // B half of the buffer just multiplied: behind the last barrier nobody reads it any more, and the next copies into
         // it are the wave's own, in its next substep 0.
-        {
+        if (!TRA && p.pieces > 1) {                      // few rows: fp32 sums, 16 rows x 64 bytes an instruction
+            float* out = static_cast<float*>(p.C) + (static_cast<size_t>(cur.piece) * p.E + cur.e) * p.capacity * p.N;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int m = cur.m0 + wm * 128 + i * 16 + l16;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int n = cur.n0 + wn * 64 + j * 16 + kq * 4;
+                    if (m < cur.count && n < p.N) *reinterpret_cast<f32x4*>(out + static_cast<size_t>(m) * p.N + n) = acc[i][j];
+                }
+            }
+        } else {
             const uint32_t patch = lds_base + static_cast<uint32_t>((g - 1) & 1) * (STAGE * 16) + HALF * 16 + wave * 1024;
             const int nb = cur.n0 + wn * 64;
             auto pack4 = [](const f32x4& v) { return pack_bf16x4(v[0], v[1], v[2], v[3]); };
@@ -1601,10 +1620,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
 // gradients (p[1]: down; p[2] and, with two, p[3]: gate and up), with FETCH the rows of A, resp. B, through an index.  They do
 // not depend on each other, and the input gradient is few tiles with a long contraction (2 H): its last round leaves
 // workgroups idle, which here start on the weight gradients' many short tiles, as many rounds of them as its k-tiles stand
-// for.  Bound as the kernels above are.  Training step, a launch for each product / this: 12 experts of 677 rows, 1080 x 2744
-// (180 tiles of 86 k-tiles): 990 / 880 us; 4 of 300, 2048 x 5632: 721 / 633; 8 of 512, 1024 x 2816: 520 / 434; 16 of 166-1024,
-// 2048 x 5632 (1.6 rounds, at the power limit): 2665 / 2625; without fetched rows, 8 of 64, 2048 x 5632: 763 / 646, 32 of 32,
-// 512 x 1024: 193 / 157.
+// for.  Where even so a tile of the input gradient is longer than all the rest (few rows), its contraction comes in parts
+// (p[0].pieces, see dx_pieces in backward.hip).  Bound as the kernels above are.  Training step, a launch for each product /
+// this: 12 experts of 677 rows, 1080 x 2744 (180 tiles of 86 k-tiles): 990 / 880 us; 4 of 300, 2048 x 5632: 721 / 633; 8 of 512,
+// 1024 x 2816: 520 / 434; 16 of 166-1024, 2048 x 5632 (1.6 rounds, at the power limit): 2665 / 2625; without fetched rows, in one
+// part, 8 of 64, 2048 x 5632: 763 / 646, 32 of 32, 512 x 1024: 193 / 157.
 struct BackwardProducts { GemmParams p[4]; int n_gates; };
 template <bool TAIL, bool FETCH>
 __global__ __launch_bounds__(512) void gemm_bf16_backward_kernel(BackwardProducts b) {
@@ -2074,6 +2094,7 @@ template <bool TAIL, bool FETCH>
 hipError_t launch_bf16_backward_form(BackwardProducts b, hipStream_t st, int n_cu) {
     constexpr size_t lds = 2ull * 512 * 64 * 2;
     for (int i = 0; i < 2 + b.n_gates; ++i) plan_tiles(b.p[i], 256, 256);
+    b.p[0].NT *= b.p[0].pieces;
     auto kern = gemm_bf16_backward_kernel<TAIL, FETCH>;
     hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (err != hipSuccess) return err;
@@ -2263,6 +2284,7 @@ static GemmParams params_of(const GroupedGemm& q) {
     g.k_index = q.k_index; g.k_index_stride = q.k_index_stride; g.k_rows = q.k_rows; g.k_gather = q.k_gather;
     g.split_m = q.split_m;
     g.rows_total = q.rows_total;
+    g.pieces = q.pieces;
     return g;
 }
 
@@ -2311,6 +2333,10 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
     BackwardProducts b{};
     const bool fetch = down.k_gather == 1;
     if (n_gates < 1 || n_gates > 2 || dx.ta || !down.ta || down.k_gather == 2) return hipErrorInvalidValue;
+    if (dx.pieces > 1) {                                 // parts of two k-tiles at least, and the list of their tiles in LDS
+        const int half = dx.B1 ? dx.K / 2 : dx.K, k_all = (half + 63) / 64 * (dx.B1 ? 2 : 1), k_piece = (k_all + dx.pieces - 1) / dx.pieces;
+        if (k_all - (dx.pieces - 1) * k_piece < 2 || !persist_ok(params_of(dx), false, kMaxSuper / dx.pieces)) return hipErrorInvalidValue;
+    }
     b.n_gates = n_gates;
     b.p[0] = params_of(dx);
     b.p[1] = params_of(down);
@@ -2327,7 +2353,7 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
 
 hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
     GemmParams g = params_of(q);
-    if (q.N % 4 != 0 || q.K < 0 || q.G < 1 || q.M < 1) return hipErrorInvalidValue;
+    if (q.N % 4 != 0 || q.K < 0 || q.G < 1 || q.M < 1 || q.pieces != 1) return hipErrorInvalidValue;
     if (q.dtype == ETR_F32 && q.tb) {
         if (q.ta || q.epilogue != GEMM_PLAIN || q.N < 8) return hipErrorInvalidValue;
         return launch_f32<false, false, true>(g, st);
