@@ -10,10 +10,10 @@
 //   4. dx[t] = sum_e dXp[e][slot] + sum_e dscore[t][e] * d score[t][e] / d x[t]  (softmax and Eq. 4 differentiated)
 // Every matrix product runs on the grouped kernels of ffn.hip.  Operands whose contraction index is the
 // slow one in memory (Wd for u, Wg / Wu for dXp, the row-major activations for the weight gradients) are
-// read as they lie: the persistent kernel stages such k-tiles k-major in LDS and takes its MFMA fragments
-// through transposing LDS reads, so nothing is transposed in memory.  Only shapes that kernel does not take
-// (fp32, widths below 128) go through the fall-back that transposes the weights once per
-// call and has the element-wise kernel write transposed copies of the per-row quantities.
+// read as they lie: the bf16 kernels stage such k-tiles k-major in LDS and take their MFMA fragments through
+// transposing LDS reads, the fp32 ones read single elements, so nothing is transposed in memory.  Only bf16 widths
+// below 128 go through the fall-back that transposes the weights once per call and has the element-wise kernel
+// write transposed copies of the per-row quantities.  Products that do not depend on each other share a launch.
 #include "etr_internal.h"
 
 namespace etr {
@@ -592,7 +592,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     t5.ta = t5.tb = true;
     GroupedGemm t6 = t5;
     t6.A = at(L.dab) + H; t6.C = dw_up;
-    const bool f32 = c.dtype == ETR_F32;                 // its kernel takes all widths
+    constexpr bool f32 = sizeof(T) == 4;                 // its kernel takes all widths
     const bool direct = f32 || (grouped_gemm_transposed_ok(t2) && grouped_gemm_transposed_ok(t3) && grouped_gemm_transposed_ok(t4) &&
                         grouped_gemm_transposed_ok(t5) && grouped_gemm_transposed_ok(t6));
     // The same three weight-gradient products with the rows of dOut and x fetched through slot_token by the
@@ -614,6 +614,12 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     both.M = 2 * H; both.a_rows = 2 * H; both.C = dw_gate; both.C2 = dw_up; both.split_m = H;
     const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;        // (fp32: 2)
     if (n_gates == 1) gates[0] = both;
+    // dst[e][c][col0 + r] = src[e][r][c] for a [R][Cc] weight
+    auto transpose_weights = [&](const void* src, size_t dst, int R, int Cc, int ld, int col0) {
+        if constexpr (!f32)
+            hipLaunchKernelGGL(transpose_kernel<T>, dim3((Cc + kTile - 1) / kTile, (R + kTile - 1) / kTile, E), dim3(kTileThreads), 0, st,
+                               static_cast<const T*>(src), at(dst), R, Cc, ld, col0);
+    };
     int dxp_rows = C, pieces = 1;
     if (direct) {
         // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
@@ -625,8 +631,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         const bool many_rows = !f32 && C >= 8192;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
-            hipLaunchKernelGGL(transpose_kernel<T>, dim3(cH, cd, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_down),
-                               at(L.wdT), d, H, d, 0);
+            transpose_weights(w_down, L.wdT, d, H, d, 0);
             ETR_BW(hipGetLastError());
             GroupedGemm g2{dout, at(L.wdT), nullptr, at(L.u), nullptr, counts, nullptr, slot_token, E, C, H, d, 0, 0, Tn, GEMM_PLAIN, c.dtype};
             ETR_BW(launch_grouped_gemm(g2, st));
@@ -637,7 +642,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             hipLaunchKernelGGL((swiglu_backward_kernel<T, true, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a,
                                pre_b, gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr),
                                at(L.hT), dgate_part, Tn, E, C, Cp, H);
-        } else {
+        } else if constexpr (!f32) {
             hipLaunchKernelGGL((swiglu_backward_kernel<T, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a, pre_b,
                                gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr), at(L.hT),
                                dgate_part, Tn, E, C, Cp, H);
@@ -649,10 +654,8 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         }
         ETR_BW(hipGetLastError());
         if (nt_dxp) {
-            hipLaunchKernelGGL(transpose_kernel<T>, dim3(cd, cH, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_gate),
-                               at(L.wguT), H, d, 2 * H, 0);
-            hipLaunchKernelGGL(transpose_kernel<T>, dim3(cd, cH, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_up),
-                               at(L.wguT), H, d, 2 * H, H);
+            transpose_weights(w_gate, L.wguT, H, d, 2 * H, 0);
+            transpose_weights(w_up, L.wguT, H, d, 2 * H, H);
             ETR_BW(hipGetLastError());
             GroupedGemm g3{at(L.dab), at(L.wguT), nullptr, at(L.dxp), nullptr, counts, nullptr, nullptr, E, Cp, d, 2 * H, 0, 0, Cp, GEMM_PLAIN, c.dtype};
             ETR_BW(launch_grouped_gemm(g3, st));
@@ -665,16 +668,13 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             ETR_BW(launch_backward_products(t3, down, gates, n_gates, st));
         }
         dxp_rows = Cp;
-    } else {
-        // Fallback (fp32, or shapes the transposing kernel does not take): every product on the "NT" kernel, with
+    } else if constexpr (!f32) {
+        // Fallback (bf16 shapes that the transposing kernel does not take): every product on the "NT" kernel, with
         // the weights transposed once per call and transposed copies of the per-row quantities.
         // WdT[e][H][d], WguT[e][d][2H] = (Wg^T | Wu^T)
-        hipLaunchKernelGGL(transpose_kernel<T>, dim3(cH, cd, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_down),
-                           at(L.wdT), d, H, d, 0);
-        hipLaunchKernelGGL(transpose_kernel<T>, dim3(cd, cH, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_gate),
-                           at(L.wguT), H, d, 2 * H, 0);
-        hipLaunchKernelGGL(transpose_kernel<T>, dim3(cd, cH, E), dim3(kTileThreads), 0, st, static_cast<const T*>(w_up),
-                           at(L.wguT), H, d, 2 * H, H);
+        transpose_weights(w_down, L.wdT, d, H, d, 0);
+        transpose_weights(w_gate, L.wguT, H, d, 2 * H, 0);
+        transpose_weights(w_up, L.wguT, H, d, 2 * H, H);
         ETR_BW(hipGetLastError());
         GroupedGemm g2{dout, at(L.wdT), nullptr, at(L.u), nullptr, counts, nullptr, slot_token, E, C, H, d, 0, 0, Tn, GEMM_PLAIN, c.dtype};
         ETR_BW(launch_grouped_gemm(g2, st));

@@ -68,7 +68,7 @@ long long rows_total(const etr_config& c);   // rows of all experts together tha
 // A is [G][M][lda] (or, with row_index[G][M], row row_index[g][m] of one [a_rows][lda] matrix),
 // B0/B1 are [G][N][ldb], C/C2 are [G][M][N], all of the layer's dtype.  m_counts (optional) bounds the
 // rows of each group, k_counts (optional) its contraction length: it is rounded up to a multiple of
-// 64, at least 128 (at most K), and the operands must hold zeros in that padding.
+// 64, at least 128 (at most K), and the operands must hold zeros in that padding (fp32 with ta: exactly k_counts).
 enum GemmEpilogue { GEMM_PLAIN = 0, GEMM_SWIGLU = 1, GEMM_DUAL = 2 };   // C = A B0^T | SiLU(A B0^T) .* (A B1^T) | both products
 struct GroupedGemm {
     const void* A; const void* B0; const void* B1;
@@ -77,7 +77,7 @@ struct GroupedGemm {
     int G, M, N, K, lda, ldb, a_rows;
     int epilogue;
     int dtype;
-    // Operands with the contraction index slow (bf16, plain epilogue only; see grouped_gemm_transposed_ok):
+    // Operands with the contraction index slow (plain epilogue only; bf16: see grouped_gemm_transposed_ok):
     // ta: A is [G][K][lda] holding A[g][m][k] at (k, m); tb: B0 is [G][K][ldb] holding B[g][n][k] at (k, n).
     // With tb and B1 the contraction is split in the middle: B0 and B1 are [G][K/2][ldb] each.
     bool ta = false, tb = false;

@@ -161,8 +161,8 @@ __device__ __forceinline__ bool decode_tile(const GemmParams& p, int& e, int& mt
 // slice share an L2.  Dealing super-tiles of the capacity instead left XCDs with half-dead ones: 8 fp32 experts of
 // 66-640 rows, gate/up product: 127 us against 92.
 // by_chunks: groups of very unequal cost per tile (their own contraction lengths): chunks of 8 tiles go round the XCDs, so
-// that each has its part of every group (weight gradients of 8 fp32 experts of 66-640 rows, one expert to an XCD: 57 us each, 52
-// so).  The grid is then whole 64s.
+// that each has its part of every group (weight gradients of 8 fp32 experts of 66-640 rows, one expert to an XCD: the training
+// step 502 us, 486 so).  The grid is then whole 64s.
 // j: place in the XCD's share, whose length is handed back.  With a workgroup for every tile of the capacity it is
 // blockIdx.x / 8 and done; a smaller grid (whole rounds of 8 all the same) goes on in steps of gridDim.x / 8 to the end.
 __device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt,
@@ -1157,7 +1157,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 //
 // Bound as the kernel above is.  Measured against the form it replaces (32-wide k-tiles in a ring of four, v_mfma_f32_32x32x16,
 // the wait of every fragment read in the open): weight gradients of 8 experts x 32 000 gathered rows, 4096 x 1408: 2864 ->
-// 2452 us and, both gate and up, 5561 -> 4757 us (1.06 -> 1.24 PFLOP/s); 16 experts of 166-1024 rows, 2048 x 5632: 281 -> 278 us
+// 2452 us and, both gate and up, 5561 -> 4603 us (1.06 -> 1.28 PFLOP/s); 16 experts of 166-1024 rows, 2048 x 5632: 281 -> 268 us
 // each, input gradient 603 -> 586 us.
 // ---------------------------------------------------------------------------------------
 struct TransposingLds {                                  // beside the two buffers
@@ -1239,7 +1239,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     const int k_row = wave * 8 + (lane >> 3);
     const int lane_r = 16 * (((lane & 7) >> 1) ^ (((k_row >> 1) & 1) | ((k_row >> 2) & 2))) + 8 * (lane & 1);
     const bool over_b = TAIL && k_row >= k_rem;
-    const uint32_t fixedA = KG == 1 ? 0u : static_cast<uint32_t>(k_row) * lda * 2u;      // (a gathered row comes from the ring)
+    const uint32_t fixedA = KG == 1 ? 0u : static_cast<uint32_t>(k_row) * lda * 2u;      // (a gathered row comes from the index)
     const uint32_t fixedB = KG == 2 ? 0u : static_cast<uint32_t>(k_row) * ldb * 2u;
     const int limitA = p.capacity - 8, limitB = p.N - 8; // copies stay inside the k row; what they repeat is never stored
 
@@ -2041,7 +2041,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
 
 // The last products of the backward in one launch, as in gemm_bf16_backward_kernel: the workgroups of p[0], the input
 // gradient, come first, and the tiles of the weight gradients fill in behind them as CUs fall free.
-// MEASURED
+// Training step, the operands transposed in memory and a launch for each product / this: 8 experts of 66-640 rows, 512 x 1024:
+// 499 / 435 us; 8 of 1200, 1024 x 2048: 2754 / 2322; 4 of 64, 256 x 512: 88 / 63.
 struct BackwardProductsF32 { GemmParams p[4]; int first[4]; };       // first[i]: workgroup at which product i begins (a multiple of 8)
 template <int BM, int BN, int NBUF>
 __global__ __launch_bounds__(256, 2) void gemm_f32_backward_kernel(BackwardProductsF32 b) {
