@@ -3,9 +3,10 @@
 //
 // HBM-bound: every token row is read exactly once with 16-byte loads; one
 // wavefront owns one token.  The pooled vector g (P floats) is reduced inside
-// the wave with lane shuffles and staged in LDS; the expert embeddings sit in
+// the wave (vector-unit permutes) and staged in LDS; the expert embeddings sit in
 // LDS with a padded row stride so that the E x L lane grid of the dot-product
 // stage reads conflict-free.  Scores and gates leave as fp32.
+#include <algorithm>
 #include <type_traits>
 
 #include "etr_internal.h"
@@ -13,13 +14,11 @@
 namespace etr {
 namespace {
 
-constexpr int kRouteThreads = 256;
-constexpr int kRouteWaves = kRouteThreads / kWave;
 constexpr int kUnroll = 8;
-// Workgroups resident per CU.  Measured on the 32-expert workload (57 us at 4): 5 and 6 per CU need 96 / 80 registers,
-// spill, and take 66 / 99 us; keeping a lane's share of its embedding row in registers (172 registers, two waves
+// Waves resident per SIMD.  Measured on the 32-expert workload (48 us at 4): 5 need at most 96 registers, spill, and take
+// 59 us; keeping a lane's share of its embedding row in registers (172 registers, two waves
 // per SIMD) takes 83 us.  The kernel lives on loads in flight, but not at the price of spills.
-constexpr int kRouteBlocksPerCU = 4;
+constexpr int kRouteWavesPerSimd = 4;
 
 // g lives in a per-wave LDS region: a wave's LDS instructions execute in issue order, so ordering
 // them in the instruction stream is all that is needed (no workgroup barrier, no waiting)
@@ -29,9 +28,58 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
+// f(value of this lane, value of lane ^ M) in the vector unit, in either order (f commutes); all lanes active.  Through LDS
+// (__shfl_xor), some 40 a token, 32768 tokens x 32 experts x 128 features took 51.5 us, 48.5 so; 512 x 8 x 32 (fp32) 5.6, 4.6.
+template <int CTRL>
+__device__ __forceinline__ uint32_t permuted(uint32_t u) { return __builtin_amdgcn_update_dpp(0, u, CTRL, 0xF, 0xF, true); }
+template <int M, typename F>
+__device__ __forceinline__ float with_lane_xor(float v, F f) {
+    const uint32_t u = __float_as_uint(v);
+    if constexpr (M >= 16) {                             // rows, halves of the wave swapped between two copies
+        const auto r = [&] {
+            if constexpr (M == 32) return __builtin_amdgcn_permlane32_swap(u, u, false, false);
+            else return __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        }();
+        return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    } else {
+        uint32_t o;
+        if constexpr (M == 8) o = permuted<0x128>(u);                                // row_ror:8
+        else if constexpr (M == 4) o = permuted<0x1B>(permuted<0x141>(u));           // ^ 7 (row_half_mirror), ^ 3 (quad_perm 3210)
+        else if constexpr (M == 2) o = permuted<0x4E>(u);                            // quad_perm 2301
+        else o = permuted<0xB1>(u);                                                  // quad_perm 1032
+        return f(v, __uint_as_float(o));
+    }
+}
+struct Add { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
+// Butterfly steps from, 2 from, ... below to (powers of two, wave-uniform), N values at a time.
+template <int N, typename F>
+__device__ __forceinline__ void butterflies(float (&v)[N], int from, int to, F f) {
+    auto step = [&](auto m) {
+        constexpr int M = decltype(m)::value;
+        if (from <= M && M < to) {
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
+            for (int i = 0; i < N; ++i) v[i] = with_lane_xor<M>(v[i], f);
+        }
+    };
+    step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 4>{});
+    step(std::integral_constant<int, 8>{});
+    step(std::integral_constant<int, 16>{});
+    step(std::integral_constant<int, 32>{});
+}
+template <typename F>
+__device__ __forceinline__ float butterflies(float v, int from, int to, F f) {
+    float one[1] = {v};
+    butterflies(one, from, to, f);
+    return one[0];
+}
+template <int M = 32>
+__device__ __forceinline__ float wave_sum(float v) {     // widest step first
+    v = with_lane_xor<M>(v, Add{});
+    if constexpr (M > 1) v = wave_sum<M / 2>(v);
     return v;
 }
 
@@ -95,8 +143,9 @@ struct RouteParams {
 
 // FAST: the whole row fits one pass of kUnroll loads per lane and pools with lane shuffles;
 // otherwise the general walk (several passes, or one lane per pooled feature).
-template <bool BF16, bool FAST>
-__global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel(RouteParams p, const void* __restrict__ x,
+// W: waves of a workgroup, which share one copy of the embeddings in LDS.
+template <bool BF16, bool FAST, int W>
+__global__ __launch_bounds__(W * kWave, kRouteWavesPerSimd) void route_kernel(RouteParams p, const void* __restrict__ x,
                                                               const float* __restrict__ w_emb,
                                                               float* __restrict__ score, float* __restrict__ gate) {
     using C = Chunk<BF16>;
@@ -125,14 +174,14 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
         }
     };
     // the first row is requested before the embeddings are staged, so both latencies overlap
-    if (one_pass) fetch(blockIdx.x * kRouteWaves + wave);
+    if (one_pass) fetch(blockIdx.x * W + wave);
 
     // Embeddings and their norms: a wave takes R rows at a time, so that as many loads and then as many butterflies are
     // in flight.  Row after row, with a division per element, this prologue was half of a small call: 256 tokens x 32
     // experts, 128 pooled features, 19.6 -> 10.8 us; 2 x 64 experts 29 -> 16 us; 32768 x 32 experts 74 -> 66 us.
     auto stage = [&](auto rows) {
         constexpr int R = decltype(rows)::value;
-        for (int e0 = wave; e0 < p.E; e0 += kRouteWaves * R) {
+        for (int e0 = wave; e0 < p.E; e0 += W * R) {
             float s[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) s[r] = 0.f;
@@ -140,26 +189,24 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
                 float w[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int e = e0 + r * kRouteWaves;
+                    const int e = e0 + r * W;
                     w[r] = e < p.E ? w_emb[static_cast<size_t>(e) * p.P + q] : 0.f;
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int e = e0 + r * kRouteWaves;
+                    const int e = e0 + r * W;
                     if (e < p.E) Ws[e * p.w_stride + q] = w[r];
                     s[r] += w[r] * w[r];
                 }
             }
 #pragma unroll
-            for (int m = 32; m >= 1; m >>= 1)
-#pragma unroll
-                for (int r = 0; r < R; ++r) s[r] += __shfl_xor(s[r], m, kWave);
+            for (int r = 0; r < R; ++r) s[r] = wave_sum(s[r]);
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (lane == 0 && e0 + r * kRouteWaves < p.E) wn[e0 + r * kRouteWaves] = sqrtf(s[r]);
+                if (lane == 0 && e0 + r * W < p.E) wn[e0 + r * W] = sqrtf(s[r]);
         }
     };
-    if (p.E <= 2 * kRouteWaves) stage(std::integral_constant<int, 2>{});
+    if (p.E <= 2 * W) stage(std::integral_constant<int, 2>{});
     else stage(std::integral_constant<int, 8>{});
     __syncthreads();
 
@@ -168,7 +215,7 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
     const float sqrtD = sqrtf(static_cast<float>(p.D));
     const int e_lane = lane / p.L, sub = lane & (p.L - 1);
 
-    for (int t0 = blockIdx.x * kRouteWaves; t0 < p.T; t0 += gridDim.x * kRouteWaves) {
+    for (int t0 = blockIdx.x * W; t0 < p.T; t0 += gridDim.x * W) {
         const int t = t0 + wave;
         const bool live = t < p.T;
         const char* row = reinterpret_cast<const char*>(x) + static_cast<size_t>(live ? t : 0) * row_bytes;
@@ -180,13 +227,12 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
                 s[u] = 0.f;
                 C::accumulate(raw[u], s[u], xx);
             }
-            fetch(t + gridDim.x * kRouteWaves);          // next token of this wave (masked past T)
+            fetch(t + gridDim.x * W);          // next token of this wave (masked past T)
+            butterflies(s, 1, p.R, Add{});
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int c = u * kWave + lane;
-                float v = s[u];
-                for (int m = 1; m < p.R; m <<= 1) v += __shfl_xor(v, m, kWave);
-                if ((lane & (p.R - 1)) == 0 && c < nchunks) g[c / p.R] = v * invD;
+                if ((lane & (p.R - 1)) == 0 && c < nchunks) g[c / p.R] = s[u] * invD;
             }
         } else if (p.R > 0) {
             for (int c0 = 0; c0 < nchunks; c0 += kWave * kUnroll) {
@@ -204,7 +250,7 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
                     float s = 0.f;
 #pragma unroll
                     for (int j = 0; j < V; ++j) { s += ff[j]; xx += ff[j] * ff[j]; }
-                    for (int m = 1; m < p.R; m <<= 1) s += __shfl_xor(s, m, kWave);
+                    s = butterflies(s, 1, p.R, Add{});
                     if ((lane & (p.R - 1)) == 0 && c < nchunks) g[c / p.R] = s * invD;
                 }
             }
@@ -254,18 +300,27 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
                 const float4* g4 = reinterpret_cast<const float4*>(g);
                 const float4* w4 = reinterpret_cast<const float4*>(wr);
                 float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 4
-                for (int q = sub; q < (p.P >> 2); q += p.L) {
-                    const float4 gv = g4[q], wv = w4[q];
+                auto add = [&](const float4& gv, const float4& wv) {
                     a0 = fmaf(gv.x, wv.x, a0); a1 = fmaf(gv.y, wv.y, a1);
                     a2 = fmaf(gv.z, wv.z, a2); a3 = fmaf(gv.w, wv.w, a3);
+                };
+                const int n = p.P >> 2;
+                int q = sub;
+                for (; q + 3 * p.L < n; q += 4 * p.L) {
+                    float4 gv[4], wv[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { gv[i] = g4[q + i * p.L]; wv[i] = w4[q + i * p.L]; }
+                    __builtin_amdgcn_sched_barrier(0);   // (or each pair is waited for before the next is requested: 388 / 551 us)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) add(gv[i], wv[i]);
                 }
+                for (; q < n; q += p.L) add(g4[q], w4[q]);
                 acc = (a0 + a1) + (a2 + a3);
             } else {
                 for (int q = sub; q < p.P; q += p.L) acc += g[q] * wr[q];
             }
         }
-        for (int m = 1; m < p.L; m <<= 1) acc += __shfl_xor(acc, m, kWave);
+        acc = butterflies(acc, 1, p.L, Add{});
         float den;
         if (p.cos_mode == ETR_COS_POOLED) {
             for (int q = lane; q < p.P; q += kWave) gg += g[q] * g[q];
@@ -278,11 +333,9 @@ __global__ __launch_bounds__(kRouteThreads, kRouteBlocksPerCU) void route_kernel
         const bool is_e = e_lane < p.E;
         den *= is_e ? wn[e_lane] : 0.f;
         const float sc = (is_e && den > 0.f) ? acc / den : 0.f;
-        float mx = is_e ? sc : -INFINITY;
-        for (int m = p.L; m < kWave; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, kWave));
+        const float mx = butterflies(is_e ? sc : -INFINITY, p.L, kWave, Max{});
         const float ex = is_e ? expf(sc - mx) : 0.f;
-        float z = ex;
-        for (int m = p.L; m < kWave; m <<= 1) z += __shfl_xor(z, m, kWave);
+        const float z = butterflies(ex, p.L, kWave, Add{});
         if (live && is_e && sub == 0) {
             score[static_cast<size_t>(t) * p.E + e_lane] = sc;
             gate[static_cast<size_t>(t) * p.E + e_lane] = ex / z;
@@ -311,18 +364,35 @@ hipError_t launch_route(const etr_config& c, const void* x, const float* w_emb, 
         int r = c.D / V;
         if (r <= 64 && (r & (r - 1)) == 0) p.R = r;
     }
-    const size_t lds = sizeof(float) * (static_cast<size_t>(p.E) * p.w_stride + 64 + kRouteWaves * p.P);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    int blocks = (c.T + kRouteWaves - 1) / kRouteWaves;
-    const int resident = cu_count() * kRouteBlocksPerCU;    // what is resident at once: the embeddings are staged once per workgroup
+    // Waves of a workgroup: the fewest that leave the most waves on a CU, between the embeddings' copies in its 160 KiB and the
+    // registers (a call that is resident as a whole with 4 stays there: more workgroups share the staging).  64 experts x 512 pooled features (131 KiB) with 4 / 8 waves, 65536 tokens: 388 / 223 us;
+    // 32 x 512 (73 KiB), 4 / 16: 156 / 126; 64 x 256 (74 KiB), 4 / 8: 159 / 133; 48 x 240 (53 KiB), 40000 tokens, 4 / 8: 102 / 74.
+    auto lds_of = [&](int waves) { return sizeof(float) * (static_cast<size_t>(p.E) * p.w_stride + 64 + static_cast<size_t>(waves) * p.P); };
+    auto resident_waves = [&](int waves) {
+        const size_t fit = 160 * 1024 / lds_of(waves);
+        return waves * static_cast<int>(std::min<size_t>(fit, 4 * kRouteWavesPerSimd / waves));
+    };
+    if (lds_of(4) > 160 * 1024) return hipErrorInvalidValue;
+    int waves = 4;
+    for (int w = 8; w <= 16; w *= 2)
+        if (c.T > cu_count() * resident_waves(4) && resident_waves(w) > resident_waves(waves)) waves = w;
+    const size_t lds = lds_of(waves);
+    int blocks = (c.T + waves - 1) / waves;
+    // what the registers let be resident at once: the embeddings are staged once per workgroup
+    const int resident = cu_count() * (4 * kRouteWavesPerSimd / waves);
     if (blocks > resident) blocks = resident;
     if (blocks < 1) blocks = 1;
     const bool fast = p.R > 0 && p.d / V <= kWave * kUnroll;
-    auto kern = c.dtype == ETR_BF16 ? (fast ? route_kernel<true, true> : route_kernel<true, false>)
-                                    : (fast ? route_kernel<false, true> : route_kernel<false, false>);
+    auto of_waves = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        return c.dtype == ETR_BF16 ? (fast ? route_kernel<true, true, W> : route_kernel<true, false, W>)
+                                   : (fast ? route_kernel<false, true, W> : route_kernel<false, false, W>);
+    };
+    auto kern = waves == 4 ? of_waves(std::integral_constant<int, 4>{})
+                           : (waves == 8 ? of_waves(std::integral_constant<int, 8>{}) : of_waves(std::integral_constant<int, 16>{}));
     hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kRouteThreads), lds, st, p, x, w_emb, score, gate);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(waves * kWave), lds, st, p, x, w_emb, score, gate);
     return hipGetLastError();
 }
 
