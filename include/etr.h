@@ -252,7 +252,8 @@ size_t etr_backward_workspace_bytes(const etr_config* cfg);
  *        (not accumulated); dgate, dscore [T][E] fp32, optional (may be NULL)
  *   a_saved, b_saved [E][capacity][H] dtype in, optional (see above)
  * bf16: products accumulate in fp32; a, b, W_d^T dout and the per-row gradients are rounded to bf16
- * once each between the stages.  E * (d/D) * 4 bytes must fit in 120 KiB (ETR_ERR_UNSUPPORTED). */
+ * once each between the stages, and so are gate dout and h, the operands of dw_down (from a capacity
+ * of 8192 on, where dout's rows are read as they lie: gate h).  E * (d/D) * 4 bytes must fit in 120 KiB (ETR_ERR_UNSUPPORTED). */
 etr_status etr_moe_backward(const etr_config* cfg, const void* x, const float* w_emb,
                             const void* w_gate, const void* w_up, const void* w_down,
                             const float* score, const float* gate, const int32_t* slot_of,

@@ -14,6 +14,8 @@
 // transposing LDS reads, the fp32 ones read single elements, so nothing is transposed in memory.  Only bf16 widths
 // below 128 go through the fall-back that transposes the weights once per call and has the element-wise kernel
 // write transposed copies of the per-row quantities.  Products that do not depend on each other share a launch.
+#include <type_traits>
+
 #include "etr_internal.h"
 
 namespace etr {
@@ -502,10 +504,10 @@ int padded_capacity(const etr_config& c) {
 // weights' transposes would.  Step, one part / cut: 8 experts, 1024 x 2816, 64 tokens
 // (32 tiles of 88 k-tiles, 3 parts): 246 / 186 us; 8 of 64 rows, 2048 x 5632: 646 / 588; 16 of 64, 1024 x 2816: 369 / 336; 8 of
 // 128, 2048 x 2816: 417 / 395; 16 of 64, 1080 x 1000: 202 / 195.
-int dx_pieces(const etr_config& c, int Cp, bool fetch_rows) {
+int dx_pieces(const etr_config& c, int Cp, bool fetch_x) {
     const int KT = 2 * ((c.H + 63) / 64), rows = rows_expected(c), kr = (rows + 63) / 64;
     const double columns = (c.d + 255) / 256, tiles = c.E * ((rows + 255) / 256) * columns;
-    const double steps = tiles * KT + 3.0 * c.E * columns * ((c.H + 255) / 256) * ((kr > (fetch_rows ? 4 : 2) ? kr : (fetch_rows ? 4 : 2)) + 2);
+    const double steps = tiles * KT + 3.0 * c.E * columns * ((c.H + 255) / 256) * ((kr > (fetch_x ? 4 : 2) ? kr : (fetch_x ? 4 : 2)) + 2);
     const double share = steps / cu_count() > 12.0 ? steps / cu_count() : 12.0;
     const double room = 3.0 * c.E * c.H * c.d * elt_bytes(c.dtype), each = 4.0 * c.E * Cp * c.d;
     const long long supers = static_cast<long long>(c.E) * ((Cp + 255) / 256) * ((c.d + 255) / 256);
@@ -601,15 +603,17 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     GroupedGemm k4 = t4, k5 = t5, k6 = t6;
     k4.A = dout; k4.k_gather = 1; k5.B0 = x; k5.k_gather = 2; k6.B0 = x; k6.k_gather = 2;
     for (GroupedGemm* g : {&k4, &k5, &k6}) { g->k_index = slot_token; g->k_index_stride = C; g->k_rows = Tn; }
-    // It saves the two copies (8 experts x 32 000 rows: 1.6 ms of 23; 16 experts of 166-1024 rows, 2048 wide: 42 us, the step
-    // 2652 -> 2633 us; 12 experts of 677 rows, 1080 wide: 21 us, 1000 -> 978) at the price of at least 256 contraction rows
-    // per expert, so experts that expect no more than 128 rows take the copies.
-    const bool fetch_rows = f32 || (rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k4) &&
-                                    grouped_gemm_transposed_ok(k5) && grouped_gemm_transposed_ok(k6));
+    // Rows of x: the same bits without the copy of x_p (step of 16 experts of 166-1024 rows, 2048 wide: 2610 / 2605 us; 12 of 677
+    // rows, 1080 wide: 907 / 895), at the price of at least 256 contraction rows per expert, so experts that expect no more than 128
+    // rows take the copy.  Rows of dOut: they arrive unscaled, so the gate goes to the other operand and other values are
+    // rounded, bf16(gate h) instead of bf16(gate dOut) and bf16(h): 3e-3 of the gradient.  Only where the copies are large (8
+    // experts x 32 000 rows: the two 1.6 ms of 23).  As below, the capacity stands in for the row count there.
+    const bool fetch_x = f32 || (rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k5) && grouped_gemm_transposed_ok(k6));
+    const bool fetch_dout = f32 || (fetch_x && C >= 8192 && grouped_gemm_transposed_ok(k4));
     // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
     // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
-    const GroupedGemm down = fetch_rows ? k4 : t4;
-    GroupedGemm gates[2] = {fetch_rows ? k5 : t5, fetch_rows ? k6 : t6};
+    const GroupedGemm down = fetch_dout ? k4 : t4;
+    GroupedGemm gates[2] = {fetch_x ? k5 : t5, fetch_x ? k6 : t6};
     GroupedGemm both = gates[0];
     both.M = 2 * H; both.a_rows = 2 * H; both.C = dw_gate; both.C2 = dw_up; both.split_m = H;
     const int n_gates = H % 32 == 0 && grouped_gemm_transposed_ok(both) ? 1 : 2;        // (fp32: 2)
@@ -638,17 +642,19 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         } else {
             ETR_BW(launch_grouped_gemm(t2, st));
         }
-        if (fetch_rows) {
-            hipLaunchKernelGGL((swiglu_backward_kernel<T, true, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a,
-                               pre_b, gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr),
-                               at(L.hT), dgate_part, Tn, E, C, Cp, H);
+        auto middle = [&](auto scale_h) {
+            hipLaunchKernelGGL((swiglu_backward_kernel<T, true, decltype(scale_h)::value>), dim3(cH, cC, E), dim3(kTileThreads), 0, st,
+                               at(L.u), pre_a, pre_b, gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr),
+                               static_cast<T*>(nullptr), at(L.hT), dgate_part, Tn, E, C, Cp, H);
+        };
+        if (fetch_dout) {
+            middle(std::integral_constant<bool, true>{});
         } else if constexpr (!f32) {
-            hipLaunchKernelGGL((swiglu_backward_kernel<T, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a, pre_b,
-                               gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr), at(L.hT),
-                               dgate_part, Tn, E, C, Cp, H);
+            middle(std::integral_constant<bool, false>{});
             const unsigned row_blocks = static_cast<unsigned>((static_cast<long long>(E) * Cp + 3) / 4);
-            hipLaunchKernelGGL((gather_rows_kernel<T, false>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(x),
-                               slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp);
+            if (!fetch_x)
+                hipLaunchKernelGGL((gather_rows_kernel<T, false>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(x),
+                                   slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp);
             hipLaunchKernelGGL((gather_rows_kernel<T, true>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(dout),
                                slot_token, counts, gate_w, at(L.dypT), Tn, d, E, C, Cp);
         }
@@ -662,7 +668,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             ETR_BW(launch_grouped_gemm(down, st));
             for (int i = 0; i < n_gates; ++i) ETR_BW(launch_grouped_gemm(gates[i], st));
         } else {
-            if (!f32 && !nt_u) pieces = dx_pieces(c, Cp, fetch_rows);
+            if (!f32 && !nt_u) pieces = dx_pieces(c, Cp, fetch_x);
             t3.pieces = pieces;
             if (pieces > 1) t3.C = at(L.wdT);            // (behind it the gate and up projections' room, unused here as well)
             ETR_BW(launch_backward_products(t3, down, gates, n_gates, st));

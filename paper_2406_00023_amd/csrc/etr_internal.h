@@ -101,8 +101,8 @@ struct GroupedGemm {
 };
 hipError_t launch_grouped_gemm(const GroupedGemm& g, hipStream_t st);
 bool grouped_gemm_transposed_ok(const GroupedGemm& g);
-// The input gradient (tb) and the weight gradients (ta and tb; down: k_gather 1, one or two gates: k_gather 2, or none of them
-// with k_gather) in one launch.
+// The input gradient (tb) and the weight gradients (ta and tb) in one launch; down with k_gather 1 and one or two gates with
+// k_gather 2, only the gates, or none of them (fp32: any).
 hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& down, const GroupedGemm* gates, int n_gates, hipStream_t st);
 
 // backward.hip

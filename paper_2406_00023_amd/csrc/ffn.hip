@@ -1617,7 +1617,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
 }
 
 // The last products of the backward in one launch: the input gradient (p[0]: row-major A, TAIL as above), then the weight
-// gradients (p[1]: down; p[2] and, with two, p[3]: gate and up), with FETCH the rows of A, resp. B, through an index.  They do
+// gradients (p[1]: down; p[2] and, with two, p[3]: gate and up), their rows through an index or not (Fetch).  They do
 // not depend on each other, and the input gradient is few tiles with a long contraction (2 H): its last round leaves
 // workgroups idle, which here start on the weight gradients' many short tiles, as many rounds of them as its k-tiles stand
 // for.  Where even so a tile of the input gradient is longer than all the rest (few rows), its contraction comes in parts
@@ -1626,17 +1626,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
 // 1024 x 2816: 520 / 434; 16 of 166-1024, 2048 x 5632 (1.6 rounds, at the power limit): 2665 / 2625; without fetched rows, in one
 // part, 8 of 64, 2048 x 5632: 763 / 646, 32 of 32, 512 x 1024: 193 / 157.
 struct BackwardProducts { GemmParams p[4]; int n_gates; };
-template <bool TAIL, bool FETCH>
+enum class Fetch { NONE, GATES, ALL };                   // contraction rows through an index: B of the gate and up products, A of down too
+template <bool TAIL, Fetch FETCH>
 __global__ __launch_bounds__(512) void gemm_bf16_backward_kernel(BackwardProducts b) {
     __shared__ TransposingLds sh;
     DealState state;
     state.idle = gridDim.x;
     transposing_tiles<false, 0, TAIL>(b.p[0], sh, state);
     __syncthreads();                                     // the tile list and the buffers are free
-    transposing_tiles<true, FETCH ? 1 : 0, false>(b.p[1], sh, state);
+    transposing_tiles<true, FETCH == Fetch::ALL ? 1 : 0, false>(b.p[1], sh, state);
     for (int i = 0; i < b.n_gates; ++i) {
         __syncthreads();
-        transposing_tiles<true, FETCH ? 2 : 0, false>(b.p[2 + i], sh, state);
+        transposing_tiles<true, FETCH == Fetch::NONE ? 0 : 2, false>(b.p[2 + i], sh, state);
     }
 }
 #undef ETR_OFF
@@ -2091,7 +2092,7 @@ hipError_t launch_bf16_transposing(GemmParams p, hipStream_t st, int n_cu) {
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
     return hipGetLastError();
 }
-template <bool TAIL, bool FETCH>
+template <bool TAIL, Fetch FETCH>
 hipError_t launch_bf16_backward_form(BackwardProducts b, hipStream_t st, int n_cu) {
     constexpr size_t lds = 2ull * 512 * 64 * 2;
     for (int i = 0; i < 2 + b.n_gates; ++i) plan_tiles(b.p[i], 256, 256);
@@ -2332,8 +2333,9 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
                                          : launch_f32_backward_tiles<32, 4>(f, 0, 2 + n_gates, st);
     }
     BackwardProducts b{};
-    const bool fetch = down.k_gather == 1;
     if (n_gates < 1 || n_gates > 2 || dx.ta || !down.ta || down.k_gather == 2) return hipErrorInvalidValue;
+    if (down.k_gather && !gates[0].k_gather) return hipErrorInvalidValue;
+    const Fetch fetch = down.k_gather ? Fetch::ALL : (gates[0].k_gather ? Fetch::GATES : Fetch::NONE);
     if (dx.pieces > 1) {                                 // parts of two k-tiles at least, and the list of their tiles in LDS
         const int half = dx.B1 ? dx.K / 2 : dx.K, k_all = (half + 63) / 64 * (dx.B1 ? 2 : 1), k_piece = (k_all + dx.pieces - 1) / dx.pieces;
         if (k_all - (dx.pieces - 1) * k_piece < 2 || !persist_ok(params_of(dx), false, kMaxSuper / dx.pieces)) return hipErrorInvalidValue;
@@ -2343,13 +2345,17 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
     b.p[1] = params_of(down);
     if (!grouped_gemm_transposed_ok(dx) || !grouped_gemm_transposed_ok(down)) return hipErrorInvalidValue;
     for (int i = 0; i < n_gates; ++i) {
-        if (!grouped_gemm_transposed_ok(gates[i]) || !gates[i].ta || gates[i].k_gather != (fetch ? 2 : 0)) return hipErrorInvalidValue;
+        if (!grouped_gemm_transposed_ok(gates[i]) || !gates[i].ta || gates[i].k_gather != (fetch == Fetch::NONE ? 0 : 2)) return hipErrorInvalidValue;
         b.p[2 + i] = params_of(gates[i]);
     }
     const int n_cu = cu_count();
-    if ((dx.B1 ? dx.K / 2 : dx.K) % 64 == 0)
-        return fetch ? launch_bf16_backward_form<false, true>(b, st, n_cu) : launch_bf16_backward_form<false, false>(b, st, n_cu);
-    return fetch ? launch_bf16_backward_form<true, true>(b, st, n_cu) : launch_bf16_backward_form<true, false>(b, st, n_cu);
+    const bool tail = (dx.B1 ? dx.K / 2 : dx.K) % 64 != 0;
+    switch (fetch) {
+        case Fetch::NONE: return tail ? launch_bf16_backward_form<true, Fetch::NONE>(b, st, n_cu) : launch_bf16_backward_form<false, Fetch::NONE>(b, st, n_cu);
+        case Fetch::GATES: return tail ? launch_bf16_backward_form<true, Fetch::GATES>(b, st, n_cu) : launch_bf16_backward_form<false, Fetch::GATES>(b, st, n_cu);
+        case Fetch::ALL: return tail ? launch_bf16_backward_form<true, Fetch::ALL>(b, st, n_cu) : launch_bf16_backward_form<false, Fetch::ALL>(b, st, n_cu);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {

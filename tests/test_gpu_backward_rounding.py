@@ -1,0 +1,63 @@
+"""What the backward rounds to bf16 between its stages, on the gradients themselves: the values are computed in 64 bits from the
+operands as documented, rounded once more, and all but a few elements have to be the same bits.  What may differ is what lies
+within an fp32 sum's error (some 1e-6 of its terms) of a rounding boundary (2^-9 of the value apart): under 1 % of the
+elements; an operand rounded elsewhere moves the gradient by 3e-3 and half of its elements."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_00023_amd import binding as B
+from paper_2406_00023_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(T, E, d, Hh, C, k, gate_norm=0):
+    import gpu_helpers as H
+    B.load_library()
+    shape = I.EtrShape("rounding", 31, T=T, d=d, E=E, D=8, k=k, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR, recipe="bias",
+                       n_centroids=E)
+    L = H.GpuLayer(shape, gate_norm=gate_norm)
+    t = L.t
+    saved = [torch.zeros(E, C, Hh, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    B.etr_moe_forward_train(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.out, *saved,
+                            B.alloc_workspace(B.etr_workspace_bytes(L.cfg)), score=L.score, gate=L.gate, topk_expert=L.topk,
+                            slot_of=L.slot_of, slot_token=L.slot_token, counts=L.counts)
+    return shape, L, saved
+
+
+def _backward(shape, L, saved, dout):
+    t = L.t
+    out = [torch.full(s, 7.0, dtype=torch.bfloat16, device="cuda")
+           for s in ((shape.T, shape.d), *2 * ((shape.E, shape.H, shape.d),), (shape.E, shape.d, shape.H))]
+    ws = B.alloc_workspace(B.etr_backward_workspace_bytes(L.cfg))
+    ws.fill_(0xFF)
+    B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, L.slot_of, L.slot_token,
+                       L.counts, dout, *out, ws, a_saved=saved[0], b_saved=saved[1])
+    torch.cuda.synchronize()
+    return [v.cpu() for v in out]
+
+
+# (T, E, d, H, C, k, gate_norm): rows copied, x fetched, both fetched (there the gate goes to the other operand)
+@pytest.mark.parametrize("T,E,d,Hh,C,k,gate_norm", [(200, 4, 264, 328, 120, 2, 0), (700, 4, 264, 328, 400, 2, 0),
+                                                    (700, 4, 136, 200, 400, 2, 1), (900, 4, 264, 72, 8192, 2, 0)])
+def test_down_gradient_operands(T, E, d, Hh, C, k, gate_norm):
+    print(f"down gradient T={T} E={E} d={d} H={Hh} C={C}", flush=True)
+    shape, L, saved = _layer(T, E, d, Hh, C, k, gate_norm)
+    dout = I.make_upstream_gradient(shape, "cuda")
+    dwd = _backward(shape, L, saved, dout)[3]
+    counts, slot_token, slot_of = L.counts.cpu(), L.slot_token.cpu(), L.slot_of.cpu()
+    gate, dout, (a, b) = L.gate.cpu(), dout.cpu(), [v.cpu() for v in saved]
+    if gate_norm:                                        # the weights of the forward: renormalised over the kept experts
+        kept = torch.where(slot_of >= 0, gate, torch.zeros_like(gate))
+        gate = kept / kept.sum(1, keepdim=True)
+    bf = lambda v: v.to(torch.bfloat16).double()
+    for e in range(E):
+        n = int(counts[e])
+        t = slot_token[e, :n].long()
+        ae, g = a[e, :n].double(), gate[t, e].unsqueeze(1)
+        h = ae / (1 + torch.exp(-ae)) * b[e, :n].double()
+        ref = (dout[t].double().t() @ bf(g.double() * h)) if C >= 8192 else (bf(g * dout[t].float()).t() @ bf(h))
+        moved = (dwd[e] != ref.to(torch.bfloat16)).float().mean().item() if n else float(dwd[e].any())
+        print(f"  expert {e}: {n} rows, {moved:.2e} of the elements differ", flush=True)
+        assert moved <= 0.01, (e, moved)
