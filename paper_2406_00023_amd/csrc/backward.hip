@@ -455,20 +455,27 @@ __global__ __launch_bounds__(256) void dx_kernel(const T* __restrict__ x, const 
         }
         // ascending expert order, as in the forward sum; four rows requested at a time (past the last kept pair the
         // last one is requested again and not added)
-        for (int i0 = 0; pieces > 1 && i0 < n_kept * pieces; i0 += 4) {          // (few rows: out of the caches)
-            float r[4][V];
+        if (pieces > 1) {                                // (few rows: out of the caches)
+            float row[V] = {};                           // a pair's parts, added up; rounded as a row in one part is
+            for (int i0 = 0; i0 < n_kept * pieces; i0 += 4) {
+                float r[4][V];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int at = min(i0 + q, n_kept * pieces - 1), i = at / pieces;
-                const float* src = reinterpret_cast<const float*>(dxp) + (static_cast<size_t>(at - i * pieces) * E * Cx + sl[i]) * d + j;
+                for (int q = 0; q < 4; ++q) {
+                    const int at = min(i0 + q, n_kept * pieces - 1), i = at / pieces;
+                    const float* src = reinterpret_cast<const float*>(dxp) + (static_cast<size_t>(at - i * pieces) * E * Cx + sl[i]) * d + j;
 #pragma unroll
-                for (int h = 0; h < V; h += 4) Elt<float>::load_vec(src + h, r[q] + h);
-            }
+                    for (int h = 0; h < V; h += 4) Elt<float>::load_vec(src + h, r[q] + h);
+                }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (i0 + q < n_kept * pieces) {
+                for (int q = 0; q < 4; ++q) {
+                    if (i0 + q < n_kept * pieces) {
+                        const bool whole = (i0 + q + 1) % pieces == 0;
 #pragma unroll
-                    for (int i = 0; i < V; ++i) acc[i] += r[q][i];
+                        for (int i = 0; i < V; ++i) {
+                            row[i] += r[q][i];
+                            if (whole) { acc[i] += Elt<T>::widen(Elt<T>::narrow(row[i])); row[i] = 0.f; }
+                        }
+                    }
                 }
             }
         }

@@ -61,3 +61,19 @@ def test_down_gradient_operands(T, E, d, Hh, C, k, gate_norm):
         moved = (dwd[e] != ref.to(torch.bfloat16)).float().mean().item() if n else float(dwd[e].any())
         print(f"  expert {e}: {n} rows, {moved:.2e} of the elements differ", flush=True)
         assert moved <= 0.01, (e, moved)
+
+
+def test_rows_of_the_input_gradient():
+    """The rows that the input gradient adds up are rounded whether their contraction ran in parts (here three, a few rows and a
+    small capacity) or in one (a capacity whose parts the workspace does not hold)."""
+    T, E, d, Hh, k = 96, 2, 136, 1000, 2
+    small, large = _layer(T, E, d, Hh, 100, k), _layer(T, E, d, Hh, 800, k)
+    assert int(small[1].counts.sum()) == T * k and torch.equal(small[1].slot_token[:, :T], large[1].slot_token[:, :T])
+    dout = I.make_upstream_gradient(small[0], "cuda")
+    parts = _backward(*small[:2], [v[:, :100].contiguous() for v in large[2]], dout)
+    whole = _backward(*large, dout)
+    moved = (parts[0] != whole[0]).float().mean().item()
+    print(f"input gradient in parts: {moved:.2e} of the elements differ", flush=True)
+    assert moved <= 0.01
+    for p, w in zip(parts[1:], whole[1:]):
+        assert torch.equal(p, w)
