@@ -606,7 +606,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
                         grouped_gemm_transposed_ok(t5) && grouped_gemm_transposed_ok(t6));
     // The same three weight-gradient products with the rows of dOut and x fetched through slot_token by the
     // products themselves: dWd = dOut_p^T (gate h), dWg = da^T x_p, dWu = db^T x_p.  (da, db, h hold zeros from
-    // counts[e] on, so whatever row an empty slot fetches is multiplied by zero.)
+    // counts[e] on; there the products fetch the expert's last kept row again.)
     GroupedGemm k4 = t4, k5 = t5, k6 = t6;
     k4.A = dout; k4.k_gather = 1; k5.B0 = x; k5.k_gather = 2; k6.B0 = x; k6.k_gather = 2;
     for (GroupedGemm* g : {&k4, &k5, &k6}) { g->k_index = slot_token; g->k_index_stride = C; g->k_rows = Tn; }

@@ -83,9 +83,8 @@ struct GroupedGemm {
     bool ta = false, tb = false;
     // With ta and tb, the contraction rows of one operand may come through an index (k_gather 1: A, 2: B0): that
     // operand is then one [k_rows][ld] matrix for all groups and row k of group g is its row
-    // k_index[g * k_index_stride + min(k, k_index_stride - 1)], clamped into [0, k_rows); the other operand must hold
-    // zeros wherever the index does not name the wanted row (empty slots, padding).  Per-group contraction lengths
-    // are then rounded up to at least 256.
+    // k_index[g * k_index_stride + k], clamped into [0, k_rows).  Per-group contraction lengths are then rounded up to at
+    // least 256 (bf16); in that padding, where the other operand must hold zeros, the group's last row is fetched again.
     const int32_t* k_index = nullptr;
     int k_index_stride = 0, k_rows = 0, k_gather = 0;
     // With ta and the plain epilogue: output rows m < split_m go to C, the others (as rows m - split_m) to C2, both

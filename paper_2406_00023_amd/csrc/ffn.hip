@@ -46,9 +46,9 @@ struct GemmParams {
                                          // that padding
     void* C2 = nullptr;         // DUAL epilogue: the B1 product goes here, the B0 product to C, no activation
     void* C3 = nullptr;         // SwiGLU epilogue that also keeps the two products: B0 product to C2, B1 product to C3
-    // Contraction rows fetched through an index (transposing kernel only; k_gather 1: A, 2: B0): row k of group g of
-    // that operand is row k_index[g * k_index_stride + min(k, k_index_stride - 1)] of a [k_rows][ld] matrix, clamped
-    // into [0, k_rows).  The per-group contraction length is then at least 256.
+    // Contraction rows fetched through an index (transposing and fp32 kernels; k_gather 1: A, 2: B0): row k of group g of
+    // that operand is row k_index[g * k_index_stride + k] of a [k_rows][ld] matrix, clamped into [0, k_rows); k in the padding:
+    // the group's last row again.  The per-group contraction length is then at least 256 (bf16).
     const int32_t* k_index = nullptr;
     int k_index_stride = 0, k_rows = 0, k_gather = 0;
     // Plain epilogue of the transposing kernel with the output rows split between two arrays: rows below split_m go
@@ -1150,7 +1150,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 //
 // KG (1: A, 2: B): the contraction rows of that operand are fetched through p.k_index (a gather along the slow index).  The
 // four copies of a lane share one k row, so a lane needs one row number per k-tile, loaded three k-tiles ahead.  Row
-// numbers are clamped into [0, k_rows).
+// numbers are clamped into [0, k_rows).  In the padding of a group's contraction, where the other operand is zero, its own last
+// row is fetched again: any other row's infinities or NaNs would turn those zeros into NaNs of a group that never had the row.
+// A group without rows has none to repeat: its tiles are stored as zeros whatever was multiplied.
 //
 // TAIL (row-major A): the contraction, or each half of a split one, need not be whole k-tiles.  The last k-tile of it is
 // short: pieces of a token row and whole weight rows past its end are zero-filled (buffer_copy_to_lds).
@@ -1164,6 +1166,7 @@ struct TransposingLds {                                  // beside the two buffe
     int pre[kMaxSuper + 1];
     int wave_tot[8], rows_of_group[128];
     int row_ids[3][256];                                 // gathered rows of a tile: this, the next, the one after
+    int k_last[64];                                      // KG: last row of each group's contraction (-1: it has none)
 };
 // What a product leaves to the ones behind it in the same launch: the workgroups from place `idle` on are `ahead` k-tiles
 // ahead of the others (a tile counts kTileSteps more than it has); the next list's rounds begin at place `turn`.
@@ -1218,8 +1221,9 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 63) / 64;         // of the whole product, or of each half of a split one
     const int k_rem = (Kh & 63) ? (Kh & 63) : 64;        // valid k of the last k-tile
 
+    if (KG != 0 && tid < p.E) sh.k_last[tid] = min(min(p.k_counts ? max(p.k_counts[tid], 0) : p.K, p.K), p.k_index_stride) - 1;
     LiveTiles tiles;
-    tiles.build<NW * 64>(p, BM, sh.pre, sh.wave_tot, sh.rows_of_group);
+    tiles.build<NW * 64>(p, BM, sh.pre, sh.wave_tot, sh.rows_of_group);          // (its barriers cover k_last)
     const int total = tiles.total;
     Deal deal;
     const int k_all = splitB ? 2 * KTh : KTh, k_piece = (k_all + p.pieces - 1) / p.pieces;      // k-tiles of the product, of a part
@@ -1228,6 +1232,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     struct Tile {
         int e, m0, n0, count, KT;
         int k0, piece;                                   // first k-tile, part of the contraction
+        int k_last;                                      // KG: last row of the contraction
         uint64_t Abase, Bbase, Bbase1;                   // wave-uniform; Bbase1: second half of a split B
         uint32_t offA[TRA ? 1 : NCP];                    // row-major A: byte offsets of this lane's row groups
     };
@@ -1251,6 +1256,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         t.count = tiles.count(e);
         t.k0 = t.piece * k_piece;
         t.KT = TRA ? tiles.k_tiles(e) : min(k_piece, k_all - t.k0);
+        t.k_last = KG != 0 ? __builtin_amdgcn_readfirstlane(sh.k_last[e]) : 0;
         t.Abase = reinterpret_cast<uint64_t>(p.A);
         if (KG != 1) t.Abase += TRA ? static_cast<uint64_t>(e) * p.K * lda * 2
                                     : (p.row_index ? 0 : static_cast<uint64_t>(e) * p.capacity * lda * 2);
@@ -1306,10 +1312,9 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         if (TAIL) off = last && over_b ? kPastRange : off;
         copy_to(base, off, lds + buf * STAGE + HALF + i * (HALF / 4) + wave * 64);
     };
-    // KG: this lane's row number in k-tile kl of group e (positions past the index row are clamped onto its last entry),
-    // and the byte offset of that row
-    auto load_index = [&](int e, int kl) -> int {
-        return p.k_index[static_cast<size_t>(e) * p.k_index_stride + min(kl * 64 + k_row, p.k_index_stride - 1)];
+    // KG: this lane's row number in k-tile kl of group e, whose last row is k_last, and the byte offset of that row
+    auto load_index = [&](int e, int k_last, int kl) -> int {
+        return p.k_index[static_cast<size_t>(e) * p.k_index_stride + max(min(kl * 64 + k_row, k_last), 0)];
     };
     auto row_offset = [&](int index) -> uint32_t {
         return static_cast<uint32_t>(min(max(index, 0), p.k_rows - 1)) * static_cast<uint32_t>(KG == 1 ? lda : ldb) * 2u;
@@ -1478,11 +1483,11 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     finish(cur, 0);
     int g = 0;                                           // global step: buffer g & 1
     int index = 0;                                       // KG: this lane's row number in k-tile g + 2
-    if constexpr (KG != 0) index = load_index(cur.e, 2); // (KT >= 4)
+    if constexpr (KG != 0) index = load_index(cur.e, cur.k_last, 2); // (KT >= 4)
     uint32_t row_a = fixedA, row_b = fixedB;             // byte offset of this lane's k row in the k-tile to copy next
     for (int t = 0; t < 2; ++t) {                        // KT >= 2 is a launch condition
-        if constexpr (KG == 1) row_a = row_offset(load_index(cur.e, t));
-        if constexpr (KG == 2) row_b = row_offset(load_index(cur.e, t));
+        if constexpr (KG == 1) row_a = row_offset(load_index(cur.e, cur.k_last, t));
+        if constexpr (KG == 2) row_b = row_offset(load_index(cur.e, cur.k_last, t));
         const uint64_t baseA = a_ktile(cur.Abase, cur.k0 + t), baseB = b_ktile(cur.Bbase, cur.Bbase1, cur.k0 + t);
 #pragma unroll
         for (int i = 0; i < NCP; ++i) {
@@ -1546,7 +1551,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
             substep(ETR_OFF(1), buf, [&](int m) {        // and the row number in k-tile g + 3, wanted one step from now
                 if constexpr (KG != 0) {
                     const bool stay = kt + 3 < KT || !has_next;
-                    if (m == 0) index = load_index(stay ? cur.e : nxt.e, stay ? kt + 3 : kt + 3 - KT);
+                    if (m == 0) index = load_index(stay ? cur.e : nxt.e, stay ? cur.k_last : nxt.k_last, stay ? kt + 3 : kt + 3 - KT);
                 }
             });
             substep(ETR_OFF(2), buf, [&](int) {});
@@ -1564,6 +1569,12 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
             late_last = last;
         }
         settle();
+        if (KG != 0 && cur.k_last < 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
         // ---- epilogue of cur (the copies of the next tile are in flight).  The patch is the wave's own copy target in the
         // B half of the buffer just multiplied: behind the last barrier nobody reads it any more, and the next copies into
         // it are the wave's own, in its next substep 0.
