@@ -613,10 +613,12 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     // Rows of x: the same bits without the copy of x_p (step of 16 experts of 166-1024 rows, 2048 wide: 2610 / 2605 us; 12 of 677
     // rows, 1080 wide: 907 / 895), at the price of at least 256 contraction rows per expert, so experts that expect no more than 128
     // rows take the copy.  Rows of dOut: they arrive unscaled, so the gate goes to the other operand and other values are
-    // rounded, bf16(gate h) instead of bf16(gate dOut) and bf16(h): 3e-3 of the gradient.  Only where the copies are large (8
-    // experts x 32 000 rows: the two 1.6 ms of 23).  As below, the capacity stands in for the row count there.
-    const bool fetch_x = f32 || (rows_expected(c) > 128 && direct && grouped_gemm_transposed_ok(k5) && grouped_gemm_transposed_ok(k6));
-    const bool fetch_dout = f32 || (fetch_x && C >= 8192 && grouped_gemm_transposed_ok(k4));
+    // rounded, bf16(gate h) instead of bf16(gate dOut) and bf16(h): 3e-3 of the gradient.  So that is decided by the capacity alone,
+    // large where the copies are (8 experts x 32 000 rows: the two 1.6 ms of 23); few rows in such a buffer fetch both, as the
+    // copies' grids are those of the capacity (8 experts of 64 rows, 4096 x 1408, capacity 32768: copies / this 571 / 542 us).
+    const bool large = C >= 8192;
+    const bool fetch_x = f32 || ((large || rows_expected(c) > 128) && direct && grouped_gemm_transposed_ok(k5) && grouped_gemm_transposed_ok(k6));
+    const bool fetch_dout = f32 || (large && fetch_x && grouped_gemm_transposed_ok(k4));
     // dWg and dWu share x_p: one product with the 2H rows of (da | db)^T, its output rows split between the two
     // gradients (H = 1408: 11 whole row tiles instead of twice 5.5)
     const GroupedGemm down = fetch_dout ? k4 : t4;
@@ -639,7 +641,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         // 22.74 ms with 0.1 ms of copies; 16 experts with 760 rows each: 0.43 ms of copies for less than 0.1 ms, and the
         // input gradient shares a launch with the weight gradients there).  The row count lives on the device; the capacity
         // stands in for it.  The kernel wants at least one whole 256-column tile of the output.
-        const bool many_rows = !f32 && C >= 8192;
+        const bool many_rows = !f32 && large;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
             transpose_weights(w_down, L.wdT, d, H, d, 0);

@@ -38,9 +38,9 @@ def _backward(shape, L, saved, dout):
     return [v.cpu() for v in out]
 
 
-# (T, E, d, H, C, k, gate_norm): rows copied, x fetched, both fetched (there the gate goes to the other operand)
+# (T, E, d, H, C, k, gate_norm): rows copied, x fetched, both fetched (there the gate goes to the other operand), also with few rows
 @pytest.mark.parametrize("T,E,d,Hh,C,k,gate_norm", [(200, 4, 264, 328, 120, 2, 0), (700, 4, 264, 328, 400, 2, 0),
-                                                    (700, 4, 136, 200, 400, 2, 1), (900, 4, 264, 72, 8192, 2, 0)])
+                                                    (700, 4, 136, 200, 400, 2, 1), (900, 4, 264, 72, 8192, 2, 0), (200, 4, 264, 72, 8192, 2, 0)])
 def test_down_gradient_operands(T, E, d, Hh, C, k, gate_norm):
     print(f"down gradient T={T} E={E} d={d} H={Hh} C={C}", flush=True)
     shape, L, saved = _layer(T, E, d, Hh, C, k, gate_norm)
