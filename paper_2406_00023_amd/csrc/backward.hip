@@ -636,12 +636,12 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     int dxp_rows = C, pieces = 1;
     if (direct) {
         // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
-        // that weight transposed once per call.  The copy moves E*d*H elements, the product works on every kept row, so it
-        // pays from a few thousand rows per expert on (8-expert workload, 32 000 rows per expert: the training step 22.95 ->
-        // 22.74 ms with 0.1 ms of copies; 16 experts with 760 rows each: 0.43 ms of copies for less than 0.1 ms, and the
-        // input gradient shares a launch with the weight gradients there).  The row count lives on the device; the capacity
-        // stands in for it.  The kernel wants at least one whole 256-column tile of the output.
-        const bool many_rows = !f32 && large;
+        // that weight transposed once per call, where experts have very many rows: the copies move E*d*H elements and the input
+        // gradient loses its launch with the weight gradients.  Step, as they lie / transposed: 8 experts x 32 000 rows, 4096 x
+        // 1408 22954 / 22741 us; some 16384 rows, 4 experts, 4096 x 4096 16166 / 16013, 8, 2048 x 1408 6654 / 6662, 4096 x 1408 12290 /
+        // 12451, 1080 x 1000 3761 / 4312; 8192 rows, 8, 2048 x 1408 3218 / 3335; 1024, 602 / 724; 64 rows, 235 / 345.  The kernel
+        // wants at least one whole 256-column tile of the output.
+        const bool many_rows = !f32 && rows_expected(c) > 16384;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
             transpose_weights(w_down, L.wdT, d, H, d, 0);

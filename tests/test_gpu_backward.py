@@ -75,14 +75,16 @@ SMALL = {
     # 64-wide persistent kernel (two-product and pre-activation-keeping epilogues, rows gathered through LDS)
     "cfg2w": lambda: I.small_variant(I.CONFIGS["cfg2"], T=1300, d=512, H=640),
     "cfg5w": lambda: I.small_variant(I.CONFIGS["cfg5"], T=900, H=256),
-    # a capacity of 8192 rows and whole 256-column tiles for both u and the input gradient: the two products against
-    # a weight matrix run on the row-major kernel with the weight transposed once (the overloaded experts of this
-    # recipe keep a few thousand rows, the others few)
+    # from a capacity of 8192 on the weight-gradient products also fetch the rows of dOut through slot_token (the
+    # overloaded experts of this recipe keep a few thousand rows, the others few)
     "cfg2r": lambda: I.CONFIGS["cfg2"].with_(T=12000, d=256, H=256, capacity=8192, name="cfg2-rows"),
-    # from that capacity on the weight-gradient products also fetch the rows of dOut and x through slot_token
-    # themselves; here with a capacity that is no multiple of 64 (row numbers past the end of an expert's slot list),
-    # a ragged last column tile of dW_down and experts of very different sizes
+    # the same with a capacity that is no multiple of 64 (row numbers past the end of an expert's slot list), a ragged
+    # last column tile of dW_down and experts of very different sizes
     "cfg2q": lambda: I.CONFIGS["cfg2"].with_(T=9000, d=256, H=200, capacity=8200, name="cfg2-rows-ragged"),
+    # more than 16384 rows expected (expert choice) and whole 256-column tiles: the products against a weight matrix run on
+    # the row-major kernel with the weight transposed once, u and the input gradient or, with H = 200, only the latter
+    "cfg2n": lambda: I.CONFIGS["cfg2"].with_(T=17000, d=256, H=256, E=3, capacity=16500, name="cfg2-many-rows"),
+    "cfg2m": lambda: I.CONFIGS["cfg2"].with_(T=17000, d=264, H=200, D=8, E=2, capacity=17100, name="cfg2-many-rows-ragged"),
 }
 
 
@@ -90,7 +92,7 @@ SMALL = {
                                            ("cfg2s", TCR, FULL), ("cfg3s", ECR, FULL), ("cfg4s", BIDIR, POOLED),
                                            ("cfg5s", BIDIR, FULL), ("cfg2w", TCR, FULL), ("cfg5w", BIDIR, POOLED),
                                            ("cfg2r", TCR, FULL), ("cfg2r", BIDIR, POOLED), ("cfg2q", BIDIR, FULL),
-                                           ("cfg2q", ECR, FULL)])
+                                           ("cfg2q", ECR, FULL), ("cfg2n", ECR, FULL), ("cfg2m", ECR, POOLED)])
 def test_backward_small_all_gradients(H, oracle, name, mode, cos):
     shape = SMALL[name]()
     _say(f"backward case {name} mode={mode} cos={cos} T={shape.T} d={shape.d} E={shape.E} C={shape.capacity} H={shape.H}")
