@@ -2132,11 +2132,12 @@ hipError_t launch_bf16_persistent(GemmParams p, hipStream_t st, int n_cu) {
 // the 64-wide persistent kernel bounds no weight-row address: at least one whole column tile, and 16-byte stores
 // (its ragged last tile overlaps the one before)
 inline bool whole_column_tiles(const GemmParams& g, bool glu) { return g.N >= (glu ? 128 : 256) && g.N % 8 == 0; }
-inline bool persist_ok(const GemmParams& g, bool glu, int max_super = kMaxSuper) {
+// wide: the row-major kernel's super-tiles (see plan_tiles)
+inline bool persist_ok(const GemmParams& g, bool glu, bool wide, int max_super) {
     GemmParams t = g;
-    plan_tiles(t, 256, glu ? 128 : 256, max_super == kMaxSuperWide);
+    plan_tiles(t, 256, glu ? 128 : 256, wide);
     const long long MG = (t.MT + t.SM - 1) / t.SM, NG = (t.NT + t.SN - 1) / t.SN;
-    // (with k_counts the contraction is at least min(128, K) long: four k-tiles)
+    // (with k_counts the contraction is at least min(128, K) long: two k-tiles)
     return g.K >= 128 && static_cast<long long>(g.E) * MG * NG <= max_super;
 }
 
@@ -2274,7 +2275,7 @@ static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int 
     if (g.K % 8 != 0 || a_row_bytes % 16 != 0 || b_row_bytes % 16 != 0 || a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32))
         return Bf16Kernel::STAGED;
     const bool whole = g.K % 64 == 0;
-    const bool persistent = persist_ok(g, glu, kMaxSuperWide) && whole_column_tiles(g, glu) &&
+    const bool persistent = persist_ok(g, glu, true, kMaxSuperWide) && whole_column_tiles(g, glu) &&
                             (whole || (!g.k_counts && a_bytes < kBufferRange && b_bytes < kBufferRange));
     if (rows_expected <= 0 || g.k_counts)
         return persistent ? Bf16Kernel::PERSISTENT : (whole ? Bf16Kernel::RING : Bf16Kernel::STAGED);
@@ -2327,7 +2328,7 @@ bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
         if (q.K < 256 || q.B1) return false;
         if (static_cast<size_t>(q.k_rows) * (q.k_gather == 1 ? lda : ldb) * 2 >= (1ull << 32)) return false;
     }
-    return persist_ok(params_of(q), false);
+    return persist_ok(params_of(q), false, false, kMaxSuper);
 }
 
 hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& down, const GroupedGemm* gates, int n_gates, hipStream_t st) {
@@ -2349,7 +2350,7 @@ hipError_t launch_backward_products(const GroupedGemm& dx, const GroupedGemm& do
     const Fetch fetch = down.k_gather ? Fetch::ALL : (gates[0].k_gather ? Fetch::GATES : Fetch::NONE);
     if (dx.pieces > 1) {                                 // parts of two k-tiles at least, and the list of their tiles in LDS
         const int half = dx.B1 ? dx.K / 2 : dx.K, k_all = (half + 63) / 64 * (dx.B1 ? 2 : 1), k_piece = (k_all + dx.pieces - 1) / dx.pieces;
-        if (k_all - (dx.pieces - 1) * k_piece < 2 || !persist_ok(params_of(dx), false, kMaxSuper / dx.pieces)) return hipErrorInvalidValue;
+        if (k_all - (dx.pieces - 1) * k_piece < 2 || !persist_ok(params_of(dx), false, false, kMaxSuper / dx.pieces)) return hipErrorInvalidValue;
     }
     b.n_gates = n_gates;
     b.p[0] = params_of(dx);
