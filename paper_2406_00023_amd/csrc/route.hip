@@ -365,8 +365,9 @@ hipError_t launch_route(const etr_config& c, const void* x, const float* w_emb, 
         if (r <= 64 && (r & (r - 1)) == 0) p.R = r;
     }
     // Waves of a workgroup: the fewest that leave the most waves on a CU, between the embeddings' copies in its 160 KiB and the
-    // registers (a call that is resident as a whole with 4 stays there: more workgroups share the staging).  64 experts x 512 pooled features (131 KiB) with 4 / 8 waves, 65536 tokens: 388 / 223 us;
-    // 32 x 512 (73 KiB), 4 / 16: 156 / 126; 64 x 256 (74 KiB), 4 / 8: 159 / 133; 48 x 240 (53 KiB), 40000 tokens, 4 / 8: 102 / 74.
+    // registers (a call that is resident as a whole with 4 stays there: more workgroups share the staging).  64 experts x 512
+    // pooled features (131 KiB) with 4 / 8 waves, 65536 tokens: 388 / 223 us; 32 x 512 (73 KiB), 4 / 16: 156 / 126; 64 x 256 (74
+    // KiB), 4 / 8: 159 / 133; 48 x 240 (53 KiB), 40000 tokens, 4 / 8: 102 / 74.
     auto lds_of = [&](int waves) { return sizeof(float) * (static_cast<size_t>(p.E) * p.w_stride + 64 + static_cast<size_t>(waves) * p.P); };
     auto resident_waves = [&](int waves) {
         const size_t fit = 160 * 1024 / lds_of(waves);
@@ -378,8 +379,9 @@ hipError_t launch_route(const etr_config& c, const void* x, const float* w_emb, 
         if (c.T > cu_count() * resident_waves(4) && resident_waves(w) > resident_waves(waves)) waves = w;
     const size_t lds = lds_of(waves);
     int blocks = (c.T + waves - 1) / waves;
-    // what the registers let be resident at once: the embeddings are staged once per workgroup
-    const int resident = cu_count() * (4 * kRouteWavesPerSimd / waves);
+    // What is resident at once, so that a CU stages the embeddings once per place (64 x 512, two workgroups for each place / one:
+    // 65536 tokens 211 / 203 us, 6000 tokens 37 / 29).
+    const int resident = cu_count() * (resident_waves(waves) / waves);
     if (blocks > resident) blocks = resident;
     if (blocks < 1) blocks = 1;
     const bool fast = p.R > 0 && p.d / V <= kWave * kUnroll;
