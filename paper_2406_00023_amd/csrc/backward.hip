@@ -508,9 +508,9 @@ int padded_capacity(const etr_config& c) {
 // Parts of the input gradient's contraction (bf16, one launch with the weight gradients).  It has few tiles of 2 H / 64
 // k-tiles; where one of them is longer than an even share of all the launch's k-tiles, it is what the launch waits for, so it
 // is cut until it is not: each part's sums go to memory in fp32 and dx_kernel adds them up.  The parts lie where the
-// weights' transposes would.  Step, one part / cut: 8 experts, 1024 x 2816, 64 tokens
-// (32 tiles of 88 k-tiles, 3 parts): 246 / 186 us; 8 of 64 rows, 2048 x 5632: 646 / 588; 16 of 64, 1024 x 2816: 369 / 336; 8 of
-// 128, 2048 x 2816: 417 / 395; 16 of 64, 1080 x 1000: 202 / 195.
+// weights' transposes would.  Step, one part / cut: 8 experts, 1024 x 2816, 64 tokens (32 tiles of 88 k-tiles, 3 parts): 245 /
+// 185 us; 4 of 300 rows, 2048 x 5632: 639 / 531; 8 of 64, 2048 x 5632: 646 / 586; 8 of 512, 1024 x 2816: 428 / 374; 16 of 64, 1024 x
+// 2816: 369 / 336; 8 of 128, 2048 x 2816: 417 / 395; 16 of 64, 1080 x 1000: 202 / 195.
 int dx_pieces(const etr_config& c, int Cp, bool fetch_x) {
     const int KT = 2 * ((c.H + 63) / 64), rows = rows_expected(c), kr = (rows + 63) / 64;
     const double columns = (c.d + 255) / 256, tiles = c.E * ((rows + 255) / 256) * columns;

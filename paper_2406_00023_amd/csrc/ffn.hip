@@ -124,13 +124,7 @@ __device__ __forceinline__ void store_blocks(const GemmParams& p, const f32x16 (
                         }
                     }
                 } else {
-                    uint16_t* dst = Cg + o;
-                    if (p.split_m) {
-                        const bool second = m >= p.split_m;
-                        dst = reinterpret_cast<uint16_t*>(second ? p.C2 : p.C) +
-                              (static_cast<size_t>(e) * p.split_m + (second ? m - p.split_m : m)) * p.N + n;
-                    }
-                    *reinterpret_cast<uint2*>(dst) = pack_bf16x4(g0[q * 4], g0[q * 4 + 1], g0[q * 4 + 2], g0[q * 4 + 3]);
+                    *reinterpret_cast<uint2*>(Cg + o) = pack_bf16x4(g0[q * 4], g0[q * 4 + 1], g0[q * 4 + 2], g0[q * 4 + 3]);
                 }
             }
         __builtin_amdgcn_sched_barrier(0);               // one row of blocks at a time: keeps the live set small
@@ -1633,9 +1627,10 @@ __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p
 // workgroups idle, which here start on the weight gradients' many short tiles, as many rounds of them as its k-tiles stand
 // for.  Where even so a tile of the input gradient is longer than all the rest (few rows), its contraction comes in parts
 // (p[0].pieces, see dx_pieces in backward.hip).  Bound as the kernels above are.  Training step, a launch for each product /
-// this: 12 experts of 677 rows, 1080 x 2744 (180 tiles of 86 k-tiles): 990 / 880 us; 4 of 300, 2048 x 5632: 721 / 633; 8 of 512,
-// 1024 x 2816: 520 / 434; 16 of 166-1024, 2048 x 5632 (1.6 rounds, at the power limit): 2665 / 2625; without fetched rows, in one
-// part, 8 of 64, 2048 x 5632: 763 / 646, 32 of 32, 512 x 1024: 193 / 157.
+// this, in one part: 12 experts of 677 rows, 1080 x 2744 (180 tiles of 86 k-tiles): 994 / 898 us; 4 of 300, 2048 x 5632: 719 / 639;
+// 8 of 512, 1024 x 2816: 482 / 428; 16 of 166-1024, 2048 x 5632 (1.6 rounds, at the power limit): 2678 / 2580; 8 of 64, 2048 x
+// 5632: 753 / 646, 32 of 32, 512 x 1024: 186 / 156.
+// All instantiations spill: 4 to 7 vector registers in the set-up of a product and of a tile, none in the loop over k-tiles.
 struct BackwardProducts { GemmParams p[4]; int n_gates; };
 enum class Fetch { NONE, GATES, ALL };                   // contraction rows through an index: B of the gate and up products, A of down too
 template <bool TAIL, Fetch FETCH>
@@ -2302,7 +2297,7 @@ static GemmParams params_of(const GroupedGemm& q) {
     return g;
 }
 
-// Operands stored with the contraction index slow run only on the persistent bf16 kernel.
+// bf16 operands stored with the contraction index slow run only on the transposing kernel.
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !q.tb) return false;
     // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
@@ -2323,7 +2318,7 @@ bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
     if (a_span >= limit || b_span >= limit) return false;
     if (q.split_m && (!q.ta || q.split_m % 32 != 0 || q.M != 2 * q.split_m || !q.C2 || q.m_counts)) return false;
     if (q.k_gather) {
-        // gathered contraction rows: both operands transposed, eight k-tiles per group at least, 32-bit row offsets
+        // gathered contraction rows: both operands transposed, four k-tiles per group at least, 32-bit row offsets
         if (!(q.ta && q.tb) || (q.k_gather != 1 && q.k_gather != 2) || !q.k_index || q.k_index_stride < 1 || q.k_rows < 1) return false;
         if (q.K < 256 || q.B1) return false;
         if (static_cast<size_t>(q.k_rows) * (q.k_gather == 1 ? lda : ldb) * 2 >= (1ull << 32)) return false;
@@ -2382,7 +2377,7 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
         const int n_cu = cu_count();
         if (q.k_gather == 1) return launch_bf16_transposing<true, 1>(g, st, n_cu);
         if (q.k_gather == 2) return launch_bf16_transposing<true, 2>(g, st, n_cu);
-        if (q.ta) return launch_bf16_transposing<true>(g, st, n_cu);
+        if (q.ta) return hipErrorInvalidValue;           // (such products come in launch_backward_products)
         // a contraction (or half of a split one) that is not whole k-tiles: the zero-filling instantiation
         return (q.B1 ? q.K / 2 : q.K) % 64 == 0 ? launch_bf16_transposing<false>(g, st, n_cu)
                                                 : launch_bf16_transposing<false, 0, true>(g, st, n_cu);
