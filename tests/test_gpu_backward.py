@@ -35,23 +35,31 @@ class Backward:
         self.H, self.shape = H, shape
         self.L = L = H.GpuLayer(shape, mode=mode, cos=cos, gate_norm=gate_norm)
         L.route(); L.select()
-        dev, dt = "cuda", shape.torch_dtype
-        E, Hh, d, T = shape.E, shape.H, shape.d, shape.T
+        dev = "cuda"
         self.dout = I.make_upstream_gradient(shape, dev)
+        self.ws = B.alloc_workspace(B.etr_backward_workspace_bytes(L.cfg))
+        self.ws.fill_(0xFF)               # NaN patterns: nothing may be read before it is written
+        out = self.call(L.slot_of, L.slot_token, L.counts)
+        self.dx, self.dwg, self.dwu, self.dwd, self.dgate, self.dscore = out
+
+    def call(self, slot_of, slot_token, counts):
+        L, t, (T, E, d, Hh) = self.L, self.L.t, (self.shape.T, self.shape.E, self.shape.d, self.shape.H)
         # poisoned outputs: everything the call is meant to overwrite must be overwritten
-        self.dx = torch.full((T, d), 7.0, dtype=dt, device=dev)
-        self.dwg = torch.full((E, Hh, d), 7.0, dtype=dt, device=dev)
-        self.dwu = torch.full((E, Hh, d), 7.0, dtype=dt, device=dev)
-        self.dwd = torch.full((E, d, Hh), 7.0, dtype=dt, device=dev)
-        self.dgate = torch.full((T, E), 7.0, dtype=torch.float32, device=dev)
-        self.dscore = torch.full((T, E), 7.0, dtype=torch.float32, device=dev)
-        ws = B.alloc_workspace(B.etr_backward_workspace_bytes(L.cfg))
-        ws.fill_(0xFF)                    # NaN patterns: nothing may be read before it is written
-        t = L.t
-        B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, L.slot_of,
-                           L.slot_token, L.counts, self.dout, self.dx, self.dwg, self.dwu, self.dwd, ws,
-                           dgate=self.dgate, dscore=self.dscore)
+        out = [torch.full(s, 7.0, dtype=self.shape.torch_dtype, device="cuda") for s in ((T, d), (E, Hh, d), (E, Hh, d), (E, d, Hh))]
+        out += [torch.full((T, E), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+        B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, slot_of, slot_token,
+                           counts, self.dout, *out[:4], self.ws, dgate=out[4], dscore=out[5])
         torch.cuda.synchronize()
+        return out
+
+    def check_second_call(self):
+        """The same call on the workspace as it was left by a call whose experts had each other's rows: the same bits."""
+        L = self.L
+        self.call(*(v.flip(n).contiguous() for v, n in ((L.slot_of, 1), (L.slot_token, 0), (L.counts, 0))))
+        again = self.call(L.slot_of, L.slot_token, L.counts)
+        for name, a, b in zip(("dx", "dw_gate", "dw_up", "dw_down", "dgate", "dscore"), again,
+                              (self.dx, self.dwg, self.dwu, self.dwd, self.dgate, self.dscore)):
+            assert torch.equal(a, b), name
 
     def host(self):
         hx = self.L.host_inputs()
