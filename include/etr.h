@@ -230,8 +230,8 @@ etr_status etr_capacity_lower_bound(const etr_config* cfg, const float* score, f
 
 /* ---- backward of the layer ---------------------------------------------------------------- */
 
-/* Scratch of etr_moe_backward (transposed weights, recomputed pre-activations, transposed
- * per-row gradients, the permuted input gradient). 0 for an invalid config. */
+/* Scratch of etr_moe_backward (recomputed pre-activations, per-row gradients, the permuted input gradient;
+ * bf16: room for transposed weights and copied rows too). 0 for an invalid config. */
 size_t etr_backward_workspace_bytes(const etr_config* cfg);
 
 /* Gradient of the layer of Eqs. 1-6 for an upstream gradient dout, with the routing tables of the

@@ -534,17 +534,18 @@ BackwardWs backward_layout(const etr_config& c) {
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
     const size_t es = elt_bytes(c.dtype), E = c.E, C = c.capacity, H = c.H, d = c.d;
     const size_t Cp = padded_capacity(c);
-    w.wdT = take(E * H * d * es);
-    w.wguT = take(E * d * 2 * H * es);
+    const size_t copies = c.dtype == ETR_F32 ? 0 : es;   // transposed weights, copied and transposed rows: fp32 reads all as they lie
+    w.wdT = take(E * H * d * copies);
+    w.wguT = take(E * d * 2 * H * copies);
     w.a = take(E * C * H * es);
     w.b = take(E * C * H * es);
     w.u = take(E * C * H * es);
     w.dab = take(E * Cp * 2 * H * es);
-    w.daT = take(E * H * Cp * es);
-    w.dbT = take(E * H * Cp * es);
+    w.daT = take(E * H * Cp * copies);
+    w.dbT = take(E * H * Cp * copies);
     w.hT = take(E * H * Cp * es);
-    w.xpT = take(E * d * Cp * es);
-    w.dypT = take(E * d * Cp * es);
+    w.xpT = take(E * d * Cp * copies);
+    w.dypT = take(E * d * Cp * copies);
     w.dxp = take(E * Cp * d * es);
     w.dgate_part = take((H + kTile - 1) / kTile * E * C * 4);
     w.gate_eff = take(static_cast<size_t>(c.T) * E * 4);

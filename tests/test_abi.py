@@ -57,6 +57,15 @@ def test_workspace_queries(lib):
     assert big < 8 * 2 ** 30
 
 
+def test_backward_workspace_of_fp32_holds_what_its_kernels_use(lib):
+    """Three pre-activation buffers, da | db, h and the input gradient by padded rows, the gate-gradient partials and the
+    effective gates, each rounded up to 256 bytes; no room for transposed weights or copied rows."""
+    for s in (I.CONFIGS["cfg1"], I.CONFIGS["cfg1"].with_(T=37, d=24, H=40, E=2, D=8, capacity=40)):
+        E, C, d, H, Cp = s.E, s.capacity, s.d, s.H, (s.capacity + 63) // 64 * 64
+        floats = [E * C * H] * 3 + [E * Cp * 2 * H, E * H * Cp, E * Cp * d, (H + 63) // 64 * E * C, s.T * E]
+        assert B.etr_backward_workspace_bytes(B.make_config(s)) == sum((4 * n + 255) // 256 * 256 for n in floats)
+
+
 def _bad(**kw):
     return B.make_config(I.CONFIGS["cfg1"].with_(**kw))
 
