@@ -12,8 +12,8 @@
 // slow one in memory (Wd for u, Wg / Wu for dXp, the row-major activations for the weight gradients) are
 // read as they lie: the bf16 kernels stage such k-tiles k-major in LDS and take their MFMA fragments through
 // transposing LDS reads, the fp32 ones read single elements, so nothing is transposed in memory.  Only bf16 widths
-// below 128 go through the fall-back that transposes the weights once per call and has the element-wise kernel
-// write transposed copies of the per-row quantities.  Products that do not depend on each other share a launch.
+// below 128 and operands of 4 GiB or more go through the fall-back that transposes the weights once per call and has the
+// element-wise kernel write transposed copies of the per-row quantities.  Products that do not depend on each other share a launch.
 #include <type_traits>
 
 #include "etr_internal.h"
