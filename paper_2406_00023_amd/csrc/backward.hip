@@ -639,10 +639,11 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
         // that weight transposed once per call, where experts have very many rows: the copies move E*d*H elements and the input
         // gradient loses its launch with the weight gradients.  Step, as they lie / transposed: 8 experts x 32 000 rows, 4096 x
-        // 1408 22954 / 22741 us; some 16384 rows, 4 experts, 4096 x 4096 16166 / 16013, 8, 2048 x 1408 6654 / 6662, 4096 x 1408 12290 /
-        // 12451, 1080 x 1000 3761 / 4312; 8192 rows, 8, 2048 x 1408 3218 / 3335; 1024, 602 / 724; 64 rows, 235 / 345.  The kernel
-        // wants at least one whole 256-column tile of the output.
-        const bool many_rows = !f32 && rows_expected(c) > 16384;
+        // 1408 22954 / 22741 us; even counts, 4 experts, 4096 x 4096, 12288 rows 11682 / 11586, 8192 7779 / 7814, 4096 3960 / 4077,
+        // 2048 2064 / 2190; 512 x 4096, 8192 rows 1756 / 1706, 4096 919 / 1029; 8, 2048 x 1408, 1024 rows 602 / 724, 64 235 / 345.  From
+        // 8192 rows on it depends on the widths and on how even the counts are (uneven ones gain from the common launch).  The
+        // kernel wants at least one whole 256-column tile of the output.
+        const bool many_rows = !f32 && rows_expected(c) >= 8192;
         const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
         if (nt_u) {
             transpose_weights(w_down, L.wdT, d, H, d, 0);

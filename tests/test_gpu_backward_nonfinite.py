@@ -19,7 +19,7 @@ CASES = [
     (I.DT_BF16, 700, 264, 200, 330, (0, 2, 255, 256, 257, 330)),    # fetched, a product for each gate; a ragged last column tile
     (I.DT_BF16, 700, 264, 264, 8192, (0, 1, 255, 256, 257, 690)),   # dout fetched as well
     (I.DT_BF16, 300, 136, 200, 8200, (0, 1, 64, 65, 128, 290)),     # few rows of a large capacity, no multiple of 64
-    (I.DT_BF16, 50000, 264, 96, 16900, (0, 1, 255, 256, 257, 16800)),         # more than 16384 expected: launches of their own
+    (I.DT_BF16, 50000, 264, 96, 16900, (0, 1, 255, 256, 257, 16800)),         # 8192 or more expected: launches of their own
     (I.DT_BF16, 300, 64, 72, 200, (0, 1, 63, 64, 65, 200)),         # narrow: transposed copies
     (I.DT_F32, 300, 136, 72, 200, (0, 1, 31, 32, 33, 200)),
 ]

@@ -58,7 +58,8 @@ def test_random_shape_forward_and_backward(oracle, seed):
 
 
 def _many_rows_shape(seed):
-    """Capacities from 8192 on: the backward's weight-gradient products fetch the rows of dOut and x through slot_token, with
+    """Capacities from 8192 on: the backward's weight-gradient products fetch the rows of dOut and x through slot_token and,
+    where as many rows are expected (expert choice), the products against a weight matrix take the row-major kernel; with
     ragged last column tiles."""
     rng = np.random.default_rng(9500 + seed)
     D = int(rng.choice([8, 16, 32]))
