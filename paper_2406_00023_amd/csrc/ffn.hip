@@ -1011,12 +1011,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     auto read_b = [&](int buf, int ks, int idx) {
         fbk[ks][idx] = __builtin_bit_cast(bf16x8, lds[buf * STAGE + b_row[idx] + ck[ks]]);
     };
-    // substep u = 2 ks + h; `mem(m)` is the memory work behind its m-th MFMA
+    // substep u = 2 ks + h; `mem(m)` is the memory work behind its m-th MFMA.  Consecutive MFMAs share one operand (back and
+    // forth over the token blocks): registers that do not change cost no power, and power is the limit.  FFN of 16 experts of
+    // 1280 rows, 4096 x 11008, the layer, weight blocks restarted at each token block / this: 4346 / 4303 us; 8 of 32 000,
+    // 4096 x 1408: 7451 / 7389; back and forth over the weight blocks 4337 and 7397.
     auto substep = [&](int u, auto&& mem) {
         const int ks = u >> 1, h = u & 1;
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
-            const int i = m >> 2, j = m & 3;
+            const int j = m >> 2, i = (j & 1) ? 3 - (m & 3) : (m & 3);
             acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbk[ks][j], fah[h][i], acc[4 * h + i][j], 0, 0, 0);
             mem(m);
             __builtin_amdgcn_sched_barrier(0);
@@ -1341,7 +1344,8 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     };
     // The transposing reads are assembly: through the compiler's builtin every such read waits for ALL outstanding copies
     // (vmcnt(0)), because it is taken to alias the asynchronous LDS writes.  A statement holds eight MFMAs (two token blocks,
-    // four weight blocks) with the reads of up to four fragments behind the first of them and its own wait at the end: the
+    // four weight blocks, back and forth as in the kernel above: training step of 16 experts of 166-1024 rows, 2048 x 5632, 2637 ->
+    // 2620 us) with the reads of up to four fragments behind the first of them and its own wait at the end: the
     // reads land under the remaining MFMAs, and the outputs are ordinary, fully written registers when it ends.  (The reads
     // in statements of their own, with the wait right behind them: 5 % slower over 32 000 rows.)  What the compiler
     // cannot see inside: two wait states between an ordinary write of an operand and its use (the s_nop in front); it must
@@ -1362,25 +1366,27 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         v2i x[4], y[4];
         if constexpr (R == 1)
             asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_MF(2, 2, 0) ETR_MF(3, 3, 0)
-                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         ETR_MF(7, 3, 1) ETR_MF(6, 2, 1) ETR_MF(5, 1, 1) ETR_MF(4, 0, 1) "s_waitcnt lgkmcnt(0)"
                          : ETR_ACC(I), ETR_OUT(0) : ETR_FRAGS, ETR_AT(0, O0));
         if constexpr (R == 2)
             asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_MF(3, 3, 0)
-                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         ETR_MF(7, 3, 1) ETR_MF(6, 2, 1) ETR_MF(5, 1, 1) ETR_MF(4, 0, 1) "s_waitcnt lgkmcnt(0)"
                          : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1) : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1));
         if constexpr (R == 3)
             asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_TR(2) ETR_MF(3, 3, 0)
-                         ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         ETR_MF(7, 3, 1) ETR_MF(6, 2, 1) ETR_MF(5, 1, 1) ETR_MF(4, 0, 1) "s_waitcnt lgkmcnt(0)"
                          : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1), ETR_OUT(2) : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1), ETR_AT(2, O2));
         if constexpr (R == 4)
             asm volatile("s_nop 1\n\t" ETR_MF(0, 0, 0) ETR_TR(0) ETR_MF(1, 1, 0) ETR_TR(1) ETR_MF(2, 2, 0) ETR_TR(2) ETR_MF(3, 3, 0)
-                         ETR_TR(3) ETR_MF(4, 0, 1) ETR_MF(5, 1, 1) ETR_MF(6, 2, 1) ETR_MF(7, 3, 1) "s_waitcnt lgkmcnt(0)"
+                         ETR_TR(3) ETR_MF(7, 3, 1) ETR_MF(6, 2, 1) ETR_MF(5, 1, 1) ETR_MF(4, 0, 1) "s_waitcnt lgkmcnt(0)"
                          : ETR_ACC(I), ETR_OUT(0), ETR_OUT(1), ETR_OUT(2), ETR_OUT(3)
                          : ETR_FRAGS, ETR_AT(0, O0), ETR_AT(1, O1), ETR_AT(2, O2), ETR_AT(3, O3));
         if constexpr (R == 0) {
 #pragma unroll
-            for (int m = 0; m < 8; ++m)
-                acc[I + (m >> 2)][m & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[m & 3], fa[m >> 2], acc[I + (m >> 2)][m & 3], 0, 0, 0);
+            for (int m = 0; m < 8; ++m) {
+                const int i = m >> 2, j = i ? 7 - m : m;
+                acc[I + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[I + i][j], 0, 0, 0);
+            }
         }
         if constexpr (R > 0) *f0 = tr_pack(x[0], y[0]);
         if constexpr (R > 1) *f1 = tr_pack(x[1], y[1]);
