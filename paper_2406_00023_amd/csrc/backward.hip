@@ -5,7 +5,8 @@
 //
 // Stages (all on one stream, nothing leaves the device):
 //   1. a = Xp Wg^T, b = Xp Wu^T recomputed (rows gathered through slot_token), u = dOut_p Wd
-//   2. element-wise: h = SiLU(a) b, da = gate u b SiLU'(a), db = gate u SiLU(a), <u, h> per row (= d out / d gate)
+//   2. element-wise: h = SiLU(a) b, da = gate u b SiLU'(a), db = gate u SiLU(a), <u, h> per row (= d out / d gate); bf16: the
+//      epilogue of u's product, fp32 and the fall-back: a pass of its own
 //   3. dXp = da Wg + db Wu;  dWd = (gate dOut_p)^T h;  dWg = da^T Xp;  dWu = db^T Xp
 //   4. dx[t] = sum_e dXp[e][slot] + sum_e dscore[t][e] * d score[t][e] / d x[t]  (softmax and Eq. 4 differentiated)
 // Every matrix product runs on the grouped kernels of ffn.hip.  Operands whose contraction index is the
@@ -152,8 +153,9 @@ __global__ __launch_bounds__(kTileThreads) void gather_transpose_kernel(const T*
 //        dgate_part [H/64][E][C]: this tile's share of <u, h> per row (summed by dx_kernel in a fixed order)
 // ROWS: no transposed copies; dab and h are [E][Cp][.] row-major with zero rows from counts[e] to padded_rows (the
 // products that contract over the rows read them through transposing LDS reads); hT then is that row-major h.
-// SCALE_H (with ROWS): hT holds gate * h, so that dW_down = dOut_p^T (gate h) needs no scaled copy of dOut's rows.
-template <typename T, bool ROWS, bool SCALE_H = false>
+// fp32 only: hT then holds gate * h, so that dW_down = dOut_p^T (gate h) needs no scaled copy of dOut's rows.  (bf16 has this as
+// the epilogue of the product u, see GEMM_MIDDLE.)
+template <typename T, bool ROWS>
 __global__ __launch_bounds__(kTileThreads) void swiglu_backward_kernel(
     const T* __restrict__ u, const T* __restrict__ a, const T* __restrict__ b, const float* __restrict__ gate,
     const int32_t* __restrict__ slot_token, const int32_t* __restrict__ counts, T* __restrict__ dab, T* __restrict__ daT,
@@ -195,10 +197,8 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_backward_kernel(
             if (s < Cp && n < H) {                                   // (s < padded_rows: the block starts below it)
                 Elt<T>::store_vec(dab + (obase + s) * 2 * H + n, dav);
                 Elt<T>::store_vec(dab + (obase + s) * 2 * H + H + n, dbv);
-                if constexpr (SCALE_H) {
 #pragma unroll
-                    for (int i = 0; i < V; ++i) hv[i] *= g_row;
-                }
+                for (int i = 0; i < V; ++i) hv[i] *= g_row;
                 Elt<T>::store_vec(hT + (obase + s) * H + n, hv);
             }
         } else {
@@ -222,12 +222,29 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_backward_kernel(
     }
 }
 
+// Zero rows of the two products' other operands, dab [E][Cp][2H] and h [E][Cp][H], by one wavefront: row `row` of them
+template <typename T>
+__device__ __forceinline__ void zero_padding(T* dab, T* h, size_t row, int H) {
+    constexpr int V = Elt<T>::kVec;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    for (int j = (threadIdx.x & 63) * V; j < 2 * H; j += 64 * V) *reinterpret_cast<uint4*>(dab + row * 2 * H + j) = zero;
+    for (int j = (threadIdx.x & 63) * V; j < H; j += 64 * V) *reinterpret_cast<uint4*>(h + row * H + j) = zero;
+}
+// The padding of the per-row buffers alone, where no rows are copied: the at most 256 rows from counts[e] to padded_rows
+template <typename T>
+__global__ __launch_bounds__(256) void zero_padding_kernel(const int32_t* __restrict__ counts, T* __restrict__ dab, T* __restrict__ h, int C, int Cp,
+                                                           int H) {
+    const int e = blockIdx.y, count = min(counts[e], C), s = count + blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (count > 0 && s < padded_rows(count, Cp)) zero_padding(dab, h, static_cast<size_t>(e) * Cp + s, H);
+}
+
 // dst[e][s][:] = src[slot_token[e][s]][:] (* gate[slot_token[e][s]][e]) for s < counts[e], zero rows from counts[e] to
-// padded_rows; dst is [E][Cp][d].  One wavefront per row, 16 bytes per lane and access.
+// padded_rows, there also of dab and h where given; dst is [E][Cp][d].  One wavefront per row, 16 bytes per lane and access.
 template <typename T, bool SCALE>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const T* __restrict__ src, const int32_t* __restrict__ slot_token,
                                                           const int32_t* __restrict__ counts, const float* __restrict__ gate,
-                                                          T* __restrict__ dst, int T_, int d, int E, int C, int Cp) {
+                                                          T* __restrict__ dst, int T_, int d, int E, int C, int Cp, T* __restrict__ dab,
+                                                          T* __restrict__ h, int H) {
     constexpr int V = Elt<T>::kVec;
     const int lane = threadIdx.x & 63;
     const long long row = static_cast<long long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
@@ -235,6 +252,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const T* __restrict__ 
     const int e = static_cast<int>(row / Cp), s = static_cast<int>(row - static_cast<long long>(e) * Cp);
     const int count = min(counts[e], C);
     if (s >= padded_rows(count, Cp)) return;
+    if (dab && count > 0 && s >= count) zero_padding(dab, h, static_cast<size_t>(row), H);
     int t = -1;
     float gt = 1.0f;
     if (s < count) {
@@ -592,8 +610,12 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     // LDS reads, so neither the weights nor the per-row quantities are transposed in memory.
     //   u = dOut_p Wd (Wd as [d][H]);  dXp = (da|db) (Wg ; Wu) (two [H][d] halves of the contraction);
     //   dWd = dYp^T h;  dWg = da^T Xp;  dWu = db^T Xp  (contraction over the rows, all operands row-major)
-    GroupedGemm t2{dout, w_down, nullptr, at(L.u), nullptr, counts, nullptr, slot_token, E, C, H, d, 0, H, Tn, GEMM_PLAIN, c.dtype};
+    constexpr bool f32 = sizeof(T) == 4;                 // its kernel takes all widths
+    // (bf16: with the element-wise middle as its epilogue, so u itself is not written)
+    GroupedGemm t2{dout, w_down, nullptr, f32 ? at(L.u) : at(L.dab), f32 ? nullptr : at(L.hT), counts, nullptr, slot_token, E, C, H, d, 0, H, Tn,
+                   f32 ? GEMM_PLAIN : GEMM_MIDDLE, c.dtype};
     t2.tb = true;
+    t2.mid_a = pre_a; t2.mid_b = pre_b; t2.mid_gate = gate_w; t2.mid_part = dgate_part; t2.mid_rows = Cp;
     GroupedGemm t3{at(L.dab), w_gate, w_up, at(L.dxp), nullptr, counts, nullptr, nullptr, E, Cp, d, 2 * H, 0, d, Cp, GEMM_PLAIN, c.dtype};
     t3.tb = true;
     GroupedGemm t4{at(L.dypT), at(L.hT), nullptr, dw_down, nullptr, nullptr, counts, nullptr, E, d, H, Cp, d, H, d, GEMM_PLAIN, c.dtype};
@@ -602,7 +624,6 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     t5.ta = t5.tb = true;
     GroupedGemm t6 = t5;
     t6.A = at(L.dab) + H; t6.C = dw_up;
-    constexpr bool f32 = sizeof(T) == 4;                 // its kernel takes all widths
     const bool direct = f32 || (grouped_gemm_transposed_ok(t2) && grouped_gemm_transposed_ok(t3) && grouped_gemm_transposed_ok(t4) &&
                         grouped_gemm_transposed_ok(t5) && grouped_gemm_transposed_ok(t6));
     // The same three weight-gradient products with the rows of dOut and x fetched through slot_token by the
@@ -636,38 +657,29 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     };
     int dxp_rows = C, pieces = 1;
     if (direct) {
-        // The two products whose only awkward operand is a weight matrix run a little faster on the row-major kernel with
-        // that weight transposed once per call, where experts have very many rows: the copies move E*d*H elements and the input
-        // gradient loses its launch with the weight gradients.  Step, as they lie / transposed: 8 experts x 32 000 rows, 4096 x
+        // The input gradient, whose only awkward operand is a weight matrix, runs a little faster on the row-major kernel with
+        // that weight transposed once per call, where experts have very many rows: the copies move 2*E*d*H elements and it
+        // loses its launch with the weight gradients.  Step (u then went the same way), as they lie / transposed: 8 experts x 32 000 rows, 4096 x
         // 1408 22954 / 22741 us; even counts, 4 experts, 4096 x 4096, 12288 rows 11682 / 11586, 8192 7779 / 7814, 4096 3960 / 4077,
         // 2048 2064 / 2190; 512 x 4096, 8192 rows 1756 / 1706, 4096 919 / 1029; 8, 2048 x 1408, 1024 rows 602 / 724, 64 235 / 345.  From
         // 8192 rows on it depends on the widths and on how even the counts are (uneven ones gain from the common launch).  The
         // kernel wants at least one whole 256-column tile of the output.
-        const bool many_rows = !f32 && rows_expected(c) >= 8192;
-        const bool nt_dxp = many_rows && d >= 256 && d % 8 == 0, nt_u = many_rows && H >= 256 && H % 8 == 0;
-        if (nt_u) {
-            transpose_weights(w_down, L.wdT, d, H, d, 0);
-            ETR_BW(hipGetLastError());
-            GroupedGemm g2{dout, at(L.wdT), nullptr, at(L.u), nullptr, counts, nullptr, slot_token, E, C, H, d, 0, 0, Tn, GEMM_PLAIN, c.dtype};
-            ETR_BW(launch_grouped_gemm(g2, st));
-        } else {
-            ETR_BW(launch_grouped_gemm(t2, st));
-        }
-        auto middle = [&](auto scale_h) {
-            hipLaunchKernelGGL((swiglu_backward_kernel<T, true, decltype(scale_h)::value>), dim3(cH, cC, E), dim3(kTileThreads), 0, st,
-                               at(L.u), pre_a, pre_b, gate_w, slot_token, counts, at(L.dab), static_cast<T*>(nullptr),
-                               static_cast<T*>(nullptr), at(L.hT), dgate_part, Tn, E, C, Cp, H);
-        };
-        if (fetch_dout) {
-            middle(std::integral_constant<bool, true>{});
-        } else if constexpr (!f32) {
-            middle(std::integral_constant<bool, false>{});
+        const bool nt_dxp = !f32 && rows_expected(c) >= 8192 && d >= 256 && d % 8 == 0;
+        t2.mid_scale_h = fetch_dout;
+        ETR_BW(launch_grouped_gemm(t2, st));
+        if constexpr (f32) {
+            hipLaunchKernelGGL((swiglu_backward_kernel<T, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a, pre_b, gate_w,
+                               slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr), at(L.hT), dgate_part, Tn, E,
+                               C, Cp, H);
+        } else if (!fetch_dout) {
             const unsigned row_blocks = static_cast<unsigned>((static_cast<long long>(E) * Cp + 3) / 4);
             if (!fetch_x)
                 hipLaunchKernelGGL((gather_rows_kernel<T, false>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(x),
-                                   slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp);
+                                   slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp, static_cast<T*>(nullptr), static_cast<T*>(nullptr), H);
             hipLaunchKernelGGL((gather_rows_kernel<T, true>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(dout),
-                               slot_token, counts, gate_w, at(L.dypT), Tn, d, E, C, Cp);
+                               slot_token, counts, gate_w, at(L.dypT), Tn, d, E, C, Cp, at(L.dab), at(L.hT), H);
+        } else {
+            hipLaunchKernelGGL(zero_padding_kernel<T>, dim3(64, E), dim3(256), 0, st, counts, at(L.dab), at(L.hT), C, Cp, H);
         }
         ETR_BW(hipGetLastError());
         if (nt_dxp) {
@@ -679,7 +691,7 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
             ETR_BW(launch_grouped_gemm(down, st));
             for (int i = 0; i < n_gates; ++i) ETR_BW(launch_grouped_gemm(gates[i], st));
         } else {
-            if (!f32 && !nt_u) pieces = dx_pieces(c, Cp, fetch_x);
+            if (!f32) pieces = dx_pieces(c, Cp, fetch_x);
             t3.pieces = pieces;
             if (pieces > 1) t3.C = at(L.wdT);            // (behind it the gate and up projections' room, unused here as well)
             ETR_BW(launch_backward_products(t3, down, gates, n_gates, st));

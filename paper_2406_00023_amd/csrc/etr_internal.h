@@ -69,7 +69,8 @@ long long rows_total(const etr_config& c);   // rows of all experts together tha
 // B0/B1 are [G][N][ldb], C/C2 are [G][M][N], all of the layer's dtype.  m_counts (optional) bounds the
 // rows of each group, k_counts (optional) its contraction length: it is rounded up to a multiple of
 // 64, at least 128 (at most K), and the operands must hold zeros in that padding (fp32 with ta: exactly k_counts).
-enum GemmEpilogue { GEMM_PLAIN = 0, GEMM_SWIGLU = 1, GEMM_DUAL = 2 };   // C = A B0^T | SiLU(A B0^T) .* (A B1^T) | both products
+// GEMM_MIDDLE (bf16, tb, rows through row_index): the element-wise middle of the backward on the product u, which is not stored.
+enum GemmEpilogue { GEMM_PLAIN = 0, GEMM_SWIGLU = 1, GEMM_DUAL = 2, GEMM_MIDDLE = 3 };   // C = A B0^T | SiLU(A B0^T) .* (A B1^T) | both products | dab, h
 struct GroupedGemm {
     const void* A; const void* B0; const void* B1;
     void* C; void* C2;
@@ -97,6 +98,14 @@ struct GroupedGemm {
     long long rows_total = 0;
     // input gradient in launch_backward_products, bf16: the contraction in this many parts; C is float [pieces][G][M][N]
     int pieces = 1;
+    // GEMM_MIDDLE: a = W_g x and b = W_u x are [G][M][N]; gate is [a_rows][G], read at the rows' tokens.  Out come C = (da | db)
+    // [G][mid_rows][2 N], C2 = h [G][mid_rows][N] (mid_scale_h: gate * h) and mid_part [ceil(N / 64)][G][M], the share of
+    // <u, h> of each 64 columns, the group's rows of each.
+    const void* mid_a = nullptr; const void* mid_b = nullptr;
+    const float* mid_gate = nullptr;
+    float* mid_part = nullptr;
+    int mid_rows = 0;
+    bool mid_scale_h = false;
 };
 hipError_t launch_grouped_gemm(const GroupedGemm& g, hipStream_t st);
 bool grouped_gemm_transposed_ok(const GroupedGemm& g);

@@ -58,6 +58,12 @@ struct GemmParams {
     // Input gradient only (transposing kernel, row-major A): the contraction in `pieces` parts, each a tile of its own whose
     // fp32 sums go to C as [pieces][E][capacity][N] (NT counts the column tiles of all parts)
     int pieces = 1;
+    // Product of the backward's middle (gemm_bf16_transposing_kernel<.., MID>): see GEMM_MIDDLE
+    const void* mid_a = nullptr;
+    const void* mid_b = nullptr;
+    const float* mid_gate = nullptr;
+    float* mid_part = nullptr;
+    int mid_rows = 0, mid_scale_h = 0;
 };
 
 // rows of group e (counts may be absent: every group has `capacity` rows) and its contraction length
@@ -521,8 +527,8 @@ __device__ __forceinline__ void store_blocks_staged16(const GemmParams& p, const
 // The patch is four pieces of 1 KiB, 8 KiB apart (8 rows x 128 bytes each): the wave's own copy target, see the kernel.  The
 // 16-byte pieces of a row are XORed with the row (no padding fits): two-way bank conflicts on the writes, none on the
 // reads.  In assembly for the reason given above.  N % 8 == 0: a 16-byte piece is all in or all out.
-__device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4], uint16_t* dst, int ldc, int rows_live, int cols_live,
-                                                        uint32_t patch, int lane) {
+// v[u]: row 8 u + lane / 8, columns 8 (lane % 8) .. + 7
+__device__ __forceinline__ void rows_through_patch(const uint2 (&pk)[2][4], uint32_t patch, int lane, epi_v4i (&v)[4]) {
     const int l16 = lane & 15, kq = lane >> 4;
     const uint32_t wbase = patch + (l16 >> 3) * 8192 + (l16 & 7) * 128 + (kq & 1) * 8;
     uint32_t wa[4];
@@ -530,7 +536,6 @@ __device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4],
     for (int bj = 0; bj < 4; ++bj) wa[bj] = wbase + (((2 * bj + (kq >> 1)) ^ (l16 & 7)) * 16);
     const int rr = lane >> 3, ch = lane & 7;
     const uint32_t ra = patch + rr * 128 + ((ch ^ rr) * 16);
-    epi_v4i v0, v1, v2, v3;
     asm volatile(
         "ds_write_b64 %4, %9\n\t"
         "ds_write_b64 %5, %10\n\t"
@@ -545,13 +550,18 @@ __device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4],
         "ds_read_b128 %2, %8 offset:16384\n\t"
         "ds_read_b128 %3, %8 offset:24576\n\t"
         "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3)
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
         : "v"(wa[0]), "v"(wa[1]), "v"(wa[2]), "v"(wa[3]), "v"(ra), "v"(as_v2i(pk[0][0])), "v"(as_v2i(pk[0][1])),
           "v"(as_v2i(pk[0][2])), "v"(as_v2i(pk[0][3])), "v"(as_v2i(pk[1][0])), "v"(as_v2i(pk[1][1])), "v"(as_v2i(pk[1][2])),
           "v"(as_v2i(pk[1][3]))
         : "memory");
+}
+__device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4], uint16_t* dst, int ldc, int rows_live, int cols_live,
+                                                        uint32_t patch, int lane) {
+    epi_v4i v[4];
+    rows_through_patch(pk, patch, lane, v);
+    const int rr = lane >> 3, ch = lane & 7;
     const bool col = ch * 8 < cols_live;
-    const epi_v4i v[4] = {v0, v1, v2, v3};
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int r = 8 * u + rr;
@@ -559,15 +569,137 @@ __device__ __forceinline__ void store_rows_staged_lines(const uint2 (&pk)[2][4],
     }
 }
 
+// s_waitcnt immediate: vmcnt(n) (6 bits, split 3:0 and 15:14), expcnt untouched, lgkmcnt(0) or untouched
+constexpr int waitcnt_imm(int vm, bool lgkm0) { return (vm & 15) | ((vm >> 4) << 14) | 0x70 | (lgkm0 ? 0 : 0x0F00); }
+
+// Buffer descriptors: the range of one that bounds nothing that exists, and an offset past any range (see buffer_copy_to_lds)
+constexpr uint32_t kBufferRange = 0xFFFFFF00u, kPastRange = 0xFFFFFF80u;
+
+// v of the lane whose number differs in bit M (1, 2 or 4), in the vector unit; all lanes active
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+    const int u = __builtin_bit_cast(int, v);
+    int o;
+    if constexpr (M == 4) o = __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, u, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else o = __builtin_amdgcn_update_dpp(0, u, M == 2 ? 0x4E : 0xB1, 0xF, 0xF, true);
+    return __builtin_bit_cast(float, o);
+}
+
+// The epilogue of the product u = dOut_p Wd in the backward: the element-wise middle (see backward.hip) on the wave's 128 rows x
+// 64 columns while they are in registers.  u, rounded to bf16, passes through the patch into whole lines as above; a and b of the
+// same piece are loaded beside it, a block of 32 rows ahead, and da, db and h leave as whole lines.  gates: LDS address of the
+// weights of the wave's rows.
+// Bound by the vector unit (25 issue slots an element, 8 of them the exponential and the reciprocal) and by the 640 KiB that a tile
+// moves, with the matrix pipe idle: some 20 us a tile.  A pass of its own, which also writes and reads u, took longer.  Training
+// step, pass / this: 16 experts of 166-1024 rows, 2048 x 5632: 2615 / 2532 us; 12 of 677, 1080 x 2744: 897 / 865; 8 of 32 000,
+// 4096 x 1408: 23316 / 22977; 8 of 564, 896 x 5248: 1251 / 1210.
+// Not kept: waits counted by hand instead of the compiler's (the same); workgroups with a tile less than others half a tile behind
+// them, so that not all epilogues meet in memory (0-2 % of the product).
+__device__ __forceinline__ void store_middle(const GemmParams& p, const f32x4 (&acc)[8][4], int e, int m_base, int nb, int count, uint32_t gates,
+                                             uint32_t patch, int lane) {
+    if (nb >= p.N || m_base >= count) return;            // wave-uniform
+    asm volatile("" : "+v"(lane));                       // (what depends on it is not worth registers of the loop over k-tiles)
+    const int rr = lane >> 3, ch = lane & 7, N = p.N;
+    const bool col = nb + ch * 8 < N;
+    typedef __attribute__((address_space(1))) char* global_bytes;
+    typedef const __attribute__((address_space(1))) epi_v4i* global_piece;
+    auto uniform = [](const void* base, size_t bytes) -> uint64_t {
+        const uint64_t b = reinterpret_cast<uint64_t>(base) + bytes;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b));
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b >> 32));
+        return (static_cast<uint64_t>(hi) << 32) | lo;
+    };
+    // Stores through a descriptor of each of the group's outputs: a lane that has nothing to store asks for an offset past it.
+    // (Byte offsets inside a group fit 32 bits: a launch condition.)
+    auto output = [&](const void* base, size_t before, size_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform(base, before)), 0, static_cast<int>(bytes), 0x00027000);
+    };
+    const size_t in_bytes = static_cast<size_t>(p.capacity) * N * 2, out_bytes = static_cast<size_t>(p.mid_rows) * N * 2;
+    const global_bytes a_base = (global_bytes)uniform(p.mid_a, e * in_bytes), b_base = (global_bytes)uniform(p.mid_b, e * in_bytes);
+    const __amdgpu_buffer_rsrc_t dab = output(p.C, 2 * e * out_bytes, 2 * out_bytes), hid = output(p.C2, e * out_bytes, out_bytes);
+    const __amdgpu_buffer_rsrc_t part = output(p.mid_part, (static_cast<size_t>(nb >> 6) * p.E + e) * p.capacity * 4, static_cast<size_t>(p.capacity) * 4);
+    // byte offsets of this lane's row m_base + rr and of its piece (a lane past the row repeats the first one; never stored)
+    const uint32_t lane_row = static_cast<uint32_t>(m_base + rr) * N * 2u, piece = (nb + (col ? ch * 8 : 0)) * 2u;
+    const uint32_t last_row = static_cast<uint32_t>(count - 1) * N * 2u;
+    epi_v4i av[4], bv[4];
+    auto request = [&](int ib, int u) {
+        const uint32_t off = min(lane_row + (ib * 32 + 8 * u) * 2u * N, last_row) + piece;
+        av[u] = *(global_piece)(a_base + off);
+        bv[u] = *(global_piece)(b_base + off);
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u) request(0, u);
+#pragma unroll
+    for (int ib = 0; ib < 4; ++ib) {
+        const int mb = m_base + ib * 32;
+        if (mb >= count) break;                          // wave-uniform
+        uint2 pk[2][4];
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < 4; ++bj) {
+                const f32x4& v = acc[2 * ib + bi][bj];
+                pk[bi][bj] = pack_bf16x4(v[0], v[1], v[2], v[3]);
+            }
+        epi_v4i uv[4];
+        rows_through_patch(pk, patch, lane, uv);
+        float gv[4];
+        asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:32\n\tds_read_b32 %2, %4 offset:64\n\tds_read_b32 %3, %4 offset:96\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(gv[0]), "=&v"(gv[1]), "=&v"(gv[2]), "=&v"(gv[3]) : "v"(gates + (ib * 32 + rr) * 4) : "memory");
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int m = mb + 8 * u + rr;
+            const float gate = gv[u], h_scale = p.mid_scale_h ? gate : 1.0f;
+            float dot = 0.f;
+            uint32_t da[4], db[4], hh[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                float fda[2], fdb[2], fh[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    auto half = [&](int word) { return __uint_as_float(j ? static_cast<uint32_t>(word) & 0xFFFF0000u : static_cast<uint32_t>(word) << 16); };
+                    const float uf = half(uv[u][w]), af = half(av[u][w]), bf = half(bv[u][w]);
+                    const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896341f * af));
+                    const float sl = af * sg, h = sl * bf, dh = gate * uf;
+                    fda[j] = dh * bf * (sg * (1.0f + af * (1.0f - sg)));
+                    fdb[j] = dh * sl;
+                    dot += uf * h;
+                    fh[j] = h * h_scale;
+                }
+                da[w] = pack_bf16(fda[0], fda[1]);
+                db[w] = pack_bf16(fdb[0], fdb[1]);
+                hh[w] = pack_bf16(fh[0], fh[1]);
+            }
+            if (ib < 3) request(ib + 1, u);              // (in front of this piece's stores)
+            dot = col ? dot : 0.f;                       // added up over the eight lanes of a row
+            dot += lane_xor<4>(dot);
+            dot += lane_xor<2>(dot);
+            dot += lane_xor<1>(dot);
+            const uint32_t row = lane_row + (ib * 32 + 8 * u) * 2u * N;
+            auto put = [&](const __amdgpu_buffer_rsrc_t& rsrc, uint32_t off, const uint32_t (&v)[4]) {
+                typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], v[2], v[3]}, rsrc, static_cast<int>(col && m < count ? off : kPastRange), 0, 0);
+            };
+            put(dab, 2 * row + piece, da);
+            put(dab, 2 * row + piece + 2u * N, db);
+            put(hid, row + piece, hh);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dot), part, static_cast<int>(m < count && ch == 0 ? m * 4u : kPastRange), 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
 typedef const __attribute__((address_space(1))) void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
+
+__device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
 
 // Ragged contractions (TAIL instantiations of the persistent kernels).  A copy into LDS cannot be masked per lane
 // without leaving stale data behind, so the lanes whose 16-byte piece lies past the end of the contraction ask a
 // buffer descriptor for an offset past its range: such a lane reads nothing and zeros land in its LDS slot.  The
 // descriptor spans all but the last 256 bytes of 4 GiB from the tile's base; real offsets stay below it (a launch
 // condition), so the check never touches a piece that exists.
-constexpr uint32_t kBufferRange = 0xFFFFFF00u, kPastRange = 0xFFFFFF80u;
 __device__ __forceinline__ void buffer_copy_to_lds(uint32_t base_lo, uint32_t base_hi, uint32_t off, uint4* dst) {
     void* base = reinterpret_cast<void*>((static_cast<uint64_t>(base_hi) << 32) | base_lo);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(kBufferRange), 0x00027000);
@@ -589,8 +721,6 @@ __device__ __forceinline__ void buffer_copy_to_lds(uint32_t base_lo, uint32_t ba
 // and the epilogue is SiLU(gate)*up.  With row_index the A rows are gathered straight from the
 // token matrix (dispatch folded into the load).
 // ---------------------------------------------------------------------------------------
-// s_waitcnt immediate: vmcnt(n) (6 bits, split 3:0 and 15:14), expcnt untouched, lgkmcnt(0) or untouched
-constexpr int waitcnt_imm(int vm, bool lgkm0) { return (vm & 15) | ((vm >> 4) << 14) | 0x70 | (lgkm0 ? 0 : 0x0F00); }
 
 template <bool GLU, int WN = 2, bool DUAL = false, int NBUF = 4>
 __global__ __launch_bounds__(128 * WN) void gemm_bf16_ring_kernel(GemmParams p) {
@@ -1154,7 +1284,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
 // four copies of a lane share one k row, so a lane needs one row number per k-tile, loaded three k-tiles ahead.  Row
 // numbers are clamped into [0, k_rows).  In the padding of a group's contraction, where the other operand is zero, its own last
 // row is fetched again: any other row's infinities or NaNs would turn those zeros into NaNs of a group that never had the row.
-// A group without rows has none to repeat: its tiles are stored as zeros whatever was multiplied.
+// A group without rows has none to repeat, and nobody has written its padding: its tiles are stored as zeros whatever was
+// multiplied (TRA).
 //
 // TAIL (row-major A): the contraction, or each half of a split one, need not be whole k-tiles.  The last k-tile of it is
 // short: pieces of a token row and whole weight rows past its end are zero-filled (buffer_copy_to_lds).
@@ -1168,7 +1299,8 @@ struct TransposingLds {                                  // beside the two buffe
     int pre[kMaxSuper + 1];
     int wave_tot[8], rows_of_group[128];
     int row_ids[3][256];                                 // gathered rows of a tile: this, the next, the one after
-    int k_last[64];                                      // KG: last row of each group's contraction (-1: it has none)
+    float gates[3][256];                                 // MID: weights of a tile's rows, in the same three slots
+    int k_last[64];                                      // TRA: last row of each group's contraction (-1: it has none)
 };
 // What a product leaves to the ones behind it in the same launch: the workgroups from place `idle` on are `ahead` k-tiles
 // ahead of the others (a tile counts kTileSteps more than it has); the next list's rounds begin at place `turn`.
@@ -1202,10 +1334,11 @@ struct DealState {
         turn = turn + late < d.W ? turn + late : turn + late - d.W;
     }
 };
-template <bool TRA, int KG, bool TAIL>
+template <bool TRA, int KG, bool TAIL, bool MID = false>
 __device__ __forceinline__ void transposing_tiles(const GemmParams& p, TransposingLds& sh, DealState& state) {
     static_assert(KG == 0 || TRA, "gathered contraction rows: both operands transposed");
     static_assert(!TAIL || (!TRA && KG == 0), "short k-tiles: row-major A");
+    static_assert(!MID || !TRA, "the middle of the backward: row-major A");
     constexpr int NW = 8, BM = 256, BN = 256, CPR = 8, SWZ = 1;
     constexpr int HALF = 256 * CPR;                      // uint4 per operand and LDS buffer (32 KiB)
     constexpr int STAGE = 2 * HALF;
@@ -1223,7 +1356,10 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     const int Kh = splitB ? p.K / 2 : p.K, KTh = (Kh + 63) / 64;         // of the whole product, or of each half of a split one
     const int k_rem = (Kh & 63) ? (Kh & 63) : 64;        // valid k of the last k-tile
 
-    if (KG != 0 && tid < p.E) sh.k_last[tid] = min(min(p.k_counts ? max(p.k_counts[tid], 0) : p.K, p.K), p.k_index_stride) - 1;
+    if (TRA && tid < p.E) {
+        const int n = min(p.k_counts ? max(p.k_counts[tid], 0) : p.K, p.K);
+        sh.k_last[tid] = (KG != 0 ? min(n, p.k_index_stride) : n) - 1;
+    }
     LiveTiles tiles;
     tiles.build<NW * 64>(p, BM, sh.pre, sh.wave_tot, sh.rows_of_group);          // (its barriers cover k_last)
     const int total = tiles.total;
@@ -1234,7 +1370,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     struct Tile {
         int e, m0, n0, count, KT;
         int k0, piece;                                   // first k-tile, part of the contraction
-        int k_last;                                      // KG: last row of the contraction
+        int k_last;                                      // TRA: last row of the contraction
         uint64_t Abase, Bbase, Bbase1;                   // wave-uniform; Bbase1: second half of a split B
         uint32_t offA[TRA ? 1 : NCP];                    // row-major A: byte offsets of this lane's row groups
     };
@@ -1258,7 +1394,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         t.count = tiles.count(e);
         t.k0 = t.piece * k_piece;
         t.KT = TRA ? tiles.k_tiles(e) : min(k_piece, k_all - t.k0);
-        t.k_last = KG != 0 ? __builtin_amdgcn_readfirstlane(sh.k_last[e]) : 0;
+        t.k_last = TRA ? __builtin_amdgcn_readfirstlane(sh.k_last[e]) : 0;
         t.Abase = reinterpret_cast<uint64_t>(p.A);
         if (KG != 1) t.Abase += TRA ? static_cast<uint64_t>(e) * p.K * lda * 2
                                     : (p.row_index ? 0 : static_cast<uint64_t>(e) * p.capacity * lda * 2);
@@ -1472,6 +1608,16 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
             asm volatile("s_nop 15\n\ts_nop 3" : ETR_ACC(i));
     };
 
+    // MID: the weights of the rows whose token numbers lie in a slot, beside them (zero for a number that is none)
+    auto request_gates = [&](int e, int slot) {
+        if (wave < 4) {
+            const int token = row_ids[slot][wave * 64 + lane];
+            const bool in = token >= 0 && token < p.a_rows;
+            const float* src = in ? p.mid_gate + static_cast<size_t>(token) * p.E + e : kZeroPiece;
+            __builtin_amdgcn_global_load_lds((global_cptr)src, (lds_ptr)(sh.gates[slot] + wave * 64), 4, 0, 0);
+        }
+    };
+
     if (deal.tile(0) >= total) return;                   // uniform: nothing for this workgroup
     Tile cur, nxt;
     LiveTiles::Place next_at{}, after{};
@@ -1486,6 +1632,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         __builtin_amdgcn_s_barrier();                    // the indices were fetched by other waves
     }
     finish(cur, 0);
+    if constexpr (MID) request_gates(cur.e, 0);
     int g = 0;                                           // global step: buffer g & 1
     int index = 0;                                       // KG: this lane's row number in k-tile g + 2
     if constexpr (KG != 0) index = load_index(cur.e, cur.k_last, 2); // (KT >= 4)
@@ -1514,6 +1661,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         if (has_next) {
             fill(next_at, nxt);
             finish(nxt, (seq + 1) % 3);
+            if constexpr (MID) request_gates(nxt.e, (seq + 1) % 3);
         }
         const bool has_after = deal.tile(seq + 2) < total;               // its row indices are requested two tiles ahead
         if (has_after) {
@@ -1574,7 +1722,7 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
             late_last = last;
         }
         settle();
-        if (KG != 0 && cur.k_last < 0) {
+        if (TRA && cur.k_last < 0) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1583,7 +1731,10 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
         // ---- epilogue of cur (the copies of the next tile are in flight).  The patch is the wave's own copy target in the
         // B half of the buffer just multiplied: behind the last barrier nobody reads it any more, and the next copies into
         // it are the wave's own, in its next substep 0.
-        if (!TRA && p.pieces > 1) {                      // few rows: fp32 sums, 16 rows x 64 bytes an instruction
+        const uint32_t patch = lds_base + static_cast<uint32_t>((g - 1) & 1) * (STAGE * 16) + HALF * 16 + wave * 1024;
+        if constexpr (MID) {
+            store_middle(p, acc, cur.e, cur.m0 + wm * 128, cur.n0 + wn * 64, cur.count, lds_address(sh.gates[seq % 3] + wm * 128), patch, lane);
+        } else if (!TRA && p.pieces > 1) {               // few rows: fp32 sums, 16 rows x 64 bytes an instruction
             float* out = static_cast<float*>(p.C) + (static_cast<size_t>(cur.piece) * p.E + cur.e) * p.capacity * p.N;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -1595,7 +1746,6 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
                 }
             }
         } else {
-            const uint32_t patch = lds_base + static_cast<uint32_t>((g - 1) & 1) * (STAGE * 16) + HALF * 16 + wave * 1024;
             const int nb = cur.n0 + wn * 64;
             auto pack4 = [](const f32x4& v) { return pack_bf16x4(v[0], v[1], v[2], v[3]); };
 #pragma unroll
@@ -1624,12 +1774,12 @@ __device__ __forceinline__ void transposing_tiles(const GemmParams& p, Transposi
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));   // the re-fetched k-tiles of the last two steps
 }
-template <bool TRA, int KG = 0, bool TAIL = false>
+template <bool TRA, int KG, bool TAIL, bool MID>
 __global__ __launch_bounds__(512) void gemm_bf16_transposing_kernel(GemmParams p) {
     __shared__ TransposingLds sh;
     DealState state;
     state.idle = gridDim.x;
-    transposing_tiles<TRA, KG, TAIL>(p, sh, state);
+    transposing_tiles<TRA, KG, TAIL, MID>(p, sh, state);
 }
 
 // The last products of the backward in one launch: the input gradient (p[0]: row-major A, TAIL as above), then the weight
@@ -1686,7 +1836,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_backward_kernel(BackwardProduct
 // ---------------------------------------------------------------------------------------
 constexpr int kRowsBM = 64;                             // token rows per workgroup
 constexpr int kRowsBuffers = 3, kRowsPieces = 16;       // LDS buffers; 16-byte pieces of a staged token row (128 k)
-__device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
 
 template <int MB, bool GLU, bool DUAL, bool KEEP>
 __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, int n0, int count, uint4* lds) {
@@ -2099,11 +2248,11 @@ hipError_t launch_bf16_ring(GemmParams p, hipStream_t st) {
 
 // Transposing kernel: needs every group's contraction length >= 128 (two k-tiles to prefetch; 256 where it fetches rows
 // through an index) and the super-tile prefix to fit in LDS.
-template <bool TRA, int KG = 0, bool TAIL = false>
+template <bool TRA, int KG, bool TAIL = false, bool MID = false>
 hipError_t launch_bf16_transposing(GemmParams p, hipStream_t st, int n_cu) {
     constexpr size_t lds = 2ull * 512 * 64 * 2;                             // two buffers of 256 + 256 rows x 64 bf16
     plan_tiles(p, 256, 256);
-    auto kern = gemm_bf16_transposing_kernel<TRA, KG, TAIL>;
+    auto kern = gemm_bf16_transposing_kernel<TRA, KG, TAIL, MID>;
     hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(n_cu / 8 * 8)), dim3(512), lds, st, p);
@@ -2305,12 +2454,16 @@ static GemmParams params_of(const GroupedGemm& q) {
     g.split_m = q.split_m;
     g.rows_total = q.rows_total;
     g.pieces = q.pieces;
+    g.mid_a = q.mid_a; g.mid_b = q.mid_b; g.mid_gate = q.mid_gate; g.mid_part = q.mid_part;
+    g.mid_rows = q.mid_rows; g.mid_scale_h = q.mid_scale_h ? 1 : 0;
     return g;
 }
 
 // bf16 operands stored with the contraction index slow run only on the transposing kernel.
 bool grouped_gemm_transposed_ok(const GroupedGemm& q) {
-    if (q.dtype != ETR_BF16 || q.epilogue != GEMM_PLAIN || !q.tb) return false;
+    if (q.dtype != ETR_BF16 || (q.epilogue != GEMM_PLAIN && q.epilogue != GEMM_MIDDLE) || !q.tb) return false;
+    if (q.epilogue == GEMM_MIDDLE && (q.ta || q.B1 || !q.row_index || !q.C2 || !q.mid_a || !q.mid_b || !q.mid_gate || !q.mid_part || q.mid_rows < q.M ||
+                                          static_cast<size_t>(q.mid_rows) * 4 * q.N >= kBufferRange)) return false;
     // (row-major A and transposed B take any multiple of 8; a contraction over padded rows is whole k-tiles anyway)
     if (q.N % 8 != 0 || q.N < 8) return false;                     // 16-byte stores, and chunks along the rows of a [K][rows] operand
     if (!q.ta && q.k_counts) return false;
@@ -2389,9 +2542,10 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
         if (q.k_gather == 1) return launch_bf16_transposing<true, 1>(g, st, n_cu);
         if (q.k_gather == 2) return launch_bf16_transposing<true, 2>(g, st, n_cu);
         if (q.ta) return hipErrorInvalidValue;           // (such products come in launch_backward_products)
-        // a contraction (or half of a split one) that is not whole k-tiles: the zero-filling instantiation
-        return (q.B1 ? q.K / 2 : q.K) % 64 == 0 ? launch_bf16_transposing<false>(g, st, n_cu)
-                                                : launch_bf16_transposing<false, 0, true>(g, st, n_cu);
+        if (q.epilogue != GEMM_MIDDLE) return hipErrorInvalidValue;
+        // a contraction that is not whole k-tiles: the zero-filling instantiation
+        return q.K % 64 == 0 ? launch_bf16_transposing<false, 0, false, true>(g, st, n_cu)
+                             : launch_bf16_transposing<false, 0, true, true>(g, st, n_cu);
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;

@@ -1,0 +1,55 @@
+"""The element-wise middle of the bf16 backward as the epilogue of its product: experts whose rows end inside the pieces of 8 and
+the blocks of 32 rows that it goes by, in the second half of a tile, past one tile, and none at all; widths that end inside a
+piece of 64 hidden units; kept pre-activations and recomputed ones, invalid entries of the slot list.  All gradients, with that
+of the gate, against the oracle with the layer's tolerance; the workspace holds NaN patterns."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2406_00023_amd import binding as B
+from paper_2406_00023_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# (T, d, H, C, rows of each expert)
+@pytest.mark.parametrize("T,d,Hh,C,rows", [
+    (120, 128, 72, 100, (1, 7, 8, 9, 31, 32, 33, 100)), (400, 136, 64, 300, (0, 127, 128, 129, 255, 256, 257, 300)),
+    (700, 264, 328, 640, (159, 160, 161, 512, 513, 640, 2, 64)), (200, 128, 1024, 200, (65, 0, 200)),
+    (900, 128, 200, 8192, (0, 1, 255, 256, 257, 900))])
+@pytest.mark.parametrize("gate_norm", [0, 1])
+def test_middle_at_the_edges_of_its_blocks(oracle, T, d, Hh, C, rows, gate_norm):
+    import gpu_helpers as H
+    B.load_library()
+    E = len(rows)
+    shape = I.EtrShape("middle", 43, T=T, d=d, E=E, D=8, k=2, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR, recipe="iso",
+                       n_centroids=E)
+    print(f"backward middle T={T} d={d} H={Hh} C={C} rows={rows} gate_norm={gate_norm}", flush=True)
+    L = H.GpuLayer(shape, gate_norm=gate_norm)
+    L.route()
+    slot_of, slot_token = np.full((T, E), -1, np.int32), np.full((E, C), -1, np.int32)
+    rng = np.random.default_rng(5)
+    for e, n in enumerate(rows):
+        tokens = np.sort(rng.choice(T, n, replace=False))
+        slot_token[e, :n] = tokens
+        slot_of[tokens, e] = np.arange(n)
+    tables = [torch.from_numpy(v).cuda() for v in (slot_of, slot_token, np.array(rows, np.int32))]
+    dout = I.make_upstream_gradient(shape, "cuda")
+    t = L.t
+    out = [torch.full(s, 7.0, dtype=shape.torch_dtype, device="cuda") for s in ((T, d), (E, Hh, d), (E, Hh, d), (E, d, Hh))]
+    dgate = torch.full((T, E), 7.0, device="cuda")
+    ws = B.alloc_workspace(B.etr_backward_workspace_bytes(L.cfg))
+    ws.fill_(0xFF)
+    B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, *tables, dout, *out, ws, dgate=dgate)
+    torch.cuda.synchronize()
+    hx = L.host_inputs()
+    ref = oracle.moe_backward(*(hx[n] for n in ("x", "w_emb", "w_gate", "w_up", "w_down")), slot_of, H.to_np(dout), D=8, dtype=shape.dtype,
+                              gate_norm=gate_norm)
+    tol = H.TOL_OUT[shape.dtype]
+    for name, v in zip(("dx", "dw_gate", "dw_up", "dw_down"), out):
+        a = oracle.to_f64(H.to_np(v), shape.dtype)
+        assert np.isfinite(a).all() and H.scale_rel_err(a, ref[name]) <= tol, name
+        if name != "dx":
+            for e, n in enumerate(rows):                 # each expert on its own scale; no rows: exact zeros
+                assert H.scale_rel_err(a[e], ref[name][e]) <= tol if n else not a[e].any(), (name, e)
+    assert H.scale_rel_err(H.to_np(dgate).astype(np.float64), ref["dgate"]) <= tol
