@@ -689,11 +689,13 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
 // Everything in one launch for short batches (T <= kSmallTokens, no strict intersection):
 // one workgroup per expert, one thread per token.  What a small call pays for is launches and dependent latencies, so
 // each workgroup reads all scores (they are in the caches) and finds its expert's place in every token's list by
-// counting the better experts of the row; the keys of its column meet in LDS, and a candidate is kept if fewer than
-// `capacity` candidates precede it (a larger key, or the same key and a lower token), again by counting: T / 4
-// broadcast reads per thread instead of a radix search.  The slot is the number of kept tokens in front, from ballots.
-// Counting grows with T^2.  One call against the three launches, T x E: 32 x 16 5.4 / 12.3 us, 256 x 32 9.0 / 14.5,
-// 512 x 8 10.2 / 12.3, 512 x 64 15.6 / 20.7; from 1024 tokens on it would be the slower one.
+// counting the better experts of the row; the candidates of its column are brought together in LDS, and one is kept if
+// fewer than `capacity` precede it (a larger key, or the same key and a lower token), again by counting: a quarter of them
+// in broadcast reads per thread instead of a radix search, and none where all fit (as in decode steps).  The slot is the number
+// of kept tokens in front, from ballots.  Counting grows with the square of the candidates.  One call against the three
+// launches, T x E: 32 x 16 3.4 / 12.3 us, 256 x 32 5.2 / 14.5, 512 x 8 3.5 / 12.3, 512 x 64 11 / 20.7 (with every token of the
+// column in the count, candidate or not: 5.6, 9.2, 10.3 and 15.7); where experts choose, 512 x 8: 9.5; from 1024 tokens on
+// that would be the slower one.
 // ---------------------------------------------------------------------------------------
 // ADAPT: with the affinity-sum threshold (ECR and BIDIR).  The walk from the highest affinity down stops at the first
 // prefix whose sum of positive affinities reaches it, so a candidate is kept if the terms of those that precede it do
@@ -708,7 +710,7 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
                                                                     int32_t* __restrict__ slot_token, int32_t* __restrict__ counts) {
     __shared__ __attribute__((aligned(16))) uint32_t keys[kSmallTokens];
     __shared__ __attribute__((aligned(16))) uint32_t terms[ADAPT ? kSmallTokens : 4];
-    __shared__ int wave_kept[kSmallTokens / kWave];
+    __shared__ int tokens[kSmallTokens], wave_count[kSmallTokens / kWave], wave_kept[kSmallTokens / kWave];
     const int e = blockIdx.x, t = threadIdx.x, nthreads = blockDim.x;       // nthreads: T rounded up to whole waves
     const int lane = t & (kWave - 1), wave = t / kWave;
     const int capacity = capacity_dev ? min(capacity_host, max(1, *capacity_dev)) : capacity_host;
@@ -741,34 +743,52 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         }
         key = selection_key(own_score, mode == ETR_MODE_ECR || rank < k, mode, k, rank);
     }
-    if (mode == ETR_MODE_TCR) {                          // equal keys: the first `capacity` candidates, in their own order
-        const uint64_t in_wave = __ballot(key != 0u);
-        if (lane == 0) wave_kept[wave] = __popcll(in_wave);
+    int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
+    int n = T;                                           // candidates (a key of 0 is none)
+    // Where every token is a candidate and some are turned away there is nothing to bring together.
+    if (mode == ETR_MODE_TCR || capacity >= T || (mode != ETR_MODE_ECR && k < E)) {
+        // place among the column's candidates, in token order
+        const uint64_t in_column = __ballot(key != 0u);
+        if (lane == 0) wave_count[wave] = __popcll(in_column);
         __syncthreads();
-        int slot = __popcll(in_wave & ((1ull << lane) - 1ull)), total = 0;
+        int place = __popcll(in_column & ((1ull << lane) - 1ull));
+        n = 0;
         for (int w = 0; w < nthreads / kWave; ++w) {
-            if (w < wave) slot += wave_kept[w];
-            total += wave_kept[w];
+            if (w < wave) place += wave_count[w];
+            n += wave_count[w];
         }
-        total = min(total, capacity);
-        const bool kept = key != 0u && slot < capacity;
-        if (t < T) slot_of[static_cast<size_t>(t) * E + e] = kept ? slot : -1;
-        int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
-        if (kept) mine[slot] = t;
-        for (int i = total + t; i < capacity_host; i += nthreads) mine[i] = -1;
-        if (t == 0) counts[e] = total;
-        return;
+        if (mode == ETR_MODE_TCR || (!ADAPT && n <= capacity)) {   // uniform: the first ones, or all, in their own order
+            const bool kept = key != 0u && place < capacity;
+            const int total = min(n, capacity);
+            if (t < T) slot_of[static_cast<size_t>(t) * E + e] = kept ? place : -1;
+            if (kept) mine[place] = t;
+            for (int i = total + t; i < capacity_host; i += nthreads) mine[i] = -1;
+            if (t == 0) counts[e] = total;
+            return;
+        }
+        // side by side; from here on a thread has the candidate of its own number
+        if (t < T && key == 0u) slot_of[static_cast<size_t>(t) * E + e] = -1;
+        if (key != 0u) {
+            keys[place] = key;
+            tokens[place] = t;
+            if constexpr (ADAPT) terms[place] = key >= 0x80000000u ? affinity_term(key) : 0u;
+        }
+        if (t >= n) keys[t] = 0u;
+        __syncthreads();
+        key = keys[t];
+    } else {
+        keys[t] = key;
+        tokens[t] = t;
+        if constexpr (ADAPT) terms[t] = key >= 0x80000000u ? affinity_term(key) : 0u;
+        __syncthreads();
     }
-    keys[t] = key;
-    if constexpr (ADAPT) terms[t] = key >= 0x80000000u ? affinity_term(key) : 0u;
-    __syncthreads();
     // candidates that precede this one: of the waves before, >=; of the waves behind, >; inside the wave by lane
     int before = 0;
     unsigned long long before_sum = 0ull;
     const uint4* k4 = reinterpret_cast<const uint4*>(keys);
     const uint4* t4 = reinterpret_cast<const uint4*>(terms);
-    const int uwave = __builtin_amdgcn_readfirstlane(wave), waves = nthreads / kWave;
-    for (int w = 0; w < waves; ++w) {
+    const int uwave = __builtin_amdgcn_readfirstlane(wave), waves = (n + kWave - 1) / kWave;
+    for (int w = 0; w < waves && uwave < waves; ++w) {
         if (w == uwave) continue;
         uint4 v[kWave / 4];                             // a wave's 64 keys requested together
 #pragma unroll
@@ -786,18 +806,20 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
             }
         }
     }
+    if (uwave < waves) {
 #pragma unroll 4
-    for (int i = 0; i < kWave / 4; ++i) {
-        const uint4 v = k4[wave * (kWave / 4) + i];
-        const uint32_t f[4] = {v.x, v.y, v.z, v.w};
+        for (int i = 0; i < kWave / 4; ++i) {
+            const uint4 v = k4[uwave * (kWave / 4) + i];
+            const uint32_t f[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool first = f[j] > key || (f[j] == key && 4 * i + j < lane);
-            before += first;
-            if constexpr (ADAPT) before_sum += first ? terms[wave * kWave + 4 * i + j] : 0u;
+            for (int j = 0; j < 4; ++j) {
+                const bool first = f[j] > key || (f[j] == key && 4 * i + j < lane);
+                before += first;
+                if constexpr (ADAPT) before_sum += first ? terms[uwave * kWave + 4 * i + j] : 0u;
+            }
         }
     }
-    bool kept = key != 0u && before < capacity;          // (a key of 0 is no candidate)
+    bool kept = key != 0u && before < capacity;
     if constexpr (ADAPT) kept = kept && before_sum < static_cast<unsigned long long>(sum_need);
     const uint64_t in_wave = __ballot(kept);
     if (lane == 0) wave_kept[wave] = __popcll(in_wave);
@@ -807,9 +829,11 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         if (w < wave) slot += wave_kept[w];
         total += wave_kept[w];
     }
-    if (t < T) slot_of[static_cast<size_t>(t) * E + e] = kept ? slot : -1;
-    int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
-    if (kept) mine[slot] = t;
+    if (t < n) {
+        const int token = tokens[t];
+        slot_of[static_cast<size_t>(token) * E + e] = kept ? slot : -1;
+        if (kept) mine[slot] = token;
+    }
     for (int i = total + t; i < capacity_host; i += nthreads) mine[i] = -1;
     if (t == 0) counts[e] = total;
 }
