@@ -14,6 +14,7 @@
 //                            the (key > tau, key == tau) counts of each chunk are scanned into exclusive prefixes
 //                            (long columns: the first digit is counted beforehand by key_histogram_kernel,
 //                            up to 16 workgroups per expert)
+//   (where experts keep few of the tokens: choice_lists_kernel, expert_lists_kernel, slot_lists_kernel, see by_lists)
 //   3. slot_kernel           one lane per (expert, token): the position inside the chunk comes from a
 //                            ballot, so slot_of / slot_token are written without any serial walk; the slots of
 //                            64 tokens leave as whole rows of slot_of
@@ -200,6 +201,24 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
     return v;
 }
 
+// The same for 64-bit sums.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_from(long long v) {
+    const uint32_t lo = static_cast<uint32_t>(v), hi = static_cast<uint32_t>(static_cast<unsigned long long>(v) >> 32);
+    const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), CTRL, ROWS, 0xF, false));
+    const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(hi), CTRL, ROWS, 0xF, false));
+    return static_cast<long long>((static_cast<unsigned long long>(h) << 32) | l);
+}
+__device__ __forceinline__ long long wave_scan_incl(long long v) {
+    v += dpp_from<0x111, 0xF>(v);
+    v += dpp_from<0x112, 0xF>(v);
+    v += dpp_from<0x114, 0xF>(v);
+    v += dpp_from<0x118, 0xF>(v);
+    v += dpp_from<0x142, 0xA>(v);
+    v += dpp_from<0x143, 0xC>(v);
+    return v;
+}
+
 // Sum over aligned groups of Q lanes (Q = 1, 2, 4, 8, 16), every lane of a group gets the group's total:
 // swaps inside quads, then the mirror images of the half row and of the row.  Call with all lanes active.
 template <int Q>
@@ -272,6 +291,102 @@ __device__ __forceinline__ void digit_pick(const uint32_t* hist, const DigitView
     const int j = m2 ? __builtin_ctzll(m2) : 31;
     digit = kBins - 1 - 32 * g - j;
     above = before + __builtin_amdgcn_readlane(upto - h, j);
+}
+
+// The key at which the sum of the affinities' terms, walked from the highest down, reaches sum_need, digit by digit: an LDS
+// histogram of the terms (64-bit sums) over up to 11 bits at a time of the low `shift` ones, walked from the top; the positive keys
+// agree with th above those.  True where that happens within n_keep candidates, which then is their number.  By a whole
+// workgroup; for_keys(f) calls f on this thread's keys.
+template <typename Keys>
+__device__ __forceinline__ bool sum_threshold(Keys&& for_keys, long long sum_need, uint32_t th, int shift, unsigned long long* sums, int& n_keep,
+                                              uint32_t& theta) {
+    __shared__ int red_cnt[kSelThreads / kWave], picked_digit;
+    __shared__ long long wave_sums[kSelThreads / kWave], picked_above;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    long long above_sum = 0;                             // sum over the candidates above th, the settled bits of theta
+    while (shift > 0) {
+        const int w = shift < kRadixBits ? shift : kRadixBits;
+        shift -= w;
+        const uint32_t span = (1u << (shift + w)) - 1u, dmask = (1u << w) - 1u;
+        __syncthreads();                                 // the histogram's previous readers are done
+        sums[2 * tid] = 0ull; sums[2 * tid + 1] = 0ull;
+        __syncthreads();
+        for_keys([&](uint32_t key) {
+            if (key - th <= span) atomicAdd(&sums[(key >> shift) & dmask], static_cast<unsigned long long>(affinity_term(key)));
+        });
+        __syncthreads();
+        // the highest bin at which the sum from the top reaches the threshold: two bins to a thread, the highest to thread 0
+        const long long need = sum_need - above_sum;     // > 0
+        const int low = kBins - 2 - 2 * tid;
+        const long long high_bin = static_cast<long long>(sums[low + 1]), both = high_bin + static_cast<long long>(sums[low]);
+        const long long upto = wave_scan_incl(both);
+        if (lane == kWave - 1) wave_sums[wave] = upto;
+        __syncthreads();
+        long long before = upto - both, total = 0;
+#pragma unroll
+        for (int w = 0; w < kSelThreads / kWave; ++w) {
+            if (w < wave) before += wave_sums[w];
+            total += wave_sums[w];
+        }
+        if (total < need) return false;                  // (uniform; from the second digit on never) the positive affinities never get there: take all
+        if (before < need && need <= before + both) {    // one thread
+            const bool high = before + high_bin >= need;
+            picked_digit = high ? low + 1 : low;
+            picked_above = high ? before : before + high_bin;
+        }
+        __syncthreads();
+        above_sum += picked_above;
+        th |= static_cast<uint32_t>(picked_digit) << shift;
+    }
+    // th is settled: above_sum is the sum over the keys above it; count them
+    int n_gt = 0;
+    for_keys([&](uint32_t key) { n_gt += key > th; });
+    n_gt = wave_sum_i(n_gt);
+    if (lane == 0) red_cnt[wave] = n_gt;
+    __syncthreads();
+    n_gt = 0;
+#pragma unroll
+    for (int w = 0; w < kSelThreads / kWave; ++w) n_gt += red_cnt[w];
+    const long long q_th = affinity_term(th);
+    if (q_th == 0) return false;                         // (only where all positive keys are the same)
+    const long long ell = n_gt + (sum_need - above_sum + q_th - 1) / q_th;       // q_th > 0: its bin reached the sum
+    if (ell > n_keep) return false;
+    n_keep = static_cast<int>(ell);
+    theta = th;
+    return true;
+}
+
+// The n_keep-th largest key, by radix search from the top; the bits above the low `shift` ones are those of prefix.  The first
+// `counted` digits (0 or 1) have been counted, the first one's view is `first`.  hist: kMaxDigits histograms of zeros.
+template <typename Keys>
+__device__ __forceinline__ uint32_t count_threshold(Keys&& for_keys, int n_keep, int shift, uint32_t prefix, uint32_t (*hist)[kBins], int counted,
+                                                    const DigitView& first) {
+    int need = n_keep;
+    for (int p = 0; p < kMaxDigits && shift > 0; ++p) {
+        const int w = shift < kRadixBits ? shift : kRadixBits;
+        const int top = shift;                           // bits [31:top] are settled
+        shift -= w;
+        int digit, above;
+        if (p < counted) {
+            digit_pick(hist[0], first, need, digit, above);
+        } else {
+            // candidates whose settled bits equal the prefix: lo <= key <= lo + span
+            const uint32_t lo = prefix > 1u ? prefix : 1u;
+            const uint32_t span = (top >= 32 ? 0xFFFFFFFFu : prefix + ((1u << top) - 1u)) - lo;
+            const uint32_t dmask = (1u << w) - 1u;
+            uint32_t* h = hist[p];
+            for_keys([&](uint32_t key) {
+                if (key - lo <= span) atomicAdd(&h[(key >> shift) & dmask], 1u);     // LDS; integer adds, so order-free
+            });
+            __syncthreads();
+            const DigitView d = digit_view(h);
+            digit_pick(h, d, need, digit, above);
+        }
+        prefix |= static_cast<uint32_t>(digit) << shift;
+        need -= above;
+        if (static_cast<int>(hist[p][digit]) == need) break;         // all of the digit's keys are kept: its first value will do
+    }
+    return prefix;
 }
 
 // One 1024-thread workgroup per expert.
@@ -371,79 +486,22 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
     // for: the n_keep candidates end among the keys equal to it.
     bool settled = false;
     uint32_t theta = 0u;
+    auto for_keys = [&](auto&& f) {
+        if constexpr (IPT > 0) {
+#pragma unroll
+            for (int j = 0; j < IPT; ++j) f(keys[j]);
+        } else {
+            for (int idx = tid; idx < T; idx += kSelThreads) f(col[idx]);
+        }
+    };
     if constexpr (ADAPT) if (sum_need > 0 && (mode == ETR_MODE_ECR || mode == ETR_MODE_BIDIR) && n_keep > 0) {
         __shared__ __attribute__((aligned(16))) unsigned long long sums[kBins];
-        __shared__ int red_cnt[kSelThreads / kWave];
-        auto for_keys = [&](auto&& f) {
-            if constexpr (IPT > 0) {
-#pragma unroll
-                for (int j = 0; j < IPT; ++j) {
-                    uint32_t key = keys[j];
-                    asm volatile("" : "+v"(key));       // computed anew for each digit: kept terms would spill
-                    f(key);
-                }
-            } else {
-                for (int idx = tid; idx < T; idx += kSelThreads) f(col[idx]);
-            }
-        };
-        uint32_t th = 0x80000000u;                      // the settled bits of theta
-        long long above_sum = 0;                        // sum over the candidates above them
-        bool reached = true;                            // otherwise the positive affinities never get there: take all
-        int shift = 31;
-        for (int p = 0; p < 3 && reached; ++p) {
-            const int w = p < 2 ? 11 : 9;
-            shift -= w;
-            const uint32_t span = (1u << (shift + w)) - 1u, dmask = (1u << w) - 1u;
-            __syncthreads();                            // the histogram's previous readers are done
-            sums[2 * tid] = 0ull; sums[2 * tid + 1] = 0ull;
-            __syncthreads();
+        settled = sum_threshold([&](auto&& f) {
             for_keys([&](uint32_t key) {
-                if (key - th <= span) atomicAdd(&sums[(key >> shift) & dmask], static_cast<unsigned long long>(affinity_term(key)));
+                asm volatile("" : "+v"(key));           // computed anew for each digit: kept terms would spill
+                f(key);
             });
-            __syncthreads();
-            // every wave by itself: the highest bin at which the sum from the top reaches the threshold
-            const long long need = sum_need - above_sum;                  // > 0
-            long long own = 0;
-            for (int i = 0; i < 32; ++i)                // lane g: bins [kBins - 32 (g + 1), kBins - 32 g), rotated by the lane
-                own += static_cast<long long>(sums[kBins - 32 * (lane + 1) + ((i + lane) & 31)]);
-            auto scan = [&](long long v) {
-#pragma unroll
-                for (int m = 1; m < kWave; m <<= 1) {
-                    const long long o = __shfl_up(v, m, kWave);
-                    if (lane >= m) v += o;
-                }
-                return v;
-            };
-            const long long upto = scan(own);
-            const uint64_t m1 = __ballot(upto >= need);
-            reached = m1 != 0ull;                       // (uniform; from the second digit on always true)
-            if (reached) {
-                const int g = __builtin_ctzll(m1);
-                const long long before = __shfl(upto - own, g, kWave);
-                const long long h = lane < 32 ? static_cast<long long>(sums[kBins - 1 - 32 * g - lane]) : 0;
-                const long long upto2 = scan(h);
-                const uint64_t m2 = __ballot(before + upto2 >= need);
-                const int j = m2 ? __builtin_ctzll(m2) : 31;
-                above_sum += before + __shfl(upto2 - h, j, kWave);
-                th |= static_cast<uint32_t>(kBins - 1 - 32 * g - j) << shift;
-            }
-        }
-        if (reached) {
-            // theta is settled: above_sum is the sum over the keys above it; count them
-            int n_gt = 0;
-            for_keys([&](uint32_t key) { n_gt += key > th; });
-            n_gt = wave_sum_i(n_gt);
-            if (lane == 0) red_cnt[wave] = n_gt;
-            __syncthreads();
-            n_gt = 0;
-#pragma unroll
-            for (int w = 0; w < kSelThreads / kWave; ++w) n_gt += red_cnt[w];
-            const long long q_th = affinity_term(th);
-            const long long ell = n_gt + (sum_need - above_sum + q_th - 1) / q_th;       // q_th > 0: its bin reached the sum
-            settled = ell <= n_keep;
-            theta = th;
-            if (settled) n_keep = static_cast<int>(ell);
-        }
+        }, sum_need, 0x80000000u, 31, sums, n_keep, theta);
     }
 
     uint32_t tau;
@@ -481,37 +539,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_choice_kernel(const uint32
             shift = diff ? 32 - __builtin_clz(diff) : 0;             // low bits that vary among the candidates
             prefix = shift >= 32 ? 0u : (kmax >> shift) << shift;
         }
-        int need = n_keep;
-        for (int p = 0; p < kMaxDigits && shift > 0; ++p) {
-            const int w = shift < kRadixBits ? shift : kRadixBits;
-            const int top = shift;                                   // bits [31:top] are settled
-            shift -= w;
-            int digit, above;
-            if (PRE && p == 0) {
-                digit_pick(hist[0], first, need, digit, above);      // the first digit was counted by the slices
-            } else {
-                // candidates whose settled bits equal the prefix: lo <= key <= lo + span
-                const uint32_t lo = prefix > 1u ? prefix : 1u;
-                const uint32_t span = (top >= 32 ? 0xFFFFFFFFu : prefix + ((1u << top) - 1u)) - lo;
-                const uint32_t dmask = (1u << w) - 1u;
-                uint32_t* h = hist[p];
-                auto bin = [&](uint32_t key) {
-                    if (key - lo <= span) atomicAdd(&h[(key >> shift) & dmask], 1u);   // LDS; integer adds, so order-free
-                };
-                if constexpr (IPT > 0) {
-#pragma unroll
-                    for (int j = 0; j < IPT; ++j) bin(keys[j]);
-                } else {
-                    for (int idx = tid; idx < T; idx += kSelThreads) bin(col[idx]);
-                }
-                __syncthreads();
-                const DigitView d = digit_view(h);
-                digit_pick(h, d, need, digit, above);
-            }
-            prefix |= static_cast<uint32_t>(digit) << shift;
-            need -= above;
-        }
-        tau = prefix;
+        tau = count_threshold(for_keys, n_keep, shift, prefix, hist, PRE ? 1 : 0, first);
     }
 
     // per-chunk counts of (key > tau, key == tau) in token order, then an exclusive block scan
@@ -682,6 +710,322 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
     for (long long i = gid; i < static_cast<long long>(E) * capacity; i += total) {
         const int ee = static_cast<int>(i / capacity), sl = static_cast<int>(i - static_cast<long long>(ee) * capacity);
         if (sl >= counts[ee]) slot_token[i] = -1;
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Selection by lists, where experts keep few of the tokens (see by_lists): three launches that pass on the chosen pairs only, where
+// the ones above write, read and read again a key for every (token, expert).
+//   1. choice_lists_kernel   a workgroup per tile of 64 tokens, a lane per token: the k best experts by insertion while the row is
+//                            walked; then the tile's pairs, sorted by expert and token, and where each expert's begin
+//   2. expert_lists_kernel   a workgroup per expert: its pairs of all tiles brought together in LDS, the threshold search on
+//                            them, and the (key > tau, key == tau) counts in front of each tile
+//   3. slot_lists_kernel     a workgroup per tile, a thread per pair: its place among the tile's pairs of the expert from
+//                            ballots; the slots leave as whole rows of slot_of
+// Bound by launches and latency and by the tables themselves.  65536 tokens x 64 experts, k = 4: the choice 20 -> 9.3 us, the
+// threshold with the affinity sum 6 + 31 -> 16, the slots 15 -> 7.6.
+// ---------------------------------------------------------------------------------------
+constexpr int kListK = 4;                                // experts of a token, at most
+constexpr int kTileTokens = 64;
+struct ChoiceLists {
+    uint32_t* keys;      // [tiles][64 k]   selection keys of the tile's pairs by (expert, token)
+    uint16_t* pairs;     // [tiles][64 k]   token of the tile | expert << 6
+    uint16_t* begin;     // [tiles][E + 1]  where each expert's pairs begin
+    int tiles;
+};
+// They lie where the column-major keys would: 6 k + (E + 1) / 32 bytes a token, and k <= E / 4.
+inline ChoiceLists carve_lists(const SelectWs& w, int T, int E, int k) {
+    ChoiceLists l;
+    l.tiles = (T + kTileTokens - 1) / kTileTokens;
+    l.keys = w.keyT;
+    l.pairs = reinterpret_cast<uint16_t*>(l.keys + static_cast<size_t>(l.tiles) * kTileTokens * k);
+    l.begin = l.pairs + static_cast<size_t>(l.tiles) * kTileTokens * k;
+    return l;
+}
+
+__global__ __launch_bounds__(256) void choice_lists_kernel(const float* __restrict__ score, int T, int E, int k, int mode,
+                                                           int32_t* __restrict__ topk, ChoiceLists lists) {
+    __shared__ float tile[kTileTokens * (kWave + 1)];
+    __shared__ uint32_t part_key[4][kListK][kTileTokens];
+    __shared__ int part_e[4][kListK][kTileTokens];
+    __shared__ uint32_t chosen[kWave][2];                // tokens that chose the expert
+    __shared__ int begin[kWave];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int t0 = blockIdx.x * kTileTokens, rows = min(kTileTokens, T - t0), ld = E | 1;       // (odd: no bank conflicts)
+    const float* in = score + static_cast<size_t>(t0) * E;
+    const int width = (E & 3) == 0 ? 4 : 1, step = 256 * width, dr = step / E, dc = step - dr * E;
+    int r = tid * width / E, c = tid * width - r * E;
+    for (int i = tid * width; i < rows * E; i += step) {
+        float* at = tile + r * ld + c;
+        if (width == 4) {
+            const float4 v = *reinterpret_cast<const float4*>(in + i);
+            at[0] = v.x; at[1] = v.y; at[2] = v.z; at[3] = v.w;
+        } else {
+            at[0] = in[i];
+        }
+        r += dr; c += dc;
+        if (c >= E) { c -= E; ++r; }
+    }
+    if (tid < kWave) chosen[tid][0] = chosen[tid][1] = 0u;
+    __syncthreads();
+    // the best of this wave's quarter of the experts, largest key first, the lower expert first among equals: they come in
+    // ascending order and move up only past smaller keys
+    uint32_t best[kListK] = {0u, 0u, 0u, 0u};
+    int who[kListK] = {0, 0, 0, 0};
+    auto insert = [&](uint32_t key, int e) {
+        bool up[kListK];
+#pragma unroll
+        for (int i = 0; i < kListK; ++i) up[i] = key > best[i];
+#pragma unroll
+        for (int i = kListK - 1; i > 0; --i) {
+            best[i] = up[i - 1] ? best[i - 1] : (up[i] ? key : best[i]);
+            who[i] = up[i - 1] ? who[i - 1] : (up[i] ? e : who[i]);
+        }
+        best[0] = up[0] ? key : best[0];
+        who[0] = up[0] ? e : who[0];
+    };
+    const int quarter = (E + 3) / 4, e_end = min(E, (wave + 1) * quarter);
+    const int mine = min(lane, rows - 1) * ld;
+#pragma unroll 4
+    for (int e = wave * quarter; e < e_end; ++e) insert(max(order_key(tile[mine + e]), 1u), e);
+#pragma unroll
+    for (int i = 0; i < kListK; ++i) { part_key[wave][i][lane] = best[i]; part_e[wave][i][lane] = who[i]; }
+    __syncthreads();
+    if (wave != 0) return;                               // (no barrier below)
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+#pragma unroll
+        for (int i = 0; i < kListK; ++i) insert(part_key[w][i][lane], part_e[w][i][lane]);
+    const bool live = lane < rows;
+    uint32_t pair_key[kListK];                           // (a key of 0 is no candidate: not listed)
+#pragma unroll
+    for (int i = 0; i < kListK; ++i) pair_key[i] = i < k && live ? selection_key(tile[mine + who[i]], true, mode, k, i) : 0u;
+#pragma unroll
+    for (int i = 0; i < kListK; ++i)
+        if (pair_key[i] != 0u) atomicOr(&chosen[who[i]][lane >> 5], 1u << (lane & 31));
+    auto in_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    in_order();
+    const int n = __popc(chosen[lane][0]) + __popc(chosen[lane][1]);    // (experts past E: none)
+    const int upto = wave_scan_incl(n);
+    begin[lane] = upto - n;
+    uint16_t* out = lists.begin + static_cast<size_t>(blockIdx.x) * (E + 1);
+    if (lane < E) out[lane] = static_cast<uint16_t>(upto - n);
+    if (lane == E - 1) out[E] = static_cast<uint16_t>(upto);
+    in_order();
+    const size_t first = static_cast<size_t>(blockIdx.x) * kTileTokens * k;
+#pragma unroll
+    for (int i = 0; i < kListK; ++i) {
+        const int e = who[i];
+        if (i < k && live && topk) topk[static_cast<size_t>(t0 + lane) * k + i] = e;
+        if (pair_key[i] != 0u) {
+            const uint64_t all = chosen[e][0] | (static_cast<uint64_t>(chosen[e][1]) << 32);
+            const size_t at = first + begin[e] + __popcll(all & ((1ull << lane) - 1ull));
+            lists.keys[at] = pair_key[i];
+            lists.pairs[at] = static_cast<uint16_t>(lane | (e << 6));
+        }
+    }
+}
+
+// A column's keys in LDS where they fit, else read again from the lists for each pass.
+constexpr int kListKeys = 24576;
+template <bool ADAPT>
+__global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists lists, int E, int k, int capacity_host, int mode,
+                                                                   const int32_t* __restrict__ capacity_dev, long long sum_need,
+                                                                   uint32_t* __restrict__ tau_out, int32_t* __restrict__ need_eq_out,
+                                                                   int32_t* __restrict__ pre_gt, int32_t* __restrict__ pre_eq,
+                                                                   int32_t* __restrict__ counts) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t keys[];     // kListKeys
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kMaxDigits][kBins];
+    __shared__ __attribute__((aligned(16))) unsigned long long sums[ADAPT ? kBins : 2];
+    __shared__ int place[kSelThreads], from[kSelThreads], many[kSelThreads];             // of each tile's pairs
+    __shared__ int wave_tot[kSelThreads / kWave][2];
+    __shared__ uint32_t range[kSelThreads / kWave][2];
+    const int e = blockIdx.x, tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int capacity = capacity_dev ? min(capacity_host, max(1, *capacity_dev)) : capacity_host;
+    int own = 0, src = 0;
+    if (tid < lists.tiles) {
+        const uint16_t* b = lists.begin + static_cast<size_t>(tid) * (E + 1) + e;
+        own = b[1] - b[0];
+        src = tid * kTileTokens * k + b[0];
+    }
+#pragma unroll
+    for (int p = 0; p < kMaxDigits; ++p) { hist[p][2 * tid] = 0u; hist[p][2 * tid + 1] = 0u; }
+    const int upto = wave_scan_incl(own);
+    if (lane == kWave - 1) wave_tot[wave][0] = upto;
+    __syncthreads();
+    int n = 0, first = upto - own;
+#pragma unroll
+    for (int w = 0; w < kSelThreads / kWave; ++w) {
+        if (w < wave) first += wave_tot[w][0];
+        n += wave_tot[w][0];
+    }
+    int n_keep = min(n, capacity), gt = 0, eq = 0;       // gt, eq: this tile's pairs with key > tau, key == tau
+    uint32_t tau;
+    const bool by_sum = ADAPT && sum_need > 0 && mode == ETR_MODE_BIDIR && n_keep > 0;
+    if (mode == ETR_MODE_TCR) {                          // every candidate carries key 1
+        tau = n_keep > 0 ? 1u : 0xFFFFFFFFu;
+        eq = own;
+    } else if (!by_sum && n <= capacity) {               // nobody is turned away: all are above 0
+        tau = 0u;
+        gt = own;
+    } else {
+        place[tid] = first; from[tid] = src; many[tid] = own;
+        __syncthreads();
+        const bool in_lds = n <= kListKeys;
+        // every pair of the column, 16 lanes to a tile (a tile has k / E of its 64 tokens on average), kAtOnce tiles at a time
+        constexpr int kAtOnce = 8, kApart = kSelThreads / 16;
+        auto walk = [&](auto&& f) {
+            const int sub = tid & 15;
+            for (int c0 = tid >> 4; c0 < lists.tiles; c0 += kAtOnce * kApart) {
+                int m[kAtOnce], at[kAtOnce], g[kAtOnce];
+                uint32_t v[kAtOnce];
+#pragma unroll
+                for (int i = 0; i < kAtOnce; ++i) {
+                    const int c = min(c0 + i * kApart, kSelThreads - 1);         // (tiles past the last have no pairs)
+                    m[i] = many[c]; at[i] = place[c]; g[i] = from[c];
+                }
+#pragma unroll
+                for (int i = 0; i < kAtOnce; ++i) v[i] = sub < m[i] ? lists.keys[g[i] + sub] : 0u;
+#pragma unroll
+                for (int i = 0; i < kAtOnce; ++i) {
+                    if (sub < m[i]) f(at[i] + sub, v[i]);
+                    for (int j = sub + 16; j < m[i]; j += 16) f(at[i] + j, lists.keys[g[i] + j]);
+                }
+            }
+        };
+        uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+        walk([&](int at, uint32_t key) {
+            if (in_lds) keys[at] = key;
+            kmax = max(kmax, key); kmin = min(kmin, key);
+        });
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            kmax = max(kmax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmax), m, kWave)));
+            kmin = min(kmin, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmin), m, kWave)));
+        }
+        if (lane == 0) { range[wave][0] = kmax; range[wave][1] = kmin; }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSelThreads / kWave; ++w) { kmax = max(kmax, range[w][0]); kmin = min(kmin, range[w][1]); }
+        auto for_keys = [&](auto&& f) {
+            if (in_lds) for (int i = tid; i < n; i += kSelThreads) f(keys[i]);
+            else walk([&](int, uint32_t key) { f(key); });
+        };
+        // Only the low bits in which the keys differ have to be resolved.  (The affinities of one expert crowd into few values
+        // of the bits above, and adds to one word of LDS wait for each other.)
+        auto varying = [](uint32_t diff) { return diff ? 32 - __builtin_clz(diff) : 0; };
+        auto settled = [](uint32_t key, int shift) { return shift >= 32 ? 0u : (key >> shift) << shift; };
+        bool found = false;
+        if constexpr (ADAPT) {
+            if (by_sum && kmax >= 0x80000000u) {
+                const int shift = varying(kmax ^ max(kmin, 0x80000000u));
+                found = sum_threshold(for_keys, sum_need, settled(kmax, shift), shift, sums, n_keep, tau);
+            }
+        }
+        if (found) {
+        } else if (n_keep == n) {
+            tau = 0u;
+        } else {
+            const int shift = varying(kmax ^ kmin);
+            tau = count_threshold(for_keys, n_keep, shift, settled(kmax, shift), hist, 0, DigitView{0, 0, 0});
+        }
+        for (int j0 = 0; j0 < own; j0 += 4) {
+            uint32_t v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = min(j0 + i, own - 1);
+                v[i] = in_lds ? keys[first + j] : lists.keys[src + j];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                gt += j0 + i < own && v[i] > tau;
+                eq += j0 + i < own && v[i] == tau;
+            }
+        }
+    }
+    const int igt = wave_scan_incl(gt), ieq = wave_scan_incl(eq);
+    __syncthreads();                                     // (wave_tot has been read)
+    if (lane == kWave - 1) { wave_tot[wave][0] = igt; wave_tot[wave][1] = ieq; }
+    __syncthreads();
+    int off_gt = 0, off_eq = 0, tot_gt = 0;
+#pragma unroll
+    for (int w = 0; w < kSelThreads / kWave; ++w) {
+        if (w < wave) { off_gt += wave_tot[w][0]; off_eq += wave_tot[w][1]; }
+        tot_gt += wave_tot[w][0];
+    }
+    if (tid < lists.tiles) {
+        pre_gt[e * kSelThreads + tid] = off_gt + igt - gt;
+        pre_eq[e * kSelThreads + tid] = off_eq + ieq - eq;
+    }
+    if (tid == 0) {
+        tau_out[e] = tau;
+        need_eq_out[e] = n_keep - tot_gt;
+        counts[e] = n_keep;
+    }
+}
+
+__global__ __launch_bounds__(kTileTokens * kListK) void slot_lists_kernel(ChoiceLists lists, int T, int E, int k, int capacity,
+                                                                          const uint32_t* __restrict__ tau_in,
+                                                                          const int32_t* __restrict__ need_eq_in,
+                                                                          const int32_t* __restrict__ pre_gt,
+                                                                          const int32_t* __restrict__ pre_eq,
+                                                                          const int32_t* __restrict__ counts,
+                                                                          int32_t* __restrict__ slot_of,
+                                                                          int32_t* __restrict__ slot_token) {
+    constexpr int NT = kTileTokens * kListK;
+    __shared__ __attribute__((aligned(16))) int32_t tile[kTileTokens * kWave];           // [token][E]
+    __shared__ uint64_t above[kListK], equal[kListK];    // of the tile's pairs, 64 to a word
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int t0 = blockIdx.x * kTileTokens, rows = min(kTileTokens, T - t0);
+    const uint16_t* begins = lists.begin + static_cast<size_t>(blockIdx.x) * (E + 1);
+    const bool on = tid < begins[E];
+    uint32_t key = 0u;
+    int e = 0, token = 0;
+    if (on) {
+        const size_t at = static_cast<size_t>(blockIdx.x) * kTileTokens * k + tid;
+        const int pair = lists.pairs[at];
+        key = lists.keys[at];
+        e = pair >> 6;
+        token = pair & (kTileTokens - 1);
+    }
+    const uint32_t tau = tau_in[e];
+    const int need = need_eq_in[e], gt = pre_gt[e * kSelThreads + blockIdx.x], eq = pre_eq[e * kSelThreads + blockIdx.x];
+    const int begin = begins[e];
+    const int4 none = make_int4(-1, -1, -1, -1);
+    for (int i = 4 * tid; i < rows * E; i += 4 * NT) *reinterpret_cast<int4*>(tile + i) = none;          // (the tile ends at a multiple of 4)
+    const bool is_gt = on && key > tau, is_eq = on && key == tau && key != 0u;
+    const uint64_t w_gt = __ballot(is_gt), w_eq = __ballot(is_eq);
+    if (lane == 0) { above[wave] = w_gt; equal[wave] = w_eq; }
+    __syncthreads();
+    // set bits of places [begin, tid): an expert has at most 64 pairs here, so they lie in two words
+    auto before = [&](const uint64_t* words) {
+        const int w0 = begin >> 6;
+        const uint64_t upto = (1ull << lane) - 1ull, from = ~0ull << (begin & 63);
+        return w0 == wave ? __popcll(words[wave] & upto & from) : __popcll(words[wave] & upto) + __popcll(words[w0] & from);
+    };
+    if (on) {
+        const int gt_before = gt + before(above), eq_before = eq + before(equal);
+        int slot = -1;
+        if (is_gt) slot = gt_before + min(eq_before, need);
+        else if (is_eq && eq_before < need) slot = gt_before + eq_before;
+        tile[token * E + e] = slot;
+        if (slot >= 0) slot_token[static_cast<size_t>(e) * capacity + slot] = t0 + token;
+    }
+    __syncthreads();
+    int32_t* out = slot_of + static_cast<size_t>(t0) * E;
+    const int whole = rows * E & ~3;
+    for (int i = 4 * tid; i < whole; i += 4 * NT) *reinterpret_cast<int4*>(out + i) = *reinterpret_cast<const int4*>(tile + i);
+    if (tid < rows * E - whole) out[whole + tid] = tile[whole + tid];
+    // empty slots
+    const unsigned total = static_cast<unsigned>(E) * capacity, stride = gridDim.x * NT;
+    for (unsigned i = blockIdx.x * NT + tid; i < total; i += stride) {
+        const unsigned ee = i / static_cast<unsigned>(capacity);
+        if (static_cast<int>(i - ee * capacity) >= counts[ee]) slot_token[i] = -1;
     }
 }
 
@@ -902,6 +1246,20 @@ hipError_t static_select_scratch(void** out) {
     return hipSuccess;
 }
 
+// Lists of the chosen pairs instead of a key for every (token, expert): where experts are chosen by an eighth of the tokens at
+// most, and by a quarter where the capacity leaves room, so that few have to be turned away: a threshold among many candidates is
+// found sooner with the whole column in registers, and with none to find the lists are ahead at any density.  Selection,
+// keys / lists, T x E, k, capacity over the even share: 65536 x 64, 4, 1.25: 58 / 20 us; 32768 x 32, 2, 0.75: 26 / 17; 8192 x 16,
+// 2, 1.0: 14.6 / 13.8; position priority, 32768 x 32: 18 / 11; a quarter, 2048 x 8, 2, 1.25: 13.1 / 9.0, but 4096 x 8, 2, 1.0:
+// 11.4 / 14.9 and 65536 x 8, 2, 0.9: 28 / 30; a half, 65536 x 8, 4, 0.9: 31 / 54.  Up to 1024 tokens, 1000 x 16: 13.0 / 13.8.
+// A tile is a thread of the per-expert kernel.
+static bool by_lists(const etr_config& c) {
+    if (c.mode != ETR_MODE_TCR && c.mode != ETR_MODE_TCR_RANK && c.mode != ETR_MODE_BIDIR) return false;
+    if (c.k > kListK || c.T <= 1024 || c.T > kTileTokens * kSelThreads) return false;
+    const bool room = c.mode == ETR_MODE_TCR || 4ll * c.E * c.capacity >= 5ll * c.T * c.k;
+    return 8 * c.k <= c.E || (4 * c.k <= c.E && room);
+}
+
 hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_expert, int32_t* slot_of,
                          int32_t* slot_token, int32_t* counts, const SelectWs& w, hipStream_t st,
                          const int32_t* capacity_dev, long long sum_need) {
@@ -910,6 +1268,20 @@ hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_
         hipLaunchKernelGGL(by_sum ? small_select_kernel<true> : small_select_kernel<false>, dim3(c.E),
                            dim3((c.T + kWave - 1) / kWave * kWave), 0, st, score, c.T, c.E, c.k, c.capacity, c.mode, capacity_dev,
                            sum_need, topk_expert, slot_of, slot_token, counts);
+        return hipGetLastError();
+    }
+    if (by_lists(c)) {
+        const ChoiceLists lists = carve_lists(w, c.T, c.E, c.k);
+        const bool adapt = sum_need > 0;
+        hipLaunchKernelGGL(choice_lists_kernel, dim3(lists.tiles), dim3(256), 0, st, score, c.T, c.E, c.k, c.mode, topk_expert, lists);
+        auto kern = adapt ? expert_lists_kernel<true> : expert_lists_kernel<false>;
+        constexpr size_t lds = kListKeys * sizeof(uint32_t);
+        const hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(kern, dim3(c.E), dim3(kSelThreads), lds, st, lists, c.E, c.k, c.capacity, c.mode, capacity_dev, sum_need, w.tau,
+                           w.need_eq, w.pre_gt, w.pre_eq, counts);
+        hipLaunchKernelGGL(slot_lists_kernel, dim3(lists.tiles), dim3(kTileTokens * kListK), 0, st, lists, c.T, c.E, c.k, c.capacity, w.tau,
+                           w.need_eq, w.pre_gt, w.pre_eq, counts, slot_of, slot_token);
         return hipGetLastError();
     }
     int G = 1;
