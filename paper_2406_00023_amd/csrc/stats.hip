@@ -15,12 +15,14 @@ constexpr int kStatThreads = 256;
 // partial[b][e] = sum of gate[t][e] over the block's tokens, partial[b][E] = its unrouted tokens (as int bits).
 // HBM-bound at best: reads T*E*8 bytes once.  kStatUnroll tokens of a thread are requested together (one at a time left
 // it waiting for memory: 65536 tokens x 64 experts 56 us, now 10 us); the sums run in the same order either way.
+// A workgroup has 16 waves where a token takes 16 lanes or more (four left its CU waiting: 65536 x 64 10.4 -> 7 us).
 constexpr int kStatUnroll = 8;
+template <int G> constexpr int stat_threads() { return G >= 16 ? 1024 : kStatThreads; }
 template <int G>   // lanes per token, power of two >= E
-__global__ __launch_bounds__(kStatThreads) void stats_partial_kernel(const float* __restrict__ gate,
+__global__ __launch_bounds__(stat_threads<G>()) void stats_partial_kernel(const float* __restrict__ gate,
                                                                      const int32_t* __restrict__ slot_of, int T, int E,
                                                                      int tokens_per_block, float* __restrict__ partial) {
-    constexpr int TPP = kStatThreads / G;              // tokens per pass
+    constexpr int TPP = stat_threads<G>() / G;         // tokens per pass
     __shared__ float red[TPP][G];
     __shared__ int unrouted[TPP];
     const int tid = threadIdx.x, e = tid % G, j = tid / G;
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(kFinalWaves * 64) void stats_final_kernel(const flo
     const int e = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     double s = 0.0;
     int un = 0;
-#pragma unroll 4
+#pragma unroll 16
     for (int b = wave; b < nblk; b += kFinalWaves) {
         const float* row = partial + static_cast<size_t>(b) * (E + 1);
         if (e < E) s += static_cast<double>(row[e]);
@@ -181,7 +183,7 @@ hipError_t launch_route_stats(const etr_config& c, const float* gate, const int3
     int G = 1;
     while (G < c.E) G <<= 1;
 #define ETR_SP(GG)                                                                                             \
-    hipLaunchKernelGGL(stats_partial_kernel<GG>, dim3(nblk), dim3(kStatThreads), 0, st, gate, slot_of, c.T, c.E, \
+    hipLaunchKernelGGL(stats_partial_kernel<GG>, dim3(nblk), dim3(stat_threads<GG>()), 0, st, gate, slot_of, c.T, c.E, \
                        tpb, partial)
     switch (G) {
         case 1: ETR_SP(1); break;
