@@ -163,18 +163,16 @@ __device__ __forceinline__ bool decode_tile(const GemmParams& p, int& e, int& mt
 // by_chunks: groups of very unequal cost per tile (their own contraction lengths): chunks of 8 tiles go round the XCDs, so
 // that each has its part of every group (weight gradients of 8 fp32 experts of 66-640 rows, one expert to an XCD: the training
 // step 502 us, 486 so).  The grid is then whole 64s.
+// What a small tile pays before its first load is latency, so the group's row count is handed back too, and the scan is in the vector
+// unit (through LDS, and the count loaded again, 8 fp32 experts of 64 rows, 256 x 512: 10.6 and 8.2 us, now 9.5 and 7.4).
 // j: place in the XCD's share, whose length is handed back.  With a workgroup for every tile of the capacity it is
 // blockIdx.x / 8 and done; a smaller grid (whole rounds of 8 all the same) goes on in steps of gridDim.x / 8 to the end.
-__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt,
+__device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, int j, int& share, int& e, int& mt, int& nt, int& count,
                                                  bool by_chunks = false) {
     const int lane = threadIdx.x & 63;
-    const int mine = lane < p.E ? max((group_rows(p, lane) + BM - 1) / BM, 0) : 0;     // this group's row tiles
-    int incl = mine;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const int o = __shfl_up(incl, m, 64);
-        if (lane >= m) incl += o;
-    }
+    const int rows_here = lane < p.E ? group_rows(p, lane) : 0;
+    const int mine = max((rows_here + BM - 1) / BM, 0);  // this group's row tiles
+    const int incl = wave_scan_incl(mine);
     const int total = __builtin_amdgcn_readlane(incl, 63) * p.NT;
     share = (total + 7) >> 3;
     if (by_chunks) share = (share + 7) & ~7;
@@ -182,6 +180,7 @@ __device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, in
     if (j >= share || q >= total) return false;
     const uint64_t in = __ballot(incl * p.NT > q);
     e = __builtin_ctzll(in);
+    count = __builtin_amdgcn_readlane(rows_here, e);
     const int rows = __builtin_amdgcn_readlane(mine, e);
     const int u = q - (__builtin_amdgcn_readlane(incl, e) - rows) * p.NT;
     nt = u / rows;
@@ -1966,9 +1965,8 @@ __device__ __forceinline__ void rows_tile(const GemmParams& p, int e, int m0, in
 template <bool GLU, bool DUAL = false, bool KEEP = false>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) uint4 lds[kRowsBuffers * kRowsBM * kRowsPieces];
-    int share, e, mt, nt;
-    for (int j = blockIdx.x >> 3; decode_live_tile(p, kRowsBM, j, share, e, mt, nt);) {
-        const int count = group_rows(p, e);
+    int share, e, mt, nt, count;
+    for (int j = blockIdx.x >> 3; decode_live_tile(p, kRowsBM, j, share, e, mt, nt, count);) {
         const int m0 = mt * kRowsBM, n0 = nt * (GLU ? 32 : 64);
         const int rows = count - m0;
         if (rows <= 16) rows_tile<1, GLU, DUAL, KEEP>(p, e, m0, n0, count, lds);
@@ -2016,9 +2014,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
     constexpr int NCA = BM / 32, NCB = BROWS / 32;      // copies (1 KiB: 8 rows x 128 bytes, or 4 k rows x 256) per wave and k-tile
     constexpr int TM = BM / 32, TN = BN / 32;           // 16 x 16 blocks per wave and product
     constexpr int AHEAD = NBUF - 1;
-    int share, e, mt, nt;
-    if (!decode_live_tile(p, BM, j, share, e, mt, nt, TRA)) return;
-    const int count = group_rows(p, e);
+    int share, e, mt, nt, count;
+    if (!decode_live_tile(p, BM, j, share, e, mt, nt, count, TRA)) return;
     const int m0 = mt * BM, n0 = nt * BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -188,37 +188,6 @@ __device__ __forceinline__ int wave_sum_i(int v) {
     return v;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave, lane 0 first, by data-parallel-primitive moves: shifts by
-// 1, 2, 4, 8 inside each row of 16 lanes (a lane whose source lies outside its row adds nothing), then lane 15 of
-// row 0 / 2 is added to all of row 1 / 3 and lane 31 to all of rows 2 and 3.  Call with all lanes active.
-__device__ __forceinline__ int wave_scan_incl(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 -> rows 1, 3
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 -> rows 2, 3
-    return v;
-}
-
-// The same for 64-bit sums.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ long long dpp_from(long long v) {
-    const uint32_t lo = static_cast<uint32_t>(v), hi = static_cast<uint32_t>(static_cast<unsigned long long>(v) >> 32);
-    const uint32_t l = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo), CTRL, ROWS, 0xF, false));
-    const uint32_t h = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(hi), CTRL, ROWS, 0xF, false));
-    return static_cast<long long>((static_cast<unsigned long long>(h) << 32) | l);
-}
-__device__ __forceinline__ long long wave_scan_incl(long long v) {
-    v += dpp_from<0x111, 0xF>(v);
-    v += dpp_from<0x112, 0xF>(v);
-    v += dpp_from<0x114, 0xF>(v);
-    v += dpp_from<0x118, 0xF>(v);
-    v += dpp_from<0x142, 0xA>(v);
-    v += dpp_from<0x143, 0xC>(v);
-    return v;
-}
-
 // Sum over aligned groups of Q lanes (Q = 1, 2, 4, 8, 16), every lane of a group gets the group's total:
 // swaps inside quads, then the mirror images of the half row and of the row.  Call with all lanes active.
 template <int Q>
