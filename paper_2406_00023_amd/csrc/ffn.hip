@@ -1987,8 +1987,12 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
 // reads row l % 16 and the 16-byte piece 4 ks + l / 16 of a 16-row block, four floats, and MFMA v of the k-step contracts
 // component v of both operands (the k order inside a step is permuted alike on both sides).  A ring of NBUF buffers
 // is filled by copies that bypass the registers, NBUF - 1 k-tiles ahead; behind the end of the contraction the last
-// k-tile is copied again, which keeps the wait count constant.  Copies carry per-lane 64-bit addresses (operands of
-// any size); a piece past the contraction, in the last k-tile, comes from a zero page.
+// k-tile is copied again, which keeps the wait count constant.  Copies go through a buffer descriptor whose base moves with the
+// k-tile, so a lane carries one 32-bit offset that never changes, and a piece past the contraction asks for an offset past the
+// range (see buffer_copy_to_lds).  The other form of a copy into LDS is a flat instruction to the compiler, which then waits for
+// every LDS read and every load in flight, not for those it needs; with its 64-bit addresses the layer took, 8192 tokens on 8
+// experts, 1024 x 2048, 1786 us, now 1630; 2048 tokens, 512 x 1024 140 / 130; 1024 tokens 108 / 103.  WIDE keeps it, for operands of
+// 4 GiB and more (f32_wide): the zeros then come from a zero page.
 // Tile: 64 x 64, or 32 x 32 where the capacity gives fewer than two 64 x 64 tiles per CU (see launch_f32).  Measured
 // against the plain-FMA kernel this replaces: 8 experts of 66-640 rows, 512 x 1024: gate/up 298 -> 91 us (86 TFLOP/s),
 // the plain products 182 -> 60 us on average; 8 experts of 80 rows, 256 x 512: 71 -> 11 us and 55 -> 8 us; 8 x 2048 rows,
@@ -1999,13 +2003,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
 // Operands whose contraction index is the slow one (backward; TRB: B is [K][N], TRA: A is [K][M] too): a k-tile is staged as
 // [32 k][rows], and lane l takes its elements one by one: row l % 16 of a block at k = 16 ks + 4 (l / 16) + v, 64 bytes of four k
 // rows per read.  The 64-byte piece b of k row k is stored at b ^ (k / 4 % 4) (applied on the copy's source side), so that
-// the four lie on different banks (32-row tiles have two pieces: two-way conflicts).  k rows past the contraction come
-// from the zero page.  With B1 the contraction is split in the middle ([K/2][ldb] each); with k_gather (1: A, 2: B) the k
+// the four lie on different banks (32-row tiles have two pieces: two-way conflicts).  With B1 the contraction is split in the
+// middle ([K/2][ldb] each; the k-tiles of each half are its own, the last one may be short); with k_gather (1: A, 2: B) the k
 // rows of that operand are rows k_index[g * k_index_stride + k] of one [k_rows][ld] matrix.
 // ---------------------------------------------------------------------------------------
 template <int BM, int BN, int NBUF, bool GLU> constexpr int f32_pieces() { return NBUF * (BM + (GLU ? 2 : 1) * BN) * 8; }
 // tile j of this XCD's share of the list; lds: f32_pieces
-template <int BM, int BN, int NBUF, bool GLU, bool DUAL, bool TRA, bool TRB>
+template <int BM, int BN, int NBUF, bool GLU, bool DUAL, bool TRA, bool TRB, bool WIDE>
 __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4* lds) {
     static_assert(!GLU || !TRB, "epilogues: row-major operands");
     static_assert(!TRA || TRB, "transposed A: both are");
@@ -2020,17 +2024,21 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    // (transposed: the zero page stands for the k rows past the group's own, so that no padding is multiplied)
-    const int K = TRA ? (p.k_counts ? min(max(p.k_counts[e], 0), p.K) : p.K) : group_k(p, e), KT = max((K + BK - 1) / BK, 1);
+    // (transposed: zeros stand for the k rows past the group's own, so that no padding is multiplied)
+    const int K = TRA ? (p.k_counts ? min(max(p.k_counts[e], 0), p.K) : p.K) : group_k(p, e);
+    const bool splitB = TRB && !TRA && p.B1 != nullptr;
+    const int Kh = splitB ? K / 2 : K, KTh = max((Kh + BK - 1) / BK, 1), KT = splitB ? 2 * KTh : KTh;   // of a half, of all
+    const int k_rem = Kh - (KTh - 1) * BK;               // valid k of the last k-tile of a half
     const int LA = p.lda ? p.lda : p.K, LB = p.ldb ? p.ldb : p.K;
-    const bool splitB = TRB && p.B1 != nullptr;
 
-    // copy sources of this lane: row and 16-byte piece (the swizzle is applied here, on the source side)
-    const float* src[NCA + NCB];
+    // copy sources: a wave-uniform base and this lane's offset in bytes: row and 16-byte piece (the swizzle is applied here, on the
+    // source side)
+    typedef std::conditional_t<WIDE, size_t, uint32_t> Offset;
+    Offset off[NCA + NCB];
     const int r8 = lane >> 3;
-    bool past[2];                                       // piece of the last k-tile that lies past the contraction
+    bool past[2];                                       // row-major: piece of the last k-tile that lies past the contraction
 #pragma unroll
-    for (int h = 0; h < 2; ++h) past[h] = (KT - 1) * BK + 4 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7)) >= K;
+    for (int h = 0; h < 2; ++h) past[h] = 4 * ((lane & 7) ^ ((4 * h + (lane >> 4)) & 7)) >= k_rem;
     // transposed: k row of copy i of a wave's NC and first row of the piece
     constexpr int PA = BM / 4, PB = BN / 4;             // 16-byte pieces of a k row
     auto k_of = [&](int i, int NC, int pieces) { return ((wave * NC + i) * 64 + lane) / pieces; };
@@ -2038,33 +2046,31 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
         const int slot = ((wave * NC + i) * 64 + lane) % pieces;
         return 16 * ((slot >> 2) ^ ((k_of(i, NC, pieces) >> 2) & (pieces / 4 - 1))) + 4 * (slot & 3);
     };
+    const bool gathered_a = TRA && p.k_gather == 1, gathered_b = TRA && p.k_gather == 2;       // (their k rows come from `rows`)
 #pragma unroll
     for (int i = 0; i < NCA; ++i) {
-        if constexpr (TRA) {
-            src[i] = static_cast<const float*>(p.A) + (p.k_gather == 1 ? 0 : static_cast<size_t>(e) * p.K * LA) +
-                     min(m0 + r_of(i, NCA, PA), p.capacity - 4);         // (pieces past the row repeat; never stored)
+        if constexpr (TRA) {                            // (pieces past the row repeat; never stored)
+            off[i] = (static_cast<Offset>(gathered_a ? 0 : k_of(i, NCA, PA)) * LA + min(m0 + r_of(i, NCA, PA), p.capacity - 4)) * 4;
         } else {
             const int r = (wave * NCA + i) * 8 + r8;
             int m = min(m0 + r, count - 1);             // rows past the count replay a valid row; never stored
             if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
-            src[i] = static_cast<const float*>(p.A) + (p.row_index ? 0 : static_cast<size_t>(e) * p.capacity * LA) +
-                     static_cast<size_t>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7));
+            off[i] = (static_cast<Offset>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7))) * 4;
         }
     }
 #pragma unroll
     for (int i = 0; i < NCB; ++i) {
         if constexpr (TRB) {
-            src[NCA + i] = static_cast<const float*>(p.B0) +
-                           (p.k_gather == 2 ? 0 : static_cast<size_t>(e) * (splitB ? p.K / 2 : p.K) * LB) + min(n0 + r_of(i, NCB, PB), p.N - 4);
+            off[NCA + i] = (static_cast<Offset>(gathered_b ? 0 : k_of(i, NCB, PB)) * LB + min(n0 + r_of(i, NCB, PB), p.N - 4)) * 4;
         } else {
             const int r = (wave * NCB + i) * 8 + r8;
-            const bool second = GLU && r >= BN;
-            const int n = min(n0 + (second ? r - BN : r), p.N - 1);
-            src[NCA + i] = static_cast<const float*>(second ? p.B1 : p.B0) + (static_cast<size_t>(e) * p.N + n) * LB +
-                           4 * ((lane & 7) ^ ((r >> 1) & 7));
+            const int n = min(n0 + (GLU && r >= BN ? r - BN : r), p.N - 1);
+            off[NCA + i] = (static_cast<Offset>(n) * LB + 4 * ((lane & 7) ^ ((r >> 1) & 7))) * 4;
         }
     }
-    const ptrdiff_t to_second = splitB ? static_cast<const float*>(p.B1) - static_cast<const float*>(p.B0) - static_cast<ptrdiff_t>(K / 2) * LB : 0;
+    const uint64_t a_base = reinterpret_cast<uint64_t>(p.A) +
+                            (gathered_a || (!TRA && p.row_index) ? 0 : static_cast<uint64_t>(e) * (TRA ? p.K : p.capacity) * LA * 4);
+    const uint64_t b_group = gathered_b ? 0 : static_cast<uint64_t>(e) * (TRB ? (splitB ? p.K / 2 : p.K) : p.N) * LB * 4;
     // row numbers of this lane's gathered k rows in the k-tile requested next
     constexpr int NG = TRA ? (NCA > NCB ? NCA : NCB) : 1;
     int rows[NG], rows_next[NG];
@@ -2080,24 +2086,33 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
         }
     };
     auto copy_tile = [&](int kt, int buf) {
-        const bool last = kt == KT - 1;
+        const bool second = splitB && kt >= KTh;         // half of a split contraction
+        const int kh = second ? kt - KTh : kt;
+        const bool last = kh == KTh - 1;
+        const uint64_t row_step = static_cast<uint64_t>(kh) * (BK * 4);
+        const uint64_t a_at = a_base + (TRA ? (gathered_a ? 0 : row_step * LA) : row_step + (second ? static_cast<uint64_t>(Kh) * 4 : 0));
+        const uint64_t b_step = TRB ? (gathered_b ? 0 : row_step * LB) : row_step;
 #pragma unroll
         for (int i = 0; i < NCA + NCB; ++i) {
             const bool a = i < NCA;
             const int n = a ? i : i - NCA, group = wave * (a ? NCA : NCB) + n;           // of 8 rows; its parity picks the swizzle half
-            const float* g;
+            const bool up = !a && (second || (GLU && group * 8 >= BN));
+            const uint64_t at = a ? a_at : reinterpret_cast<uint64_t>(up ? p.B1 : p.B0) + b_group + b_step;
+            Offset o = off[i];
+            bool over = last && past[group & 1];
             if (a ? TRA : TRB) {
-                const int k = kt * BK + (a ? k_of(n, NCA, PA) : k_of(n, NCB, PB));
-                const bool by_index = TRA && p.k_gather == (a ? 1 : 2);
-                const int row = by_index ? rows[n < NG ? n : 0] : k;
-                g = src[i] + static_cast<size_t>(row) * (a ? LA : LB);
-                if (!a && splitB && k >= K / 2) g += to_second;
-                if (k >= K) g = kZeroPiece;
-            } else {
-                g = last && past[group & 1] ? kZeroPiece : src[i] + static_cast<size_t>(kt) * BK;
+                over = last && (a ? k_of(n, NCA, PA) : k_of(n, NCB, PB)) >= k_rem;
+                if (a ? gathered_a : gathered_b) o += static_cast<Offset>(rows[n < NG ? n : 0]) * (a ? LA : LB) * 4;
             }
             uint4* dst = lds + buf * STAGE + (a ? 0 : BM * CPR) + group * 64;
-            __builtin_amdgcn_global_load_lds((global_cptr)g, (lds_ptr)dst, 16, 0, 0);
+            if constexpr (WIDE) {
+                const char* g = over ? reinterpret_cast<const char*>(kZeroPiece) : reinterpret_cast<const char*>(at) + o;
+                __builtin_amdgcn_global_load_lds((global_cptr)g, (lds_ptr)dst, 16, 0, 0);
+            } else {
+                const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at));
+                const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at >> 32));
+                buffer_copy_to_lds(lo, hi, over ? kPastRange : o, dst);
+            }
         }
     };
 
@@ -2206,10 +2221,10 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
         }
     }
 }
-template <int BM, int BN, int NBUF, bool GLU, bool DUAL = false, bool TRB = false>
+template <int BM, int BN, int NBUF, bool GLU, bool DUAL, bool TRB, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
     __shared__ __attribute__((aligned(16))) uint4 lds[f32_pieces<BM, BN, NBUF, GLU>()];
-    gemm_f32_tile<BM, BN, NBUF, GLU, DUAL, false, TRB>(p, blockIdx.x >> 3, lds);
+    gemm_f32_tile<BM, BN, NBUF, GLU, DUAL, false, TRB, WIDE>(p, blockIdx.x >> 3, lds);
 }
 
 // The last products of the backward in one launch, as in gemm_bf16_backward_kernel: the workgroups of p[0], the input
@@ -2217,16 +2232,16 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(GemmParams p) {
 // Training step, the operands transposed in memory and a launch for each product / this: 8 experts of 66-640 rows, 512 x 1024:
 // 499 / 435 us; 8 of 1200, 1024 x 2048: 2754 / 2322; 4 of 64, 256 x 512: 88 / 63.
 struct BackwardProductsF32 { GemmParams p[4]; int first[4]; };       // first[i]: workgroup at which product i begins (a multiple of 8)
-template <int BM, int BN, int NBUF>
+template <int BM, int BN, int NBUF, bool WIDE>
 __global__ __launch_bounds__(256, 2) void gemm_f32_backward_kernel(BackwardProductsF32 b) {
     __shared__ __attribute__((aligned(16))) uint4 lds[f32_pieces<BM, BN, NBUF, false>()];
     const int blk = blockIdx.x;
     if (blk < b.first[1]) {
-        gemm_f32_tile<BM, BN, NBUF, false, false, false, true>(b.p[0], blk >> 3, lds);
+        gemm_f32_tile<BM, BN, NBUF, false, false, false, true, WIDE>(b.p[0], blk >> 3, lds);
         return;
     }
     const int i = blk >= b.first[3] ? 3 : (blk >= b.first[2] ? 2 : 1);
-    gemm_f32_tile<BM, BN, NBUF, false, false, true, true>(b.p[i], (blk - b.first[i]) >> 3, lds);
+    gemm_f32_tile<BM, BN, NBUF, false, false, true, true, WIDE>(b.p[i], (blk - b.first[i]) >> 3, lds);
 }
 
 template <int BM, int BN, int BK, int WGM, int WGN, bool GLU, int SWZ, bool DUAL = false>
@@ -2330,24 +2345,40 @@ hipError_t launch_bf16_rows(GemmParams p, hipStream_t st) {
 inline bool f32_large_tiles(const GemmParams& p) {
     return static_cast<long long>(p.E) * ((p.capacity + 63) / 64) * ((p.N + 63) / 64) >= 2ll * cu_count();
 }
-template <bool GLU, bool DUAL = false, bool TRB = false>
-hipError_t launch_f32(GemmParams p, hipStream_t st) {
+// Whether the byte offsets of a product's copies, which span a group's rows (operands with the contraction slow: a k-tile, or the
+// rows that the index may name), need more than the 32 bits of a buffer descriptor's range.
+inline bool f32_wide(const GemmParams& p, bool ta, bool tb) {
+    const size_t a_row = static_cast<size_t>(p.lda ? p.lda : p.K) * 4, b_row = static_cast<size_t>(p.ldb ? p.ldb : p.K) * 4;
+    const size_t a_rows = ta ? (p.k_gather == 1 ? p.k_rows : 32) : (p.row_index ? p.a_rows : p.capacity);
+    const size_t b_rows = tb ? (p.k_gather == 2 ? p.k_rows : 32) : p.N;
+    return (a_rows + 1) * a_row >= kBufferRange || (b_rows + 1) * b_row >= kBufferRange;
+}
+template <bool GLU, bool DUAL, bool TRB, bool WIDE>
+hipError_t launch_f32_form(GemmParams p, hipStream_t st) {
     if (f32_large_tiles(p)) {
         const long long blocks = plan_live_tiles(p, 64, 64);
-        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL, TRB>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 3, GLU, DUAL, TRB, WIDE>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     } else {
         const long long blocks = plan_live_tiles(p, 32, 32);
-        hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4, GLU, DUAL, TRB>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((gemm_f32_kernel<32, 32, 4, GLU, DUAL, TRB, WIDE>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, p);
     }
     return hipGetLastError();
+}
+template <bool GLU, bool DUAL = false, bool TRB = false>
+hipError_t launch_f32(const GemmParams& p, hipStream_t st) {
+    return f32_wide(p, false, TRB) ? launch_f32_form<GLU, DUAL, TRB, true>(p, st) : launch_f32_form<GLU, DUAL, TRB, false>(p, st);
 }
 // Products [from, to) of b in one launch (as many workgroups as one launch may hold, else one by one).
 template <int T, int NBUF>
 hipError_t launch_f32_backward_tiles(BackwardProductsF32 b, int from, int to, hipStream_t st) {
     long long at = 0;
+    bool wide = false;
     for (int i = 0; i < 4; ++i) {
         b.first[i] = static_cast<int>(std::min<long long>(at, 1 << 30));
-        if (i >= from && i < to) at += (plan_live_tiles(b.p[i], T, T) + 63) / 64 * 64;
+        if (i >= from && i < to) {
+            at += (plan_live_tiles(b.p[i], T, T) + 63) / 64 * 64;
+            wide = wide || f32_wide(b.p[i], i > 0, true);
+        }
     }
     if (at > (1 << 23) && to - from > 1) {               // 2^31 threads
         for (int i = from; i < to; ++i) {
@@ -2356,7 +2387,8 @@ hipError_t launch_f32_backward_tiles(BackwardProductsF32 b, int from, int to, hi
         }
         return hipSuccess;
     }
-    hipLaunchKernelGGL((gemm_f32_backward_kernel<T, T, NBUF>), dim3(static_cast<unsigned>(at)), dim3(256), 0, st, b);
+    auto kern = wide ? gemm_f32_backward_kernel<T, T, NBUF, true> : gemm_f32_backward_kernel<T, T, NBUF, false>;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(at)), dim3(256), 0, st, b);
     return hipGetLastError();
 }
 
