@@ -2149,8 +2149,9 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
         const uint4* Bb = Ab + BM * CPR;
         const uint4* As = Ab + (wm * (BM / 2) + l16) * CPR;
         const uint4* Bs = Bb + (wn * (BN / 2) + l16) * CPR;
-        f32x4 fa[TM], fb[NB][TN];
+        f32x4 fas[2][TM], fbs[2][NB][TN];
         auto read = [&](int ks) {
+            auto& fa = fas[ks]; auto& fb = fbs[ks];
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 if constexpr (TRA) fa[i] = transposed(Ab, PA, wm * TM + i, ks);
@@ -2164,9 +2165,10 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
                     else fb[b][n] = __builtin_bit_cast(f32x4, Bs[(b * BN + n * 16) * CPR + ck[ks]]);
                 }
         };
-        auto multiply = [&]() {
+        auto multiply = [&](int ks, int v0, int v1) {
+            auto& fa = fas[ks]; auto& fb = fbs[ks];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
+            for (int v = v0; v < v1; ++v)
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -2175,16 +2177,24 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
                         for (int n = 0; n < TN; ++n)
                             acc[b][i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][n][v], fa[i][v], acc[b][i][n], 0, 0, 0);
         };
-        // the first fragments are on their way while the copies go out (copies first: 8192 tokens, 8 experts, 1024 x 2048, the
-        // layer 1814 us, now 1788; all fragments of the k-tile, then the copies: 1937)
+        // The copies go out behind a quarter of the first k-step's MFMAs, the second one's fragments are asked for behind three:
+        // before both, or with the copies in front, LDS and the address unit are busy while the matrix pipe waits.  2048 tokens on 8
+        // experts, 512 x 1024, training step: copies, fragments, MFMAs 434 us; first fragments, copies, MFMAs 400; this 395 (copies
+        // behind half 396, behind all 407).
         read(0);
         __builtin_amdgcn_sched_barrier(0);
-        load_rows(kt + AHEAD + 1, rows_next);            // in front of the copies: its wait leaves them in flight
+        load_rows(kt + AHEAD + 1, rows_next);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0, 0, 1);
+        __builtin_amdgcn_sched_barrier(0);
         copy_tile(min(kt + AHEAD, KT - 1), buf == 0 ? NBUF - 1 : buf - 1);
         __builtin_amdgcn_sched_barrier(0);
-        multiply();
+        multiply(0, 1, 3);
+        __builtin_amdgcn_sched_barrier(0);
         read(1);
-        multiply();
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0, 3, 4);
+        multiply(1, 0, 4);
         buf = buf == NBUF - 1 ? 0 : buf + 1;
 #pragma unroll
         for (int i = 0; i < NG; ++i) rows[i] = rows_next[i];
