@@ -694,11 +694,12 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 
 __device__ __align__(16) const float kZeroPiece[4] = {0.f, 0.f, 0.f, 0.f};
 
-// Ragged contractions (TAIL instantiations of the persistent kernels).  A copy into LDS cannot be masked per lane
-// without leaving stale data behind, so the lanes whose 16-byte piece lies past the end of the contraction ask a
-// buffer descriptor for an offset past its range: such a lane reads nothing and zeros land in its LDS slot.  The
-// descriptor spans all but the last 256 bytes of 4 GiB from the tile's base; real offsets stay below it (a launch
-// condition), so the check never touches a piece that exists.
+// A copy into LDS through a buffer descriptor: a scalar base and a 32-bit offset per lane, no 64-bit address in vector
+// registers (and not the flat form, behind which the compiler cannot count its waits).  In a ragged contraction a copy
+// cannot be masked per lane without leaving stale data behind, so the lanes whose 16-byte piece lies past the end ask for an
+// offset past the descriptor's range: such a lane reads nothing and zeros land in its LDS slot.  The descriptor spans all but
+// the last 256 bytes of 4 GiB from the tile's base; real offsets stay below it (a launch condition), so the check never
+// touches a piece that exists.
 __device__ __forceinline__ void buffer_copy_to_lds(uint32_t base_lo, uint32_t base_hi, uint32_t off, uint4* dst) {
     void* base = reinterpret_cast<void*>((static_cast<uint64_t>(base_hi) << 32) | base_lo);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(kBufferRange), 0x00027000);
@@ -1012,12 +1013,12 @@ __device__ __forceinline__ void request_row_ids(const GemmParams& p, int e, int 
 // for nobody reads that buffer any more: behind one wait (all copies landed, all own LDS reads done) and one
 // barrier it is released.
 //
-// Copies (global_load_lds, no registers).  A wave's copies of k-tile g + 2 go out in two bursts, each behind the first MFMA
+// Copies (into LDS, no registers).  A wave's copies of k-tile g + 2 go out in two bursts, each behind the first MFMA
 // of a substep: its groups of token rows in the fourth substep of step g (right behind the barrier), its groups of weight
 // rows in the first substep of step g + 1.  They are bound by the time they take to land, before the barrier of step
 // g + 1: spread behind every other MFMA of half a substep they cost 1-2 % more (gate/up and down product, 16 experts of 1280,
 // 4096 x 11008: 4177 / 4110 us; 8 of 32 000, 4096 x 1408: 6601 / 6525; 16 of 600-1024, 2048 x 5632: 871 / 852), half a substep
-// later another 1-4 %.  All eight in one substep is twice what a CU's address unit takes in that time (5-10 %).  The weight rows of a
+// later another 1-4 %.  All eight in one substep is twice what a CU's address unit takes in that time (4-7 %).  The weight rows of a
 // tile are whole column tiles (a launch condition), so their addresses are a wave-uniform base plus one of two
 // per-lane offsets that never change; only the token rows carry per-tile lane offsets.  There is always something
 // to copy: past the end of a workgroup's list the last k-tile is fetched again into a buffer nobody reads any
@@ -1038,7 +1039,7 @@ __device__ __forceinline__ void request_row_ids(const GemmParams& p, int e, int 
 //
 // TAIL: the contraction need not be whole k-tiles (K % 8 == 0 suffices); the 16-byte pieces of the last k-tile that
 // lie past its end are zero-filled by the copy (buffer_copy_to_lds).  An instantiation of its own, so that the plain
-// one keeps its address forms and scalar registers.
+// one keeps its scalar registers.
 template <bool GLU, bool DUAL = false, bool KEEP = false, bool TAIL = false>
 __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p) {
     static_assert(!KEEP || (GLU && !DUAL), "the pre-activations are kept by the SwiGLU epilogue only");
@@ -1108,14 +1109,8 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
         for (int i = 0; i < NCP; ++i) t.offA[i] = (static_cast<uint32_t>(row[i]) * KCA + (c0 ^ (4 * (i & 1)))) * 16u;
     };
     auto copy_to = [&](uint64_t b64, uint32_t off, uint4* dst) {
-        const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
-        const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
-        if constexpr (TAIL) {
-            buffer_copy_to_lds(lo, hi, off, dst);
-        } else {
-            const char* base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-            __builtin_amdgcn_global_load_lds((global_cptr)(base + off), (lds_ptr)dst, 16, 0, 0);
-        }
+        buffer_copy_to_lds(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64)),
+                           __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32)), off, dst);
     };
     // token-row group i / weight-row group i of the k-tile at abase / bbase into buffer buf; `last`: the short k-tile
     auto copy_a = [&](uint64_t abase, uint32_t off, int buf, int i) {
@@ -1149,12 +1144,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_persistent_kernel(GemmParams p)
     // forth over the token blocks): registers that do not change cost no power, and power is the limit.  FFN of 16 experts of
     // 1280 rows, 4096 x 11008, the layer, weight blocks restarted at each token block / this: 4346 / 4303 us; 8 of 32 000,
     // 4096 x 1408: 7451 / 7389; back and forth over the weight blocks 4337 and 7397.
+    // (Without the barrier in front of mem(m) the compiler moves a substep's first reads before its first MFMA, where the wait
+    // for the fragments then waits for these reads as well: 4128 / 4085 us and 7128 / 6972, 16 of 1024 bidirectional 2666 / 2627.)
     auto substep = [&](int u, auto&& mem) {
         const int ks = u >> 1, h = u & 1;
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int j = m >> 2, i = (j & 1) ? 3 - (m & 3) : (m & 3);
             acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fbk[ks][j], fah[h][i], acc[4 * h + i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
             mem(m);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -2479,7 +2477,7 @@ static Bf16Kernel choose_bf16(const GemmParams& g, bool glu, size_t a_rows, int 
         return Bf16Kernel::STAGED;
     const bool whole = g.K % 64 == 0;
     const bool persistent = persist_ok(g, glu, true, kMaxSuperWide) && whole_column_tiles(g, glu) &&
-                            (whole || (!g.k_counts && a_bytes < kBufferRange && b_bytes < kBufferRange));
+                            a_bytes < kBufferRange && b_bytes < kBufferRange && (whole || !g.k_counts);
     if (rows_expected <= 0 || g.k_counts)
         return persistent ? Bf16Kernel::PERSISTENT : (whole ? Bf16Kernel::RING : Bf16Kernel::STAGED);
     Bf16Kernel best = !whole ? Bf16Kernel::STAGED : (persistent ? Bf16Kernel::PERSISTENT : Bf16Kernel::RING);
