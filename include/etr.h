@@ -12,8 +12,10 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Calls only enqueue work; they never synchronise with the host.
  *  - Stream capture: every entry point may be captured into a HIP graph, with one rule: the FIRST call of an
- *    entry point for a given shape on a device must happen outside capture (it may raise a kernel's
- *    dynamic-LDS limit and query the device once; later calls only launch kernels).
+ *    entry point for a given shape and set of optional arguments on a device must happen outside capture (it may
+ *    raise a kernel's dynamic-LDS limit and query the device once; later calls only launch kernels).  The
+ *    selections raise none: one call of etr_select, etr_select_adaptive or etr_select_noalloc on a device, at any
+ *    shape, and that entry point may be captured at every shape.
  *  - Arguments are checked on the host before anything is launched; on error
  *    nothing is launched and a status is returned:
  *      ETR_ERR_NULL         a required pointer is NULL

@@ -799,7 +799,8 @@ __global__ __launch_bounds__(256) void choice_lists_kernel(const float* __restri
     }
 }
 
-// A column's keys in LDS where they fit, else read again from the lists for each pass.
+// A column's keys in LDS where they fit, else read again from the lists for each pass.  The room is static: a dynamic one of this size
+// would need an attribute of the kernel first, and a selection may be captured without a first call at its shape.
 constexpr int kListKeys = 24576;
 template <bool ADAPT>
 __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists lists, int E, int k, int capacity_host, int mode,
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists l
                                                                    uint32_t* __restrict__ tau_out, int32_t* __restrict__ need_eq_out,
                                                                    int32_t* __restrict__ pre_gt, int32_t* __restrict__ pre_eq,
                                                                    int32_t* __restrict__ counts) {
-    extern __shared__ __attribute__((aligned(16))) uint32_t keys[];     // kListKeys
+    __shared__ __attribute__((aligned(16))) uint32_t keys[kListKeys];
     __shared__ __attribute__((aligned(16))) uint32_t hist[kMaxDigits][kBins];
     __shared__ __attribute__((aligned(16))) unsigned long long sums[ADAPT ? kBins : 2];
     __shared__ int place[kSelThreads], from[kSelThreads], many[kSelThreads];             // of each tile's pairs
@@ -1243,11 +1244,7 @@ hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_
         const ChoiceLists lists = carve_lists(w, c.T, c.E, c.k);
         const bool adapt = sum_need > 0;
         hipLaunchKernelGGL(choice_lists_kernel, dim3(lists.tiles), dim3(256), 0, st, score, c.T, c.E, c.k, c.mode, topk_expert, lists);
-        auto kern = adapt ? expert_lists_kernel<true> : expert_lists_kernel<false>;
-        constexpr size_t lds = kListKeys * sizeof(uint32_t);
-        const hipError_t err = ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-        if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(kern, dim3(c.E), dim3(kSelThreads), lds, st, lists, c.E, c.k, c.capacity, c.mode, capacity_dev, sum_need, w.tau,
+        hipLaunchKernelGGL(adapt ? expert_lists_kernel<true> : expert_lists_kernel<false>, dim3(c.E), dim3(kSelThreads), 0, st, lists, c.E, c.k, c.capacity, c.mode, capacity_dev, sum_need, w.tau,
                            w.need_eq, w.pre_gt, w.pre_eq, counts);
         hipLaunchKernelGGL(slot_lists_kernel, dim3(lists.tiles), dim3(kTileTokens * kListK), 0, st, lists, c.T, c.E, c.k, c.capacity, w.tau,
                            w.need_eq, w.pre_gt, w.pre_eq, counts, slot_of, slot_token);

@@ -57,3 +57,35 @@ def test_selection_by_lists(oracle, T, E, k, kind):
             np.testing.assert_array_equal(st[:, :o_st.shape[1]], o_st)
             assert np.all(st[:, o_st.shape[1]:] == -1)
             np.testing.assert_array_equal(topk.cpu().numpy(), o_tk)
+
+
+def test_capture_behind_a_first_call_at_another_shape(oracle):
+    """Captured calls without a first call at their shape, with a threshold and without: replays on other scores."""
+    B.load_library()
+    print("select lists under capture", flush=True)
+    small = B.make_config(I.EtrShape("s", 1, T=100, d=64, E=8, D=8, k=1, capacity=20, H=8, dtype=I.DT_F32, mode=I.MODE_BIDIR, recipe="iso"))
+    tables = lambda T, E, C, k: [torch.full(n, -7, dtype=torch.int32, device="cuda") for n in ((T, k), (T, E), (E, C), (E,))]
+    B.etr_select_noalloc(small, torch.rand(100, 8, device="cuda"), *tables(100, 8, 20, 1))
+    T, E, k, C = 3500, 20, 2, 200
+    cfg = B.make_config(I.EtrShape("l", 1, T=T, d=8 * E, E=E, D=8, k=k, capacity=C, H=8, dtype=I.DT_F32, mode=I.MODE_BIDIR, recipe="iso"))
+    score, plain, summed = torch.zeros(T, E, device="cuda"), tables(T, E, C, k), tables(T, E, C, k)
+    ws = B.alloc_workspace(B.etr_select_workspace_bytes(cfg))
+    thr = 20.0
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        B.etr_select_noalloc(cfg, score, *plain)
+        B.etr_select_adaptive(cfg, score, None, thr, *summed, ws)
+    for rep in range(3):
+        S = np.roll(_scores("any", T, E), rep, axis=1)
+        score.copy_(torch.from_numpy(S))
+        for t in plain + summed:
+            t.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in ((plain, oracle.select(S, k, C, I.MODE_BIDIR)), (summed, oracle.select_adaptive(S, k, C, I.MODE_BIDIR, thr))):
+            for t, o in zip(got, ref):
+                a = t.cpu().numpy()
+                np.testing.assert_array_equal(a[:, :o.shape[1]] if o.ndim == 2 else a, o)
+                assert o.ndim == 1 or np.all(a[:, o.shape[1]:] == -1)
