@@ -21,6 +21,7 @@
 // All three phases are one algorithm: in TCR every candidate has the same key, so
 // "the C best, lowest token first among equals" is "the first C in token order".
 #include <mutex>
+#include <type_traits>
 
 #include "etr_internal.h"
 
@@ -327,9 +328,12 @@ __device__ __forceinline__ bool sum_threshold(Keys&& for_keys, long long sum_nee
 
 // The n_keep-th largest key, by radix search from the top; the bits above the low `shift` ones are those of prefix.  The first
 // `counted` digits (0 or 1) have been counted, the first one's view is `first`.  hist: kMaxDigits histograms of zeros.
+// wide (or null): room for 4 kBins words, in which four copies of each word are counted, a lane in that of its number.  A column in
+// which many candidates lie close together, or are one key, would add to few words all at once, and one wave's adds to a word are
+// done one after the other.
 template <typename Keys>
 __device__ __forceinline__ uint32_t count_threshold(Keys&& for_keys, int n_keep, int shift, uint32_t prefix, uint32_t (*hist)[kBins], int counted,
-                                                    const DigitView& first) {
+                                                    const DigitView& first, uint32_t* wide = nullptr) {
     int need = n_keep;
     for (int p = 0; p < kMaxDigits && shift > 0; ++p) {
         const int w = shift < kRadixBits ? shift : kRadixBits;
@@ -344,9 +348,22 @@ __device__ __forceinline__ uint32_t count_threshold(Keys&& for_keys, int n_keep,
             const uint32_t span = (top >= 32 ? 0xFFFFFFFFu : prefix + ((1u << top) - 1u)) - lo;
             const uint32_t dmask = (1u << w) - 1u;
             uint32_t* h = hist[p];
-            for_keys([&](uint32_t key) {
-                if (key - lo <= span) atomicAdd(&h[(key >> shift) & dmask], 1u);     // LDS; integer adds, so order-free
-            });
+            if (wide) {
+                uint4* own = reinterpret_cast<uint4*>(wide) + 2 * threadIdx.x;           // of two words
+                own[0] = own[1] = make_uint4(0u, 0u, 0u, 0u);
+                __syncthreads();
+                for_keys([&](uint32_t key) {
+                    if (key - lo <= span) atomicAdd(&wide[4 * ((key >> shift) & dmask) + (threadIdx.x & 3)], 1u);
+                });
+                __syncthreads();
+                const uint4 x = own[0], y = own[1];
+                h[2 * threadIdx.x] = x.x + x.y + x.z + x.w;
+                h[2 * threadIdx.x + 1] = y.x + y.y + y.z + y.w;
+            } else {
+                for_keys([&](uint32_t key) {
+                    if (key - lo <= span) atomicAdd(&h[(key >> shift) & dmask], 1u);     // LDS; integer adds, so order-free
+                });
+            }
             __syncthreads();
             const DigitView d = digit_view(h);
             digit_pick(h, d, need, digit, above);
@@ -687,12 +704,12 @@ __global__ __launch_bounds__(kSelThreads) void slot_kernel(const uint64_t* __res
 // the ones above write, read and read again a key for every (token, expert).
 //   1. choice_lists_kernel   a workgroup per tile of 64 tokens, a lane per token: the k best experts by insertion while the row is
 //                            walked; then the tile's pairs, sorted by expert and token, and where each expert's begin
-//   2. expert_lists_kernel   a workgroup per expert: its pairs of all tiles brought together in LDS, the threshold search on
-//                            them, and the (key > tau, key == tau) counts in front of each tile
+//   2. expert_lists_kernel   a workgroup per expert: its pairs of all tiles brought together in LDS or, where they are many, in
+//                            registers, the threshold search on them, and the (key > tau, key == tau) counts in front of each tile
 //   3. slot_lists_kernel     a workgroup per tile, a thread per pair: its place among the tile's pairs of the expert from
 //                            ballots; the slots leave as whole rows of slot_of
-// Bound by launches and latency and by the tables themselves.  65536 tokens x 64 experts, k = 4: the choice 20 -> 9.3 us, the
-// threshold with the affinity sum 6 + 31 -> 16, the slots 15 -> 7.6.
+// Bound by launches and latency and by the tables themselves; with a crowded column by its search on one CU.  65536 tokens x 64
+// experts, k = 4, even: the choice 20 -> 9.3 us, the threshold with the affinity sum 6 + 31 -> 16, the slots 15 -> 7.6.
 // ---------------------------------------------------------------------------------------
 constexpr int kListK = 4;                                // experts of a token, at most
 constexpr int kTileTokens = 64;
@@ -799,21 +816,32 @@ __global__ __launch_bounds__(256) void choice_lists_kernel(const float* __restri
     }
 }
 
-// A column's keys in LDS where they fit, else read again from the lists for each pass.  The room is static: a dynamic one of this size
-// would need an attribute of the kernel first, and a selection may be captured without a first call at its shape.
-constexpr int kListKeys = 24576;
-template <bool ADAPT>
+// A column's keys lie in LDS where it has up to list_pairs a tile.  Where an expert is chosen by more tokens than that, as happens
+// before training has spread the load, and where there are few tiles, they stay in registers: R per thread, a wave to a tile (a tile
+// holds up to 64 pairs of an expert; with 16 lanes to a tile one load follows the other, and LDS has no room for all).  The digits
+// of a long such column are counted in four copies (see count_threshold).  65536 tokens, k = 2, all on the first of 16
+// experts, selection: the column in LDS or read again for each digit 74 us, in registers 33; half of that
+// column the same key, 64 experts, k = 4: 150, in registers 117, with four copies 65; 16384 tokens, loads of 1 to 6, 16 experts: 15.1,
+// in registers from 8 pairs a tile on 16.7, from 12 on 14.4.
+// The room is static: a dynamic one of this size would need an attribute of the kernel first, and a selection may be captured
+// without a first call at its shape.
+template <int R> constexpr int list_pairs() { return R <= 8 ? 0 : 12; }   // of a tile, on average (0: always in registers)
+template <bool ADAPT, int R>
 __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists lists, int E, int k, int capacity_host, int mode,
                                                                    const int32_t* __restrict__ capacity_dev, long long sum_need,
                                                                    uint32_t* __restrict__ tau_out, int32_t* __restrict__ need_eq_out,
                                                                    int32_t* __restrict__ pre_gt, int32_t* __restrict__ pre_eq,
                                                                    int32_t* __restrict__ counts) {
-    __shared__ __attribute__((aligned(16))) uint32_t keys[kListKeys];
+    constexpr int kWaves = kSelThreads / kWave, kTiles = R * kWaves;    // tiles of R to a wave, at most
+    constexpr int kPairs = list_pairs<R>();
+    constexpr int kRoom = kPairs * kTiles > 4 * kBins ? kPairs * kTiles : 4 * kBins;     // crowded: of the four copies
+    __shared__ __attribute__((aligned(16))) uint32_t keys[kPairs > 0 ? kRoom : 4];
     __shared__ __attribute__((aligned(16))) uint32_t hist[kMaxDigits][kBins];
     __shared__ __attribute__((aligned(16))) unsigned long long sums[ADAPT ? kBins : 2];
     __shared__ int place[kSelThreads], from[kSelThreads], many[kSelThreads];             // of each tile's pairs
     __shared__ int wave_tot[kSelThreads / kWave][2];
-    __shared__ uint32_t range[kSelThreads / kWave][2];
+    __shared__ uint32_t range[kWaves][2];
+    __shared__ int by_rank[kWaves][kListK];
     const int e = blockIdx.x, tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int capacity = capacity_dev ? min(capacity_host, max(1, *capacity_dev)) : capacity_host;
@@ -846,75 +874,120 @@ __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists l
     } else {
         place[tid] = first; from[tid] = src; many[tid] = own;
         __syncthreads();
-        const bool in_lds = n <= kListKeys;
-        // every pair of the column, 16 lanes to a tile (a tile has k / E of its 64 tokens on average), kAtOnce tiles at a time
-        constexpr int kAtOnce = 8, kApart = kSelThreads / 16;
-        auto walk = [&](auto&& f) {
+        const bool crowded = kPairs == 0 || n > kPairs * lists.tiles;
+        const int uwave = __builtin_amdgcn_readfirstlane(wave);
+        uint32_t held[R];                                // crowded: tile uwave + 16 r, pair `lane` of it (0: none)
+        uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
+        if (crowded) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c = uwave + r * kWaves;        // (< kSelThreads; tiles past the last have no pairs)
+                held[r] = lane < many[c] ? lists.keys[from[c] + lane] : 0u;
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                kmax = max(kmax, held[r]);
+                kmin = min(kmin, held[r] - 1u);          // (0 wraps past all)
+            }
+            kmin += kmin != 0xFFFFFFFFu;
+        } else {
+            // every pair of the column, 16 lanes to a tile (a tile has k / E of its 64 tokens on average), kAtOnce tiles at a time
+            constexpr int kAtOnce = 8, kApart = kSelThreads / 16;
             const int sub = tid & 15;
             for (int c0 = tid >> 4; c0 < lists.tiles; c0 += kAtOnce * kApart) {
                 int m[kAtOnce], at[kAtOnce], g[kAtOnce];
-                uint32_t v[kAtOnce];
+                uint32_t v[kAtOnce], v2[kAtOnce];
 #pragma unroll
                 for (int i = 0; i < kAtOnce; ++i) {
                     const int c = min(c0 + i * kApart, kSelThreads - 1);         // (tiles past the last have no pairs)
                     m[i] = many[c]; at[i] = place[c]; g[i] = from[c];
                 }
 #pragma unroll
-                for (int i = 0; i < kAtOnce; ++i) v[i] = sub < m[i] ? lists.keys[g[i] + sub] : 0u;
+                for (int i = 0; i < kAtOnce; ++i) {
+                    v[i] = sub < m[i] ? lists.keys[g[i] + sub] : 0u;
+                    v2[i] = sub + 16 < m[i] ? lists.keys[g[i] + sub + 16] : 0u;
+                }
+                auto take = [&](int to, uint32_t key) {
+                    keys[to] = key;
+                    kmax = max(kmax, key); kmin = min(kmin, key);
+                };
 #pragma unroll
                 for (int i = 0; i < kAtOnce; ++i) {
-                    if (sub < m[i]) f(at[i] + sub, v[i]);
-                    for (int j = sub + 16; j < m[i]; j += 16) f(at[i] + j, lists.keys[g[i] + j]);
+                    if (sub < m[i]) take(at[i] + sub, v[i]);
+                    if (sub + 16 < m[i]) take(at[i] + sub + 16, v2[i]);
+                    for (int j = sub + 32; j < m[i]; j += 16) take(at[i] + j, lists.keys[g[i] + j]);
                 }
             }
-        };
-        uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
-        walk([&](int at, uint32_t key) {
-            if (in_lds) keys[at] = key;
-            kmax = max(kmax, key); kmin = min(kmin, key);
-        });
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-            kmax = max(kmax, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmax), m, kWave)));
-            kmin = min(kmin, static_cast<uint32_t>(__shfl_xor(static_cast<int>(kmin), m, kWave)));
         }
+        kmax = lane_group_fold<kWave, true>(kmax);
+        kmin = lane_group_fold<kWave, false>(kmin);
         if (lane == 0) { range[wave][0] = kmax; range[wave][1] = kmin; }
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < kSelThreads / kWave; ++w) { kmax = max(kmax, range[w][0]); kmin = min(kmin, range[w][1]); }
-        auto for_keys = [&](auto&& f) {
-            if (in_lds) for (int i = tid; i < n; i += kSelThreads) f(keys[i]);
-            else walk([&](int, uint32_t key) { f(key); });
-        };
+        for (int w = 0; w < kWaves; ++w) { kmax = max(kmax, range[w][0]); kmin = min(kmin, range[w][1]); }
         // Only the low bits in which the keys differ have to be resolved.  (The affinities of one expert crowd into few values
         // of the bits above, and adds to one word of LDS wait for each other.)
         auto varying = [](uint32_t diff) { return diff ? 32 - __builtin_clz(diff) : 0; };
         auto settled = [](uint32_t key, int shift) { return shift >= 32 ? 0u : (key >> shift) << shift; };
-        bool found = false;
-        if constexpr (ADAPT) {
-            if (by_sum && kmax >= 0x80000000u) {
-                const int shift = varying(kmax ^ max(kmin, 0x80000000u));
-                found = sum_threshold(for_keys, sum_need, settled(kmax, shift), shift, sums, n_keep, tau);
+        auto search = [&](auto&& for_keys) {
+            if constexpr (ADAPT) {
+                if (by_sum && kmax >= 0x80000000u) {
+                    const int shift = varying(kmax ^ max(kmin, 0x80000000u));
+                    if (sum_threshold(for_keys, sum_need, settled(kmax, shift), shift, sums, n_keep, tau)) return;
+                }
             }
-        }
-        if (found) {
-        } else if (n_keep == n) {
-            tau = 0u;
-        } else {
             const int shift = varying(kmax ^ kmin);
-            tau = count_threshold(for_keys, n_keep, shift, settled(kmax, shift), hist, 0, DigitView{0, 0, 0});
-        }
-        for (int j0 = 0; j0 < own; j0 += 4) {
-            uint32_t v[4];
+            if (n_keep == n) {
+                tau = 0u;
+            } else if (mode == ETR_MODE_TCR_RANK && shift > 0) {      // keys 1 to kListK: a count of each, no histogram of so few words
+                uint32_t mine = 0u;                      // (a thread has at most 64 keys)
+                for_keys([&](uint32_t key) { mine += key ? 1u << (8 * (key - 1)) : 0u; });
+                const int odd = wave_scan_incl(static_cast<int>(mine & 0x00FF00FFu)), even = wave_scan_incl(static_cast<int>((mine >> 8) & 0x00FF00FFu));
+                if (lane == kWave - 1) {
+                    by_rank[wave][0] = odd & 0xFFFF; by_rank[wave][1] = even & 0xFFFF;
+                    by_rank[wave][2] = odd >> 16; by_rank[wave][3] = even >> 16;
+                }
+                __syncthreads();
+                int above = 0;
+                for (int v = kListK; v >= 1; --v) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = min(j0 + i, own - 1);
-                v[i] = in_lds ? keys[first + j] : lists.keys[src + j];
+                    for (int w = 0; w < kWaves; ++w) above += by_rank[w][v - 1];
+                    if (above >= n_keep) { tau = static_cast<uint32_t>(v); break; }
+                }
+            } else {
+                tau = count_threshold(for_keys, n_keep, shift, settled(kmax, shift), hist, 0, DigitView{0, 0, 0},
+                                      kPairs > 0 && crowded ? keys : nullptr);
             }
+        };
+        if (crowded) {
+            search([&](auto&& f) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                gt += j0 + i < own && v[i] > tau;
-                eq += j0 + i < own && v[i] == tau;
+                for (int r = 0; r < R; ++r) {
+                    uint32_t key = held[r];
+                    asm volatile("" : "+v"(key));       // what is computed from it is not kept from one digit to the next: it would spill
+                    f(key);
+                }
+            });
+            // a tile's counts from ballots, left in place of its number of pairs
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int c = uwave + r * kWaves;
+                const uint64_t w_gt = __ballot(held[r] > tau), w_eq = __ballot(held[r] == tau && held[r] != 0u);
+                if (lane == 0) many[c] = __popcll(w_gt) | (__popcll(w_eq) << 16);
+            }
+            __syncthreads();
+            if (tid < lists.tiles) { gt = many[tid] & 0xFFFF; eq = many[tid] >> 16; }
+        } else {
+            search([&](auto&& f) { for (int i = tid; i < n; i += kSelThreads) f(keys[i]); });
+            for (int j0 = 0; j0 < own; j0 += 4) {
+                uint32_t v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = keys[first + min(j0 + i, own - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    gt += j0 + i < own && v[i] > tau;
+                    eq += j0 + i < own && v[i] == tau;
+                }
             }
         }
     }
@@ -1216,17 +1289,23 @@ hipError_t static_select_scratch(void** out) {
     return hipSuccess;
 }
 
-// Lists of the chosen pairs instead of a key for every (token, expert): where experts are chosen by an eighth of the tokens at
-// most, and by a quarter where the capacity leaves room, so that few have to be turned away: a threshold among many candidates is
-// found sooner with the whole column in registers, and with none to find the lists are ahead at any density.  Selection,
-// keys / lists, T x E, k, capacity over the even share: 65536 x 64, 4, 1.25: 58 / 20 us; 32768 x 32, 2, 0.75: 26 / 17; 8192 x 16,
-// 2, 1.0: 14.6 / 13.8; position priority, 32768 x 32: 18 / 11; a quarter, 2048 x 8, 2, 1.25: 13.1 / 9.0, but 4096 x 8, 2, 1.0:
-// 11.4 / 14.9 and 65536 x 8, 2, 0.9: 28 / 30; a half, 65536 x 8, 4, 0.9: 31 / 54.  Up to 1024 tokens, 1000 x 16: 13.0 / 13.8.
-// A tile is a thread of the per-expert kernel.
-static bool by_lists(const etr_config& c) {
+// Lists of the chosen pairs instead of a key for every (token, expert): where experts are chosen by an eighth of the tokens on
+// average, and by a quarter where the capacity has room for the even share and a quarter more.  How many tokens choose one expert the
+// host does not know, so both forms were measured with loads that are even, skewed (affinities to expert e ahead by 0.1 / e), halved
+// (half of all tokens on one expert, a quarter on the next) and with all tokens on one.  Selection in us, keys / lists, T x E, k, capacity over the even share:
+//   65536 x 64, 4, 1.25: even 58 / 21, halved 58 / 40, one 59 / 42      65536 x 16, 2, 1.25: even 37 / 12, halved 38 / 32, one 37 / 33
+//   8192 x 16, 2, 1.0: even 14.8 / 14.0, one 14.8 / 14.0              position priority, 65536 x 16, 2, 1.0: one 143 / 24
+//   a quarter: 2048 x 8, 2, 1.25: even 13.2 / 9.1, skewed 13.2 / 12.5, halved 13.3 / 13.7; 65536 x 16, 4, 1.25: even 39 / 13, halved 39 / 39
+//   a quarter without room: 2048 x 8, 2, 1.0: even 12.1 / 12.4; 16384 x 16, 4, 0.9: 16.2 / 17.8; 65536 x 8, 2, 0.9: 31 / 34, halved 31 / 37
+//   a half, 65536 x 8, 4, 0.9: 31 / 54.  Up to 1024 tokens, 1000 x 16, 2: 13.0 / 13.8
+// With room lists gain much where the load is even and lose 4 % (one figure 8 %) where it is not.  A capacity that is read on the device
+// may leave no room: up to 32768 tokens that costs little (above), beyond it only a search that the affinity sum asks for anyway is
+// worth it (65536 x 8, 2, 1.25 with a sum: 46 / 42, halved 51 / 45).  A tile is a thread of the per-expert kernel.
+static bool by_lists(const etr_config& c, bool capacity_on_device, bool by_sum) {
     if (c.mode != ETR_MODE_TCR && c.mode != ETR_MODE_TCR_RANK && c.mode != ETR_MODE_BIDIR) return false;
     if (c.k > kListK || c.T <= 1024 || c.T > kTileTokens * kSelThreads) return false;
-    const bool room = c.mode == ETR_MODE_TCR || 4ll * c.E * c.capacity >= 5ll * c.T * c.k;
+    const bool room = c.mode == ETR_MODE_TCR ||
+                      (4ll * c.E * c.capacity >= 5ll * c.T * c.k && (!capacity_on_device || by_sum || c.T <= 32768));
     return 8 * c.k <= c.E || (4 * c.k <= c.E && room);
 }
 
@@ -1240,12 +1319,17 @@ hipError_t launch_select(const etr_config& c, const float* score, int32_t* topk_
                            sum_need, topk_expert, slot_of, slot_token, counts);
         return hipGetLastError();
     }
-    if (by_lists(c)) {
+    if (by_lists(c, capacity_dev != nullptr, sum_need > 0)) {
         const ChoiceLists lists = carve_lists(w, c.T, c.E, c.k);
-        const bool adapt = sum_need > 0;
         hipLaunchKernelGGL(choice_lists_kernel, dim3(lists.tiles), dim3(256), 0, st, score, c.T, c.E, c.k, c.mode, topk_expert, lists);
-        hipLaunchKernelGGL(adapt ? expert_lists_kernel<true> : expert_lists_kernel<false>, dim3(c.E), dim3(kSelThreads), 0, st, lists, c.E, c.k, c.capacity, c.mode, capacity_dev, sum_need, w.tau,
-                           w.need_eq, w.pre_gt, w.pre_eq, counts);
+        auto kern = [&](auto adapted) {
+            constexpr bool A = decltype(adapted)::value;
+            const int per_wave = (lists.tiles + kSelThreads / kWave - 1) / (kSelThreads / kWave);
+            return per_wave <= 4 ? expert_lists_kernel<A, 4> : per_wave <= 8 ? expert_lists_kernel<A, 8> : per_wave <= 16 ? expert_lists_kernel<A, 16>
+                 : per_wave <= 32 ? expert_lists_kernel<A, 32> : expert_lists_kernel<A, 64>;
+        };
+        hipLaunchKernelGGL(sum_need > 0 ? kern(std::true_type{}) : kern(std::false_type{}), dim3(c.E), dim3(kSelThreads), 0, st, lists,
+                           c.E, c.k, c.capacity, c.mode, capacity_dev, sum_need, w.tau, w.need_eq, w.pre_gt, w.pre_eq, counts);
         hipLaunchKernelGGL(slot_lists_kernel, dim3(lists.tiles), dim3(kTileTokens * kListK), 0, st, lists, c.T, c.E, c.k, c.capacity, w.tau,
                            w.need_eq, w.pre_gt, w.pre_eq, counts, slot_of, slot_token);
         return hipGetLastError();

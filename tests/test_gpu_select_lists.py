@@ -20,6 +20,11 @@ def _scores(kind, T, E):
     if kind == "one":                                    # the first expert is everybody's choice
         s = s * np.float32(0.01)
         s[:, 0] = rng.uniform(0.2, 0.3, T).astype(np.float32)
+    if kind == "copies":                                 # half of the tokens are one token, with two experts far ahead
+        s[rng.random(T) < 0.5] = np.where(np.arange(E) < 2, np.float32(0.9), s[0] * np.float32(0.1)).astype(np.float32)
+    if kind == "half":                                   # half of the tokens on one expert, a quarter on the next, ...
+        s *= np.float32(0.05)
+        s[np.arange(T), rng.geometric(0.5, T).clip(1, E) - 1] += np.float32(0.5)
     return s
 
 
@@ -57,6 +62,14 @@ def test_selection_by_lists(oracle, T, E, k, kind):
             np.testing.assert_array_equal(st[:, :o_st.shape[1]], o_st)
             assert np.all(st[:, o_st.shape[1]:] == -1)
             np.testing.assert_array_equal(topk.cpu().numpy(), o_tk)
+
+
+@pytest.mark.parametrize("T,E,k,kind", [(1100, 8, 2, "half"), (2048, 8, 2, "copies"), (4097, 16, 4, "half"), (8192, 16, 2, "one"), (8193, 16, 4, "copies"),
+                                        (16384, 32, 4, "half"), (20000, 8, 2, "copies"), (32768, 16, 4, "half"), (32769, 64, 4, "copies"),
+                                        (65536, 8, 1, "half"), (65500, 12, 3, "copies"), (65536, 64, 1, "one")])
+def test_crowded_columns(oracle, T, E, k, kind):
+    """Columns that stay in registers, of every length: thresholds inside a run of equal keys, with and without an affinity sum."""
+    test_selection_by_lists(oracle, T, E, k, kind)
 
 
 def test_capture_behind_a_first_call_at_another_shape(oracle):
