@@ -1131,9 +1131,11 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         key = selection_key(own_score, mode == ETR_MODE_ECR || rank < k, mode, k, rank);
     }
     int32_t* mine = slot_token + static_cast<size_t>(e) * capacity_host;
-    int n = T;                                           // candidates (a key of 0 is none)
-    // Where every token is a candidate and some are turned away there is nothing to bring together.
-    if (mode == ETR_MODE_TCR || capacity >= T || (mode != ETR_MODE_ECR && k < E)) {
+    int n = T, token = t;                                // candidates (a key of 0 is none); whose this thread's is
+    // Where nearly every token is a candidate and some are turned away there is little to bring together.  Counted all / brought
+    // together, 0.9 of the even share: 512 x 8, k = 5 10.7 / 9.5 us, k = 7 10.6 / 10.9; 512 x 64, k = 40 16.4 / 15.3, k = 60 16.4 / 16.9.
+    // With a quarter more than the even share there may be none to count: k = 5 10.8 / 4.0.
+    if (mode == ETR_MODE_TCR || capacity >= T || (mode != ETR_MODE_ECR && (4 * k <= 3 * E || 4ll * E * capacity >= 5ll * T * k))) {
         // place among the column's candidates, in token order
         const uint64_t in_column = __ballot(key != 0u);
         if (lane == 0) wave_count[wave] = __popcll(in_column);
@@ -1163,9 +1165,9 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         if (t >= n) keys[t] = 0u;
         __syncthreads();
         key = keys[t];
+        token = tokens[t];
     } else {
         keys[t] = key;
-        tokens[t] = t;
         if constexpr (ADAPT) terms[t] = key >= 0x80000000u ? affinity_term(key) : 0u;
         __syncthreads();
     }
@@ -1198,11 +1200,16 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         for (int i = 0; i < kWave / 4; ++i) {
             const uint4 v = k4[uwave * (kWave / 4) + i];
             const uint32_t f[4] = {v.x, v.y, v.z, v.w};
+            uint32_t term[4];
+            if constexpr (ADAPT) {
+                const uint4 q = t4[uwave * (kWave / 4) + i];
+                term[0] = q.x; term[1] = q.y; term[2] = q.z; term[3] = q.w;
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool first = f[j] > key || (f[j] == key && 4 * i + j < lane);
                 before += first;
-                if constexpr (ADAPT) before_sum += first ? terms[uwave * kWave + 4 * i + j] : 0u;
+                if constexpr (ADAPT) before_sum += first ? term[j] : 0u;
             }
         }
     }
@@ -1217,7 +1224,6 @@ __global__ __launch_bounds__(kSmallTokens) void small_select_kernel(const float*
         total += wave_kept[w];
     }
     if (t < n) {
-        const int token = tokens[t];
         slot_of[static_cast<size_t>(token) * E + e] = kept ? slot : -1;
         if (kept) mine[slot] = token;
     }

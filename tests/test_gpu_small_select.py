@@ -42,3 +42,27 @@ def test_small_select(oracle, T, E, k, C, levels):
                 assert torch.all(topk == -7)
             else:
                 np.testing.assert_array_equal(topk.cpu().numpy(), o_tk)
+
+
+@pytest.mark.parametrize("T,E,k,C,levels", [(64, 8, 6, 30, 7), (65, 8, 7, 30, None), (200, 12, 10, 150, 5), (512, 64, 48, 380, None),
+                                            (512, 64, 49, 200, 9), (511, 8, 8, 100, None), (16, 4, 3, 9, None)])
+def test_small_select_around_three_quarters(oracle, T, E, k, C, levels):
+    """Experts kept by most of the tokens: candidates counted where they lie and brought together, the second again with an affinity
+    sum that ends inside the list, reaches its end, or is beyond it."""
+    test_small_select(oracle, T, E, k, C, levels)
+    rng = np.random.default_rng(T + E)
+    S = (rng.integers(-levels, levels + 1, size=(T, E)) / levels if levels else rng.uniform(-1, 1, (T, E))).astype(np.float32)
+    Sd = torch.from_numpy(S).cuda()
+    for mode in (I.MODE_ECR, I.MODE_BIDIR):
+        for thr in (0.2 * T * 0.3, 0.9 * T * 0.3, 10.0 * T):
+            cfg = B.make_config(I.EtrShape("s", 1, T=T, d=8 * E, E=E, D=8, k=k, capacity=C, H=8, dtype=I.DT_F32, mode=mode, recipe="iso"))
+            topk, slot_of, slot_token, counts = (torch.full(n, -7, dtype=torch.int32, device="cuda") for n in ((T, k), (T, E), (E, C), (E,)))
+            B.etr_select_adaptive(cfg, Sd, None, float(np.float32(thr)), topk, slot_of, slot_token, counts,
+                                  B.alloc_workspace(B.etr_select_workspace_bytes(cfg)))
+            torch.cuda.synchronize()
+            _, o_so, o_st, o_c = oracle.select_adaptive(S, k, C, mode, float(np.float32(thr)))
+            np.testing.assert_array_equal(counts.cpu().numpy(), o_c)
+            np.testing.assert_array_equal(slot_of.cpu().numpy(), o_so)
+            st = slot_token.cpu().numpy()
+            np.testing.assert_array_equal(st[:, :o_st.shape[1]], o_st)
+            assert np.all(st[:, o_st.shape[1]:] == -1)
