@@ -5,8 +5,8 @@
 //
 // Stages (all on one stream, nothing leaves the device):
 //   1. a = Xp Wg^T, b = Xp Wu^T recomputed (rows gathered through slot_token), u = dOut_p Wd
-//   2. element-wise: h = SiLU(a) b, da = gate u b SiLU'(a), db = gate u SiLU(a), <u, h> per row (= d out / d gate); bf16: the
-//      epilogue of u's product, fp32 and the fall-back: a pass of its own
+//   2. element-wise: h = SiLU(a) b, da = gate u b SiLU'(a), db = gate u SiLU(a), <u, h> per row (= d out / d gate); bf16 with enough
+//      tiles: the epilogue of u's product (middle_in_product), else a pass of its own
 //   3. dXp = da Wg + db Wu;  dWd = (gate dOut_p)^T h;  dWg = da^T Xp;  dWu = db^T Xp
 //   4. dx[t] = sum_e dXp[e][slot] + sum_e dscore[t][e] * d score[t][e] / d x[t]  (softmax and Eq. 4 differentiated)
 // Every matrix product runs on the grouped kernels of ffn.hip.  Operands whose contraction index is the
@@ -153,9 +153,9 @@ __global__ __launch_bounds__(kTileThreads) void gather_transpose_kernel(const T*
 //        dgate_part [H/64][E][C]: this tile's share of <u, h> per row (summed by dx_kernel in a fixed order)
 // ROWS: no transposed copies; dab and h are [E][Cp][.] row-major with zero rows from counts[e] to padded_rows (the
 // products that contract over the rows read them through transposing LDS reads); hT then is that row-major h.
-// fp32 only: hT then holds gate * h, so that dW_down = dOut_p^T (gate h) needs no scaled copy of dOut's rows.  (bf16 has this as
-// the epilogue of the product u, see GEMM_MIDDLE.)
-template <typename T, bool ROWS>
+// SCALE_H (with ROWS): hT holds gate * h, so that dW_down = dOut_p^T (gate h) needs no scaled copy of dOut's rows.
+// (bf16 with many tiles of u has this as the epilogue of that product, see middle_in_product.)
+template <typename T, bool ROWS, bool SCALE_H = false>
 __global__ __launch_bounds__(kTileThreads) void swiglu_backward_kernel(
     const T* __restrict__ u, const T* __restrict__ a, const T* __restrict__ b, const float* __restrict__ gate,
     const int32_t* __restrict__ slot_token, const int32_t* __restrict__ counts, T* __restrict__ dab, T* __restrict__ daT,
@@ -197,8 +197,10 @@ __global__ __launch_bounds__(kTileThreads) void swiglu_backward_kernel(
             if (s < Cp && n < H) {                                   // (s < padded_rows: the block starts below it)
                 Elt<T>::store_vec(dab + (obase + s) * 2 * H + n, dav);
                 Elt<T>::store_vec(dab + (obase + s) * 2 * H + H + n, dbv);
+                if constexpr (SCALE_H) {
 #pragma unroll
-                for (int i = 0; i < V; ++i) hv[i] *= g_row;
+                    for (int i = 0; i < V; ++i) hv[i] *= g_row;
+                }
                 Elt<T>::store_vec(hT + (obase + s) * H + n, hv);
             }
         } else {
@@ -542,6 +544,19 @@ int dx_pieces(const etr_config& c, int Cp, bool fetch_x) {
     return pieces;
 }
 
+// bf16: whether the element-wise middle is the epilogue of the product u or a pass of its own behind it.  The epilogue saves the
+// writing and reading of u, but with the tiles on a part of the CUs it runs on that part alone, for up to 20 us, where a pass has
+// all of them: the line lies at tiles for 5 of 16 CUs.  An expert of up to 64 rows leaves most of its tile empty.  Step, pass /
+// epilogue, experts, rows, d x H (tiles): 4 of 256, 256 x 256 (4) 80.6 / 86.5 us; 8 of 512, 1024 x 256 (16) 128.6 / 133.9; 32 of 256,
+// 256 x 256 (32) 127.8 / 132.6; 16 of 512, 2048 x 512 (64) 341.1 / 339.4; 8 of 512, 256 x 1280 (80) 130.2 / 132.0, 2048 wide 323.7 /
+// 321.9; 32 of 128, 1024 x 704 (96) 237.3 / 234.0; 16 of 512, 256 x 1024 (128) 162.9 / 159.8; 32 of 1024, 256 x 512 (256) 268 / 250;
+// 4 of 64, 1024 x 256 (4) 94.4 / 93.0.
+bool middle_in_product(const etr_config& c) {
+    const int rows = rows_expected(c);
+    const long long tiles = static_cast<long long>(c.E) * ((rows + 255) / 256) * ((c.H + 255) / 256);
+    return rows <= 64 || 16 * tiles >= 5ll * cu_count();
+}
+
 struct BackwardWs {
     size_t wdT, wguT, a, b, u, dab, daT, dbT, hT, xpT, dypT, dxp, dgate_part, gate_eff, total;
 };
@@ -611,9 +626,9 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
     //   u = dOut_p Wd (Wd as [d][H]);  dXp = (da|db) (Wg ; Wu) (two [H][d] halves of the contraction);
     //   dWd = dYp^T h;  dWg = da^T Xp;  dWu = db^T Xp  (contraction over the rows, all operands row-major)
     constexpr bool f32 = sizeof(T) == 4;                 // its kernel takes all widths
-    // (bf16: with the element-wise middle as its epilogue, so u itself is not written)
-    GroupedGemm t2{dout, w_down, nullptr, f32 ? at(L.u) : at(L.dab), f32 ? nullptr : at(L.hT), counts, nullptr, slot_token, E, C, H, d, 0, H, Tn,
-                   f32 ? GEMM_PLAIN : GEMM_MIDDLE, c.dtype};
+    const bool fused = !f32 && middle_in_product(c);     // with the element-wise middle as its epilogue u itself is not written
+    GroupedGemm t2{dout, w_down, nullptr, fused ? at(L.dab) : at(L.u), fused ? at(L.hT) : nullptr, counts, nullptr, slot_token, E, C, H, d, 0, H, Tn,
+                   fused ? GEMM_MIDDLE : GEMM_PLAIN, c.dtype};
     t2.tb = true;
     t2.mid_a = pre_a; t2.mid_b = pre_b; t2.mid_gate = gate_w; t2.mid_part = dgate_part; t2.mid_rows = Cp;
     GroupedGemm t3{at(L.dab), w_gate, w_up, at(L.dxp), nullptr, counts, nullptr, nullptr, E, Cp, d, 2 * H, 0, d, Cp, GEMM_PLAIN, c.dtype};
@@ -667,19 +682,25 @@ hipError_t backward_impl(const etr_config& c, const void* x, const float* w_emb,
         const bool nt_dxp = !f32 && rows_expected(c) >= 8192 && d >= 256 && d % 8 == 0;
         t2.mid_scale_h = fetch_dout;
         ETR_BW(launch_grouped_gemm(t2, st));
-        if constexpr (f32) {
-            hipLaunchKernelGGL((swiglu_backward_kernel<T, true>), dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a, pre_b, gate_w,
-                               slot_token, counts, at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr), at(L.hT), dgate_part, Tn, E,
-                               C, Cp, H);
-        } else if (!fetch_dout) {
-            const unsigned row_blocks = static_cast<unsigned>((static_cast<long long>(E) * Cp + 3) / 4);
-            if (!fetch_x)
-                hipLaunchKernelGGL((gather_rows_kernel<T, false>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(x),
-                                   slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp, static_cast<T*>(nullptr), static_cast<T*>(nullptr), H);
-            hipLaunchKernelGGL((gather_rows_kernel<T, true>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(dout),
-                               slot_token, counts, gate_w, at(L.dypT), Tn, d, E, C, Cp, at(L.dab), at(L.hT), H);
-        } else {
-            hipLaunchKernelGGL(zero_padding_kernel<T>, dim3(64, E), dim3(256), 0, st, counts, at(L.dab), at(L.hT), C, Cp, H);
+        if (!fused) {                                    // (writes the zero rows behind an expert's own too)
+            auto middle = swiglu_backward_kernel<T, true, true>;
+            if constexpr (!f32)
+                if (!fetch_dout) middle = swiglu_backward_kernel<T, true, false>;
+            hipLaunchKernelGGL(middle, dim3(cH, cC, E), dim3(kTileThreads), 0, st, at(L.u), pre_a, pre_b, gate_w, slot_token, counts,
+                               at(L.dab), static_cast<T*>(nullptr), static_cast<T*>(nullptr), at(L.hT), dgate_part, Tn, E, C, Cp, H);
+        }
+        if constexpr (!f32) {
+            if (!fetch_dout) {
+                const unsigned row_blocks = static_cast<unsigned>((static_cast<long long>(E) * Cp + 3) / 4);
+                if (!fetch_x)
+                    hipLaunchKernelGGL((gather_rows_kernel<T, false>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(x),
+                                       slot_token, counts, gate, at(L.xpT), Tn, d, E, C, Cp, static_cast<T*>(nullptr), static_cast<T*>(nullptr), H);
+                hipLaunchKernelGGL((gather_rows_kernel<T, true>), dim3(row_blocks), dim3(256), 0, st, static_cast<const T*>(dout),
+                                   slot_token, counts, gate_w, at(L.dypT), Tn, d, E, C, Cp, fused ? at(L.dab) : static_cast<T*>(nullptr),
+                                   at(L.hT), H);
+            } else if (fused) {
+                hipLaunchKernelGGL(zero_padding_kernel<T>, dim3(64, E), dim3(256), 0, st, counts, at(L.dab), at(L.hT), C, Cp, H);
+            }
         }
         ETR_BW(hipGetLastError());
         if (nt_dxp) {

@@ -2588,10 +2588,11 @@ hipError_t launch_grouped_gemm(const GroupedGemm& q, hipStream_t st) {
         if (q.k_gather == 1) return launch_bf16_transposing<true, 1>(g, st, n_cu);
         if (q.k_gather == 2) return launch_bf16_transposing<true, 2>(g, st, n_cu);
         if (q.ta) return hipErrorInvalidValue;           // (such products come in launch_backward_products)
-        if (q.epilogue != GEMM_MIDDLE) return hipErrorInvalidValue;
         // a contraction that is not whole k-tiles: the zero-filling instantiation
-        return q.K % 64 == 0 ? launch_bf16_transposing<false, 0, false, true>(g, st, n_cu)
-                             : launch_bf16_transposing<false, 0, true, true>(g, st, n_cu);
+        const bool tail = (q.B1 ? q.K / 2 : q.K) % 64 != 0;
+        if (q.epilogue == GEMM_MIDDLE)
+            return tail ? launch_bf16_transposing<false, 0, true, true>(g, st, n_cu) : launch_bf16_transposing<false, 0, false, true>(g, st, n_cu);
+        return tail ? launch_bf16_transposing<false, 0, true>(g, st, n_cu) : launch_bf16_transposing<false, 0>(g, st, n_cu);
     }
     if (q.dtype == ETR_BF16) {
         if (q.K % 8 != 0 || (q.lda ? q.lda : q.K) % 8 != 0 || (q.ldb ? q.ldb : q.K) % 8 != 0) return hipErrorInvalidValue;

@@ -1,4 +1,5 @@
-"""The element-wise middle of the bf16 backward as the epilogue of its product: experts whose rows end inside the pieces of 8 and
+"""The element-wise middle of the bf16 backward, a pass of its own where few tiles are expected and else the epilogue of its product,
+here also behind the second and third tile of a workgroup: experts whose rows end inside the pieces of 8 and
 the blocks of 32 rows that it goes by, in the second half of a tile, past one tile, and none at all; widths that end inside a
 piece of 64 hidden units; kept pre-activations and recomputed ones, invalid entries of the slot list.  All gradients, with that
 of the gate, against the oracle with the layer's tolerance; the workspace holds NaN patterns."""
@@ -19,14 +20,36 @@ pytestmark = pytest.mark.gpu
     (900, 128, 200, 8192, (0, 1, 255, 256, 257, 900))])
 @pytest.mark.parametrize("gate_norm", [0, 1])
 def test_middle_at_the_edges_of_its_blocks(oracle, T, d, Hh, C, rows, gate_norm):
+    _check(oracle, T, d, Hh, C, rows, gate_norm, 2)
+
+
+# The tables are given, so T, k and the number of experts only say which form is taken: 64 expected rows and fewer, or many tiles, take
+# the epilogue.  The last ones have 576 tiles, whose contraction is two k-tiles, whole or with a short one.
+@pytest.mark.parametrize("T,d,Hh,C,rows,k,saved", [
+    (400, 136, 64, 300, (0, 127, 128, 129, 255, 256, 257, 300), 1, True),
+    (700, 264, 328, 640, (159, 160, 161, 512, 513, 640, 2, 64, 0, 1, 33), 1, False),
+    (700, 128, 72, 640, (31, 640, 0, 257, 8, 9, 7, 384, 385, 65, 1), 1, True),
+    (900, 128, 200, 8192, (0, 1, 255, 256, 257, 900) + (30,) * 9, 1, False),
+    (420, 128, 4392, 400, (257, 300, 310, 400, 333, 288, 289, 260, 384, 385, 290, 352, 353, 399, 270, 320), 8, True),
+    (420, 136, 4392, 400, (257, 300, 310, 400, 333, 288, 289, 260, 384, 385, 290, 352, 353, 399, 270, 320), 8, False)])
+def test_middle_in_the_product(oracle, T, d, Hh, C, rows, k, saved):
+    expected = min(C, -(-T * k // len(rows)))
+    assert expected <= 64 or len(rows) * -(-expected // 256) * -(-Hh // 256) >= 128
+    _check(oracle, T, d, Hh, C, rows, len(rows) & 1, k, saved)
+
+
+def _check(oracle, T, d, Hh, C, rows, gate_norm, k, saved=False):
     import gpu_helpers as H
     B.load_library()
     E = len(rows)
-    shape = I.EtrShape("middle", 43, T=T, d=d, E=E, D=8, k=2, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR, recipe="iso",
+    shape = I.EtrShape("middle", 43, T=T, d=d, E=E, D=8, k=k, capacity=C, H=Hh, dtype=I.DT_BF16, mode=I.MODE_BIDIR, recipe="iso",
                        n_centroids=E)
     print(f"backward middle T={T} d={d} H={Hh} C={C} rows={rows} gate_norm={gate_norm}", flush=True)
     L = H.GpuLayer(shape, gate_norm=gate_norm)
     L.route()
+    kept = {}
+    if saved:                                            # x W_gate and x W_up of the given rows, as the forward call keeps them
+        kept = {n: torch.full((E, C, Hh), float("nan"), dtype=shape.torch_dtype, device="cuda") for n in ("a_saved", "b_saved")}
     slot_of, slot_token = np.full((T, E), -1, np.int32), np.full((E, C), -1, np.int32)
     rng = np.random.default_rng(5)
     for e, n in enumerate(rows):
@@ -36,11 +59,14 @@ def test_middle_at_the_edges_of_its_blocks(oracle, T, d, Hh, C, rows, gate_norm)
     tables = [torch.from_numpy(v).cuda() for v in (slot_of, slot_token, np.array(rows, np.int32))]
     dout = I.make_upstream_gradient(shape, "cuda")
     t = L.t
+    for name, w in zip(kept, (t["w_gate"], t["w_up"])):
+        for e, n in enumerate(rows):
+            kept[name][e, :n] = (t["x"][tables[1][e, :n].long()].float() @ w[e].float().t()).to(shape.torch_dtype)
     out = [torch.full(s, 7.0, dtype=shape.torch_dtype, device="cuda") for s in ((T, d), (E, Hh, d), (E, Hh, d), (E, d, Hh))]
     dgate = torch.full((T, E), 7.0, device="cuda")
     ws = B.alloc_workspace(B.etr_backward_workspace_bytes(L.cfg))
     ws.fill_(0xFF)
-    B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, *tables, dout, *out, ws, dgate=dgate)
+    B.etr_moe_backward(L.cfg, t["x"], t["w_emb"], t["w_gate"], t["w_up"], t["w_down"], L.score, L.gate, *tables, dout, *out, ws, dgate=dgate, **kept)
     torch.cuda.synchronize()
     hx = L.host_inputs()
     ref = oracle.moe_backward(*(hx[n] for n in ("x", "w_emb", "w_gate", "w_up", "w_down")), slot_of, H.to_np(dout), D=8, dtype=shape.dtype,
