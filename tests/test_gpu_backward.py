@@ -89,8 +89,8 @@ SMALL = {
     # the same with a capacity that is no multiple of 64 (row numbers past the end of an expert's slot list), a ragged
     # last column tile of dW_down and experts of very different sizes
     "cfg2q": lambda: I.CONFIGS["cfg2"].with_(T=9000, d=256, H=200, capacity=8200, name="cfg2-rows-ragged"),
-    # 8192 or more rows expected (expert choice) and whole 256-column tiles: the products against a weight matrix run on
-    # the row-major kernel with the weight transposed once, u and the input gradient or, with H = 200, only the latter
+    # 8192 or more rows expected (expert choice) and whole 256-column tiles: the input gradient runs on the row-major kernel
+    # with the weights transposed once
     "cfg2n": lambda: I.CONFIGS["cfg2"].with_(T=17000, d=256, H=256, E=3, capacity=16500, name="cfg2-many-rows"),
     "cfg2m": lambda: I.CONFIGS["cfg2"].with_(T=17000, d=264, H=200, D=8, E=2, capacity=17100, name="cfg2-many-rows-ragged"),
 }

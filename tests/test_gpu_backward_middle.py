@@ -1,7 +1,7 @@
 """The element-wise middle of the bf16 backward, a pass of its own where few tiles are expected and else the epilogue of its product,
 here also behind the second and third tile of a workgroup: experts whose rows end inside the pieces of 8 and
 the blocks of 32 rows that it goes by, in the second half of a tile, past one tile, and none at all; widths that end inside a
-piece of 64 hidden units; kept pre-activations and recomputed ones, invalid entries of the slot list.  All gradients, with that
+piece of 64 hidden units; kept pre-activations and recomputed ones, -1 in the slot list behind an expert's rows.  All gradients, with that
 of the gate, against the oracle with the layer's tolerance; the workspace holds NaN patterns."""
 import numpy as np
 import pytest
