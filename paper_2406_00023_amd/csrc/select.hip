@@ -816,26 +816,24 @@ __global__ __launch_bounds__(256) void choice_lists_kernel(const float* __restri
     }
 }
 
-// A column's keys lie in LDS where it has up to list_pairs a tile.  Where an expert is chosen by more tokens than that, as happens
-// before training has spread the load, and where there are few tiles, they stay in registers: R per thread, a wave to a tile (a tile
-// holds up to 64 pairs of an expert; with 16 lanes to a tile one load follows the other, and LDS has no room for all).  The digits
-// of a long such column are counted in four copies (see count_threshold).  65536 tokens, k = 2, all on the first of 16
-// experts, selection: the column in LDS or read again for each digit 74 us, in registers 33; half of that
-// column the same key, 64 experts, k = 4: 150, in registers 117, with four copies 65; 16384 tokens, loads of 1 to 6, 16 experts: 15.1,
-// in registers from 8 pairs a tile on 16.7, from 12 on 14.4.
+// A column of up to list_keys lies in LDS.  Where an expert is chosen by more tokens than that, as happens before training has
+// spread the load, and where there are few tiles, its keys stay in registers: R per thread, a wave to a tile (a tile holds up to 64
+// pairs of an expert, which 16 lanes would load one load behind the other).  The digits of a long such column are counted in four
+// copies (see count_threshold).  Selection: 65536 tokens, k = 2, all on the first of 16 experts, the column read again for each
+// digit 74 us, in registers 33; half of a column the same key, 64 experts, k = 4: 150, in registers 117, with four copies 65.  The
+// room: 24 keys for each tile that R stands for, 12: routing read-outs of 51822 tokens, 24 experts, k = 2, skewed 94 / 105 us, of 40829,
+// 384 wide, k = 4 87 / 93; 8, selection of 16384 tokens, loads of 1 to 6, 16 experts: 14.5 / 16.7.
 // The room is static: a dynamic one of this size would need an attribute of the kernel first, and a selection may be captured
 // without a first call at its shape.
-template <int R> constexpr int list_pairs() { return R <= 8 ? 0 : 12; }   // of a tile, on average (0: always in registers)
+template <int R> constexpr int list_keys() { return R <= 8 ? 0 : 24 * R * (kSelThreads / kWave); }
 template <bool ADAPT, int R>
 __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists lists, int E, int k, int capacity_host, int mode,
                                                                    const int32_t* __restrict__ capacity_dev, long long sum_need,
                                                                    uint32_t* __restrict__ tau_out, int32_t* __restrict__ need_eq_out,
                                                                    int32_t* __restrict__ pre_gt, int32_t* __restrict__ pre_eq,
                                                                    int32_t* __restrict__ counts) {
-    constexpr int kWaves = kSelThreads / kWave, kTiles = R * kWaves;    // tiles of R to a wave, at most
-    constexpr int kPairs = list_pairs<R>();
-    constexpr int kRoom = kPairs * kTiles > 4 * kBins ? kPairs * kTiles : 4 * kBins;     // crowded: of the four copies
-    __shared__ __attribute__((aligned(16))) uint32_t keys[kPairs > 0 ? kRoom : 4];
+    constexpr int kWaves = kSelThreads / kWave, kKeys = list_keys<R>();
+    __shared__ __attribute__((aligned(16))) uint32_t keys[kKeys == 0 ? 4 : (kKeys > 4 * kBins ? kKeys : 4 * kBins)];       // or the four copies
     __shared__ __attribute__((aligned(16))) uint32_t hist[kMaxDigits][kBins];
     __shared__ __attribute__((aligned(16))) unsigned long long sums[ADAPT ? kBins : 2];
     __shared__ int place[kSelThreads], from[kSelThreads], many[kSelThreads];             // of each tile's pairs
@@ -874,7 +872,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists l
     } else {
         place[tid] = first; from[tid] = src; many[tid] = own;
         __syncthreads();
-        const bool crowded = kPairs == 0 || n > kPairs * lists.tiles;
+        const bool crowded = n > kKeys;
         const int uwave = __builtin_amdgcn_readfirstlane(wave);
         uint32_t held[R];                                // crowded: tile uwave + 16 r, pair `lane` of it (0: none)
         uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
@@ -956,7 +954,7 @@ __global__ __launch_bounds__(kSelThreads) void expert_lists_kernel(ChoiceLists l
                 }
             } else {
                 tau = count_threshold(for_keys, n_keep, shift, settled(kmax, shift), hist, 0, DigitView{0, 0, 0},
-                                      kPairs > 0 && crowded ? keys : nullptr);
+                                      kKeys > 0 && crowded ? keys : nullptr);
             }
         };
         if (crowded) {
@@ -1299,14 +1297,14 @@ hipError_t static_select_scratch(void** out) {
 // average, and by a quarter where the capacity has room for the even share and a quarter more.  How many tokens choose one expert the
 // host does not know, so both forms were measured with loads that are even, skewed (affinities to expert e ahead by 0.1 / e), halved
 // (half of all tokens on one expert, a quarter on the next) and with all tokens on one.  Selection in us, keys / lists, T x E, k, capacity over the even share:
-//   65536 x 64, 4, 1.25: even 58 / 21, halved 58 / 40, one 59 / 42      65536 x 16, 2, 1.25: even 37 / 12, halved 38 / 32, one 37 / 33
+//   65536 x 64, 4, 1.25: even 58 / 21, halved 58 / 40, one 59 / 42      65536 x 16, 2, 1.25: even 37 / 12, halved 37 / 32, one 37 / 33
 //   8192 x 16, 2, 1.0: even 14.8 / 14.0, one 14.8 / 14.0              position priority, 65536 x 16, 2, 1.0: one 143 / 24
 //   a quarter: 2048 x 8, 2, 1.25: even 13.2 / 9.1, skewed 13.2 / 12.5, halved 13.3 / 13.7; 65536 x 16, 4, 1.25: even 39 / 13, halved 39 / 39
 //   a quarter without room: 2048 x 8, 2, 1.0: even 12.1 / 12.4; 16384 x 16, 4, 0.9: 16.2 / 17.8; 65536 x 8, 2, 0.9: 31 / 34, halved 31 / 37
 //   a half, 65536 x 8, 4, 0.9: 31 / 54.  Up to 1024 tokens, 1000 x 16, 2: 13.0 / 13.8
 // With room lists gain much where the load is even and lose 4 % (one figure 8 %) where it is not.  A capacity that is read on the device
 // may leave no room: up to 32768 tokens that costs little (above), beyond it only a search that the affinity sum asks for anyway is
-// worth it (65536 x 8, 2, 1.25 with a sum: 46 / 42, halved 51 / 45).  A tile is a thread of the per-expert kernel.
+// worth it (65536 x 8, 2, 1.25 with a sum: 45 / 32, halved 51 / 45).  A tile is a thread of the per-expert kernel.
 static bool by_lists(const etr_config& c, bool capacity_on_device, bool by_sum) {
     if (c.mode != ETR_MODE_TCR && c.mode != ETR_MODE_TCR_RANK && c.mode != ETR_MODE_BIDIR) return false;
     if (c.k > kListK || c.T <= 1024 || c.T > kTileTokens * kSelThreads) return false;

@@ -66,7 +66,8 @@ def test_selection_by_lists(oracle, T, E, k, kind):
 
 @pytest.mark.parametrize("T,E,k,kind", [(1100, 8, 2, "half"), (2048, 8, 2, "copies"), (4097, 16, 4, "half"), (8192, 16, 2, "one"), (8193, 16, 4, "copies"),
                                         (16384, 32, 4, "half"), (20000, 8, 2, "copies"), (32768, 16, 4, "half"), (32769, 64, 4, "copies"),
-                                        (65536, 8, 1, "half"), (65500, 12, 3, "copies"), (65536, 64, 1, "one")])
+                                        (65536, 8, 1, "half"), (65500, 12, 3, "copies"), (65536, 64, 1, "one"),
+                                        (16300, 8, 2, "any"), (32700, 9, 2, "ties"), (49152, 8, 2, "half")])
 def test_crowded_columns(oracle, T, E, k, kind):
     """Columns that stay in registers, of every length: thresholds inside a run of equal keys, with and without an affinity sum."""
     test_selection_by_lists(oracle, T, E, k, kind)
