@@ -1986,11 +1986,14 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_rows_kernel(GemmParams p) {
 // component v of both operands (the k order inside a step is permuted alike on both sides).  A ring of NBUF buffers
 // is filled by copies that bypass the registers, NBUF - 1 k-tiles ahead; behind the end of the contraction the last
 // k-tile is copied again, which keeps the wait count constant.  Copies go through a buffer descriptor whose base moves with the
-// k-tile, so a lane carries one 32-bit offset that never changes, and a piece past the contraction asks for an offset past the
-// range (see buffer_copy_to_lds).  The other form of a copy into LDS is a flat instruction to the compiler, which then waits for
-// every LDS read and every load in flight, not for those it needs; with its 64-bit addresses the layer took, 8192 tokens on 8
-// experts, 1024 x 2048, 1786 us, now 1630; 2048 tokens, 512 x 1024 140 / 130; 1024 tokens 108 / 103.  WIDE keeps it, for operands of
-// 4 GiB and more (f32_wide): the zeros then come from a zero page.
+// k-tile, so a lane carries one 32-bit offset that never changes, and a piece past the contraction, of a row past the group's own or
+// of a weight row past the last asks for an offset past the range (see buffer_copy_to_lds).  With the last row in place of those
+// it took up to 12 % more where groups end in a nearly empty tile and the widths are ragged, 0.5 % less elsewhere: layer of 32
+// experts of 66 rows, 888 x 800: 182 / 162 us; training step of 12 of 500, 1000 x 328 597 / 573, of 8 of 512, 512 x 1024 397 / 398.
+// The other form of a copy into LDS is a flat instruction to the compiler, which then waits for every LDS read and every load in
+// flight, not for those it needs; with its 64-bit addresses the layer took, 8192 tokens on 8 experts, 1024 x 2048, 1786 us, now 1630;
+// 2048 tokens, 512 x 1024 140 / 130; 1024 tokens 108 / 103.  WIDE keeps it, for operands of 4 GiB and more (f32_wide): the zeros
+// then come from a zero page, and the last row stands for those past the end.
 // Tile: 64 x 64, or 32 x 32 where the capacity gives fewer than two 64 x 64 tiles per CU (see launch_f32).  Measured
 // against the plain-FMA kernel this replaces: 8 experts of 66-640 rows, 512 x 1024: gate/up 298 -> 91 us (86 TFLOP/s),
 // the plain products 182 -> 60 us on average; 8 experts of 80 rows, 256 x 512: 71 -> 11 us and 55 -> 8 us; 8 x 2048 rows,
@@ -2051,9 +2054,10 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
             off[i] = (static_cast<Offset>(gathered_a ? 0 : k_of(i, NCA, PA)) * LA + min(m0 + r_of(i, NCA, PA), p.capacity - 4)) * 4;
         } else {
             const int r = (wave * NCA + i) * 8 + r8;
-            int m = min(m0 + r, count - 1);             // rows past the count replay a valid row; never stored
+            int m = min(m0 + r, count - 1);
             if (p.row_index) m = min(max(p.row_index[static_cast<size_t>(e) * p.capacity + m], 0), p.a_rows - 1);
             off[i] = (static_cast<Offset>(m) * LA + 4 * ((lane & 7) ^ ((r >> 1) & 7))) * 4;
+            if (!WIDE && m0 + r >= count) off[i] = kPastRange;           // (never stored; WIDE: a valid row again)
         }
     }
 #pragma unroll
@@ -2062,8 +2066,9 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmParams& p, int j, uint4*
             off[NCA + i] = (static_cast<Offset>(gathered_b ? 0 : k_of(i, NCB, PB)) * LB + min(n0 + r_of(i, NCB, PB), p.N - 4)) * 4;
         } else {
             const int r = (wave * NCB + i) * 8 + r8;
-            const int n = min(n0 + (GLU && r >= BN ? r - BN : r), p.N - 1);
-            off[NCA + i] = (static_cast<Offset>(n) * LB + 4 * ((lane & 7) ^ ((r >> 1) & 7))) * 4;
+            const int n = n0 + (GLU && r >= BN ? r - BN : r);
+            off[NCA + i] = (static_cast<Offset>(min(n, p.N - 1)) * LB + 4 * ((lane & 7) ^ ((r >> 1) & 7))) * 4;
+            if (!WIDE && n >= p.N) off[NCA + i] = kPastRange;
         }
     }
     const uint64_t a_base = reinterpret_cast<uint64_t>(p.A) +
