@@ -194,8 +194,9 @@ __device__ __forceinline__ bool decode_live_tile(const GemmParams& p, int BM, in
 // tiles of that workload's gate/up product): then all of them in one super-tile, 2 x 11, so that no column group
 // is left ragged.  Same box, whole layer: 7.42 -> 7.36 ms.  1 x 32 and 16 x 2 lose 3-8 % everywhere.
 // With 5 to 8 row tiles per group a super-tile takes them all (5 x 6 ... 8 x 4): the weights are then fetched once, where 4 x 8
-// leaves a second row of super-tiles with a tile or two to a weight slice.  5 row tiles, 16 experts, 4096 x 11008: 4303 -> 4258 us
-// for the layer; 6, 32 experts, 4096 x 2816: 2731 -> 2720.
+// leaves a second row of super-tiles with a tile or two to a weight slice.  5 row tiles, 16 experts, 4096 x 11008: 4277 -> 4243 us
+// for the layer, 7.7-7.8 -> 6.0-6.8 GB fetched by the gate/up product, 3.61 -> 2.98 by the down product; 6, 32 experts, 4096 x 2816:
+// 2731 -> 2720 us.
 inline long long plan_tiles(GemmParams& p, int BM, int BN, bool wide = false) {
     p.MT = (p.capacity + BM - 1) / BM;
     p.NT = (p.N + BN - 1) / BN;
@@ -590,8 +591,8 @@ __device__ __forceinline__ float lane_xor(float v) {
 // weights of the wave's rows.
 // Bound by the vector unit (25 issue slots an element, 8 of them the exponential and the reciprocal) and by the 640 KiB that a tile
 // moves, with the matrix pipe idle: some 20 us a tile.  A pass of its own, which also writes and reads u, took longer.  Training
-// step, pass / this: 16 experts of 166-1024 rows, 2048 x 5632: 2615 / 2532 us; 12 of 677, 1080 x 2744: 897 / 865; 8 of 32 000,
-// 4096 x 1408: 23316 / 22977; 8 of 564, 896 x 5248: 1251 / 1210.
+// step, pass / this: 16 experts of 166-1024 rows, 2048 x 5632: 2634 / 2575 us; 12 of 677, 1080 x 2744: 910 / 877; 8 of 32 000,
+// 4096 x 1408: 23525 / 23120; 8 of 512, 896 x 5248: 560 / 557.  Where its tiles leave CUs idle see middle_in_product.
 // Not kept: waits counted by hand instead of the compiler's (the same); workgroups with a tile less than others half a tile behind
 // them, so that not all epilogues meet in memory (0-2 % of the product).
 __device__ __forceinline__ void store_middle(const GemmParams& p, const f32x4 (&acc)[8][4], int e, int m_base, int nb, int count, uint32_t gates,
